@@ -20,6 +20,7 @@ struct EpiAdjStep {
   double fac;     // 2, or 1 for l = 0
   long ld;        // np
   int row_off;    // 0, or np when only the adjoint half is launched
+  __device__ __forceinline__ void batch(int) {}
   __device__ __forceinline__ void operator()(int m, int n, double ar, double ai) const {
     const long mg = (long)m + row_off;
     const long idx = mg * ld + n;
@@ -49,6 +50,7 @@ struct EpiAdjDot {
   double w;
   double acc = 0.0;
   long q = 0;
+  __device__ __forceinline__ void batch(int) {}
   __device__ __forceinline__ void operator()(int m, int n, double ar, double ai) {
     q = n / ld;
     const long idx = (long)m * ld + (n - q * ld);

@@ -2,9 +2,8 @@
 // cores with the recurrence, the Bessel-weighted accumulation and the step
 // phase fused into the epilogue, plus the O(N^2) helpers around them.
 //
-// Complex products use four real MFMA products per operand pair on planar
-// (real / imaginary) operands, or three (Gauss) on the large tiles. Every
-// product has the form
+// Complex products use Gauss's three real MFMA products per operand pair on
+// planar (real / imaginary) operands (zgemm_f64.h). Every product has the form
 //     C(m, n) = sum_k A(m, k) B(n, k)
 // with both operands contiguous along k ("NT"), which is what the state-major
 // storage of the propagated block gives: A = P_l^T (row j = state j) and
@@ -14,216 +13,10 @@
 #include "epilogues.h"
 #include "formats.h"
 #include "internal.h"
+#include "zgemm_f64.h"
 
 namespace fq {
 namespace {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef double d2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
-  // D(16x16) += A(16x4) B(4x16); lane l supplies A(l%16, kq(l)) and
-  // B(kq(l), l%16) with kq(l) = l/16, and holds D(4*r + l/16, l%16), r = 0..3
-  // (layout measured with one-hot operands on gfx950).
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-struct Operands {
-  const double* ar;
-  const double* ai;
-  const double* br;
-  const double* bi;
-  int ld;      // row stride of A and B (elements)
-  int kdim;    // reduction length, multiple of BK
-  int tiles_n; // tiles along n
-  int tiles_m;
-};
-
-// ---------------------------------------------------------------------------------------
-// Main loop: one workgroup computes a BM x BN complex tile with WGM x WGN waves.
-// K is consumed in BK-wide stages staged through LDS; the next stage's global
-// loads are issued before the current stage's MFMAs (register prefetch).
-// Within a stage, lane l reads the k pair (8p + 2(l/16), +1) of its row with one
-// 16-byte LDS read and feeds two MFMA k-steps; A and B use the same k order, so
-// the sum over k is unchanged.
-//
-// GAUSS: three real products per k-step instead of four, T1 = Ar Br, T2 = Ai Bi,
-// T3 = (Ar + Ai)(Br + Bi), Re = T1 - T2, Im = T3 - T1 - T2 (Gauss's complex
-// multiplication). The sums Ar + Ai and Br + Bi are formed in registers from
-// the fragments just read, so LDS keeps two planes per operand.
-// ---------------------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, bool GAUSS,
-          class Epi>
-__global__ __launch_bounds__(WGM* WGN * 64) void zgemm_nt_f64_kernel(Operands op, Epi epi) {
-  constexpr int NT = WGM * WGN * 64;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int FM = WTM / 16, FN = WTN / 16;
-  constexpr int S = BK + 2;  // LDS row stride (doubles): conflict-free 16-byte reads
-  constexpr int CPR = BK / 2;  // 16-byte chunks per row
-  constexpr int RA = BM * CPR / NT, RB = BN * CPR / NT;
-  static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "load split");
-  static_assert(BK % 8 == 0, "BK");
-
-  __shared__ __attribute__((aligned(16))) double As[2][2][BM * S];  // [stage][re, im]
-  __shared__ __attribute__((aligned(16))) double Bs[2][2][BN * S];
-
-  int tm, tn;
-  tile_coords(blockIdx.x, op.tiles_m, op.tiles_n, tm, tn);
-  if (tm >= op.tiles_m) return;  // grid padding
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int wm = wid / WGN, wn = wid % WGN;
-  const long ld = op.ld;
-
-  // 4M: accR = Re, accI = Im; GAUSS: accR = T1, accI = T2, accS = T3
-  constexpr int SM = GAUSS ? FM : 1, SN = GAUSS ? FN : 1;
-  d4 accR[FM][FN], accI[FM][FN], accS[SM][SN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      accR[i][j] = d4{0, 0, 0, 0};
-      accI[i][j] = d4{0, 0, 0, 0};
-    }
-#pragma unroll
-  for (int i = 0; i < SM; ++i)
-#pragma unroll
-    for (int j = 0; j < SN; ++j) accS[i][j] = d4{0, 0, 0, 0};
-
-  d2 ga[2][RA], gb[2][RB];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int r = 0; r < RA; ++r) {
-      const int c = tid + r * NT, row = c / CPR, col = 2 * (c % CPR);
-      const long off = (long)(m0 + row) * ld + k0 + col;
-      ga[0][r] = *reinterpret_cast<const d2*>(op.ar + off);
-      ga[1][r] = *reinterpret_cast<const d2*>(op.ai + off);
-    }
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const int c = tid + r * NT, row = c / CPR, col = 2 * (c % CPR);
-      const long off = (long)(n0 + row) * ld + k0 + col;
-      gb[0][r] = *reinterpret_cast<const d2*>(op.br + off);
-      gb[1][r] = *reinterpret_cast<const d2*>(op.bi + off);
-    }
-  };
-  auto lstore = [&](int st) {
-#pragma unroll
-    for (int r = 0; r < RA; ++r) {
-      const int c = tid + r * NT, row = c / CPR, col = 2 * (c % CPR);
-      *reinterpret_cast<d2*>(&As[st][0][row * S + col]) = ga[0][r];
-      *reinterpret_cast<d2*>(&As[st][1][row * S + col]) = CONJ_A ? -ga[1][r] : ga[1][r];
-    }
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const int c = tid + r * NT, row = c / CPR, col = 2 * (c % CPR);
-      *reinterpret_cast<d2*>(&Bs[st][0][row * S + col]) = gb[0][r];
-      *reinterpret_cast<d2*>(&Bs[st][1][row * S + col]) = CONJ_B ? -gb[1][r] : gb[1][r];
-    }
-  };
-
-  // Two LDS stages, one barrier per K-stage: the next stage is written from
-  // registers (loaded one stage earlier) while the waves multiply out of the
-  // current one.
-  const int nk = op.kdim / BK;
-  gload(0);
-  lstore(0);
-  if (nk > 1) gload(BK);
-  __syncthreads();
-  for (int kb = 0; kb < nk; ++kb) {
-    const int cur = kb & 1;
-    if (kb + 1 < nk) lstore(cur ^ 1);  // that stage was last read before the previous barrier
-    if (kb + 2 < nk) gload((kb + 2) * BK);
-    const int rr = lane & 15;
-    if constexpr (GAUSS) {
-#pragma unroll
-      for (int p = 0; p < BK / 8; ++p) {
-        const int kk = 8 * p + 2 * (lane >> 4);
-        d2 fbr[FN], fbi[FN], fbs[FN];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int row = wn * WTN + j * 16 + rr;
-          fbr[j] = *reinterpret_cast<const d2*>(&Bs[cur][0][row * S + kk]);
-          fbi[j] = *reinterpret_cast<const d2*>(&Bs[cur][1][row * S + kk]);
-          fbs[j] = fbr[j] + fbi[j];
-        }
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-          const int row = wm * WTM + i * 16 + rr;
-          const d2 far_ = *reinterpret_cast<const d2*>(&As[cur][0][row * S + kk]);
-          const d2 fai = *reinterpret_cast<const d2*>(&As[cur][1][row * S + kk]);
-          const d2 fas = far_ + fai;
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accR[i][j] = mfma_f64(far_[t], fbr[j][t], accR[i][j]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accI[i][j] = mfma_f64(fai[t], fbi[j][t], accI[i][j]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-              accS[i % SM][j % SN] = mfma_f64(fas[t], fbs[j][t], accS[i % SM][j % SN]);
-          }
-        }
-      }
-      __syncthreads();
-      continue;
-    }
-#pragma unroll
-    for (int p = 0; p < BK / 8; ++p) {
-      const int kk = 8 * p + 2 * (lane >> 4);
-      d2 far_[FM], fai[FM], fbr[FN], fbi[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const int row = wm * WTM + i * 16 + rr;
-        far_[i] = *reinterpret_cast<const d2*>(&As[cur][0][row * S + kk]);
-        fai[i] = *reinterpret_cast<const d2*>(&As[cur][1][row * S + kk]);
-      }
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int row = wn * WTN + j * 16 + rr;
-        fbr[j] = *reinterpret_cast<const d2*>(&Bs[cur][0][row * S + kk]);
-        fbi[j] = *reinterpret_cast<const d2*>(&Bs[cur][1][row * S + kk]);
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) accR[i][j] = mfma_f64(far_[i][t], fbr[j][t], accR[i][j]);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) accI[i][j] = mfma_f64(far_[i][t], fbi[j][t], accI[i][j]);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) accR[i][j] = mfma_f64(-fai[i][t], fbi[j][t], accR[i][j]);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) accI[i][j] = mfma_f64(fai[i][t], fbr[j][t], accI[i][j]);
-      }
-    }
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm * WTM + i * 16 + 4 * r + (lane >> 4);
-        const int n = n0 + wn * WTN + j * 16 + (lane & 15);
-        if constexpr (GAUSS) {
-          const double t1 = accR[i][j][r], t2 = accI[i][j][r];
-          epi(m, n, t1 - t2, accS[i % SM][j % SN][r] - t1 - t2);
-        } else {
-          epi(m, n, accR[i][j][r], accI[i][j][r]);
-        }
-      }
-  epi.finish();
-}
 
 // ---- epilogues ------------------------------------------------------------------------------
 
@@ -231,6 +24,7 @@ template <int KIND>
 struct EpiCheb {
   ChebTerm t;
   long ld;
+  __device__ __forceinline__ void batch(int) {}
   __device__ __forceinline__ void operator()(int m, int n, double ar, double ai) const {
     const long idx = (long)m * ld + n;
     if (KIND == CHEB_FIRST) {
@@ -275,6 +69,7 @@ struct EpiStore {
   double* ci;
   long ld;
   double alr, ali, ber, bei;
+  __device__ __forceinline__ void batch(int) {}
   __device__ __forceinline__ void operator()(int m, int n, double ar, double ai) const {
     const long idx = (long)m * ld + n;
     double r = alr * ar - ali * ai, i = alr * ai + ali * ar;
@@ -289,16 +84,18 @@ struct EpiStore {
   __device__ __forceinline__ void finish() const {}
 };
 
+// The Gram matrix is Hermitian: an element above the diagonal's tiles counts twice.
 struct EpiUnitarity {
   int n;
   double* out;
   double mx = 0.0, ss = 0.0;
-  __device__ __forceinline__ void operator()(int m, int c, double ar, double ai) {
+  __device__ __forceinline__ void batch(int) {}
+  __device__ __forceinline__ void herm(int m, int c, double ar, double ai, bool mirror) {
     if (m < n && c < n) {
       const double dr = ar - (m == c ? 1.0 : 0.0);
       const double a2 = dr * dr + ai * ai;
       mx = fmax(mx, a2);
-      ss += a2;
+      ss += mirror ? 2.0 * a2 : a2;
     }
   }
   __device__ void finish() {
@@ -318,31 +115,63 @@ struct EpiUnitarity {
 // A "stack" holds two state-major blocks as one 2np-row operand: rows [0, np)
 // the forward term P_l, rows [np, 2np) the adjoint term Pbar_{l+1}.
 
-// 128 x 128 tiles take Gauss's three products with 8-wide K-stages: the third
-// accumulator set (64 VGPRs) fits the 256-VGPR budget of two waves per SIMD only
-// once the staged loads shrink to one 16-byte chunk per plane (8.15 -> 6.49 ms
-// per N = 4096 product; with 16-wide stages it spills and takes 9.97 ms). The
-// 64 x 64 tiles keep four products: with a third set their accumulators move
-// between AGPRs and VGPRs on every stage.
-constexpr bool kGaussBig = true, kGaussSmall = false;
-constexpr int kBigBK = 8;
+// Tile of a product with t64 tiles of 64 x 64 (or 4 t64 of 32 x 32). Both take
+// Gauss's three real products. 64 x 64 tiles run with eight waves of 32 x 16
+// (90 VGPRs, 41 KB of LDS: two workgroups per CU): 84.7 TF/s algorithmic
+// (63.5 TF/s of MFMA, 81 % of peak) at N = 4096, the rate that 128 x 128 tiles
+// reached there with one workgroup per CU, and 831 us against 1103 us at
+// N = 2048. 32 x 32 tiles (four waves of 16 x 16) reach 70 TF/s but fill the
+// chip earlier: 425 us against 471 us at N = 1536, 80 against 91 us at 768, 13
+// against 31 us at 256. Time per k in rounds of 256 workgroups, fitted on
+// N = 256 .. 4096: 0.102 us a round (0.12 us for a single one) with 64 x 64
+// tiles, 0.045 us and 0.029 us for each further round with 32 x 32 tiles.
+inline bool take_tile64(long t64, long t32) {
+  const long r64 = (t64 + 255) / 256, r32 = (t32 + 255) / 256;
+  const double c64 = r64 == 1 ? 0.12 : 0.102 * (double)r64;
+  const double c32 = 0.045 + 0.029 * (double)(r32 - 1);
+  return c64 <= c32;
+}
 
+// C_z(m, n) over mrows x ncols (multiples of 64) for `batch` operand pairs.
 template <bool CONJ_A, bool CONJ_B, class Epi>
-hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, Epi epi, hipStream_t s) {
+hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi epi,
+                       hipStream_t s) {
+  if (mrows % 64 != 0 || ncols % 64 != 0 || op0.kdim % 16 != 0 || batch < 1 || batch > 65535)
+    return hipErrorInvalidValue;
   Operands op = op0;
-  if (mrows % 128 == 0 && ncols % 128 == 0 && (long)mrows * ncols >= kBigTileElems) {
-    op.tiles_m = mrows / 128;
-    op.tiles_n = ncols / 128;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<128, 128, kBigBK, 2, 4, CONJ_A, CONJ_B, kGaussBig, Epi>),
-                       dim3(grid_rows(op.tiles_m) * op.tiles_n), dim3(512), 0, s, op, epi);
-  } else if (mrows % 64 == 0 && ncols % 64 == 0) {
+  const long t64 = (long)(mrows / 64) * (ncols / 64) * batch;
+  if (take_tile64(t64, 4 * t64)) {
     op.tiles_m = mrows / 64;
     op.tiles_n = ncols / 64;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 16, 2, 2, CONJ_A, CONJ_B, kGaussSmall, Epi>),
-                       dim3(grid_rows(op.tiles_m) * op.tiles_n), dim3(256), 0, s, op, epi);
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, true, false,
+                                            4, Epi>),
+                       dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(512), 0, s, op, epi);
   } else {
-    return hipErrorInvalidValue;
+    op.tiles_m = mrows / 32;
+    op.tiles_n = ncols / 32;
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, true, false,
+                                            1, Epi>),
+                       dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(256), 0, s, op, epi);
   }
+  return hipGetLastError();
+}
+
+// The same for a Hermitian np x np result: the tiles on and above the diagonal
+// (at N = 4096 3.82 ms against 6.49 ms for all tiles).
+template <bool CONJ_A, bool CONJ_B, class Epi>
+hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hipStream_t s) {
+  if (np % 64 != 0 || op0.kdim % 16 != 0 || batch < 1 || batch > 65535)
+    return hipErrorInvalidValue;
+  const long a = np / 64, b = np / 32;
+  const long t64 = a * (a + 1) / 2, t32 = b * (b + 1) / 2;
+  if (take_tile64(t64 * batch, t32 * batch))
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, true, true, 4,
+                                            Epi>),
+                       dim3(t64, batch), dim3(512), 0, s, op0, epi);
+  else
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, true, true, 1,
+                                            Epi>),
+                       dim3(t32, batch), dim3(256), 0, s, op0, epi);
   return hipGetLastError();
 }
 
@@ -729,16 +558,16 @@ __global__ __launch_bounds__(256) void transpose_planar_kernel(const double* __r
 }  // namespace
 
 hipError_t launch_cheb_f64(const ChebTerm& t, int mrows, int np, hipStream_t s) {
-  Operands op{t.a_re, t.a_im, t.b_re, t.b_im, np, np, 0, 0};
+  Operands op{t.a_re, t.a_im, t.b_re, t.b_im, np, np, 0, 0, 0, 0};
   switch (t.kind) {
     case CHEB_FIRST:
-      return launch_gemm<false, false>(op, mrows, np, EpiCheb<CHEB_FIRST>{t, np}, s);
+      return launch_gemm<false, false>(op, mrows, np, 1, EpiCheb<CHEB_FIRST>{t, np}, s);
     case CHEB_FIRST_LAST:
-      return launch_gemm<false, false>(op, mrows, np, EpiCheb<CHEB_FIRST_LAST>{t, np}, s);
+      return launch_gemm<false, false>(op, mrows, np, 1, EpiCheb<CHEB_FIRST_LAST>{t, np}, s);
     case CHEB_MID:
-      return launch_gemm<false, false>(op, mrows, np, EpiCheb<CHEB_MID>{t, np}, s);
+      return launch_gemm<false, false>(op, mrows, np, 1, EpiCheb<CHEB_MID>{t, np}, s);
     case CHEB_LAST:
-      return launch_gemm<false, false>(op, mrows, np, EpiCheb<CHEB_LAST>{t, np}, s);
+      return launch_gemm<false, false>(op, mrows, np, 1, EpiCheb<CHEB_LAST>{t, np}, s);
   }
   return hipErrorInvalidValue;
 }
@@ -747,36 +576,36 @@ hipError_t launch_adj_step(const double* ar, const double* ai, int mrows, const 
                            const double* hti, double* sr, double* si, const double* lr,
                            const double* li, double dr, double di, double fac, int row_off, int np,
                            hipStream_t s) {
-  Operands op{ar, ai, htr, hti, np, np, 0, 0};
+  Operands op{ar, ai, htr, hti, np, np, 0, 0, 0, 0};
   EpiAdjStep e{sr, si, lr, li, dr, di, fac, np, row_off};
-  return launch_gemm<false, false>(op, mrows, np, e, s);
+  return launch_gemm<false, false>(op, mrows, np, 1, e, s);
 }
 
 hipError_t launch_adj_dot(const double* pr, const double* pi, const double* dr_, const double* di_,
                           int ncols, const double* pbr, const double* pbi, double w, double* out,
                           int np, hipStream_t s) {
-  Operands op{pr, pi, dr_, di_, np, np, 0, 0};
+  Operands op{pr, pi, dr_, di_, np, np, 0, 0, 0, 0};
   EpiAdjDot e{pbr, pbi, out, np, w};
-  return launch_gemm<false, false>(op, np, ncols, e, s);
+  return launch_gemm<false, false>(op, np, ncols, 1, e, s);
 }
 
 hipError_t launch_zgemm_nt_f64(const double* ar, const double* ai, bool conj_a, const double* br,
                                const double* bi, bool conj_b, double* cr, double* ci, int mrows,
                                int ncols, int kdim, int ld, double alr, double ali, double ber,
                                double bei, hipStream_t s) {
-  Operands op{ar, ai, br, bi, ld, kdim, 0, 0};
+  Operands op{ar, ai, br, bi, ld, kdim, 0, 0, 0, 0};
   EpiStore e{cr, ci, ld, alr, ali, ber, bei};
-  if (conj_a && conj_b) return launch_gemm<true, true>(op, mrows, ncols, e, s);
-  if (conj_a) return launch_gemm<true, false>(op, mrows, ncols, e, s);
-  if (conj_b) return launch_gemm<false, true>(op, mrows, ncols, e, s);
-  return launch_gemm<false, false>(op, mrows, ncols, e, s);
+  if (conj_a && conj_b) return launch_gemm<true, true>(op, mrows, ncols, 1, e, s);
+  if (conj_a) return launch_gemm<true, false>(op, mrows, ncols, 1, e, s);
+  if (conj_b) return launch_gemm<false, true>(op, mrows, ncols, 1, e, s);
+  return launch_gemm<false, false>(op, mrows, ncols, 1, e, s);
 }
 
 hipError_t launch_unitarity_f64(const double* xr, const double* xi, int n, int np, double* out,
                                 hipStream_t s) {
-  Operands op{xr, xi, xr, xi, np, np, 0, 0};
+  Operands op{xr, xi, xr, xi, np, np, 0, 0, 0, 0};
   EpiUnitarity e{n, out};
-  return launch_gemm<true, false>(op, np, np, e, s);
+  return launch_gemm_herm<true, false>(op, np, 1, e, s);
 }
 
 hipError_t launch_pack_planar(const void* src, long rows, long cols, long ld_src, double* re,

@@ -1,0 +1,53 @@
+"""FP64 products on both tile sizes (32 x 32 and 64 x 64) and their Hermitian
+form (unitarity of U_T, upper tiles only), at sizes on either side of the
+choice between them, against plain FP64 matrix products.
+
+Tolerances: a step's Chebyshev sum has L terms of products over n columns; in
+FP64 with n <= 1100 their rounding stays below 1e-13 in a column's 2-norm.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from workloads import gue
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fl(require_gpu):
+    from paper_1508_07621_amd import floquet
+    floquet.node_times(1.0, 1)          # loads the library or raises
+    return floquet
+
+
+# padded size 64 .. 1152; 64 x 64 tiles make 1, 4, 9, 100, 256 (exactly one per
+# CU) and 324 of them
+@pytest.mark.parametrize("n", [64, 65, 192, 640, 1024, 1100])
+def test_fp64_products_on_both_tiles(fl, n):
+    print("[case] products", n, flush=True)
+    rng = np.random.default_rng(90 + n)
+    H0, V = gue(n, rng), gue(n, rng)
+    T, M = 0.3, 3
+    f = np.cos(fl.node_times(T, M))
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f)
+    U = ctx.build_ut()
+    rep = ctx.last_report
+    cols = np.unique(np.array([0, 1, n // 2, n - 1]))
+    X = np.eye(n, dtype=complex)[:, cols]
+    a, b = orc.magnus4_weights(f, T / M)
+    K = orc.commutator(H0, V)
+    for k in range(M):
+        H = H0 + a[k] * V + b[k] * K
+        w, Q = np.linalg.eigh(H)
+        X = Q @ (np.exp(-1j * (T / M) * w)[:, None] * (Q.conj().T @ X))
+    err = orc.column_error(U.cpu().numpy()[:, cols], X)
+    G = U.conj().T @ U - torch.eye(n, dtype=U.dtype, device=U.device)
+    print("[case] e_col", err, "unitarity", rep["unitarity_max"], rep["unitarity_fro"], flush=True)
+    # truncation 1e-12 a step beside rounding
+    assert err < M * 1e-12 + 1e-13
+    assert abs(rep["unitarity_max"] - G.abs().max().item()) < 1e-13
+    assert abs(rep["unitarity_fro"] - torch.linalg.norm(G).item()) < 1e-13 * math.sqrt(n)
