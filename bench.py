@@ -205,8 +205,7 @@ def _blas_threads() -> int:
 
 #: MFMA operations issued per algorithmic real flop of a complex product
 #: (algorithmic: four real products, 8 N^3 flop): FP32 runs the four real
-#: products once; FP64 on 128 x 128 tiles runs three (Gauss), 3 / 4, and four on
-#: 64 x 64 tiles; BF16x3 runs three real products (Gauss) for each of six piece
+#: products once; FP64 runs three (Gauss), 3 / 4; BF16x3 runs three real products (Gauss) for each of six piece
 #: pairs, 18 / 4 = 4.5.
 MFMA_FLOPS_PER_FLOP = {"fp64": 0.75, "fp32": 1.0, "bf16x3": 4.5}
 
@@ -216,13 +215,11 @@ BIG_TILE_ELEMS = 256 * 128 * 128
 
 def mfma_flops_per_flop(precision: str, n: int, rows: int = 0) -> float:
     """MFMA flops per algorithmic flop of a product with (rows or n) x n outputs."""
-    if precision == "fp64" and (rows or n) * n < BIG_TILE_ELEMS:
-        return 1.0
     return MFMA_FLOPS_PER_FLOP[precision]
 PEAKS = {"fp64": PEAK_FP64_MFMA_TFLOPS, "fp32": PEAK_FP32_MFMA_TFLOPS,
          "bf16x3": PEAK_BF16_MFMA_TFLOPS}
-KERNEL_NAMES = {"fp64": "zgemm_nt_f64_kernel<128,128,8,2,4,Gauss,EpiCheb<MID>> (FP64 MFMA 16x16x4, "
-                        "3 real products)",
+KERNEL_NAMES = {"fp64": "zgemm_nt_f64_kernel<64,64,8,2,4,Gauss> (FP64 MFMA 16x16x4, 3 real "
+                        "products; the product that applies a step's propagator)",
                 "fp32": "cheb_f32_kernel<128,128,32,2,4,EpiMix<MID>> (FP32 MFMA 16x16x4)",
                 "bf16x3": "cheb_bf3_kernel<128,128,2,4,MID> (BF16 MFMA 32x32x16, 3 real products "
                           "x 6 piece pairs)"}
@@ -231,7 +228,8 @@ def kernel_name(precision: str, n: int) -> str:
     """The middle product's kernel: 128 x 128 tiles, or 64 x 64 below BIG_TILE_ELEMS outputs."""
     if n * n >= BIG_TILE_ELEMS:
         return KERNEL_NAMES[precision]
-    return {"fp64": "zgemm_nt_f64_kernel<64,64,16,2,2,EpiCheb<MID>> (FP64 MFMA 16x16x4)",
+    return {"fp64": "zgemm_nt_f64_kernel<64,64,8,2,4> or <32,32,16,2,2> (FP64 MFMA 16x16x4, 3 real "
+                    "products; the product that applies a step's propagator)",
             "fp32": "cheb_f32_kernel<64,64,32,2,2,EpiMix<MID>> (FP32 MFMA 16x16x4)",
             "bf16x3": "cheb_bf3_kernel<64,64,2,2,MID> (BF16 MFMA 32x32x16, 3 real products "
                       "x 6 piece pairs)"}[precision]
@@ -240,7 +238,7 @@ def kernel_name(precision: str, n: int) -> str:
 #: Kernel sources behind each roofline entry; HBM traffic recorded under
 #: profiles/ is reported only while these files are unchanged.
 TRAFFIC_SOURCES = {
-    "fp64": ["kernels_dense.hip", "formats.h", "internal.h"],
+    "fp64": ["kernels_dense.hip", "zgemm_f64.h", "formats.h", "internal.h"],
     "fp32": ["kernels_mixed.hip", "formats.h", "internal.h"],
     "bf16x3": ["kernels_mixed.hip", "formats.h", "internal.h"],
     "bf16x3_f64acc": ["kernels_mixed.hip", "formats.h", "internal.h"],
@@ -363,12 +361,14 @@ ALGO_NOTE = ("algorithmic flops: 8 N^3 per complex N x N x N product (four real 
 
 
 def dense_roofline(reports, n: int, precision: str, workload: str):
-    """The middle Chebyshev product: achieved = algorithmic flops (8 N^3) per
-    launch over the launch time, against the MFMA peak of the precision the
-    product runs in; the MFMA flops actually issued are reported beside it."""
-    from paper_1508_07621_amd._abi import K_MID
-    n_launch = sum(r["n_kernel"][K_MID] for r in reports)
-    ms_launch = sum(r["ms_kernel"][K_MID] for r in reports) / max(n_launch, 1)
+    """The middle Chebyshev product (FP64 builds: the product that applies a
+    step's propagator): achieved = algorithmic flops (8 N^3) per launch over the
+    launch time, against the MFMA peak of the precision the product runs in; the
+    MFMA flops actually issued are reported beside it."""
+    from paper_1508_07621_amd._abi import K_LAST, K_MID
+    kind = K_MID if any(r["n_kernel"][K_MID] for r in reports) else K_LAST
+    n_launch = sum(r["n_kernel"][kind] for r in reports)
+    ms_launch = sum(r["ms_kernel"][kind] for r in reports) / max(n_launch, 1)
     flops = 8.0 * n ** 3                                   # one complex N x N x N product
     mfma_flops = flops * mfma_flops_per_flop(precision, n)
     achieved = flops / (ms_launch * 1e-3) / 1e12
@@ -425,7 +425,7 @@ def term_kernel(name: str, n: int) -> str:
 
 
 TERM_KERNEL = {
-    "fp64": "zgemm_nt_f64_kernel<128,128,8,2,4,Gauss,EpiCheb> (FP64 MFMA 16x16x4)",
+    "fp64": "zgemm_nt_f64_kernel<64,64,8,2,4,Gauss,EpiCheb> (FP64 MFMA 16x16x4)",
     "bf16x3_f64acc": "cheb_acc_kernel<128> (BF16 MFMA 32x32x16, 4 real products x 6 piece "
                      "pairs, FP64 sums per 64-column block)",
     "bf16x3": "cheb_bf3_kernel<128,128,2,4,KIND,P,3> (BF16 MFMA 32x32x16, 3 real products x 6 "
@@ -608,7 +608,7 @@ def shard_share(ctx, U, wl, P: int, warmup: int, steps: int, s_full: float, prec
     this (its own columns, no communication inside the period); the result must
     equal those columns of the full build."""
     import torch
-    from paper_1508_07621_amd._abi import K_MID, K_TRIDIAG
+    from paper_1508_07621_amd._abi import K_LAST, K_MID, K_TRIDIAG
     n = U.shape[0]
     if P < 2 or n % P:
         raise SystemExit(f"--shard {P}: P must be >= 2 and divide N = {n}")
@@ -626,7 +626,9 @@ def shard_share(ctx, U, wl, P: int, warmup: int, steps: int, s_full: float, prec
         _log(f"shard 1/{P} timed propagation {i + 1}/{steps}")
     torch.cuda.synchronize()
     t = (time.perf_counter() - t0) / steps
-    kind = K_MID if wl.layout == "dense" else K_TRIDIAG
+    kind = K_TRIDIAG
+    if wl.layout == "dense":
+        kind = K_MID if any(r["n_kernel"][K_MID] for r in reps) else K_LAST
     n_launch = sum(r["n_kernel"][kind] for r in reps)
     ms_launch = sum(r["ms_kernel"][kind] for r in reps) / max(n_launch, 1)
     res = {"P": P, "columns": cols, "s_per_share": round(t, 6),

@@ -248,7 +248,10 @@ enum {
   FQ_K_TERM_X1 = 12,        /* FQ_TERM_BF16X1 */
   FQ_K_CONVERT = 13,        /* FP64 planes rounded into the BF16X3 format */
   FQ_K_CHAIN = 14,          /* dense N <= 64 in FP64: every step of the range in one
-                               launch (Ht, all terms and the hand-off per step) */
+                               launch (Ht, all terms and the hand-off per step; a
+                               build in segments, whose products appear under LAST) */
+  FQ_K_POLY = 15,           /* FP64 dense builds: products that form a step's propagator
+                               (FQ_K_LAST then counts the products that apply it) */
   FQ_K_SLOTS = 16
 };
 #define FQ_TERM_SLOTS 16

@@ -4,6 +4,14 @@
 
 #include "internal.h"
 
+// The step propagator sum_l c_l T_l(Ht) as matrix products: T_1 .. T_s, then
+// Clenshaw's recurrence in T_s over the blocks Q_0 .. Q_J-1 (g: s + 1
+// coefficients of T_0 .. T_s per block, step phase included).
+struct PolyPlan {
+  int s = 0, J = 0;
+  std::vector<double> gr, gi;
+};
+
 // ---- the context ---------------------------------------------------------------------------
 struct fq_ctx {
   // system
@@ -72,6 +80,17 @@ struct fq_ctx {
   bool adj_f32 = false;               // reverse-sweep products on FP32 matrix cores
   double* save_pl = nullptr;          // when set, a step also stores P_L and P_{L-1} here
   double* save_plm1 = nullptr;
+  // FP64 step operators: the matrices of H_eff (weights per step in d_w) and
+  // scratch beyond the planes above. pool: pool_mats matrices for the segments
+  // of a build run as one batch; extra: further matrices of a single step.
+  std::vector<std::pair<const double*, const double*>> heff_ops;
+  std::vector<int> heff_slot;
+  double* d_w = nullptr;
+  double* pool = nullptr;
+  int pool_mats = 0;
+  double* extra = nullptr;
+  int n_extra = 0;
+  bool from_identity = false;         // the running build starts at X = 1
   double* small = nullptr;            // 64 doubles of reduction scratch
   double* d_ab = nullptr;             // 2*M
   double* d_coef = nullptr;           // 2*(L+1)

@@ -139,14 +139,30 @@ constexpr int kComm6 = 9;
 
 struct Layout {
   size_t total = 0;
+  size_t zeroed = 0;  // bytes cleared by fq_create (the scratch matrices after them are not)
   size_t off_h0 = 0, off_v = 0, off_k = 0, off_ht = 0, off_x = 0, off_y = 0, off_pa = 0,
          off_pb = 0, off_pc = 0, off_htx = 0, off_tape = 0, off_small = 0, off_ab = 0, off_coef = 0,
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
-         off_comm6 = 0, off_vec = 0, off_drive32 = 0;
+         off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0;
   long np = 0;
   int n_tape = 0;
+  int pool_mats = 0, n_extra = 0;
 };
+
+// Scratch matrices of the FP64 step operators (see PolyPlan). Below 1024 padded
+// states one product leaves most of the chip idle, so a build cuts the chain
+// into segments and runs one step of each as a batch: up to two 64 x 64-tile
+// workgroups per CU (N = 256: 32 segments), kPoolBufs matrices each, within
+// kPoolBytes. Above, a single step fills the chip and two matrices beyond the
+// propagation's own planes extend the polynomials it can take. Both keep inside
+// the static scratch of the one-shot build wherever the rest does.
+constexpr int kPoolBufs = 6, kExtraBufs = 2, kPoolSegments = 128;
+constexpr size_t kPoolBudget = size_t(250) << 20, kPoolBytes = size_t(144) << 20;
+long pool_segments(long np) {
+  const long t64 = (np / 64) * (np / 64);
+  return std::max(1L, std::min<long>(512 / t64, kPoolSegments));
+}
 
 // The tridiagonal gradient of columns longer than one workgroup holds runs as
 // streamed passes (tridiag_adjoint_streamed). FQ_TRIDIAG_STREAMED_ADJOINT=1 in
@@ -235,10 +251,25 @@ Layout plan(const fq_system* sys, const fq_params* par) {
       }
     }
   }
+  if (dense_like(sys->layout))  // (whole blocks of 64 steps)
+    lay.off_w = take(fq::kHeffTerms * sizeof(double) * (size_t)pad_to(Ms, 64));
   lay.off_small = take(64 * sizeof(double));
   lay.off_vec = take(3 * sizeof(double) * (size_t)n);
   lay.off_ab = take(2 * sizeof(double) * (size_t)Ms);
   lay.off_coef = take(2 * sizeof(double) * (size_t)(kMaxOrder + 1));
+  lay.zeroed = cur;
+  if (dense_like(sys->layout) && par->precision == FQ_FP64) {
+    const size_t plane2 = 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np;
+    const size_t left = kPoolBudget > cur ? kPoolBudget - cur : 0;
+    if (lay.np < 1024) {
+      lay.pool_mats = (int)std::min<size_t>(kPoolBufs * (size_t)pool_segments(lay.np),
+                                            std::min(left, kPoolBytes) / plane2);
+      if (lay.pool_mats > 0) lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
+    } else {
+      lay.n_extra = left == 0 ? kExtraBufs : (int)std::min<size_t>(kExtraBufs, left / plane2);
+      if (lay.n_extra > 0) lay.off_extra = take(plane2 * (size_t)lay.n_extra);
+    }
+  }
   lay.total = cur;
   return lay;
 }
@@ -805,8 +836,25 @@ fq_status collect_profile(fq_ctx* c) {
 
 // ---- dense step loop ----------------------------------------------------------------------------
 
+// FP64 Ht of step t of `batch` segments (see launch_heff_f64) at out + z bs.
+fq_status heff_f64(fq_ctx* c, int t, int batch, int len0, int rem, double* out) {
+  fq::HeffSum h{};
+  for (size_t j = 0; j < c->heff_ops.size(); ++j) {
+    h.re[j] = c->heff_ops[j].first;
+    h.im[j] = c->heff_ops[j].second;
+    h.slot[j] = c->heff_slot[j];
+  }
+  h.count = (int)c->heff_ops.size();
+  h.len0 = len0;
+  h.rem = rem;
+  FQ_HIP(c, fq::launch_heff_f64(h, c->d_w, t, batch, c->beta, c->dE, c->n, c->np, out,
+                                2 * c->np * c->np, c->stream));
+  return FQ_OK;
+}
+
 fq_status dense_heff(fq_ctx* c, int k) {
   FQ_MARK(c, FQ_K_HEFF);
+  if (c->precision == FQ_FP64) return heff_f64(c, k, 1, 0, 0, c->htr);
   if (c->scheme == FQ_MAGNUS6) FQ_TRY(magnus6_sum(c, k, false, c->kr, c->ki));  // K slot
   // H0 + a V + b K, or with several drive terms the whole sum, formed first in
   // the P planes (free at a step start) and passed as H0 with a = b = 0
@@ -816,14 +864,9 @@ fq_status dense_heff(fq_ctx* c, int k) {
     h0r = c->par;
     h0i = c->pai;
   }
-  if (c->precision == FQ_FP64) {
-    FQ_HIP(c, fq::launch_heff_f64(h0r, h0i, c->vr, c->vi, c->kr, c->ki, c->a[k], c->b[k],
-                                  c->beta, c->dE, c->n, c->np, c->htr, c->hti, c->stream));
-  } else {
-    FQ_HIP(c, fq::launch_heff_mixed(h0r, h0i, c->vr, c->vi, c->kr, c->ki, c->a[k],
-                                    c->b[k], c->beta, c->dE, c->n, c->np, c->htr, c->hti, c->htx,
-                                    c->precision, c->stream));
-  }
+  FQ_HIP(c, fq::launch_heff_mixed(h0r, h0i, c->vr, c->vi, c->kr, c->ki, c->a[k],
+                                  c->b[k], c->beta, c->dE, c->n, c->np, c->htr, c->hti, c->htx,
+                                  c->precision, c->stream));
   return FQ_OK;
 }
 
@@ -895,6 +938,182 @@ fq_status dense_cheb_step(fq_ctx* c, int mrows) {
     }
   }
   return FQ_OK;
+}
+
+// ---- steps as matrix polynomials --------------------------------------------------------------
+//
+// Applying sum_{l<=L} c_l T_l(Ht) to all N columns term by term costs L products
+// of N x N matrices. Forming the step's propagator E itself first is cheaper:
+// the T_l are Hermitian (half a product each), blocks of s terms turn the rest
+// of the sum into ceil(L/s) - 1 products (Paterson and Stockmeyer, SIAM J.
+// Comput. 2 (1973), in the Chebyshev basis), and one more product applies E:
+//   sum_l c_l T_l = q_0 + sum_{j>=1} T_{js} q_j,  deg q_j < s, from
+//   T_{js+i} = 2 T_{js} T_i - T_{js-i}, then Clenshaw's recurrence in T_s:
+//   W_j = q_j + 2 T_s W_{j+1} - W_{j+2},  E = q_0 + T_s W_1 - W_2.
+// With a Hermitian product at 0.6 of a full one (measured at N = 1536 and
+// 4096), L = 7 takes 3.8 instead of 7 products, L = 12 takes 4.8 instead of 12.
+// 50 steps of L = 10 at N = 1500: 195 -> 91 ms (1.83 ms a step, 57 TF/s of issued
+// MFMA). Small N in segments: 100 steps at N = 64 2.36 -> 0.16 ms, a sixth-order
+// one-shot build at N = 199 18.3 -> 12.0 ms (the rest is its setup).
+
+// The cheapest block length with at most nbuf matrices beside X (T_1 .. T_s,
+// then T_s and the blocks); `apply` = mrows / np, the cost of applying E. An
+// empty plan (s = 0) when the term-by-term form (L * apply) is cheaper or no
+// plan fits.
+PolyPlan poly_plan(const fq_ctx* c, int nbuf, double apply) {
+  const int L = c->L;
+  PolyPlan best;
+  double best_cost = L * apply;
+  int bs = 0;
+  for (int s = 2; s <= std::min({fq::kPolyMaxS, nbuf, L}); ++s) {
+    const int prods = (L + s - 1) / s - 1;
+    if (prods + 1 > fq::kPolyMaxBlocks || (prods > 0 && prods + 2 > nbuf)) continue;
+    const double cost = 0.6 * (s - 1) + prods + apply;
+    if (cost < best_cost) {
+      best_cost = cost;
+      bs = s;
+    }
+  }
+  if (bs == 0) return best;
+  const int s = best.s = bs, prods = (L + s - 1) / s - 1, top = L / s;
+  const std::complex<double> ph(c->phr, c->phi);
+  std::vector<std::complex<double>> cl(L + 1);
+  for (int l = 0; l <= L; ++l)
+    cl[l] = ph * std::complex<double>(c->coef[2 * l], c->coef[2 * l + 1]);
+  best.J = prods + 1;
+  std::vector<std::complex<double>> g((size_t)(top + 1) * (s + 1), 0.0);
+  auto G = [&](int j, int l) -> std::complex<double>& { return g[(size_t)j * (s + 1) + l]; };
+  for (int j = top; j >= 1; --j) {
+    G(j, 0) = cl[j * s];
+    for (int i = 1; i < s && j * s + i <= L; ++i) {
+      G(j, i) = 2.0 * cl[j * s + i];
+      cl[j * s - i] -= cl[j * s + i];
+    }
+  }
+  for (int i = 0; i < s; ++i) G(0, i) = cl[i];
+  if (L % s == 0) {  // the top block is a number: no product for it
+    const std::complex<double> gt = G(top, 0);
+    G(top - 1, s) = (top - 1 >= 1 ? 2.0 : 1.0) * gt;
+    if (top - 2 >= 0) G(top - 2, 0) -= gt;
+  }
+  best.gr.resize((size_t)best.J * (s + 1));
+  best.gi.resize(best.gr.size());
+  for (int j = 0; j < best.J; ++j)
+    for (int l = 0; l <= s; ++l) {
+      best.gr[(size_t)j * (s + 1) + l] = G(j, l).real();
+      best.gi[(size_t)j * (s + 1) + l] = G(j, l).imag();
+    }
+  return best;
+}
+
+// E over the Ht in b[0], for `batch` matrices with stride bs; b[1] .. are scratch.
+fq_status poly_form(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& b, int batch) {
+  const int np = (int)c->np, s = p.s, J = p.J;
+  const long bs = 2 * c->np * c->np;
+  for (int l = 2; l <= s; ++l) {
+    FQ_MARK(c, FQ_K_POLY);
+    FQ_HIP(c, fq::launch_poly_t(b[l / 2 - 1], b[(l + 1) / 2 - 1], l % 2 ? b[0] : nullptr, b[l - 1],
+                                (int)c->n, np, bs, batch, c->stream));
+  }
+  fq::PolyCombine q{};
+  q.s = s;
+  q.J = J;
+  for (int l = 0; l < s; ++l) q.t[l] = b[l];
+  std::vector<double*> w(J);
+  for (int j = 0, at = 0; j < J; ++j, ++at) {
+    if (J > 1 && at == s - 1) ++at;  // T_s stays
+    w[j] = q.q[j] = b[at];
+    for (int l = 0; l <= s; ++l) {
+      q.gr[j][l] = p.gr[(size_t)j * (s + 1) + l];
+      q.gi[j][l] = p.gi[(size_t)j * (s + 1) + l];
+    }
+  }
+  FQ_MARK(c, FQ_K_HEFF);
+  FQ_HIP(c, fq::launch_poly_combine(q, c->n, np, bs, batch, c->stream));
+  for (int j = J - 2; j >= 0; --j) {
+    FQ_MARK(c, FQ_K_POLY);
+    FQ_HIP(c, fq::launch_poly_block(w[j + 1], b[s - 1], j >= 1 ? 2.0 : 1.0,
+                                    j + 2 < J ? w[j + 2] : nullptr, w[j], np, bs, batch,
+                                    c->stream));
+  }
+  return FQ_OK;
+}
+
+// One FP64 step X <- E_k X through E_k (Ht formed here).
+fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
+  std::vector<double*> b{c->htr, c->par, c->pbr, c->yr};
+  const size_t plane2 = 2 * (size_t)c->np * (size_t)c->np;
+  for (int i = 0; i < c->n_extra; ++i) b.push_back(c->extra + (size_t)i * plane2);
+  FQ_TRY(dense_heff(c, k));
+  FQ_TRY(poly_form(c, p, b, 1));
+  FQ_MARK(c, FQ_K_LAST);
+  if (c->from_identity && k == 0)  // X = 1: the state-major E is E^T
+    FQ_HIP(c, fq::launch_transpose_planar(c->htr, c->hti, c->par, c->pai, c->np, 0, 1, c->stream));
+  else
+    FQ_HIP(c, fq::launch_poly_apply(c->xr, 0, c->htr, 0, false, c->par, 0, mrows, (int)c->np, 1,
+                                    c->stream));
+  std::swap(c->xr, c->par);
+  std::swap(c->xi, c->pai);
+  return FQ_OK;
+}
+
+// The product of cnt state-major operators at src (the first acts first), into
+// dst by pairs, ping-ponged with src; the result goes to the X planes.
+fq_status multiply_up(fq_ctx* c, double* src, double* dst, int cnt) {
+  const int np = (int)c->np;
+  const long bs = 2 * c->np * c->np;
+  const size_t bytes = sizeof(double) * (size_t)bs;
+  while (cnt > 1) {
+    const int pairs = cnt / 2;
+    double* out = cnt == 2 ? c->xr : dst;
+    FQ_MARK(c, FQ_K_LAST);
+    FQ_HIP(c, fq::launch_poly_apply(src, 2 * bs, src + bs, 2 * bs, true, out, bs, np, np, pairs,
+                                    c->stream));
+    if (cnt % 2)
+      FQ_HIP(c, hipMemcpyAsync(dst + (size_t)pairs * bs, src + (size_t)(cnt - 1) * bs, bytes,
+                               hipMemcpyDeviceToDevice, c->stream));
+    cnt = pairs + cnt % 2;
+    std::swap(src, dst);
+  }
+  return FQ_OK;
+}
+
+// Matrices a plan works on beside X (at least E and the next X).
+int poly_bufs(const PolyPlan& p) { return std::max({p.s, p.J > 1 ? p.J + 1 : 1, 2}); }
+
+// Segments of a whole build by plan p: what fills the chip and fits the pool.
+int poly_segments(const fq_ctx* c, const PolyPlan& p) {
+  return (int)std::min<long>({pool_segments(c->np), c->pool_mats / (poly_bufs(p) + 1), c->M});
+}
+
+// A whole build in nb segments: step t of every segment in one batch.
+fq_status dense_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
+  const int len0 = c->M / nb, rem = c->M % nb;
+  const int np = (int)c->np, nbuf = poly_bufs(p);
+  const long bs = 2 * c->np * c->np;
+  std::vector<double*> b;
+  for (int r = 0; r < nbuf; ++r) b.push_back(c->pool + (size_t)r * nb * bs);
+  double* x = c->pool + (size_t)nbuf * nb * bs;
+  for (int t = 0; t < len0 + (rem ? 1 : 0); ++t) {
+    const int act = t < len0 ? nb : rem;  // segments with a step t
+    FQ_MARK(c, FQ_K_HEFF);
+    FQ_TRY(heff_f64(c, t, act, len0, rem, b[0]));
+    FQ_TRY(poly_form(c, p, b, act));
+    FQ_MARK(c, FQ_K_LAST);
+    if (t == 0) {  // X = 1
+      FQ_HIP(c, fq::launch_transpose_planar(b[0], b[0] + bs / 2, x, x + bs / 2, c->np, bs, act,
+                                            c->stream));
+      continue;
+    }
+    FQ_HIP(c, fq::launch_poly_apply(x, bs, b[0], bs, false, b[1], bs, np, np, act, c->stream));
+    if (act == nb) {
+      std::swap(x, b[1]);
+    } else {  // the segments without a step t keep their X in the old place
+      FQ_HIP(c, hipMemcpyAsync(x, b[1], sizeof(double) * (size_t)bs * act,
+                               hipMemcpyDeviceToDevice, c->stream));
+    }
+  }
+  return multiply_up(c, x, b[1], nb);
 }
 
 // ---- mixed-precision builds: one format per Chebyshev term -----------------------------------
@@ -1163,8 +1382,29 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
     sc.phr = c->phr;
     sc.phi = c->phi;
     FQ_MARK(c, FQ_K_CHAIN);
-    FQ_HIP(c, fq::launch_small_chain(sc, mrows, c->stream));
+    // a build: segments for the other CUs (4 workgroups each), multiplied up
+    const int most = c->from_identity ? std::min({c->pool_mats / 2, 64, k1 - k0}) : 1;
+    if (most > 1) {
+      const int len = (k1 - k0 + most - 1) / most, nseg = (k1 - k0 + len - 1) / len;
+      sc.len0 = (k1 - k0) / nseg;
+      sc.rem = (k1 - k0) % nseg;
+      sc.bs = (long)plane2;
+      sc.xr = c->pool;
+      sc.xi = c->pool + plane2 / 2;
+      FQ_HIP(c, fq::launch_small_chain(sc, mrows, nseg, c->stream));
+      return multiply_up(c, c->pool, c->pool + (size_t)nseg * plane2, nseg);
+    }
+    FQ_HIP(c, fq::launch_small_chain(sc, mrows, 1, c->stream));
     return FQ_OK;
+  }
+  PolyPlan poly;
+  if (c->precision == FQ_FP64 && !c->save_pl && !c->save_plm1) {
+    if (c->from_identity && !record_tape && c->pool_mats > 0) {
+      poly = poly_plan(c, kPoolBufs - 1, 1.0);
+      const int nb = poly.s ? poly_segments(c, poly) : 0;
+      if (nb > 1) return dense_poly_segments(c, poly, nb);
+    }
+    poly = poly_plan(c, 4 + c->n_extra, (double)mrows / (double)c->np);
   }
   if (record_tape && k0 == 0)
     FQ_HIP(c, hipMemcpyAsync(c->tape, c->xr, plane2 / 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -1172,10 +1412,12 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
     FQ_HIP(c, hipMemcpyAsync(c->tape + plane2 / 2, c->xi, plane2 / 2 * sizeof(double),
                              hipMemcpyDeviceToDevice, c->stream));
   for (int k = k0; k < k1; ++k) {
-    fq_status st = dense_heff(c, k);
-    if (st != FQ_OK) return st;
-    st = dense_cheb_step(c, mrows);
-    if (st != FQ_OK) return st;
+    if (poly.s) {
+      FQ_TRY(dense_poly_step(c, poly, k, mrows));
+    } else {
+      FQ_TRY(dense_heff(c, k));
+      FQ_TRY(dense_cheb_step(c, mrows));
+    }
     if (c->snap && (k + 1 - c->snap_k0) % c->snap_every == 0) {  // X_{k+1} to the user's buffer
       const long j = (k + 1 - c->snap_k0) / c->snap_every - 1;
       char* dst = static_cast<char*>(c->snap) +
@@ -1217,7 +1459,7 @@ fq_status reorthonormalize(fq_ctx* c) {
   for (int it = 0; it < 2; ++it) {
     FQ_HIP(c, fq::launch_zgemm_nt_f64(c->xr, c->xi, false, c->xr, c->xi, true, c->par, c->pai, np,
                                       np, np, np, 1.0, 0.0, 0.0, 0.0, c->stream));
-    FQ_HIP(c, fq::launch_transpose_planar(c->xr, c->xi, c->pbr, c->pbi, c->np, c->stream));
+    FQ_HIP(c, fq::launch_transpose_planar(c->xr, c->xi, c->pbr, c->pbi, c->np, 0, 1, c->stream));
     FQ_HIP(c, hipMemcpyAsync(c->yr, c->xr, p2bytes, hipMemcpyDeviceToDevice, c->stream));
     FQ_HIP(c, fq::launch_zgemm_nt_f64(c->par, c->pai, false, c->pbr, c->pbi, false, c->yr, c->yi,
                                       np, np, np, np, -0.5, 0.0, 1.5, 0.0, c->stream));
@@ -1860,6 +2102,50 @@ fq_status fq_workspace_bytes(const fq_system* sys, const fq_params* par, size_t*
   return FQ_OK;
 }
 
+// The matrices of H_eff and their weights per (sub)step: slot 0 H0, then Hmod
+// and K, the drive block, or Hmod and the nine nested commutators. A matrix
+// whose weight vanishes in every step is left out of the sum.
+static fq_status upload_heff_weights(fq_ctx* c) {
+  const size_t plane = (size_t)c->np * (size_t)c->np;
+  std::vector<double> w((size_t)fq::kHeffTerms * c->M, 0.0);
+  std::vector<std::pair<const double*, const double*>> ops{{c->h0r, c->h0i}};
+  if (c->S > 1) {
+    for (int j = 0; j < c->J; ++j) ops.push_back({c->vr + j * plane, c->vi + j * plane});
+  } else {
+    ops.push_back({c->vr, c->vi});
+    if (c->scheme == FQ_MAGNUS6)
+      for (int j = 0; j < kComm6; ++j)
+        ops.push_back({c->comm6 + 2 * plane * j, c->comm6 + 2 * plane * j + plane});
+    else
+      ops.push_back({c->kr, c->ki});
+  }
+  for (int k = 0; k < c->M; ++k) {
+    double* wk = &w[(size_t)fq::kHeffTerms * k];
+    wk[0] = 1.0;
+    if (c->S > 1) {
+      std::copy_n(&c->wS[(size_t)c->J * k], c->J, wk + 1);
+    } else {
+      wk[1] = c->a[k];
+      if (c->scheme == FQ_MAGNUS6)
+        std::copy_n(&c->w6[(size_t)kComm6 * k], kComm6, wk + 2);
+      else
+        wk[2] = c->b[k];
+    }
+  }
+  c->heff_ops.clear();
+  c->heff_slot.clear();
+  for (int j = 0; j < (int)ops.size(); ++j) {
+    bool used = false;
+    for (int k = 0; k < c->M && !used; ++k) used = w[(size_t)fq::kHeffTerms * k + j] != 0.0;
+    if (!used) continue;
+    c->heff_ops.push_back(ops[j]);
+    c->heff_slot.push_back(j);
+  }
+  FQ_HIP(c, copy_sync(c->stream, c->d_w, w.data(), w.size() * sizeof(double),
+                      hipMemcpyHostToDevice));
+  return FQ_OK;
+}
+
 // Everything that follows from the drive samples: the per-(sub)step weights,
 // the spectral interval (the caller's, checked against the drive's bounds, or
 // the library's cover), beta, dE, R, the order L (unless fixed), the Bessel
@@ -1968,6 +2254,7 @@ fq_status apply_drive(fq_ctx* c, const double* f_nodes) {
   if (c->precision != FQ_FP64 && c->layout == FQ_DENSE) choose_schedule(c);
   c->phr = std::cos(c->beta * c->h);
   c->phi = -std::sin(c->beta * c->h);
+  if (c->layout == FQ_DENSE) FQ_TRY(upload_heff_weights(c));
   std::vector<double> ab(2 * c->M);
   for (int k = 0; k < c->M; ++k) {
     ab[2 * k] = c->a[k];
@@ -2067,6 +2354,15 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     if (par->precision != FQ_FP64) c->htx = P(lay.off_htx);
     if (par->precision != FQ_FP64) c->pcr = P(lay.off_pc);
     if (par->scheme == FQ_MAGNUS6) c->comm6 = P(lay.off_comm6);
+    c->d_w = P(lay.off_w);
+    if (lay.pool_mats > 0) {
+      c->pool = P(lay.off_pool);
+      c->pool_mats = lay.pool_mats;
+    }
+    if (lay.n_extra > 0) {
+      c->extra = P(lay.off_extra);
+      c->n_extra = lay.n_extra;
+    }
     if (lay.n_tape > 0) {
       c->tape = P(lay.off_tape);
       c->n_tape = lay.n_tape;
@@ -2086,7 +2382,7 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     delete c;
     return s;
   };
-  if (zero_async(c->stream, c->ws, lay.total) != hipSuccess)
+  if (zero_async(c->stream, c->ws, lay.zeroed) != hipSuccess)
     return bail(fail(FQ_ERR_HIP, "zeroing the workspace failed"));
 
   const long n = c->n;
@@ -2172,7 +2468,9 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
   if (c->layout == FQ_DENSE) {
     FQ_HIP(c, fq::launch_identity_rows(c->xr, c->xi, c->n, c->np, c->np, c->stream));
     if (e0) FQ_HIP(c, hipEventRecord(e0, c->stream));
+    c->from_identity = true;
     st = dense_steps(c, 0, c->M, (int)c->np, c->ckpt > 0);
+    c->from_identity = false;
     if (st != FQ_OK) return st;
     FQ_MARK(c, -1);
     if (e1) FQ_HIP(c, hipEventRecord(e1, c->stream));

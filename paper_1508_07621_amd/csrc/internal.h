@@ -81,9 +81,14 @@ struct SmallChain {
   long ld;                                     // np (must be 64)
   int n, L, k0, k1;
   double beta, inv_dE, phr, phi;
+  // nseg > 1: the steps k0+1 .. k1 in nseg segments (the first rem of len0 + 1
+  // steps, the others of len0), each propagating the identity into planes at
+  // xr + z * bs, xi + z * bs
+  int len0, rem;
+  long bs;
 };
 long small_chain_max_n();
-hipError_t launch_small_chain(const SmallChain& c, int mrows, hipStream_t s);
+hipError_t launch_small_chain(const SmallChain& c, int mrows, int nseg, hipStream_t s);
 
 // The same two adjoint products on FP32 matrix cores (FQ_FP32 contexts): A in
 // FP64 planes (re plane, im plane at + plane_a elements) rounded to FP32 while
@@ -181,14 +186,49 @@ hipError_t launch_unpack_planar_t(const double* re, const double* im, long ld, l
                                   long cols, void* dst, long ld_dst, bool c64, hipStream_t s);
 // Rows [0, m) x [0, ld) of the state-major planes set to the n x n identity (zero padding).
 hipError_t launch_identity_rows(double* re, double* im, long n, long m, long ld, hipStream_t s);
-// Rescaled Hamiltonian Ht = (H0 + a V + b K - beta 1) / dE on the n x n block.
-hipError_t launch_heff_f64(const double* h0r, const double* h0i, const double* vr,
-                           const double* vi, const double* kr, const double* ki, double a,
-                           double b, double beta, double dE, long n, long ld, double* hr,
-                           double* hi, hipStream_t s);
-// dst = src^T for np x np planar pairs (dst must not alias src).
+// Rescaled Hamiltonians Ht_z = (sum_j w[k_z][slot_j] M_j - beta 1) / dE on the
+// n x n block, z < batch, written to out + z * bs (re plane, then im plane).
+// k_z = z len0 + min(z, rem) + t: step t of segment z when the chain is cut into
+// segments (a single one: len0 = rem = 0). w: device, kHeffTerms weights per step.
+constexpr int kHeffTerms = 16;
+struct HeffSum {
+  const double* re[kHeffTerms];
+  const double* im[kHeffTerms];
+  int slot[kHeffTerms];  // weight of M_j
+  int count;
+  int len0, rem;
+};
+hipError_t launch_heff_f64(const HeffSum& h, const double* w, int t, int batch, double beta,
+                           double dE, long n, long ld, double* out, long bs, hipStream_t s);
+
+// ---- a step's propagator as a matrix polynomial -----------------------------------------------
+// exp(-i h H) = sum_l c_l T_l(Ht) in blocks of s terms by Clenshaw's recurrence
+// in T_s(Ht). All matrices are planar pairs (im plane np * np after the re
+// plane), member z of a batch at + z * bs.
+constexpr int kPolyMaxS = 6, kPolyMaxBlocks = 4;
+// out = 2 T_a T_b - sub (sub null: the identity), Hermitian.
+hipError_t launch_poly_t(const double* ta, const double* tb, const double* sub, double* out, int n,
+                         int np, long bs, int batch, hipStream_t s);
+// Q_q = sum_{l <= s} g_ql T_l, q < J (a Q may overwrite a T).
+struct PolyCombine {
+  const double* t[kPolyMaxS];
+  double* q[kPolyMaxBlocks];
+  double gr[kPolyMaxBlocks][kPolyMaxS + 1], gi[kPolyMaxBlocks][kPolyMaxS + 1];
+  int s, J;
+};
+hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, int batch,
+                               hipStream_t s);
+// out += f W T_s - sub (sub optional; W a polynomial of the same matrix).
+hipError_t launch_poly_block(const double* w, const double* ts, double f, const double* sub,
+                             double* out, int np, long bs, int batch, hipStream_t s);
+// State-major blocks times operators: out(j, i) = sum_k x(j, k) E(i, k) over rows
+// [0, mrows); e_trans: E is stored state-major, E(i, k) at row k, column i.
+hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,
+                             double* out, long o_bs, int mrows, int np, int batch, hipStream_t s);
+// dst = src^T for np x np planar pairs (dst must not alias src), member z of a
+// batch at + z * bs.
 hipError_t launch_transpose_planar(const double* sr, const double* si, double* dr, double* di,
-                                   long np, hipStream_t s);
+                                   long np, long bs, int batch, hipStream_t s);
 // t = d * s elementwise on count planar complex elements.
 hipError_t launch_scale_planar(const double* sr, const double* si, double dr, double di,
                                double* tr, double* ti, long count, hipStream_t s);

@@ -111,6 +111,76 @@ struct EpiUnitarity {
   }
 };
 
+// ---- step operators as matrix polynomials ------------------------------------------------------
+// All matrices of a batch lie at base + z * bs, re plane then im plane.
+
+// T_{a+b} = 2 T_a T_b - T_{|a-b|} (T_0 = 1 on the n x n block when sub is null);
+// Hermitian, so an element above the diagonal is also written below it.
+struct EpiPolyT {
+  double* o;
+  const double* sub;
+  long ld, plane, bs;
+  int n;
+  __device__ __forceinline__ void batch(int z) {
+    o += z * bs;
+    if (sub) sub += z * bs;
+  }
+  __device__ __forceinline__ void herm(int m, int c, double ar, double ai, bool mirror) const {
+    const long idx = (long)m * ld + c;
+    double r = 2.0 * ar, i = 2.0 * ai;
+    if (sub) {
+      r -= sub[idx];
+      i -= sub[plane + idx];
+    } else if (m == c && m < n) {
+      r -= 1.0;
+    }
+    o[idx] = r;
+    o[plane + idx] = i;
+    if (mirror) {
+      const long tdx = (long)c * ld + m;
+      o[tdx] = r;
+      o[plane + tdx] = -i;
+    }
+  }
+  __device__ __forceinline__ void finish() const {}
+};
+
+// Clenshaw block: O += f * acc - S (S optional).
+struct EpiPolyBlock {
+  double* o;
+  const double* sub;
+  long ld, plane, bs;
+  double f;
+  __device__ __forceinline__ void batch(int z) {
+    o += z * bs;
+    if (sub) sub += z * bs;
+  }
+  __device__ __forceinline__ void operator()(int m, int c, double ar, double ai) const {
+    const long idx = (long)m * ld + c;
+    double r = fma(f, ar, o[idx]), i = fma(f, ai, o[plane + idx]);
+    if (sub) {
+      r -= sub[idx];
+      i -= sub[plane + idx];
+    }
+    o[idx] = r;
+    o[plane + idx] = i;
+  }
+  __device__ __forceinline__ void finish() const {}
+};
+
+// O = acc.
+struct EpiPolyStore {
+  double* o;
+  long ld, plane, bs;
+  __device__ __forceinline__ void batch(int z) { o += z * bs; }
+  __device__ __forceinline__ void operator()(int m, int c, double ar, double ai) const {
+    const long idx = (long)m * ld + c;
+    o[idx] = ar;
+    o[plane + idx] = ai;
+  }
+  __device__ __forceinline__ void finish() const {}
+};
+
 // ---- adjoint epilogues -----------------------------------------------------------------------
 // A "stack" holds two state-major blocks as one 2np-row operand: rows [0, np)
 // the forward term P_l, rows [np, 2np) the adjoint term Pbar_{l+1}.
@@ -133,7 +203,7 @@ inline bool take_tile64(long t64, long t32) {
 }
 
 // C_z(m, n) over mrows x ncols (multiples of 64) for `batch` operand pairs.
-template <bool CONJ_A, bool CONJ_B, class Epi>
+template <bool CONJ_A, bool CONJ_B, bool TRANS_B = false, class Epi>
 hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi epi,
                        hipStream_t s) {
   if (mrows % 64 != 0 || ncols % 64 != 0 || op0.kdim % 16 != 0 || batch < 1 || batch > 65535)
@@ -143,13 +213,13 @@ hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi
   if (take_tile64(t64, 4 * t64)) {
     op.tiles_m = mrows / 64;
     op.tiles_n = ncols / 64;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, true, false,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, TRANS_B, true, false,
                                             4, Epi>),
                        dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(512), 0, s, op, epi);
   } else {
     op.tiles_m = mrows / 32;
     op.tiles_n = ncols / 32;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, true, false,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, TRANS_B, true, false,
                                             1, Epi>),
                        dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(256), 0, s, op, epi);
   }
@@ -165,11 +235,11 @@ hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hip
   const long a = np / 64, b = np / 32;
   const long t64 = a * (a + 1) / 2, t32 = b * (b + 1) / 2;
   if (take_tile64(t64 * batch, t32 * batch))
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, true, true, 4,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, false, true, true, 4,
                                             Epi>),
                        dim3(t64, batch), dim3(512), 0, s, op0, epi);
   else
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, true, true, 1,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, false, true, true, 1,
                                             Epi>),
                        dim3(t32, batch), dim3(256), 0, s, op0, epi);
   return hipGetLastError();
@@ -177,21 +247,73 @@ hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hip
 
 // ---- O(N^2) helpers ----------------------------------------------------------------------------
 
-__global__ void heff_kernel(const double* __restrict__ h0r, const double* __restrict__ h0i,
-                            const double* __restrict__ vr, const double* __restrict__ vi,
-                            const double* __restrict__ kr, const double* __restrict__ ki,
-                            double a, double b, double beta, double inv_dE, long n, long ld,
-                            double* __restrict__ hr, double* __restrict__ hi) {
-  const long total = n * ld;
+// Ht_z = (sum_j w_j(k) M_j - beta) / dE for the step k of every batch member z,
+// two elements of a row per thread. Bound by HBM (or L2 for the small batched
+// sizes): the planes of the operators in use are read once per member, Ht is
+// written once. Operators whose weight vanishes over the whole drive (the
+// commutator of a commutator-free scheme) are not in the list.
+__global__ __launch_bounds__(256) void heff_kernel(HeffSum h, const double* __restrict__ w, int t,
+                                                   double beta, double inv_dE, long n, long ld,
+                                                   double* __restrict__ out, long bs) {
+  const int z = blockIdx.y;
+  const long k = (long)z * h.len0 + (z < h.rem ? z : h.rem) + t;
+  const double* wk = w + k * kHeffTerms;
+  const long plane = ld * ld;
+  double* o = out + z * bs;
+  const long half = ld / 2, total = ld * half;  // padding included: zero in the operators
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total;
        e += (long)gridDim.x * blockDim.x) {
-    const long i = e / ld, k = e % ld;
-    if (k >= n) continue;
-    double re = h0r[e] + a * vr[e] + b * kr[e];
-    const double im = h0i[e] + a * vi[e] + b * ki[e];
-    if (i == k) re -= beta;
-    hr[e] = re * inv_dE;
-    hi[e] = im * inv_dE;
+    const long i = e / half, c = 2 * (e - i * half), idx = i * ld + c;
+    double r0 = 0.0, r1 = 0.0, i0 = 0.0, i1 = 0.0;
+    for (int j = 0; j < h.count; ++j) {
+      const double wj = wk[h.slot[j]];
+      const d2 a = *reinterpret_cast<const d2*>(h.re[j] + idx);
+      const d2 b = *reinterpret_cast<const d2*>(h.im[j] + idx);
+      r0 = fma(wj, a[0], r0);
+      r1 = fma(wj, a[1], r1);
+      i0 = fma(wj, b[0], i0);
+      i1 = fma(wj, b[1], i1);
+    }
+    if (i == c && i < n) r0 -= beta;
+    if (i == c + 1 && i < n) r1 -= beta;
+    *reinterpret_cast<d2*>(o + idx) = d2{r0 * inv_dE, r1 * inv_dE};
+    *reinterpret_cast<d2*>(o + plane + idx) = d2{i0 * inv_dE, i1 * inv_dE};
+  }
+}
+
+// Q_q = sum_{l=0..s} g_ql T_l for q < J, elementwise (T_0 = 1 on the n x n
+// block); a Q may take the place of a T. Each T is read and each Q written once,
+// padding included (the buffer of a Q may have held anything there).
+__global__ __launch_bounds__(256) void poly_combine_kernel(PolyCombine p, long n, long ld, long bs) {
+  const long plane = ld * ld;
+  const long zo = blockIdx.y * bs;
+  const long half = ld / 2, total = ld * half;
+  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total;
+       e += (long)gridDim.x * blockDim.x) {
+    const long i = e / half, c = 2 * (e - i * half), idx = zo + i * ld + c;
+    d2 qr[kPolyMaxBlocks], qi[kPolyMaxBlocks];
+#pragma unroll
+    for (int q = 0; q < kPolyMaxBlocks; ++q) {
+      const double d0 = i == c && i < n ? 1.0 : 0.0, d1 = i == c + 1 && i < n ? 1.0 : 0.0;
+      qr[q] = d2{p.gr[q][0] * d0, p.gr[q][0] * d1};
+      qi[q] = d2{p.gi[q][0] * d0, p.gi[q][0] * d1};
+    }
+    for (int l = 1; l <= p.s; ++l) {
+      const d2 a = *reinterpret_cast<const d2*>(p.t[l - 1] + idx);
+      const d2 b = *reinterpret_cast<const d2*>(p.t[l - 1] + plane + idx);
+#pragma unroll
+      for (int q = 0; q < kPolyMaxBlocks; ++q) {
+        const double gr = p.gr[q][l], gi = p.gi[q][l];
+        qr[q] += gr * a - gi * b;
+        qi[q] += gr * b + gi * a;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPolyMaxBlocks; ++q)
+      if (q < p.J) {
+        *reinterpret_cast<d2*>(p.q[q] + idx) = qr[q];
+        *reinterpret_cast<d2*>(p.q[q] + plane + idx) = qi[q];
+      }
   }
 }
 
@@ -412,8 +534,11 @@ __global__ void fill_zero_kernel(double* __restrict__ p, long count) {
 // ---------------------------------------------------------------------------------------
 // Whole chain for N <= 64 in one launch. The columns of U_T are independent
 // propagations (Sec. 5: the identity is split into blocks of columns), so each
-// workgroup takes 16 states (rows of the state-major block) through every
-// step on its own: per step it forms Ht_k = (H0 + a_k V + b_k K - beta) / dE in
+// workgroup takes 16 states (rows of the state-major block) through its steps
+// on its own. A build splits the chain into gridDim.y segments of consecutive
+// steps, each propagating the identity (16 N CUs alone would work otherwise:
+// 2274 us per 100-step build in one segment); the segments' operators are multiplied up
+// afterwards. Per step a workgroup forms Ht_k = (H0 + a_k V + b_k K - beta) / dE in
 // LDS, runs the L Chebyshev terms with its 16 x 64 block of P_{l-1}, P_l in
 // LDS, keeps its share of the sum Y in registers, and ends the step with
 // X_k = exp(-i beta h) Y in LDS. One barrier per term, none between
@@ -434,17 +559,25 @@ __global__ __launch_bounds__(256) void small_chain_kernel(SmallChain c) {
   const int s0 = blockIdx.x * kSmallS;                    // first state of this workgroup
   const int n = c.n;
   const long ld = c.ld;
+  // this segment's steps; segments other than a single one start from the identity
+  const int seg = blockIdx.y;
+  const int k_lo = c.k0 + seg * c.len0 + (seg < c.rem ? seg : c.rem);
+  const int k_hi = gridDim.y > 1 ? k_lo + c.len0 + (seg < c.rem ? 1 : 0) : c.k1;
+  double* const xre = c.xr + seg * c.bs;
+  double* const xim = c.xi + seg * c.bs;
   // the block of X (rows s0 .. s0 + 15 of the state-major planes) into buffer 0
   for (int e = tid; e < kSmallS * kSmallN; e += 256) {
     const int s = e / kSmallN, k = e % kSmallN;
-    ps[0][0][s * kSmallLd + k] = c.xr[(long)(s0 + s) * ld + k];
-    ps[0][1][s * kSmallLd + k] = c.xi[(long)(s0 + s) * ld + k];
+    const bool one = s0 + s == k && k < n;
+    ps[0][0][s * kSmallLd + k] =
+        gridDim.y > 1 ? (one ? 1.0 : 0.0) : xre[(long)(s0 + s) * ld + k];
+    ps[0][1][s * kSmallLd + k] = gridDim.y > 1 ? 0.0 : xim[(long)(s0 + s) * ld + k];
   }
   const int ci = 16 * wave + (lane & 15);  // output column i of this lane
   const int kq = lane >> 4;                // k within a 4-step of the matrix cores
   const int L = c.L;
   int cur = 0;                             // buffer holding X_k (then P_l)
-  for (int k = c.k0; k < c.k1; ++k) {
+  for (int k = k_lo; k < k_hi; ++k) {
     const double a = c.ab[2 * k], b = c.ab[2 * k + 1];
     __syncthreads();  // the previous step's last writes; Ht no longer read
     for (int e = tid; e < kSmallN * kSmallN; e += 256) {
@@ -524,8 +657,8 @@ __global__ __launch_bounds__(256) void small_chain_kernel(SmallChain c) {
   __syncthreads();
   for (int e = tid; e < kSmallS * kSmallN; e += 256) {
     const int s = e / kSmallN, k = e % kSmallN;
-    c.xr[(long)(s0 + s) * ld + k] = ps[cur][0][s * kSmallLd + k];
-    c.xi[(long)(s0 + s) * ld + k] = ps[cur][1][s * kSmallLd + k];
+    xre[(long)(s0 + s) * ld + k] = ps[cur][0][s * kSmallLd + k];
+    xim[(long)(s0 + s) * ld + k] = ps[cur][1][s * kSmallLd + k];
   }
 }
 
@@ -540,8 +673,13 @@ inline unsigned grid_for(long total, int block) {
 __global__ __launch_bounds__(256) void transpose_planar_kernel(const double* __restrict__ sr,
                                                                const double* __restrict__ si,
                                                                double* __restrict__ dr,
-                                                               double* __restrict__ di, long np) {
+                                                               double* __restrict__ di, long np,
+                                                               long bs) {
   __shared__ double tr[32][33], ti[32][33];
+  sr += blockIdx.z * bs;
+  si += blockIdx.z * bs;
+  dr += blockIdx.z * bs;
+  di += blockIdx.z * bs;
   const long bi = blockIdx.y * 32L, bj = blockIdx.x * 32L;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
   for (int r = ty; r < 32; r += 8) {
@@ -646,13 +784,47 @@ hipError_t launch_identity_rows(double* re, double* im, long n, long m, long ld,
   return hipGetLastError();
 }
 
-hipError_t launch_heff_f64(const double* h0r, const double* h0i, const double* vr,
-                           const double* vi, const double* kr, const double* ki, double a,
-                           double b, double beta, double dE, long n, long ld, double* hr,
-                           double* hi, hipStream_t s) {
-  hipLaunchKernelGGL(heff_kernel, dim3(grid_for(n * ld, 256)), dim3(256), 0, s, h0r, h0i, vr, vi,
-                     kr, ki, a, b, beta, 1.0 / dE, n, ld, hr, hi);
+hipError_t launch_heff_f64(const HeffSum& h, const double* w, int t, int batch, double beta,
+                           double dE, long n, long ld, double* out, long bs, hipStream_t s) {
+  if (h.count < 1 || h.count > kHeffTerms || batch < 1 || batch > 65535 || ld % 2 != 0)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(heff_kernel, dim3(grid_for(ld * (ld / 2), 256), batch), dim3(256), 0, s, h, w,
+                     t, beta, 1.0 / dE, n, ld, out, bs);
   return hipGetLastError();
+}
+
+hipError_t launch_poly_t(const double* ta, const double* tb, const double* sub, double* out, int n,
+                         int np, long bs, int batch, hipStream_t s) {
+  const long plane = (long)np * np;
+  // T_b(k, c) = conj(T_b(c, k))
+  Operands op{ta, ta + plane, tb, tb + plane, np, np, 0, 0, bs, bs};
+  return launch_gemm_herm<false, true>(op, np, batch, EpiPolyT{out, sub, np, plane, bs, n}, s);
+}
+
+hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, int batch,
+                               hipStream_t s) {
+  if (p.s < 1 || p.s > kPolyMaxS || p.J < 1 || p.J > kPolyMaxBlocks || batch < 1 || batch > 65535)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(poly_combine_kernel, dim3(grid_for(ld * (ld / 2), 256), batch), dim3(256), 0,
+                     s, p, n, ld, bs);
+  return hipGetLastError();
+}
+
+hipError_t launch_poly_block(const double* w, const double* ts, double f, const double* sub,
+                             double* out, int np, long bs, int batch, hipStream_t s) {
+  const long plane = (long)np * np;
+  // W T_s = T_s W (both are polynomials of Ht), T_s Hermitian
+  Operands op{w, w + plane, ts, ts + plane, np, np, 0, 0, bs, bs};
+  return launch_gemm<false, true>(op, np, np, batch, EpiPolyBlock{out, sub, np, plane, bs, f}, s);
+}
+
+hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,
+                             double* out, long o_bs, int mrows, int np, int batch, hipStream_t s) {
+  const long plane = (long)np * np;
+  Operands op{x, x + plane, e, e + plane, np, np, 0, 0, x_bs, e_bs};
+  const EpiPolyStore epi{out, np, plane, o_bs};
+  return e_trans ? launch_gemm<false, false, true>(op, mrows, np, batch, epi, s)
+                 : launch_gemm<false, false>(op, mrows, np, batch, epi, s);
 }
 
 hipError_t launch_scale_planar(const double* sr, const double* si, double dr, double di,
@@ -704,11 +876,14 @@ hipError_t launch_diag_commutator(const double* e, long n, long ld, const double
 
 long small_chain_max_n() { return kSmallN; }
 
-hipError_t launch_small_chain(const SmallChain& c, int mrows, hipStream_t s) {
+hipError_t launch_small_chain(const SmallChain& c, int mrows, int nseg, hipStream_t s) {
+  if (nseg < 1 || nseg > 65535 ||
+      (nseg > 1 && (long)nseg * c.len0 + c.rem != (long)c.k1 - c.k0))
+    return hipErrorInvalidValue;
   if (c.ld != kSmallN || mrows < kSmallS || mrows % kSmallS || mrows > kSmallN || c.n > kSmallN ||
       c.L < 1 || c.k0 < 0 || c.k1 < c.k0)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(small_chain_kernel, dim3(mrows / kSmallS), dim3(256), 0, s, c);
+  hipLaunchKernelGGL(small_chain_kernel, dim3(mrows / kSmallS, nseg), dim3(256), 0, s, c);
   return hipGetLastError();
 }
 
@@ -729,10 +904,12 @@ hipError_t launch_weighted_sum(const WeightedSum& ws, long total, double* outr, 
 }
 
 hipError_t launch_transpose_planar(const double* sr, const double* si, double* dr, double* di,
-                                   long np, hipStream_t s) {
-  if (np < 32 || np % 32 != 0 || np / 32 > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(transpose_planar_kernel, dim3((unsigned)(np / 32), (unsigned)(np / 32)),
-                     dim3(256), 0, s, sr, si, dr, di, np);
+                                   long np, long bs, int batch, hipStream_t s) {
+  if (np < 32 || np % 32 != 0 || np / 32 > 65535 || batch < 1 || batch > 65535)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(transpose_planar_kernel,
+                     dim3((unsigned)(np / 32), (unsigned)(np / 32), (unsigned)batch), dim3(256), 0,
+                     s, sr, si, dr, di, np, bs);
   return hipGetLastError();
 }
 

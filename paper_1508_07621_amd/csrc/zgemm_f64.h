@@ -60,8 +60,12 @@ __device__ __forceinline__ void tri_coords(int t, int& tm, int& tn) {
 //
 // HERM: C is known to be Hermitian: the grid holds the tiles on and above the
 // diagonal and the epilogue writes each element above it twice.
-template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, bool GAUSS,
-          bool HERM, int MINW, class Epi>
+//
+// TRANS_B: B is stored transposed, B_z(n, k) at row k, column n (so that
+// C = A B^T reads a state-major block as the operator it stands for); the
+// staging transposes it on the way into LDS.
+template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, bool TRANS_B,
+          bool GAUSS, bool HERM, int MINW, class Epi>
 __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Operands op, Epi epi) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -112,9 +116,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   for (int r = 0; r < RC; ++r) {
     const int c = tid + r * NT, row = c / CPR, col = 2 * (c % CPR);
     const bool is_a = row < BM;
-    const long off = is_a ? (long)(m0 + row) * ld + col + blockIdx.y * op.a_bs
+    long off = is_a ? (long)(m0 + row) * ld + col + blockIdx.y * op.a_bs
                     : (long)(n0 + row - BM) * ld + col + blockIdx.y * op.b_bs;
     lo[r] = row * S + col;
+    if (TRANS_B && !is_a) {  // chunk: columns n, n + 1 of one row k
+      const int cb = c - BM * CPR, kr = cb / (BN / 2), nc = 2 * (cb % (BN / 2));
+      off = (long)kr * ld + n0 + nc + blockIdx.y * op.b_bs;
+      lo[r] = (BM + nc) * S + kr;
+    }
     gr[r] = (is_a ? op.ar : op.br) + off;
     gi[r] = (is_a ? op.ai : op.bi) + off;
     of_a[r] = is_a;
@@ -123,8 +132,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   auto gload = [&](int k0) {
 #pragma unroll
     for (int r = 0; r < RC; ++r) {
-      vr[r] = *reinterpret_cast<const d2*>(gr[r] + k0);
-      vi[r] = *reinterpret_cast<const d2*>(gi[r] + k0);
+      const long step = TRANS_B && !of_a[r] ? (long)k0 * ld : (long)k0;
+      vr[r] = *reinterpret_cast<const d2*>(gr[r] + step);
+      vi[r] = *reinterpret_cast<const d2*>(gi[r] + step);
     }
   };
   auto lstore = [&](int st) {
@@ -132,8 +142,15 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
     for (int r = 0; r < RC; ++r) {
       const bool neg = of_a[r] ? CONJ_A : CONJ_B;
       const d2 im = neg ? -vi[r] : vi[r];
-      *reinterpret_cast<d2*>(&sh[st][0][lo[r]]) = vr[r];
-      *reinterpret_cast<d2*>(&sh[st][1][lo[r]]) = im;
+      if (TRANS_B && !of_a[r]) {
+        sh[st][0][lo[r]] = vr[r][0];
+        sh[st][0][lo[r] + S] = vr[r][1];
+        sh[st][1][lo[r]] = im[0];
+        sh[st][1][lo[r] + S] = im[1];
+      } else {
+        *reinterpret_cast<d2*>(&sh[st][0][lo[r]]) = vr[r];
+        *reinterpret_cast<d2*>(&sh[st][1][lo[r]]) = im;
+      }
     }
   };
 

@@ -51,3 +51,43 @@ def test_fp64_products_on_both_tiles(fl, n):
     assert err < M * 1e-12 + 1e-13
     assert abs(rep["unitarity_max"] - G.abs().max().item()) < 1e-13
     assert abs(rep["unitarity_fro"] - torch.linalg.norm(G).item()) < 1e-13 * math.sqrt(n)
+
+
+def _build_and_block(fl, n, M, L, T=1.2):
+    """U_T by build_ut and by propagating the identity block, and the oracle's."""
+    rng = np.random.default_rng(7 * n + L)
+    H0, V = gue(n, rng), gue(n, rng)
+    f = np.cos(fl.node_times(T, M))
+    a, b = orc.magnus4_weights(f, T / M)
+    lo, hi = orc.weyl_cover(H0, V, orc.commutator(H0, V), a, b)
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f, e_min=lo, e_max=hi, L=L)
+    U = ctx.build_ut().cpu().numpy()
+    X = ctx.propagate(np.eye(n, dtype=complex)).cpu().numpy()
+    ref = orc.build_ut(H0, V, f, T, M, route="cheb", e_min=lo, e_max=hi, L=L)
+    return U, X, ref
+
+
+# every block length and block count of the polynomial form (2 .. 20 terms in
+# a build's segments, 2 .. 12 for a single step), the term-by-term form on
+# either side of it, and a top block of one coefficient (L a multiple of s).
+# All factors have norm at most 1 (|c_l| <= 1, |T_l| <= 1), so rounding is of
+# the order of L M n eps < 1e-12 in the worst column.
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 15, 16, 17, 20, 21])
+def test_step_polynomials_of_every_order(fl, L):
+    print("[case] polynomial order", L, flush=True)
+    U, X, ref = _build_and_block(fl, 70, 5, L)
+    eu, ex = orc.column_error(U, ref), orc.column_error(X, ref)
+    print("[case] build", eu, "block", ex, flush=True)
+    assert eu < 1e-12 and ex < 1e-12
+
+
+# segments of unequal length (512 padded states run 8 segments), one segment
+# per step and odd segment counts in the product of the segments
+@pytest.mark.parametrize("n,M", [(500, 11), (500, 8), (130, 7), (130, 2), (130, 1), (50, 130),
+                                 (50, 3)])
+def test_segmented_builds(fl, n, M):
+    print("[case] segments", n, M, flush=True)
+    U, X, ref = _build_and_block(fl, n, M, 9, T=0.1 * M)
+    eu, ex = orc.column_error(U, ref), orc.column_error(X, ref)
+    print("[case] build", eu, "block", ex, flush=True)
+    assert eu < 1e-12 and ex < 1e-12
