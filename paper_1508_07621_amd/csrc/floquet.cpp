@@ -895,6 +895,15 @@ fq_status cheb_launch(fq_ctx* c, int kind, int mrows, double* a, double* p, doub
   return FQ_OK;
 }
 
+// Rows of the state-major block the products of ncols states run on: FP64
+// products of up to 64 states take 1, 2, 4, 8 or blocks of 16 rows, the others
+// whole tiles (as does the one-launch chain at np = 64, in blocks of 16).
+long product_rows(const fq_ctx* c, long ncols) {
+  if (c->precision != FQ_FP64 || ncols > 64) return pad_to(ncols, dense_tile(c->n));
+  if (ncols > 8 || c->np == 64) return pad_to(ncols, 16);
+  return ncols > 4 ? 8 : (ncols > 2 ? 4 : ncols);
+}
+
 fq_status dense_cheb_step_mixed(fq_ctx* c, int mrows);
 
 // One step on the state-major block held in the X planes: X <- E_k X.
@@ -2547,7 +2556,8 @@ fq_status floquet_propagate(fq_ctx* c, const void* X0, int64_t ncols, int32_t k0
     const long mrows = pad_to(ncols, dense_tile(c->n));
     FQ_HIP(c, fq::launch_pack_planar_t(X0, c->n, ncols, ncols, c->xr, c->xi, c->np, mrows, c->c64,
                                        c->stream));
-    fq_status st = dense_steps(c, k0, k1, (int)mrows, false);
+    const long rows = product_rows(c, ncols);
+    fq_status st = dense_steps(c, k0, k1, (int)rows, false);
     if (st != FQ_OK) return st;
     FQ_MARK(c, -1);
     FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, ncols, X_out, ncols, c->c64,
@@ -2583,7 +2593,7 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
   FQ_HIP(c, fq::launch_fill_zero(c->d_vec, 3 * c->n, c->stream));
   if (c->layout == FQ_DENSE) {
     const int np = (int)c->np;
-    const long mrows = pad_to(ncols, dense_tile(c->n));
+    const long mrows = pad_to(ncols, dense_tile(c->n)), rows = product_rows(c, ncols);
     FQ_HIP(c, fq::launch_pack_planar_t(X0, c->n, ncols, ncols, c->xr, c->xi, c->np, mrows, c->c64,
                                        c->stream));
     for (int k = 0; k < c->M_user; ++k) {
@@ -2598,11 +2608,11 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
       ws.count = 1 + c->S;
       FQ_HIP(c, fq::launch_weighted_sum(ws, c->np * c->np, c->htr, c->hti, c->stream));
       FQ_HIP(c, fq::launch_zgemm_nt_f64(c->xr, c->xi, false, c->htr, c->hti, false, c->par,
-                                        c->pai, (int)mrows, np, np, np, 1.0, 0.0, 0.0, 0.0,
+                                        c->pai, (int)rows, np, np, np, 1.0, 0.0, 0.0, 0.0,
                                         c->stream));
       FQ_HIP(c, fq::launch_energy_rows(c->xr, c->xi, c->par, c->pai, ncols, c->n, c->np, w, avg,
                                        c->stream));
-      FQ_TRY(dense_steps(c, k * spp, (k + 1) * spp, (int)mrows, false));
+      FQ_TRY(dense_steps(c, k * spp, (k + 1) * spp, (int)rows, false));
     }
   } else {
     // the states in the user layout, propagated in place one step at a time

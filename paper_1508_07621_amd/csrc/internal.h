@@ -104,7 +104,7 @@ hipError_t launch_adj_dot_f32(const double* pr, long plane_a, const float* drive
 hipError_t launch_f64_to_f32(const double* src, float* dst, long count, hipStream_t s);
 
 // Launch one Chebyshev product over rows [0, mrows) of the state-major
-// operands (mrows, np multiples of the tile size chosen by the launcher).
+// operands (np a multiple of 64; mrows too, or one of 1, 2, 4, 8, 16, 32, 48).
 hipError_t launch_cheb_f64(const ChebTerm& t, int mrows, int np, hipStream_t s);
 
 // ---- mixed-precision products (kernels_mixed.hip) ------------------------------------------

@@ -202,12 +202,44 @@ inline bool take_tile64(long t64, long t32) {
   return c64 <= c32;
 }
 
+// Few rows of A: 1, 2, 4, 8 or 16 of them on the vector units, 32, 48 or 64 on
+// the matrix cores with one block of 16 rows per workgroup, or two once those
+// fill the chip (N = 2048, 64 rows: 58 us against 97 us with four blocks and 89 us
+// with 32 x 32 tiles; N = 4096: 186 us with two, 247 us with one). 16 rows as two
+// blocks of 8: 14 us at N = 1024 (17 us on the matrix cores), equal at 2048.
+template <class Epi>
+hipError_t launch_few(const Operands& op, int mrows, int ncols, Epi epi, hipStream_t s) {
+  const dim3 gs(ncols / 4, mrows > 8 ? mrows / 8 : 1);
+  switch (mrows) {
+    case 1: hipLaunchKernelGGL((zgemm_few_states_kernel<1, Epi>), gs, dim3(256), 0, s, op, epi); break;
+    case 2: hipLaunchKernelGGL((zgemm_few_states_kernel<2, Epi>), gs, dim3(256), 0, s, op, epi); break;
+    case 4: hipLaunchKernelGGL((zgemm_few_states_kernel<4, Epi>), gs, dim3(256), 0, s, op, epi); break;
+    case 8:
+    case 16: hipLaunchKernelGGL((zgemm_few_states_kernel<8, Epi>), gs, dim3(256), 0, s, op, epi); break;
+    case 32:
+    case 48:
+    case 64:
+      if ((long)(mrows / 16) * (ncols / 16) < 512)
+        hipLaunchKernelGGL((zgemm_few_rows_kernel<1, 16, Epi>), dim3(ncols / 16, mrows / 16),
+                           dim3(1024), 0, s, op, epi);
+      else  // (48 rows: the second block's upper half is scratch rows below 64)
+        hipLaunchKernelGGL((zgemm_few_rows_kernel<2, 8, Epi>), dim3(ncols / 16, (mrows + 16) / 32),
+                           dim3(512), 0, s, op, epi);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 // C_z(m, n) over mrows x ncols (multiples of 64) for `batch` operand pairs.
 template <bool CONJ_A, bool CONJ_B, bool TRANS_B = false, class Epi>
 hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi epi,
                        hipStream_t s) {
-  if (mrows % 64 != 0 || ncols % 64 != 0 || op0.kdim % 16 != 0 || batch < 1 || batch > 65535)
+  if (ncols % 64 != 0 || op0.kdim % 64 != 0 || batch < 1 || batch > 65535)
     return hipErrorInvalidValue;
+  if constexpr (!CONJ_A && !CONJ_B && !TRANS_B)
+    if (op0.few) return batch == 1 ? launch_few(op0, mrows, ncols, epi, s) : hipErrorInvalidValue;
+  if (mrows % 64 != 0) return hipErrorInvalidValue;
   Operands op = op0;
   const long t64 = (long)(mrows / 64) * (ncols / 64) * batch;
   if (take_tile64(t64, 4 * t64)) {
@@ -696,7 +728,7 @@ __global__ __launch_bounds__(256) void transpose_planar_kernel(const double* __r
 }  // namespace
 
 hipError_t launch_cheb_f64(const ChebTerm& t, int mrows, int np, hipStream_t s) {
-  Operands op{t.a_re, t.a_im, t.b_re, t.b_im, np, np, 0, 0, 0, 0};
+  Operands op{t.a_re, t.a_im, t.b_re, t.b_im, np, np, 0, 0, 0, 0, mrows <= 64 && mrows < np};
   switch (t.kind) {
     case CHEB_FIRST:
       return launch_gemm<false, false>(op, mrows, np, 1, EpiCheb<CHEB_FIRST>{t, np}, s);
@@ -731,7 +763,7 @@ hipError_t launch_zgemm_nt_f64(const double* ar, const double* ai, bool conj_a, 
                                const double* bi, bool conj_b, double* cr, double* ci, int mrows,
                                int ncols, int kdim, int ld, double alr, double ali, double ber,
                                double bei, hipStream_t s) {
-  Operands op{ar, ai, br, bi, ld, kdim, 0, 0, 0, 0};
+  Operands op{ar, ai, br, bi, ld, kdim, 0, 0, 0, 0, mrows <= 64 && mrows < ncols};
   EpiStore e{cr, ci, ld, alr, ali, ber, bei};
   if (conj_a && conj_b) return launch_gemm<true, true>(op, mrows, ncols, 1, e, s);
   if (conj_a) return launch_gemm<true, false>(op, mrows, ncols, 1, e, s);
@@ -821,7 +853,7 @@ hipError_t launch_poly_block(const double* w, const double* ts, double f, const 
 hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,
                              double* out, long o_bs, int mrows, int np, int batch, hipStream_t s) {
   const long plane = (long)np * np;
-  Operands op{x, x + plane, e, e + plane, np, np, 0, 0, x_bs, e_bs};
+  Operands op{x, x + plane, e, e + plane, np, np, 0, 0, x_bs, e_bs, mrows <= 64 && mrows < np};
   const EpiPolyStore epi{out, np, plane, o_bs};
   return e_trans ? launch_gemm<false, false, true>(op, mrows, np, batch, epi, s)
                  : launch_gemm<false, false>(op, mrows, np, batch, epi, s);

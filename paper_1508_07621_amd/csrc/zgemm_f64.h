@@ -32,6 +32,7 @@ struct Operands {
   int tiles_m;
   long a_bs;    // batch strides (elements) of A and B: operand z at + z * stride
   long b_bs;
+  bool few = false;  // few rows of A: take the kernels below rather than tiles
 };
 
 // Tile (tm, tn), tm <= tn, number t of the upper triangle of a tiles x tiles
@@ -245,6 +246,146 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
           epi(m, n, re, im);
       }
   epi.finish();
+}
+
+// The same product for 17 to 64 rows m (a few propagated states against a large
+// operator): a workgroup takes 16 FM rows of A and 16 rows of B, its W waves
+// share the reduction in steps of 8 k and meet in LDS, and fragments go straight
+// from global memory to registers. What bounds it is the vector memory path: a
+// fragment load touches 16 rows of 64 bytes (N = 2048, 16 rows: 31.8 us, the
+// same without the MFMAs, 18 us without the loads of A). Splitting the reduction over
+// workgroups as well loses to the device-scope fences that takes (124 us).
+template <int FM, int W, class Epi>
+__global__ __launch_bounds__(W * 64) void zgemm_few_rows_kernel(Operands op, Epi epi) {
+  __shared__ double red[W][FM * 8][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = blockIdx.y * 16 * FM, n0 = blockIdx.x * 16;
+  const int rr = lane & 15, kp = 2 * (lane >> 4);
+  const long ld = op.ld;
+  const int units = op.kdim / 8;
+  const double* br = op.br + (long)(n0 + rr) * ld + kp;
+  const double* bi = op.bi + (long)(n0 + rr) * ld + kp;
+  const double* ar = op.ar + (long)(m0 + rr) * ld + kp;
+  const double* ai = op.ai + (long)(m0 + rr) * ld + kp;
+  d4 a1[FM], a2[FM], a3[FM];  // T1, T2, T3 of Gauss's three products
+#pragma unroll
+  for (int i = 0; i < FM; ++i) a1[i] = a2[i] = a3[i] = d4{0, 0, 0, 0};
+#pragma unroll 8 / FM
+  for (int u = wave; u < units; u += W) {
+    const long k = 8L * u;
+    const d2 fbr = *reinterpret_cast<const d2*>(br + k);
+    const d2 fbi = *reinterpret_cast<const d2*>(bi + k);
+    const d2 fbs = fbr + fbi;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const d2 fr = *reinterpret_cast<const d2*>(ar + 16L * i * ld + k);
+      const d2 fi = *reinterpret_cast<const d2*>(ai + 16L * i * ld + k);
+      const d2 fs = fr + fi;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        a1[i] = mfma_f64(fr[t], fbr[t], a1[i]);
+        a2[i] = mfma_f64(fi[t], fbi[t], a2[i]);
+        a3[i] = mfma_f64(fs[t], fbs[t], a3[i]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      red[wave][8 * i + r][lane] = a1[i][r] - a2[i][r];
+      red[wave][8 * i + 4 + r][lane] = a3[i][r] - a1[i][r] - a2[i][r];
+    }
+  __syncthreads();
+  epi.batch(0);
+  for (int q = threadIdx.x; q < FM * 256; q += W * 64) {
+    const int l = q & 63, i = q >> 8, r = (q >> 6) & 3, v = 8 * i + r;
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      re += red[w][v][l];
+      im += red[w][v + 4][l];
+    }
+    epi(m0 + 16 * i + 4 * r + (l >> 4), n0 + (l & 15), re, im);
+  }
+}
+
+// Sums over the 64 lanes of N values per lane (N a power of two up to 64), by
+// halving: at each step a lane keeps one half of its values and gets the other
+// lane's share of them, so N - 1 exchanges and a few single ones replace 6 N.
+// The sum of value i ends in v[0] of the lanes whose high bits are i.
+template <int N, int O>
+__device__ __forceinline__ void lane_sums(double* v, int lane) {
+  if constexpr (N > 1) {
+    constexpr int H = N / 2;
+    const bool up = lane & O;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double keep = up ? v[i + H] : v[i], send = up ? v[i] : v[i + H];
+      v[i] = keep + __shfl_xor(send, O);
+    }
+    if constexpr (O > 1) lane_sums<H, O / 2>(v, lane);
+  } else {
+    v[0] += __shfl_xor(v[0], O);
+    if constexpr (O > 1) lane_sums<1, O / 2>(v, lane);
+  }
+}
+
+// Up to 8 rows m (S = 1, 2, 4, 8; 16 in two blocks): a wave takes 4 rows of B and
+// S rows of A, its lanes consecutive k, so that every load is one contiguous
+// KiB; W = 4 waves share k. Bound by reading B: N = 2048, 8 states 17.1 us
+// (67 MB at 3.9 TB/s; 32 us on the matrix cores above, where half of the
+// 16-row block is padding), N = 4096 49 us (5.5 TB/s, partly from the
+// Infinity Cache), one state 11.4 and 38 us.
+template <int S, class Epi>
+__global__ __launch_bounds__(256) void zgemm_few_states_kernel(Operands op, Epi epi) {
+  constexpr int R = 4, W = 4, V = 2 * S * R;
+  __shared__ double red[W][V];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = blockIdx.y * S, n0 = blockIdx.x * R;
+  const long ld = op.ld;
+  double c[V];  // (s, r): re, im
+#pragma unroll
+  for (int v = 0; v < V; ++v) c[v] = 0.0;
+  for (int k = (wave * 64 + lane) * 2; k < op.kdim; k += W * 128) {
+    d2 hr[R], hi[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      hr[r] = *reinterpret_cast<const d2*>(op.br + (long)(n0 + r) * ld + k);
+      hi[r] = *reinterpret_cast<const d2*>(op.bi + (long)(n0 + r) * ld + k);
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const d2 xr = *reinterpret_cast<const d2*>(op.ar + (long)(m0 + s) * ld + k);
+      const d2 xi = *reinterpret_cast<const d2*>(op.ai + (long)(m0 + s) * ld + k);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          double& re = c[2 * (s * R + r)];
+          double& im = c[2 * (s * R + r) + 1];
+          re = fma(xr[t], hr[r][t], re);
+          re = fma(-xi[t], hi[r][t], re);
+          im = fma(xr[t], hi[r][t], im);
+          im = fma(xi[t], hr[r][t], im);
+        }
+    }
+  }
+  lane_sums<V, 32>(c, lane);
+  constexpr int per = 64 / V;  // lanes that hold the same sum
+  if (lane % per == 0) red[wave][lane / per] = c[0];
+  __syncthreads();
+  epi.batch(0);
+  const int q = threadIdx.x;
+  if (q < S * R) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      re += red[w][2 * q];
+      im += red[w][2 * q + 1];
+    }
+    epi(m0 + q / R, n0 + q % R, re, im);
+  }
 }
 
 }  // namespace fq

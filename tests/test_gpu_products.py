@@ -91,3 +91,40 @@ def test_segmented_builds(fl, n, M):
     eu, ex = orc.column_error(U, ref), orc.column_error(X, ref)
     print("[case] build", eu, "block", ex, flush=True)
     assert eu < 1e-12 and ex < 1e-12
+
+
+# 1, 2, 4, 8 and 16 rows on the vector units, 32, 48 and 64 on the matrix cores
+# in blocks of 16 and (2500 states) 32 rows, each with and without remainder,
+# with fewer and more columns than the waves of a workgroup cover; 65 states
+# take whole tiles, 50 the one-launch chain
+@pytest.mark.parametrize("n,ncols", [(50, 3), (100, 1), (100, 16), (500, 2), (500, 17), (700, 4),
+                                     (700, 33), (1100, 8), (1100, 9), (1100, 48), (1100, 49),
+                                     (2000, 3), (2000, 64), (2000, 65), (2500, 48), (2500, 60)])
+def test_few_states(fl, n, ncols):
+    print("[case] few states", n, ncols, flush=True)
+    rng = np.random.default_rng(n + ncols)
+    H0, V = gue(n, rng), gue(n, rng)
+    T, M = 0.4, 3
+    f = np.cos(fl.node_times(T, M))
+    X0 = rng.standard_normal((n, ncols)) + 1j * rng.standard_normal((n, ncols))
+    X0 /= np.linalg.norm(X0, axis=0)
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f)
+    U = ctx.build_ut().cpu().numpy()
+    for _ in range(2):
+        X, snaps = ctx.propagate(X0, snap_every=2)
+        err = orc.column_error(X.cpu().numpy(), U @ X0)
+        print("[case] e_col", err, flush=True)
+        # both carry at most the truncation of 1e-12 a step
+        assert err < 2 * M * 1e-12
+    assert snaps.shape == (1, n, ncols)
+    fg = np.cos(np.arange(M) * T / M)
+    e = ctx.period_average(X0, fg)
+    a, b = orc.magnus4_weights(f, T / M)
+    K = orc.commutator(H0, V)
+    Y, ref = X0, 0.0
+    for k in range(M):
+        H = H0 + fg[k] * V
+        ref = ref + np.real(np.sum(Y.conj() * (H @ Y), axis=0)) / np.linalg.norm(Y, axis=0) ** 2
+        w, Q = np.linalg.eigh(H0 + a[k] * V + b[k] * K)
+        Y = Q @ (np.exp(-1j * (T / M) * w)[:, None] * (Q.conj().T @ Y))
+    assert np.max(np.abs(e - ref / M)) < 1e-11
