@@ -148,6 +148,7 @@ struct Layout {
   long np = 0;
   int n_tape = 0;
   int pool_mats = 0, n_extra = 0;
+  size_t adj_mats = 0;
 };
 
 // Scratch matrices of the FP64 step operators (see PolyPlan). Below 1024 padded
@@ -159,6 +160,11 @@ struct Layout {
 // the static scratch of the one-shot build wherever the rest does.
 constexpr int kPoolBufs = 6, kExtraBufs = 2, kPoolSegments = 128;
 constexpr size_t kPoolBudget = size_t(250) << 20, kPoolBytes = size_t(144) << 20;
+// The gradient's scratch: matrices per member of a batch (adj_bufs at the longest
+// plan), the most they may take before the term-by-term sweep stays, and the most
+// the sweep in segments may take (it holds a matrix per step).
+constexpr size_t kAdjBufs = 2 * fq::kPolyMaxS + 2 * fq::kPolyMaxBlocks + 2;
+constexpr size_t kAdjBudget = size_t(48) << 30, kAdjSegBudget = size_t(4) << 30;
 long pool_segments(long np) {
   const long t64 = (np / 64) * (np / 64);
   return std::max(1L, std::min<long>(512 / t64, kPoolSegments));
@@ -213,7 +219,15 @@ Layout plan(const fq_system* sys, const fq_params* par) {
     if (par->checkpoint_every > 0) {
       lay.n_tape = (Ms + cks - 1) / cks + 1;
       lay.off_tape = take(plane2 * (size_t)lay.n_tape);
-      lay.off_seg = take(3 * plane2 * (size_t)cks);
+      // the segment store of the term-by-term sweep, or the scratch of the step
+      // polynomials (and, with every P_t of the chain, of the sweep in segments)
+      size_t mats = 3 * (size_t)cks;
+      if (kAdjBufs * plane2 <= kAdjBudget) {
+        mats = std::max(mats, kAdjBufs + (size_t)cks);
+        const size_t all = (size_t)std::min(pool_segments(lay.np), Ms) * (kAdjBufs + 3) + Ms;
+        if (lay.np < 1024 && all * plane2 <= kAdjSegBudget) mats = std::max(mats, all);
+      }
+      lay.adj_mats = mats;
       lay.off_stack = take(4 * plane2);
       lay.off_lam = take(plane2);
       lay.off_grad = take((size_t)J * sizeof(double) * (size_t)Ms);
@@ -258,15 +272,22 @@ Layout plan(const fq_system* sys, const fq_params* par) {
   lay.off_ab = take(2 * sizeof(double) * (size_t)Ms);
   lay.off_coef = take(2 * sizeof(double) * (size_t)(kMaxOrder + 1));
   lay.zeroed = cur;
+  if (lay.adj_mats > 0)
+    lay.off_seg = take(lay.adj_mats * 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np);
   if (dense_like(sys->layout) && par->precision == FQ_FP64) {
     const size_t plane2 = 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np;
-    const size_t left = kPoolBudget > cur ? kPoolBudget - cur : 0;
+    // (a gradient tape is never in the static scratch)
+    const size_t left = par->checkpoint_every > 0 ? kPoolBudget
+                        : kPoolBudget > cur       ? kPoolBudget - cur
+                                                  : 0;
     if (lay.np < 1024) {
       lay.pool_mats = (int)std::min<size_t>(kPoolBufs * (size_t)pool_segments(lay.np),
                                             std::min(left, kPoolBytes) / plane2);
       if (lay.pool_mats > 0) lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
     } else {
-      lay.n_extra = left == 0 ? kExtraBufs : (int)std::min<size_t>(kExtraBufs, left / plane2);
+      lay.n_extra = left == 0 || par->checkpoint_every > 0
+                        ? kExtraBufs
+                        : (int)std::min<size_t>(kExtraBufs, left / plane2);
       if (lay.n_extra > 0) lay.off_extra = take(plane2 * (size_t)lay.n_extra);
     }
   }
@@ -965,25 +986,10 @@ fq_status dense_cheb_step(fq_ctx* c, int mrows) {
 // MFMA). Small N in segments: 100 steps at N = 64 2.36 -> 0.16 ms, a sixth-order
 // one-shot build at N = 199 18.3 -> 12.0 ms (the rest is its setup).
 
-// The cheapest block length with at most nbuf matrices beside X (T_1 .. T_s,
-// then T_s and the blocks); `apply` = mrows / np, the cost of applying E. An
-// empty plan (s = 0) when the term-by-term form (L * apply) is cheaper or no
-// plan fits.
-PolyPlan poly_plan(const fq_ctx* c, int nbuf, double apply) {
+// Blocks of length bs.
+PolyPlan poly_blocks(const fq_ctx* c, int bs) {
   const int L = c->L;
   PolyPlan best;
-  double best_cost = L * apply;
-  int bs = 0;
-  for (int s = 2; s <= std::min({fq::kPolyMaxS, nbuf, L}); ++s) {
-    const int prods = (L + s - 1) / s - 1;
-    if (prods + 1 > fq::kPolyMaxBlocks || (prods > 0 && prods + 2 > nbuf)) continue;
-    const double cost = 0.6 * (s - 1) + prods + apply;
-    if (cost < best_cost) {
-      best_cost = cost;
-      bs = s;
-    }
-  }
-  if (bs == 0) return best;
   const int s = best.s = bs, prods = (L + s - 1) / s - 1, top = L / s;
   const std::complex<double> ph(c->phr, c->phi);
   std::vector<std::complex<double>> cl(L + 1);
@@ -1015,23 +1021,44 @@ PolyPlan poly_plan(const fq_ctx* c, int nbuf, double apply) {
   return best;
 }
 
-// E over the Ht in b[0], for `batch` matrices with stride bs; b[1] .. are scratch.
-fq_status poly_form(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& b, int batch) {
+// The cheapest block length with at most nbuf matrices beside X (T_1 .. T_s,
+// then T_s and the blocks); `apply` = mrows / np, the cost of applying E. An
+// empty plan (s = 0) when the term-by-term form (L * apply) is cheaper or no
+// plan fits.
+PolyPlan poly_plan(const fq_ctx* c, int nbuf, double apply) {
+  const int L = c->L;
+  double best_cost = L * apply;
+  int bs = 0;
+  for (int s = 2; s <= std::min({fq::kPolyMaxS, nbuf, L}); ++s) {
+    const int prods = (L + s - 1) / s - 1;
+    if (prods + 1 > fq::kPolyMaxBlocks || (prods > 0 && prods + 2 > nbuf)) continue;
+    const double cost = 0.6 * (s - 1) + prods + apply;
+    if (cost < best_cost) {
+      best_cost = cost;
+      bs = s;
+    }
+  }
+  return bs ? poly_blocks(c, bs) : PolyPlan();
+}
+
+// E = w[0] over the Ht in t[0], for `batch` matrices with stride bs: T_2 .. T_s
+// into t[1] .. t[s - 1], the blocks into w (which may take the place of T_1 ..
+// T_s-1; with more than one block T_s stays).
+fq_status poly_form(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& t,
+                    const std::vector<double*>& w, int batch) {
   const int np = (int)c->np, s = p.s, J = p.J;
   const long bs = 2 * c->np * c->np;
   for (int l = 2; l <= s; ++l) {
     FQ_MARK(c, FQ_K_POLY);
-    FQ_HIP(c, fq::launch_poly_t(b[l / 2 - 1], b[(l + 1) / 2 - 1], l % 2 ? b[0] : nullptr, b[l - 1],
+    FQ_HIP(c, fq::launch_poly_t(t[l / 2 - 1], t[(l + 1) / 2 - 1], l % 2 ? t[0] : nullptr, t[l - 1],
                                 (int)c->n, np, bs, batch, c->stream));
   }
   fq::PolyCombine q{};
   q.s = s;
   q.J = J;
-  for (int l = 0; l < s; ++l) q.t[l] = b[l];
-  std::vector<double*> w(J);
-  for (int j = 0, at = 0; j < J; ++j, ++at) {
-    if (J > 1 && at == s - 1) ++at;  // T_s stays
-    w[j] = q.q[j] = b[at];
+  for (int l = 0; l < s; ++l) q.t[l] = t[l];
+  for (int j = 0; j < J; ++j) {
+    q.q[j] = w[j];
     for (int l = 0; l <= s; ++l) {
       q.gr[j][l] = p.gr[(size_t)j * (s + 1) + l];
       q.gi[j][l] = p.gi[(size_t)j * (s + 1) + l];
@@ -1039,13 +1066,24 @@ fq_status poly_form(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& b,
   }
   FQ_MARK(c, FQ_K_HEFF);
   FQ_HIP(c, fq::launch_poly_combine(q, c->n, np, bs, batch, c->stream));
-  for (int j = J - 2; j >= 0; --j) {
+  for (int j = J - 2; j >= 0; --j) {  // W_{j+1} T_s = T_s W_{j+1}
     FQ_MARK(c, FQ_K_POLY);
-    FQ_HIP(c, fq::launch_poly_block(w[j + 1], b[s - 1], j >= 1 ? 2.0 : 1.0,
-                                    j + 2 < J ? w[j + 2] : nullptr, w[j], np, bs, batch,
+    FQ_HIP(c, fq::launch_poly_block(w[j + 1], bs, t[s - 1], bs, true, j >= 1 ? 2.0 : 1.0,
+                                    j + 2 < J ? w[j + 2] : nullptr, true, w[j], bs, np, batch,
                                     c->stream));
   }
   return FQ_OK;
+}
+
+// The same with the blocks in the place of T's no longer needed; E over Ht.
+fq_status poly_form_in_place(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& b,
+                             int batch) {
+  std::vector<double*> w(p.J);
+  for (int j = 0, at = 0; j < p.J; ++j, ++at) {
+    if (p.J > 1 && at == p.s - 1) ++at;  // T_s stays
+    w[j] = b[at];
+  }
+  return poly_form(c, p, b, w, batch);
 }
 
 // One FP64 step X <- E_k X through E_k (Ht formed here).
@@ -1054,7 +1092,7 @@ fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
   const size_t plane2 = 2 * (size_t)c->np * (size_t)c->np;
   for (int i = 0; i < c->n_extra; ++i) b.push_back(c->extra + (size_t)i * plane2);
   FQ_TRY(dense_heff(c, k));
-  FQ_TRY(poly_form(c, p, b, 1));
+  FQ_TRY(poly_form_in_place(c, p, b, 1));
   FQ_MARK(c, FQ_K_LAST);
   if (c->from_identity && k == 0)  // X = 1: the state-major E is E^T
     FQ_HIP(c, fq::launch_transpose_planar(c->htr, c->hti, c->par, c->pai, c->np, 0, 1, c->stream));
@@ -1107,7 +1145,7 @@ fq_status dense_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
     const int act = t < len0 ? nb : rem;  // segments with a step t
     FQ_MARK(c, FQ_K_HEFF);
     FQ_TRY(heff_f64(c, t, act, len0, rem, b[0]));
-    FQ_TRY(poly_form(c, p, b, act));
+    FQ_TRY(poly_form_in_place(c, p, b, act));
     FQ_MARK(c, FQ_K_LAST);
     if (t == 0) {  // X = 1
       FQ_HIP(c, fq::launch_transpose_planar(b[0], b[0] + bs / 2, x, x + bs / 2, c->np, bs, act,
@@ -1741,6 +1779,251 @@ void grad_to_nodes(const fq_ctx* c, const std::vector<double>& g, double* grad_f
   }
 }
 
+// ---- gradient through the step polynomials ---------------------------------------------------
+//
+// With E_k formed as above, dL = Re Tr(G_k dE_k), G_k = X_{k-1} Lambda_k^dagger.
+// For the steps t = 1 .. len of a segment with operators E_1 .. E_len let
+//   P_t = E_t ... E_1 P_0,   M_{t-1} = M_t E_t,   G_t = P_{t-1} M_t,
+// where P_0 = X and M_len = Lambda^dagger at the segment's ends, or P_0 = 1 and
+// M_len = X Lambda^dagger: then every segment's P and M are independent of the
+// others. dE is carried back through the blocks (W_j commute with T_s, their
+// differentials do not):
+//   dW_j = dQ_j + f_j (dT_s W_{j+1} + T_s dW_{j+1}) - dW_{j+2}
+//   => Wbar_{j+1} = f_j Wbar_j T_s - Wbar_{j-1},  Tbar_s += f_j W_{j+1} Wbar_j,
+//      Tbar_l += sum_j g_jl Wbar_j;
+// and through T_l = 2 T_a T_b - T_{a-b} with the Hermitian part S_l of Tbar_l,
+// all that Hermitian differentials see: Tbar_a += 2 T_b S_l, Tbar_b += 2 T_a S_l,
+// Tbar_{a-b} -= S_l. Tbar_1 is dL/dHt; its traces with the drive block are the
+// derivatives. For L = 8 that is 12 products a step with the forming of E twice,
+// where the term-by-term sweep takes 5 L to 6 L. A drive-optimisation step
+// (build and node derivatives) at N = 256, M = 64: 38.0 -> 4.85 ms, the build in
+// segments included (the tape would have made it run step by step).
+
+// Matrices per batch member beside the P_t: T, W, Wbar, Tbar and two M.
+int adj_bufs(const PolyPlan& p) { return 2 * p.s + 2 * p.J + 2; }
+
+// Blocks for the gradient: forming E twice, two products per block and one or two
+// per T_l on the way back. Empty for L = 1 and beyond the longest plan.
+PolyPlan poly_plan_adjoint(const fq_ctx* c) {
+  double best_cost = 0.0;
+  int bs = 0;
+  for (int s = 2; s <= std::min(fq::kPolyMaxS, c->L); ++s) {
+    const int prods = (c->L + s - 1) / s - 1;
+    if (prods + 1 > fq::kPolyMaxBlocks) continue;
+    double cost = 2.0 * (0.6 * (s - 1) + prods) + 2.0 * prods;
+    for (int l = 2; l <= s; ++l) cost += l % 2 ? 2.0 : 1.0;
+    if (bs == 0 || cost < best_cost) {
+      best_cost = cost;
+      bs = s;
+    }
+  }
+  return bs ? poly_blocks(c, bs) : PolyPlan();
+}
+
+// Segments of the gradient that need no tape (all P_t of the chain at once in the
+// gradient's scratch); 0 where they do not fit or one product fills the chip.
+int adj_segments(const fq_ctx* c, const PolyPlan& p) {
+  if (!p.s || c->np >= 1024 || !c->adj_mats) return 0;
+  // one launch of the two chains over the segments costs as much as a step's
+  // batch, so no more segments than steps in each
+  int nb = (int)std::min<long>(pool_segments(c->np), c->M);
+  while (nb > 2 && nb > 4 * ((c->M + nb - 1) / nb)) --nb;
+  for (; nb > 0; --nb) {
+    const long len = (c->M + nb - 1) / nb;
+    if ((long)nb * (adj_bufs(p) + len + 2) <= c->adj_mats) return nb;
+  }
+  return 0;
+}
+
+struct AdjBuffers {
+  std::vector<double*> t, w, wb, tb;
+  double* m[2];
+};
+
+// dL/dHt into tb[0] from wb[0] = G, for `batch` members.
+fq_status poly_reverse(fq_ctx* c, const PolyPlan& p, const AdjBuffers& b, int batch) {
+  const int np = (int)c->np, s = p.s, J = p.J;
+  const long bs = 2 * c->np * c->np;
+  auto mul = [&](const double* x, const double* y, bool herm, double f, const double* sub, bool add,
+                 double* out) -> fq_status {
+    FQ_MARK(c, FQ_K_ADJ_REV);
+    FQ_HIP(c, fq::launch_poly_block(x, bs, y, bs, herm, f, sub, add, out, bs, np, batch,
+                                    c->stream));
+    return FQ_OK;
+  };
+  auto fac = [](int j) { return j >= 1 ? 2.0 : 1.0; };
+  for (int j = 0; j + 1 < J; ++j)
+    FQ_TRY(mul(b.wb[j], b.t[s - 1], true, fac(j), j ? b.wb[j - 1] : nullptr, false, b.wb[j + 1]));
+  fq::PolyCombine q{};
+  q.s = J;
+  q.J = s;
+  for (int j = 0; j < J; ++j) q.t[j] = b.wb[j];
+  for (int l = 1; l <= s; ++l) {
+    q.q[l - 1] = b.tb[l - 1];
+    for (int j = 0; j < J; ++j) {
+      q.gr[l - 1][j + 1] = p.gr[(size_t)j * (s + 1) + l];
+      q.gi[l - 1][j + 1] = p.gi[(size_t)j * (s + 1) + l];
+    }
+  }
+  FQ_MARK(c, FQ_K_HEFF);
+  FQ_HIP(c, fq::launch_poly_combine(q, c->n, np, bs, batch, c->stream));
+  for (int j = 0; j + 1 < J; ++j)
+    FQ_TRY(mul(b.w[j + 1], b.wb[j], false, fac(j), nullptr, true, b.tb[s - 1]));
+  for (int l = s; l >= 2; --l) {
+    double* sl = b.tb[l - 1];
+    FQ_MARK(c, FQ_K_HEFF);
+    FQ_HIP(c, fq::launch_hermitian_part(sl, np, bs, batch, c->stream));
+    const int a = (l + 1) / 2, d = l / 2;
+    if (a == d) {
+      FQ_TRY(mul(b.t[a - 1], sl, true, 4.0, nullptr, true, b.tb[a - 1]));
+      continue;
+    }
+    FQ_TRY(mul(b.t[d - 1], sl, true, 2.0, nullptr, true, b.tb[a - 1]));
+    FQ_TRY(mul(b.t[a - 1], sl, true, 2.0, d == 1 ? sl : nullptr, true, b.tb[d - 1]));
+    if (d != 1) {  // Tbar_1 -= S_l
+      fq::PolyCombine x{};
+      x.s = 2;
+      x.J = 1;
+      x.t[0] = x.q[0] = b.tb[0];
+      x.t[1] = sl;
+      x.gr[0][1] = 1.0;
+      x.gr[0][2] = -1.0;
+      FQ_MARK(c, FQ_K_HEFF);
+      FQ_HIP(c, fq::launch_poly_combine(x, c->n, np, bs, batch, c->stream));
+    }
+  }
+  return FQ_OK;
+}
+
+// One reverse step of `act` members: form E, G from P (null: 1) and M, dL/dHt and
+// its traces, M <- M E (unless `last`).
+fq_status adj_poly_step(fq_ctx* c, const PolyPlan& p, AdjBuffers& b, int t, int act, int nb,
+                        int len0, int rem, const double* pt, bool last) {
+  const int np = (int)c->np;
+  const long bs = 2 * c->np * c->np;
+  FQ_MARK(c, FQ_K_HEFF);
+  FQ_TRY(heff_f64(c, t, act, len0, rem, b.t[0]));
+  FQ_TRY(poly_form(c, p, b.t, b.w, act));
+  AdjBuffers r = b;
+  if (pt) {
+    FQ_MARK(c, FQ_K_ADJ_REV);
+    FQ_HIP(c, fq::launch_poly_apply(pt, bs, b.m[0], bs, true, b.wb[0], bs, np, np, act, c->stream));
+  } else {
+    r.wb[0] = b.m[0];
+  }
+  FQ_TRY(poly_reverse(c, p, r, act));
+  const int count = c->S > 1 ? c->J : (c->pair_sums ? 1 : 2);
+  FQ_MARK(c, FQ_K_HEFF);
+  FQ_HIP(c, fq::launch_trace_dot(r.tb[0], np, bs, act, c->vr, c->vi, count, c->J, len0, rem, t,
+                                 c->d_grad, c->stream));
+  if (last) return FQ_OK;
+  FQ_MARK(c, FQ_K_ADJ_REV);
+  FQ_HIP(c, fq::launch_poly_apply(b.m[0], bs, b.w[0], bs, true, b.m[1], bs, np, np, act, c->stream));
+  if (act == nb)
+    std::swap(b.m[0], b.m[1]);
+  else  // the members without this step keep their M in the old place
+    FQ_HIP(c, hipMemcpyAsync(b.m[0], b.m[1], sizeof(double) * (size_t)bs * act,
+                             hipMemcpyDeviceToDevice, c->stream));
+  return FQ_OK;
+}
+
+// Buffers of nb members from the gradient's scratch; *next: what follows them.
+AdjBuffers adj_carve(fq_ctx* c, const PolyPlan& p, int nb, double** next) {
+  const size_t step = (size_t)nb * 2 * (size_t)c->np * (size_t)c->np;
+  double* at = c->adj_pool;
+  auto take = [&]() {
+    double* r = at;
+    at += step;
+    return r;
+  };
+  AdjBuffers b;
+  for (int i = 0; i < p.s; ++i) b.t.push_back(take());
+  for (int i = 0; i < p.J; ++i) b.w.push_back(take());
+  for (int i = 0; i < p.J; ++i) b.wb.push_back(take());
+  for (int i = 0; i < p.s; ++i) b.tb.push_back(take());
+  b.m[0] = take();
+  b.m[1] = take();
+  *next = at;
+  return b;
+}
+
+// The whole gradient in nb segments, step t of all of them in one batch, from
+// nothing but the drive: P_0 = 1, then the segments' operators give every
+// segment's X (forwards) and Lambda^dagger (backwards).
+fq_status adjoint_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
+  const int np = (int)c->np, len0 = c->M / nb, rem = c->M % nb, len = len0 + (rem ? 1 : 0);
+  const long bs = 2 * c->np * c->np;
+  double* at;
+  AdjBuffers b = adj_carve(c, p, nb, &at);
+  std::vector<double*> P(len + 1, nullptr);  // P[t]: the nb matrices P_t, t >= 1
+  for (int t = 1; t <= len; ++t, at += (size_t)nb * bs) P[t] = at;
+  double* X = at;
+  double* D = at + (size_t)nb * bs;
+  for (int t = 0; t < len; ++t) {
+    const int act = t < len0 ? nb : rem;
+    FQ_MARK(c, FQ_K_HEFF);
+    FQ_TRY(heff_f64(c, t, act, len0, rem, b.t[0]));
+    std::vector<double*> w = b.w;
+    if (t == 0) w[0] = P[1];  // P_1 = E_1
+    FQ_TRY(poly_form(c, p, b.t, w, act));
+    if (t == 0) continue;
+    FQ_MARK(c, FQ_K_LAST);
+    FQ_HIP(c, fq::launch_poly_apply(w[0], bs, P[t], bs, true, P[t + 1], bs, np, np, act,
+                                    c->stream));
+  }
+  auto S = [&](int z) { return P[z < rem ? len0 + 1 : len0] + (size_t)z * bs; };
+  auto Xz = [&](int z) { return X + (size_t)z * bs; };
+  auto Dz = [&](int z) { return D + (size_t)z * bs; };
+  FQ_HIP(c, fq::launch_identity_rows(X, X + bs / 2, c->n, np, np, c->stream));
+  FQ_HIP(c, fq::launch_conj_planar(c->lam, np, Dz(nb - 1), c->stream));
+  for (int i = 1; i < nb; ++i) {  // X_i = S_{i-1} X_{i-1} and D_j = D_{j+1} S_{j+1}, j = nb-1-i
+    FQ_MARK(c, FQ_K_LAST);
+    FQ_HIP(c, fq::launch_poly_apply(S(i - 1), Dz(nb - i) - S(i - 1), Xz(i - 1), S(nb - i) - Xz(i - 1),
+                                    true, Xz(i), Dz(nb - 1 - i) - Xz(i), np, np, 2, c->stream));
+  }
+  FQ_MARK(c, FQ_K_LAST);
+  FQ_HIP(c, fq::launch_poly_apply(X, bs, D, bs, true, b.m[0], bs, np, np, nb, c->stream));
+  for (int t = len - 1; t >= 0; --t)
+    FQ_TRY(adj_poly_step(c, p, b, t, t < len0 ? nb : rem, nb, len0, rem, P[t], t == 0));
+  return FQ_OK;
+}
+
+// The gradient from the tape, one checkpoint segment after the other: P_t = X of
+// the segment's steps, M = Lambda^dagger.
+fq_status adjoint_poly_tape(fq_ctx* c, const PolyPlan& p) {
+  const int np = (int)c->np, s = c->ckpt;
+  const long bs = 2 * c->np * c->np;
+  double* at;
+  AdjBuffers b = adj_carve(c, p, 1, &at);
+  FQ_HIP(c, fq::launch_conj_planar(c->lam, np, b.m[0], c->stream));
+  for (int sg = (c->M + s - 1) / s - 1; sg >= 0; --sg) {
+    const int k0 = sg * s, k1 = std::min(c->M, k0 + s);
+    auto P = [&](int k) { return at + (size_t)(k - k0) * bs; };  // X_k, operator-major
+    const double* x0 = c->tape + (size_t)sg * bs;
+    FQ_HIP(c, fq::launch_transpose_planar(x0, x0 + bs / 2, P(k0), P(k0) + bs / 2, np, 0, 1,
+                                          c->stream));
+    for (int k = k0; k + 1 < k1; ++k) {
+      FQ_MARK(c, FQ_K_HEFF);
+      FQ_TRY(heff_f64(c, k, 1, 0, 0, b.t[0]));
+      FQ_TRY(poly_form(c, p, b.t, b.w, 1));
+      FQ_MARK(c, FQ_K_LAST);
+      FQ_HIP(c, fq::launch_poly_apply(b.w[0], 0, P(k), 0, true, P(k + 1), 0, np, np, 1, c->stream));
+    }
+    for (int k = k1 - 1; k >= k0; --k)
+      FQ_TRY(adj_poly_step(c, p, b, k, 1, 1, 0, 0, P(k), k == 0));
+  }
+  return FQ_OK;
+}
+
+// How floquet_grad runs the present drive: 1 segments without a tape, 2 step
+// polynomials from the tape, 0 term by term from the tape.
+int adj_mode(const fq_ctx* c, PolyPlan* p, int* nb) {
+  *p = poly_plan_adjoint(c);
+  *nb = adj_segments(c, *p);
+  if (*nb > 0) return 1;
+  return p->s && adj_bufs(*p) + c->ckpt <= c->adj_mats ? 2 : 0;
+}
+
 fq_status adjoint(fq_ctx* c, const void* U_bar, double* grad_f_nodes) {
   const int M = c->M, s = c->ckpt;
   const long plane = c->np * c->np;
@@ -1753,7 +2036,12 @@ fq_status adjoint(fq_ctx* c, const void* U_bar, double* grad_f_nodes) {
   const bool with_k = !c->pair_sums;
   const int nseg = (M + s - 1) / s;
   c->n_events = 0;  // profile mode: the recompute and reverse products go to the report
-  for (int sg = nseg - 1; sg >= 0; --sg) {
+  PolyPlan poly;
+  int nb = 0;
+  const int mode = adj_mode(c, &poly, &nb);
+  if (mode == 1) FQ_TRY(adjoint_poly_segments(c, poly, nb));
+  if (mode == 2) FQ_TRY(adjoint_poly_tape(c, poly));
+  for (int sg = mode ? -1 : nseg - 1; sg >= 0; --sg) {
     const int k0 = sg * s, k1 = std::min(M, k0 + s);
     // regenerate the segment forward in FP64 from its checkpoint
     FQ_MARK(c, -1);
@@ -2375,7 +2663,8 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     if (lay.n_tape > 0) {
       c->tape = P(lay.off_tape);
       c->n_tape = lay.n_tape;
-      c->seg = P(lay.off_seg);
+      c->seg = c->adj_pool = P(lay.off_seg);
+      c->adj_mats = (long)lay.adj_mats;
       c->stack[0] = P(lay.off_stack);
       c->stack[1] = c->stack[0] + 4 * plane;
       c->lam = P(lay.off_lam);
@@ -2478,7 +2767,9 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
     FQ_HIP(c, fq::launch_identity_rows(c->xr, c->xi, c->n, c->np, c->np, c->stream));
     if (e0) FQ_HIP(c, hipEventRecord(e0, c->stream));
     c->from_identity = true;
-    st = dense_steps(c, 0, c->M, (int)c->np, c->ckpt > 0);
+    PolyPlan gp;
+    int gnb = 0;
+    st = dense_steps(c, 0, c->M, (int)c->np, c->ckpt > 0 && adj_mode(c, &gp, &gnb) != 1);
     c->from_identity = false;
     if (st != FQ_OK) return st;
     FQ_MARK(c, -1);

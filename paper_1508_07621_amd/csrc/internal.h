@@ -205,7 +205,7 @@ hipError_t launch_heff_f64(const HeffSum& h, const double* w, int t, int batch, 
 // exp(-i h H) = sum_l c_l T_l(Ht) in blocks of s terms by Clenshaw's recurrence
 // in T_s(Ht). All matrices are planar pairs (im plane np * np after the re
 // plane), member z of a batch at + z * bs.
-constexpr int kPolyMaxS = 6, kPolyMaxBlocks = 4;
+constexpr int kPolyMaxS = 6, kPolyMaxBlocks = 6;
 // out = 2 T_a T_b - sub (sub null: the identity), Hermitian.
 hipError_t launch_poly_t(const double* ta, const double* tb, const double* sub, double* out, int n,
                          int np, long bs, int batch, hipStream_t s);
@@ -218,9 +218,19 @@ struct PolyCombine {
 };
 hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, int batch,
                                hipStream_t s);
-// out += f W T_s - sub (sub optional; W a polynomial of the same matrix).
-hipError_t launch_poly_block(const double* w, const double* ts, double f, const double* sub,
-                             double* out, int np, long bs, int batch, hipStream_t s);
+// out = [out +] f A B - sub (sub optional, with out's stride); b_herm: B is Hermitian.
+hipError_t launch_poly_block(const double* a, long a_bs, const double* b, long b_bs, bool b_herm,
+                             double f, const double* sub, bool add, double* out, long o_bs, int np,
+                             int batch, hipStream_t s);
+// A <- (A + A^dagger) / 2.
+hipError_t launch_hermitian_part(double* a, int np, long bs, int batch, hipStream_t s);
+// out[stride k_z + j] += Re Tr(A_z B_j), j < count, for the Hermitian B_j with
+// planes at b_re + j np^2 and b_im + j np^2; k_z as in launch_heff_f64.
+hipError_t launch_trace_dot(const double* a, int np, long bs, int batch, const double* b_re,
+                            const double* b_im, int count, int stride, int len0, int rem, int t,
+                            double* out, hipStream_t s);
+// dst = conj(src), planar.
+hipError_t launch_conj_planar(const double* src, int np, double* dst, hipStream_t s);
 // State-major blocks times operators: out(j, i) = sum_k x(j, k) E(i, k) over rows
 // [0, mrows); e_trans: E is stored state-major, E(i, k) at row k, column i.
 hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,

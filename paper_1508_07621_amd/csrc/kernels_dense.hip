@@ -10,6 +10,8 @@
 // B = the rescaled Hamiltonian (row i = basis index i).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "epilogues.h"
 #include "formats.h"
 #include "internal.h"
@@ -145,19 +147,24 @@ struct EpiPolyT {
   __device__ __forceinline__ void finish() const {}
 };
 
-// Clenshaw block: O += f * acc - S (S optional).
+// Clenshaw block and its adjoint: O = [O +] f * acc - S (S optional).
 struct EpiPolyBlock {
   double* o;
   const double* sub;
   long ld, plane, bs;
   double f;
+  bool add;
   __device__ __forceinline__ void batch(int z) {
     o += z * bs;
     if (sub) sub += z * bs;
   }
   __device__ __forceinline__ void operator()(int m, int c, double ar, double ai) const {
     const long idx = (long)m * ld + c;
-    double r = fma(f, ar, o[idx]), i = fma(f, ai, o[plane + idx]);
+    double r = f * ar, i = f * ai;
+    if (add) {
+      r += o[idx];
+      i += o[plane + idx];
+    }
     if (sub) {
       r -= sub[idx];
       i -= sub[plane + idx];
@@ -346,6 +353,68 @@ __global__ __launch_bounds__(256) void poly_combine_kernel(PolyCombine p, long n
         *reinterpret_cast<d2*>(p.q[q] + idx) = qr[q];
         *reinterpret_cast<d2*>(p.q[q] + plane + idx) = qi[q];
       }
+  }
+}
+
+// A <- (A + A^dagger) / 2 in place, by pairs of 32 x 32 tiles through LDS.
+__global__ __launch_bounds__(256) void hermitian_part_kernel(double* __restrict__ a, long np,
+                                                             long bs) {
+  __shared__ double ur[32][33], ui[32][33], lr[32][33], li[32][33];
+  if (blockIdx.x < blockIdx.y) return;
+  double* const re = a + blockIdx.z * bs;
+  double* const im = re + np * np;
+  const long bi = blockIdx.y * 32L, bj = blockIdx.x * 32L;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
+  for (int r = ty; r < 32; r += 8) {
+    ur[r][tx] = re[(bi + r) * np + bj + tx];
+    ui[r][tx] = im[(bi + r) * np + bj + tx];
+    lr[r][tx] = re[(bj + r) * np + bi + tx];
+    li[r][tx] = im[(bj + r) * np + bi + tx];
+  }
+  __syncthreads();
+  for (int r = ty; r < 32; r += 8) {
+    re[(bi + r) * np + bj + tx] = 0.5 * (ur[r][tx] + lr[tx][r]);
+    im[(bi + r) * np + bj + tx] = 0.5 * (ui[r][tx] - li[tx][r]);
+    if (bi != bj) {
+      re[(bj + r) * np + bi + tx] = 0.5 * (lr[r][tx] + ur[tx][r]);
+      im[(bj + r) * np + bi + tx] = 0.5 * (li[r][tx] - ui[tx][r]);
+    }
+  }
+}
+
+// out[count * k_z + j] += Re Tr(A_z B_j) for Hermitian B_j = planes at b_re + j *
+// plane, b_im + j * plane; k_z as in heff_kernel, `stride` sums per step.
+__global__ __launch_bounds__(256) void trace_dot_kernel(const double* __restrict__ a, long plane,
+                                                        long bs, const double* __restrict__ b_re,
+                                                        const double* __restrict__ b_im, int count,
+                                                        int stride, int len0, int rem, int t,
+                                                        double* __restrict__ out) {
+  const int z = blockIdx.y, j = blockIdx.z;
+  const long k = (long)z * len0 + (z < rem ? z : rem) + t;
+  const double* ar = a + z * bs;
+  const double* br = b_re + j * plane;
+  const double* bi = b_im + j * plane;
+  double s = 0.0;
+  for (long e = 2 * (blockIdx.x * 256L + threadIdx.x); e < plane; e += 512L * gridDim.x) {
+    const d2 x = *reinterpret_cast<const d2*>(ar + e), y = *reinterpret_cast<const d2*>(ar + plane + e);
+    const d2 p = *reinterpret_cast<const d2*>(br + e), q = *reinterpret_cast<const d2*>(bi + e);
+    s = fma(x[0], p[0], s);
+    s = fma(x[1], p[1], s);
+    s = fma(y[0], q[0], s);
+    s = fma(y[1], q[1], s);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) atomicAdd(out + stride * k + j, s);
+}
+
+// dst = conj(src) on planar pairs.
+__global__ void conj_planar_kernel(const double* __restrict__ src, long plane,
+                                   double* __restrict__ dst) {
+  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < plane;
+       e += (long)gridDim.x * blockDim.x) {
+    dst[e] = src[e];
+    dst[plane + e] = -src[plane + e];
   }
 }
 
@@ -842,12 +911,42 @@ hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, i
   return hipGetLastError();
 }
 
-hipError_t launch_poly_block(const double* w, const double* ts, double f, const double* sub,
-                             double* out, int np, long bs, int batch, hipStream_t s) {
+hipError_t launch_poly_block(const double* a, long a_bs, const double* b, long b_bs, bool b_herm,
+                             double f, const double* sub, bool add, double* out, long o_bs, int np,
+                             int batch, hipStream_t s) {
   const long plane = (long)np * np;
-  // W T_s = T_s W (both are polynomials of Ht), T_s Hermitian
-  Operands op{w, w + plane, ts, ts + plane, np, np, 0, 0, bs, bs};
-  return launch_gemm<false, true>(op, np, np, batch, EpiPolyBlock{out, sub, np, plane, bs, f}, s);
+  Operands op{a, a + plane, b, b + plane, np, np, 0, 0, a_bs, b_bs};
+  const EpiPolyBlock e{out, sub, np, plane, o_bs, f, add};
+  // (A B)(m, c) = sum_k A(m, k) B(k, c), B(k, c) = conj(B(c, k)) when Hermitian
+  return b_herm ? launch_gemm<false, true>(op, np, np, batch, e, s)
+                : launch_gemm<false, false, true>(op, np, np, batch, e, s);
+}
+
+hipError_t launch_hermitian_part(double* a, int np, long bs, int batch, hipStream_t s) {
+  if (np < 32 || np % 32 != 0 || np / 32 > 65535 || batch < 1 || batch > 65535)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(hermitian_part_kernel,
+                     dim3((unsigned)(np / 32), (unsigned)(np / 32), (unsigned)batch), dim3(256), 0,
+                     s, a, np, bs);
+  return hipGetLastError();
+}
+
+hipError_t launch_trace_dot(const double* a, int np, long bs, int batch, const double* b_re,
+                            const double* b_im, int count, int stride, int len0, int rem, int t,
+                            double* out, hipStream_t s) {
+  const long plane = (long)np * np;
+  if (np % 2 != 0 || batch < 1 || batch > 65535 || count < 1) return hipErrorInvalidValue;
+  const unsigned gx = (unsigned)std::min<long>(64, (plane / 2 + 255) / 256);
+  hipLaunchKernelGGL(trace_dot_kernel, dim3(gx, batch, count), dim3(256), 0, s, a, plane, bs, b_re,
+                     b_im, count, stride, len0, rem, t, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_conj_planar(const double* src, int np, double* dst, hipStream_t s) {
+  const long plane = (long)np * np;
+  hipLaunchKernelGGL(conj_planar_kernel, dim3(grid_for(plane, 256)), dim3(256), 0, s, src, plane,
+                     dst);
+  return hipGetLastError();
 }
 
 hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,

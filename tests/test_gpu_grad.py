@@ -514,3 +514,57 @@ def test_tridiag_long_column_complex64_tape(fl):
     err = np.max(np.abs(gs[0] - gs[1])) / np.max(np.abs(gs[0]))
     _say("complex64 tape rel diff", err)
     assert err < 1e-5
+
+
+# ---- dense sweep through the step polynomials ----------------------------------------------------
+
+@pytest.mark.parametrize("n,M,ckpt,L,T", [
+    (70, 9, 2, 1, 0.02), (70, 9, 2, 2, 0.1), (70, 9, 2, 3, 0.3), (70, 9, 4, 5, 0.8),
+    (70, 9, 9, 6, 1.0), (70, 9, 2, 7, 1.2), (70, 9, 2, 8, 1.5), (70, 9, 2, 9, 1.8),
+    (70, 9, 2, 12, 3.0), (70, 9, 2, 15, 4.0), (70, 9, 2, 25, 9.0), (70, 4, 2, 36, 6.0),
+    (70, 4, 2, 37, 6.0), (500, 11, 3, 8, 1.8), (1030, 5, 2, 8, 0.8), (1030, 3, 3, 9, 0.6)])
+def test_dense_gradient_of_every_order(fl, n, M, ckpt, L, T):
+    """The sweep in segments (n = 70, and 500 with unequal ones), from the tape one
+    step at a time (n = 1030) and, for L = 1 and L = 37, term by term, at every
+    block count: the derivative of the truncated map itself, against the
+    oracle's derivative of the same chain (n = 70) or against differences of
+    the library's own builds along a seeded direction. Both differ from the
+    derivative by rounding (1e-13 of the largest entry a step) or by the
+    difference quotient (its step 1e-5: 1e-10 by truncation, 1e-10 by rounding
+    of a loss of order one)."""
+    _say("dense gradient order", n, M, ckpt, L)
+    rng = np.random.default_rng(n + L)
+    H0, V = gue(n, rng), gue(n, rng)
+    f = rng.uniform(-1, 1, M)
+    nodes = np.stack([f, f], 1)
+    W = haar_unitary(n, rng)
+    a, b = orc.magnus4_weights(nodes, T / M)
+    lo, hi = orc.weyl_cover(H0, V, np.zeros_like(H0), a, b)
+    lo, hi = 1.05 * lo, 1.05 * hi
+    kw = dict(h0=H0, hmod=V, T=T, M=M, e_min=lo, e_max=hi, L=L)
+    ctx = fl.FloquetContext(f_nodes=nodes, checkpoint_every=ckpt, **kw)
+    U = ctx.build_ut().cpu().numpy()
+    if n == 70:
+        _, Ubar = _trace_loss_and_bar(U, W)
+        g = ctx.grad(Ubar)
+        ref = orc.grad_piecewise(H0, V, f, T, W, route="cheb", e_min=lo, e_max=hi, L=L)
+        err = np.max(np.abs(g.sum(axis=1) - ref)) / np.max(np.abs(ref))
+        _say("rel err", err)
+        assert err < 1e-9
+        pair = fl.FloquetContext(f_nodes=nodes, checkpoint_every=ckpt, grad_pair_sums=True, **kw)
+        pair.build_ut()
+        gp = pair.grad(Ubar)
+        assert np.max(np.abs(gp.sum(axis=1) - g.sum(axis=1))) < 1e-12 * max(1.0, np.max(np.abs(ref)))
+        return
+    # a reachable loss of order one: Re Tr(W^dagger U) / sqrt(n)
+    w = W / math.sqrt(n)
+    g = ctx.grad(w)
+    u = rng.standard_normal((M, 2))
+    u /= np.linalg.norm(u)
+    eps, vals = 1e-5, []
+    for s in (1, -1):
+        Us = fl.FloquetContext(f_nodes=nodes + s * eps * u, **kw).build_ut().cpu().numpy()
+        vals.append(np.sum(w.conj() * Us).real)
+    fd = (vals[0] - vals[1]) / (2 * eps)
+    _say("direction", np.sum(g * u), "difference", fd)
+    assert abs(np.sum(g * u) - fd) < 1e-8 * max(1.0, abs(fd))
