@@ -97,6 +97,7 @@ struct fq_ctx {
   double* d_ab = nullptr;             // 2*M
   double* d_coef = nullptr;           // 2*(L+1)
   double* d_gauge = nullptr;          // tridiagonal: M x n complex gauge factors
+  double* d_ext = nullptr;            // tridiagonal: extreme eigenvalues of every step
   double* d_stream = nullptr;         // tridiagonal n > resident size: two 8-plane states
   double* d_adj = nullptr;            // streamed reverse sweep: 10 complex n x n vectors
   double* d_vec = nullptr;            // 3 n doubles: period-average accumulators

@@ -144,7 +144,8 @@ struct Layout {
          off_pb = 0, off_pc = 0, off_htx = 0, off_tape = 0, off_small = 0, off_ab = 0, off_coef = 0,
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
-         off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0;
+         off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0,
+         off_ext = 0;
   long np = 0;
   int n_tape = 0;
   int pool_mats = 0, n_extra = 0;
@@ -244,6 +245,7 @@ Layout plan(const fq_system* sys, const fq_params* par) {
       lay.off_y = take(plane2);
     }
     lay.off_gauge = take(2 * sizeof(double) * (size_t)n * (size_t)Ms);
+    lay.off_ext = take(2 * sizeof(double) * (size_t)Ms);
     const bool streamed_grad = streamed_adjoint(sys, par);
     const size_t n16 = (size_t)(n + 15) / 16 * 16;
     const size_t splane = sizeof(double) * n16 * (size_t)n;  // one state plane
@@ -777,39 +779,22 @@ fq_status dense_inner_bounds(fq_ctx* ctx, double* lo_out, double* hi_out) {
   return FQ_OK;
 }
 
+// Exact extremes over all steps, and the gauge factors of every step for the
+// kernels' real-symmetric form of Ht_s (reads the step scalars in d_ab).
 fq_status tridiag_cover(fq_ctx* ctx, double* lo_out, double* hi_out) {
-  const long n = ctx->n;
-  std::vector<double> d0(n), v(n), off(2 * std::max<long>(n - 1, 0));
-  FQ_HIP(ctx, copy_sync(ctx->stream, d0.data(), ctx->sys.h0_diag, n * sizeof(double),
+  FQ_HIP(ctx, fq::launch_tridiag_setup(ctx->n, ctx->M, ctx->sys.h0_diag, ctx->sys.h0_off,
+                                       ctx->sys.hmod_diag, ctx->d_ab, ctx->d_ext, ctx->d_gauge,
+                                       ctx->stream));
+  std::vector<double> ext(2 * (size_t)ctx->M);
+  FQ_HIP(ctx, copy_sync(ctx->stream, ext.data(), ctx->d_ext, ext.size() * sizeof(double),
                         hipMemcpyDeviceToHost));
-  FQ_HIP(ctx, copy_sync(ctx->stream, v.data(), ctx->sys.hmod_diag, n * sizeof(double),
-                        hipMemcpyDeviceToHost));
-  if (n > 1)
-    FQ_HIP(ctx, copy_sync(ctx->stream, off.data(), ctx->sys.h0_off, 2 * (n - 1) * sizeof(double),
-                          hipMemcpyDeviceToHost));
-  std::vector<double> d(n), e(std::max<long>(n - 1, 1));
   double lo = std::numeric_limits<double>::infinity(), hi = -lo;
   for (int k = 0; k < ctx->M; ++k) {
-    const double a = ctx->a[k], b = ctx->b[k];
-    for (long i = 0; i < n; ++i) d[i] = d0[i] + a * v[i];
-    for (long i = 0; i + 1 < n; ++i) {
-      // |h (1 - i b dv)| = |h| sqrt(1 + (b dv)^2)
-      const double hm = std::hypot(off[2 * i], off[2 * i + 1]);
-      e[i] = hm * std::hypot(1.0, b * (v[i + 1] - v[i]));
-    }
-    double l, h;
-    fq::tridiag_extremes(n, d.data(), e.data(), &l, &h);
-    lo = std::min(lo, l);
-    hi = std::max(hi, h);
+    lo = std::min(lo, ext[2 * k]);
+    hi = std::max(hi, ext[2 * k + 1]);
   }
   *lo_out = lo;
   *hi_out = hi;
-  // gauge factors of every step, for the kernel's real-symmetric form of Ht_s
-  std::vector<double> wtab(2 * (size_t)n * ctx->M);
-  for (int k = 0; k < ctx->M; ++k)
-    fq::tridiag_gauge(n, off.data(), v.data(), ctx->b[k], wtab.data() + 2 * (size_t)n * k);
-  FQ_HIP(ctx, copy_sync(ctx->stream, ctx->d_gauge, wtab.data(), wtab.size() * sizeof(double),
-                        hipMemcpyHostToDevice));
   return FQ_OK;
 }
 
@@ -2501,6 +2486,14 @@ fq_status apply_drive(fq_ctx* c, const double* f_nodes) {
       c->b[k] = std::sqrt(3.0) * c->h * (f1 - f2) / 12.0;
     }
   }
+  std::vector<double> ab(2 * c->M);
+  for (int k = 0; k < c->M; ++k) {
+    ab[2 * k] = c->a[k];
+    ab[2 * k + 1] = c->b[k];
+  }
+  if (copy_sync(c->stream, c->d_ab, ab.data(), ab.size() * sizeof(double),
+                hipMemcpyHostToDevice) != hipSuccess)
+    return fail(FQ_ERR_HIP, "upload of the step tables failed");
   // spectral interval
   double lo, hi;
   const bool given = c->interval_given;
@@ -2552,14 +2545,8 @@ fq_status apply_drive(fq_ctx* c, const double* f_nodes) {
   c->phr = std::cos(c->beta * c->h);
   c->phi = -std::sin(c->beta * c->h);
   if (c->layout == FQ_DENSE) FQ_TRY(upload_heff_weights(c));
-  std::vector<double> ab(2 * c->M);
-  for (int k = 0; k < c->M; ++k) {
-    ab[2 * k] = c->a[k];
-    ab[2 * k + 1] = c->b[k];
-  }
-  if (hipMemcpyAsync(c->d_ab, ab.data(), ab.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-      hipMemcpyAsync(c->d_coef, c->coef.data(), c->coef.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-      hipStreamSynchronize(c->stream) != hipSuccess)
+  if (copy_sync(c->stream, c->d_coef, c->coef.data(), c->coef.size() * sizeof(double),
+                hipMemcpyHostToDevice) != hipSuccess)
     return fail(FQ_ERR_HIP, "upload of the step tables failed");
   c->tape_valid = false;
   fill_report(c);
@@ -2629,6 +2616,7 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
       c->yr = P(lay.off_y);   c->yi = c->yr + plane;
     }
     c->d_gauge = P(lay.off_gauge);
+    c->d_ext = P(lay.off_ext);
     if (lay.off_stream) c->d_stream = P(lay.off_stream);
     if (lay.n_tape > 0) {
       c->tape = P(lay.off_tape);

@@ -401,8 +401,12 @@ hipError_t launch_tridiag_adj_persist(const TridiagAdjStream& p, const double* t
                                       hipStream_t s);
 hipError_t launch_tridiag_stream(const TridiagJob& job, const TridiagStream& st, hipStream_t s);
 
-// Unit gauge factors of step s (host FP64): w_0 = 1, w_{i+1} = w_i conj(u_i) with
-// u_i = e_i / |e_i| the phase of Ht[i][i+1] (u_i = 1 where e_i = 0).
-void tridiag_gauge(long n, const double* h0_off, const double* v_diag, double b, double* w_out);
+// Per (sub)step k: extremes[2k], [2k + 1] = the smallest and the largest
+// eigenvalue of H_eff,k, and the unit gauge factors gauge[k][i] (complex): w_0 =
+// 1, w_{i+1} = w_i conj(u_i) with u_i = e_i / |e_i| the phase of Ht[i][i+1] (u_i = 1
+// where e_i = 0). All pointers device memory.
+hipError_t launch_tridiag_setup(long n, int M, const double* h0_diag, const void* h0_off,
+                                const double* v_diag, const double* ab, double* extremes,
+                                double* gauge, hipStream_t s);
 
 }  // namespace fq

@@ -60,6 +60,135 @@ __device__ __forceinline__ void store_part(void* base, long idx, int part, int c
     reinterpret_cast<double*>(base)[2 * idx + part] = v;
 }
 
+// ---- per-step setup: extreme eigenvalues and gauge factors ---------------------------------------
+
+// Extreme eigenvalues of every step's tridiagonal H_eff (diagonal d_i + a v_i,
+// couplings of modulus |h_i| sqrt(1 + (b dv_i)^2)), one workgroup per step: wave
+// 0 finds the smallest, wave 1 the largest (as the smallest of -H). A wave
+// evaluates the Sturm sequence at 64 points of the current interval at once
+// (the number of negative pivots of H - x is the number of eigenvalues below
+// x), so each pass keeps 1/65 of it: ten passes bring Gershgorin's interval to
+// the spacing of doubles, where bisection takes 53. Bound by the serial chain of
+// n divisions per pass; all steps run side by side.
+constexpr int kSturmRows = 2048, kSturmPasses = 11;
+
+__global__ __launch_bounds__(128) void tridiag_extremes_kernel(
+    long n, const double* __restrict__ d0, const double2* __restrict__ off,
+    const double* __restrict__ v, const double* __restrict__ ab, double* __restrict__ out) {
+  __shared__ double dd[kSturmRows], ee[kSturmRows];  // d_i, e_{i-1}^2
+  const int tid = threadIdx.x, lane = tid & 63, neg = tid >> 6;
+  const double a = ab[2 * blockIdx.x], b = ab[2 * blockIdx.x + 1];
+  auto diag = [&](long i) { return d0[i] + a * v[i]; };
+  auto e_sq = [&](long i) {  // coupling of rows i, i + 1
+    const double2 h = off[i];
+    const double q = b * (v[i + 1] - v[i]);
+    return (h.x * h.x + h.y * h.y) * (1.0 + q * q);
+  };
+  const double sgn = neg ? -1.0 : 1.0;
+  // Gershgorin's interval of +-H and the largest squared coupling
+  double lo = 1.7976931348623157e308, hi = -lo, emax = 1.0;
+  for (long i = lane; i < n; i += 64) {
+    const double el = i > 0 ? e_sq(i - 1) : 0.0, eu = i + 1 < n ? e_sq(i) : 0.0;
+    const double r = sqrt(el) + sqrt(eu), d = sgn * diag(i);
+    lo = fmin(lo, d - r);
+    hi = fmax(hi, d + r);
+    emax = fmax(emax, eu);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o));
+    hi = fmax(hi, __shfl_xor(hi, o));
+    emax = fmax(emax, __shfl_xor(emax, o));
+  }
+  // replaces a vanishing pivot: far below any pivot that matters (those of order
+  // eps sqrt(emax)), far enough from overflow for the reciprocal below
+  const double pivmin = 1e-150 * emax;
+  const double pad = 1e-14 * (hi - lo) + 1e-300;
+  lo -= pad;
+  hi += pad;
+  // invariant: no eigenvalue of +-H below lo, at least one below hi
+  for (int pass = 0; pass < kSturmPasses; ++pass) {
+    const double x = lo + (hi - lo) * ((double)(lane + 1) / 65.0);
+    double q = 1.0;
+    bool below = false;  // an eigenvalue below x: a negative pivot
+    for (long r0 = 0; r0 < n; r0 += kSturmRows) {
+      const int m = (int)(n - r0 < kSturmRows ? n - r0 : kSturmRows);
+      if (pass == 0 || n > kSturmRows) {
+        __syncthreads();
+        for (int i = tid; i < m; i += 128) {
+          dd[i] = diag(r0 + i);
+          ee[i] = r0 + i > 0 ? e_sq(r0 + i - 1) : 0.0;
+        }
+        __syncthreads();
+      }
+      if (__all(below)) continue;  // decided for every point (of this wave)
+#pragma unroll 16
+      for (int i = 0; i < m; ++i) {
+        double r = __builtin_amdgcn_rcp(q);  // 1 / q to an ulp or two: a relative
+        r = fma(fma(-q, r, 1.0), r, r);      // change of the squared coupling by eps
+        r = fma(fma(-q, r, 1.0), r, r);
+        q = fma(-ee[i], r, sgn * dd[i] - x);
+        if (fabs(q) < pivmin) q = -pivmin;
+        below = below || q < 0.0;
+      }
+    }
+    const unsigned long long mask = __ballot(below);
+    const int first = mask ? __ffsll(mask) - 1 : 64;  // points from `first` on lie above it
+    const double xa = __shfl(x, first > 0 ? first - 1 : 0), xb = __shfl(x, first < 64 ? first : 63);
+    if (first > 0 && xa > lo) lo = xa;
+    if (first < 64 && xb < hi) hi = xb;
+  }
+  if (lane == 0) out[2 * blockIdx.x + neg] = neg ? -lo : lo;
+}
+
+// Unit gauge factors of every step, one workgroup per step: w_0 = 1, w_{i+1} =
+// w_i conj(u_i) with u_i the phase of Ht[i][i+1] = h_i (1 - i b dv_i) (1 where that
+// vanishes), which makes D^+ Ht D real for D = diag(w). What matters is the
+// ratio of neighbours; each thread multiplies up a run of rows, the runs'
+// products are scanned, and every factor is renormalised, so a ratio is off by
+// a few roundings (a relative change of the coupling of that size), however
+// long the chain.
+__global__ __launch_bounds__(256) void tridiag_gauge_table_kernel(
+    long n, const double2* __restrict__ off, const double* __restrict__ v,
+    const double* __restrict__ ab, double2* __restrict__ out) {
+  __shared__ double2 run[2][256];
+  const int t = threadIdx.x;
+  const double b = ab[2 * blockIdx.x + 1];
+  const long c = (n + 255) / 256, i0 = t * c < n ? t * c : n, i1 = i0 + c < n ? i0 + c : n;
+  double2* w_out = out + (long)blockIdx.x * n;
+  auto next = [&](double2 w, long i) {  // w_i -> w_{i+1}
+    const double2 h = off[i];
+    const double q = b * (v[i + 1] - v[i]);
+    const double er = h.x + h.y * q, ei = h.y - h.x * q;
+    if (er == 0.0 && ei == 0.0) return w;
+    const double nr = w.x * er + w.y * ei, ni = w.y * er - w.x * ei;  // w conj(e)
+    const double m = 1.0 / hypot(nr, ni);
+    return make_double2(nr * m, ni * m);
+  };
+  double2 p = make_double2(1.0, 0.0);
+  for (long i = i0; i < i1 && i + 1 < n; ++i) p = next(p, i);
+  run[0][t] = p;
+  __syncthreads();
+  int cur = 0;
+  for (int o = 1; o < 256; o <<= 1) {  // inclusive products of the runs
+    double2 x = run[cur][t];
+    if (t >= o) {
+      const double2 y = run[cur][t - o];
+      const double nr = x.x * y.x - x.y * y.y, ni = x.x * y.y + x.y * y.x;
+      const double m = 1.0 / hypot(nr, ni);
+      x = make_double2(nr * m, ni * m);
+    }
+    run[cur ^ 1][t] = x;
+    __syncthreads();
+    cur ^= 1;
+  }
+  double2 w = t > 0 ? run[cur][t - 1] : make_double2(1.0, 0.0);
+  for (long i = i0; i < i1; ++i) {
+    w_out[i] = w;
+    if (i + 1 < n) w = next(w, i);
+  }
+}
+
 template <int R, int MAXT, bool MULTI>
 __global__ __launch_bounds__(MAXT) void tridiag_gauge_kernel(TridiagJob job, int G,
                                                              const double2* __restrict__ coef,
@@ -1515,6 +1644,18 @@ __global__ __launch_bounds__(128) void tridiag_adj_persist_kernel(TridiagAdjStre
 }
 
 }  // namespace
+
+hipError_t launch_tridiag_setup(long n, int M, const double* h0_diag, const void* h0_off,
+                                const double* v_diag, const double* ab, double* extremes,
+                                double* gauge, hipStream_t s) {
+  if (n < 1 || M < 1 || (n > 1 && !h0_off)) return hipErrorInvalidValue;
+  const double2* off = reinterpret_cast<const double2*>(h0_off);
+  hipLaunchKernelGGL(tridiag_extremes_kernel, dim3((unsigned)M), dim3(128), 0, s, n, h0_diag, off,
+                     v_diag, ab, extremes);
+  hipLaunchKernelGGL(tridiag_gauge_table_kernel, dim3((unsigned)M), dim3(256), 0, s, n, off, v_diag,
+                     ab, reinterpret_cast<double2*>(gauge));
+  return hipGetLastError();
+}
 
 // 16 rows per lane and up to 4 waves per part (512 threads, <= 256 VGPRs).
 long tridiag_resident_max_n() { return 4L * 64 * 16; }

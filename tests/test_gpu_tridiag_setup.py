@@ -1,0 +1,84 @@
+"""Per-step setup of the tridiagonal layout on the GPU: the extreme eigenvalues
+of every step's H_eff and the gauge factors, against the host bisection of the
+same matrices and (through U_T) the oracle, at the edges of the kernels' chunks.
+
+Tolerances: both searches end within a few spacings of doubles at the scale of
+the spectrum; U_T against the oracle at the library's FP64 bar.
+"""
+import numpy as np
+import pytest
+
+import oracle as orc
+from workloads import dimer_tridiag
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fl(require_gpu):
+    from paper_1508_07621_amd import floquet
+    floquet.node_times(1.0, 1)          # loads the library or raises
+    return floquet
+
+
+def _problem(n, seed):
+    rng = np.random.default_rng(seed)
+    d = rng.standard_normal(n) * 3.0
+    e = rng.standard_normal(max(n - 1, 0)) + 1j * rng.standard_normal(max(n - 1, 0))
+    if n > 4:
+        e[n // 2] = 0.0                 # a chain in two pieces
+    v = rng.standard_normal(n)
+    return d, e, v
+
+
+# one row, a few, the ends of 64-lane and 256-thread runs, one LDS chunk of 2048
+# rows and the next
+@pytest.mark.parametrize("n", [1, 2, 3, 64, 65, 256, 257, 2047, 2048, 2049, 4100])
+def test_extremes_of_every_step(fl, n):
+    print("[case] extremes", n, flush=True)
+    T, M = 0.7, 3
+    d, e, v = _problem(n, 300 + n)
+    f = np.random.default_rng(n).uniform(-2, 2, (M, 2))
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=f)
+    a, b = orc.magnus4_weights(f, T / M)
+    lo, hi = np.inf, -np.inf
+    for k in range(M):
+        ek = np.abs(e * (1.0 - 1j * b[k] * np.diff(v)))
+        l, h = fl.tridiag_extremes(d + a[k] * v, ek)
+        lo, hi = min(lo, l), max(hi, h)
+    rep = ctx.report
+    scale = max(abs(lo), abs(hi))
+    if n == 1:  # a constant H widens its interval
+        assert rep["e_min"] <= lo <= hi <= rep["e_max"]
+        return
+    print("[case]", rep["e_min"] - lo, rep["e_max"] - hi, flush=True)
+    assert abs(rep["e_min"] - lo) < 1e-13 * scale and abs(rep["e_max"] - hi) < 1e-13 * scale
+
+
+def test_vanishing_pivots(fl):
+    """Zero diagonal: pivots that vanish exactly at the middle of the interval."""
+    n, T, M = 201, 1.0, 2
+    e = np.ones(n - 1)
+    ctx = fl.FloquetContext(h0_diag=np.zeros(n), h0_off=e, hmod_diag=np.zeros(n), T=T, M=M,
+                            f_nodes=np.zeros((M, 2)))
+    x = 2.0 * np.cos(np.pi / (n + 1))
+    rep = ctx.report
+    assert abs(rep["e_min"] + x) < 1e-14 and abs(rep["e_max"] - x) < 1e-14
+
+
+@pytest.mark.parametrize("n", [2, 130, 257, 700])
+def test_complex_couplings_through_the_gauge(fl, n):
+    """U_T for random complex couplings with b_k != 0: the gauge factors of
+    every step against the oracle, which has no gauge."""
+    print("[case] gauge", n, flush=True)
+    T, M = 0.9, 6
+    d, e, v = _problem(n, 500 + n)
+    f = np.random.default_rng(n).uniform(-2, 2, (M, 2))
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=f)
+    U = ctx.build_ut().cpu().numpy()
+    rep = ctx.report
+    ref = orc.build_ut_tridiag(d, e, v, f, T, M, route="cheb", e_min=rep["e_min"],
+                               e_max=rep["e_max"], L=rep["L"])
+    err = orc.column_error(U, ref)
+    print("[case] e_col", err, flush=True)
+    assert err < 1e-12
