@@ -842,7 +842,7 @@ def main():
         roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP64_VECTOR_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP64_VECTOR_TFLOPS, 4),
                 "traffic": tr["bytes"] if tr else None, "traffic_detail": tr,
-                "kernel": ("tridiag_gauge_kernel<16,512> (whole chain per state column, real gauge form)"
+                "kernel": ("tridiag_chain_kernel<16> (whole chain per state column, real gauge form)"
                            if n <= TRIDIAG_RESIDENT_MAX_N else
                            "tridiag_stream_kernel<16,1> (128-term passes; 768 owned + 2 x 128 ghost "
                            "rows per workgroup, real gauge form)"),

@@ -97,6 +97,8 @@ struct fq_ctx {
   double* d_ab = nullptr;             // 2*M
   double* d_coef = nullptr;           // 2*(L+1)
   double* d_gauge = nullptr;          // tridiagonal: M x n complex gauge factors
+  double* d_tab = nullptr;            // tridiagonal: rows of every step (resident columns)
+  double* d_fgrid = nullptr;          // tridiagonal: the period average's drive samples
   double* d_ext = nullptr;            // tridiagonal: extreme eigenvalues of every step
   double* d_stream = nullptr;         // tridiagonal n > resident size: two 8-plane states
   double* d_adj = nullptr;            // streamed reverse sweep: 10 complex n x n vectors

@@ -145,7 +145,7 @@ struct Layout {
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
          off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0,
-         off_ext = 0;
+         off_ext = 0, off_tab = 0, off_fgrid = 0;
   long np = 0;
   int n_tape = 0;
   int pool_mats = 0, n_extra = 0;
@@ -161,6 +161,11 @@ struct Layout {
 // the static scratch of the one-shot build wherever the rest does.
 constexpr int kPoolBufs = 6, kExtraBufs = 2, kPoolSegments = 128;
 constexpr size_t kPoolBudget = size_t(250) << 20, kPoolBytes = size_t(144) << 20;
+constexpr size_t kStaticBytes = size_t(256) << 20;  // the one-shot build's static scratch
+// Tridiagonal builds: segments at most, bytes of their matrices, and of the step
+// rows where the static scratch sets no bound.
+constexpr int kTridiagSegments = 64;
+constexpr size_t kTridiagPool = size_t(64) << 20, kTabBytes = size_t(2) << 30;
 // The gradient's scratch: matrices per member of a batch (adj_bufs at the longest
 // plan), the most they may take before the term-by-term sweep stays, and the most
 // the sweep in segments may take (it holds a matrix per step).
@@ -246,6 +251,7 @@ Layout plan(const fq_system* sys, const fq_params* par) {
     }
     lay.off_gauge = take(2 * sizeof(double) * (size_t)n * (size_t)Ms);
     lay.off_ext = take(2 * sizeof(double) * (size_t)Ms);
+    lay.off_fgrid = take(sizeof(double) * (size_t)Ms);
     const bool streamed_grad = streamed_adjoint(sys, par);
     const size_t n16 = (size_t)(n + 15) / 16 * 16;
     const size_t splane = sizeof(double) * n16 * (size_t)n;  // one state plane
@@ -273,6 +279,23 @@ Layout plan(const fq_system* sys, const fq_params* par) {
   lay.off_vec = take(3 * sizeof(double) * (size_t)n);
   lay.off_ab = take(2 * sizeof(double) * (size_t)Ms);
   lay.off_coef = take(2 * sizeof(double) * (size_t)(kMaxOrder + 1));
+  if (!dense_like(sys->layout) && n <= fq::tridiag_resident_max_n()) {
+    // segments of a build and their products; then the rows of every step, while
+    // both keep inside the static scratch (or the rest does not anyway)
+    const size_t plane2 = 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np;
+    const bool held = par->checkpoint_every > 0 || cur > kStaticBytes;
+    size_t left = held ? kTabBytes : (kPoolBudget > cur ? kPoolBudget - cur : 0);
+    if (par->checkpoint_every == 0) {
+      lay.pool_mats = (int)std::min<size_t>(
+          2 * (size_t)std::min<long>(kTridiagSegments, Ms), std::min(left, kTridiagPool) / plane2);
+      if (lay.pool_mats < 4) lay.pool_mats = 0;  // two segments
+      if (lay.pool_mats > 0) lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
+      left -= std::min(left, plane2 * (size_t)lay.pool_mats);
+    }
+    const long R = fq::tridiag_chain_rows(n), nr = pad_to(n, R);
+    const size_t tab = 4 * sizeof(double) * (size_t)nr * (size_t)Ms;
+    if (tab <= left) lay.off_tab = take(tab);
+  }
   lay.zeroed = cur;
   if (lay.adj_mats > 0)
     lay.off_seg = take(lay.adj_mats * 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np);
@@ -1530,10 +1553,9 @@ void fill_report(fq_ctx* c) {
   c->last.e_max = c->e_max;
 }
 
-fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, void* x_out) {
+fq::TridiagJob tridiag_job(const fq_ctx* c) {
   fq::TridiagJob job{};
   job.n = c->n;
-  job.ncols = ncols;
   job.h0_diag = c->sys.h0_diag;
   job.h0_off = reinterpret_cast<const double*>(c->sys.h0_off);
   job.v_diag = c->sys.hmod_diag;
@@ -1541,17 +1563,67 @@ fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, voi
   job.coef = c->d_coef;
   job.gauge = c->d_gauge;
   job.L = c->L;
-  job.k0 = k0;
-  job.k1 = k1;
   job.beta = c->beta;
   job.inv_dE = 1.0 / c->dE;
   job.phr = c->phr;
   job.phi = c->phi;
+  job.c64 = c->c64 ? 1 : 0;
+  const long R = fq::tridiag_chain_rows(c->n);
+  job.nq = (c->n + R - 1) / R;
+  job.tab = c->d_tab;
+  job.M = c->M;
+  return job;
+}
+
+// Segments of a whole build of resident columns. A term takes the longer of a
+// lone wave's latency (45 ns and 6.7 ns per row of a lane, measured with R = 1
+// .. 16) and the issue of the waves that share a SIMD (6.7 ns per row and wave);
+// a column has 2 waves (n <= 1024), the chip 1024 SIMDs. Multiplying the
+// segments up costs a launch of about 6 us per level and 8 np^3 flop per
+// product at 50 TF/s.
+int tridiag_segments(const fq_ctx* c) {
+  if (c->n > 1024 || c->pool_mats < 4 || c->tape) return 1;
+  const double R = fq::tridiag_chain_rows(c->n), np = (double)c->np;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int nseg = 1, level = 0; nseg <= std::min(c->pool_mats / 2, c->M); nseg *= 2, ++level) {
+    const double waves = std::ceil(2.0 * (double)c->n * nseg / 1024.0);
+    const double term = std::max(45e-9 + 6.7e-9 * R, waves * 6.7e-9 * R);
+    const double cost = std::ceil((double)c->M / nseg) * (c->L + 20) * term + level * 6e-6 +
+                        (nseg - 1) * 8.0 * np * np * np / 5e13;
+    if (nseg == 1 || cost < best_cost) {
+      best_cost = cost;
+      best = nseg;
+    }
+  }
+  return best;
+}
+
+// A build in nseg segments, multiplied up into the X planes.
+fq_status tridiag_build_segments(fq_ctx* c, int nseg) {
+  fq::TridiagJob job = tridiag_job(c);
+  job.ncols = c->n;
+  job.k0 = 0;
+  job.k1 = c->M;
+  job.len0 = c->M / nseg;
+  job.rem = c->M % nseg;
+  job.planes = c->pool;
+  job.ld_planes = c->np;
+  job.bs = 2 * c->np * c->np;
+  FQ_MARK(c, FQ_K_TRIDIAG);
+  FQ_HIP(c, fq::launch_tridiag_resident(job, nseg, c->stream));
+  return multiply_up(c, c->pool, c->pool + (size_t)nseg * job.bs, nseg);
+}
+
+fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, void* x_out) {
+  fq::TridiagJob job = tridiag_job(c);
+  job.ncols = ncols;
+  job.k0 = k0;
+  job.k1 = k1;
   job.x0 = x0;
   job.ld_x0 = ncols;
   job.x_out = x_out;
   job.ld_out = ncols;
-  job.c64 = c->c64 ? 1 : 0;
   if (c->snap) {
     job.snap = static_cast<double*>(c->snap);
     job.snap_every = c->snap_every;
@@ -1563,7 +1635,7 @@ fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, voi
   }
   if (c->n <= fq::tridiag_resident_max_n()) {
     FQ_MARK(c, FQ_K_TRIDIAG);
-    FQ_HIP(c, fq::launch_tridiag_resident(job, c->stream));
+    FQ_HIP(c, fq::launch_tridiag_resident(job, 1, c->stream));
     return FQ_OK;
   }
   // Longer columns: k-term passes with ghost rows, state ping-ponged through HBM.
@@ -2080,22 +2152,9 @@ fq_status tridiag_adjoint_streamed(fq_ctx* c, const void* U_bar, double* grad_f_
   const size_t plane = (size_t)n16 * (size_t)n;  // doubles per state plane
 
   // forward passes of the recompute: the build's job and pass geometry
-  fq::TridiagJob job{};
-  job.n = n;
+  fq::TridiagJob job = tridiag_job(c);
   job.ncols = n;
-  job.h0_diag = c->sys.h0_diag;
-  job.h0_off = reinterpret_cast<const double*>(c->sys.h0_off);
-  job.v_diag = c->sys.hmod_diag;
-  job.ab = c->d_ab;
-  job.coef = c->d_coef;
-  job.gauge = c->d_gauge;
-  job.L = L;
-  job.beta = c->beta;
-  job.inv_dE = 1.0 / c->dE;
-  job.phr = c->phr;
-  job.phi = c->phi;
   job.ld_x0 = n;
-  job.c64 = c->c64 ? 1 : 0;
   fq::TridiagStream st{};
   st.G = 1;
   st.n16 = n16;
@@ -2269,7 +2328,7 @@ fq_status tridiag_adjoint(fq_ctx* c, const void* U_bar, double* grad_f_nodes) {
 // not the device array: the device address comes from hipGetSymbolAddress,
 // taken once per device with that device current, and only that address is
 // handed to kernels and copies.
-constexpr size_t kStaticScratchBytes = size_t(256) << 20;  // 256 MiB
+constexpr size_t kStaticScratchBytes = kStaticBytes;  // 256 MiB
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -2545,6 +2604,7 @@ fq_status apply_drive(fq_ctx* c, const double* f_nodes) {
   c->phr = std::cos(c->beta * c->h);
   c->phi = -std::sin(c->beta * c->h);
   if (c->layout == FQ_DENSE) FQ_TRY(upload_heff_weights(c));
+  if (c->d_tab) FQ_HIP(c, fq::launch_tridiag_table(tridiag_job(c), c->M, c->d_tab, c->stream));
   if (copy_sync(c->stream, c->d_coef, c->coef.data(), c->coef.size() * sizeof(double),
                 hipMemcpyHostToDevice) != hipSuccess)
     return fail(FQ_ERR_HIP, "upload of the step tables failed");
@@ -2617,6 +2677,12 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     }
     c->d_gauge = P(lay.off_gauge);
     c->d_ext = P(lay.off_ext);
+    c->d_fgrid = P(lay.off_fgrid);
+    if (lay.off_tab) c->d_tab = P(lay.off_tab);
+    if (lay.pool_mats > 0) {
+      c->pool = P(lay.off_pool);
+      c->pool_mats = lay.pool_mats;
+    }
     if (lay.off_stream) c->d_stream = P(lay.off_stream);
     if (lay.n_tape > 0) {
       c->tape = P(lay.off_tape);
@@ -2778,14 +2844,19 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
       c->snap_k0 = 0;
       c->snap_ncols = c->n;
     }
-    st = tridiag_run(c, nullptr, c->n, 0, c->M, U_out);
+    const int nseg = tridiag_segments(c);
+    st = nseg > 1 ? tridiag_build_segments(c, nseg) : tridiag_run(c, nullptr, c->n, 0, c->M, U_out);
     c->snap = nullptr;
     if (st != FQ_OK) return st;
     FQ_MARK(c, -1);
     if (e1) FQ_HIP(c, hipEventRecord(e1, c->stream));
     c->tape_valid = c->ckpt > 0;
-    FQ_HIP(c, fq::launch_pack_planar_t(U_out, c->n, c->n, c->n, c->xr, c->xi, c->np, c->np, c->c64,
-                                       c->stream));
+    if (nseg > 1)
+      FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, c->n, U_out, c->n, c->c64,
+                                           c->stream));
+    else
+      FQ_HIP(c, fq::launch_pack_planar_t(U_out, c->n, c->n, c->n, c->xr, c->xi, c->np, c->np,
+                                         c->c64, c->stream));
     st = unitarity(c, c->xr, c->xi);
     if (st == FQ_OK && c->reortho) st = finish_reortho(c, U_out);
   }
@@ -2893,6 +2964,21 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
                                        c->stream));
       FQ_TRY(dense_steps(c, k * spp, (k + 1) * spp, (int)rows, false));
     }
+  } else if (c->n <= fq::tridiag_resident_max_n()) {  // inside the chain's one launch
+    FQ_HIP(c, copy_sync(c->stream, c->d_fgrid, f_grid, sizeof(double) * (size_t)c->M_user,
+                        hipMemcpyHostToDevice));
+    fq::TridiagJob job = tridiag_job(c);
+    job.ncols = ncols;
+    job.k0 = 0;
+    job.k1 = c->M;
+    job.x0 = X0;
+    job.ld_x0 = ncols;
+    job.avg = avg;
+    job.f_grid = c->d_fgrid;
+    job.avg_w = w;
+    job.spp = spp;
+    FQ_MARK(c, FQ_K_TRIDIAG);
+    FQ_HIP(c, fq::launch_tridiag_resident(job, 1, c->stream));
   } else {
     // the states in the user layout, propagated in place one step at a time
     void* x = c->xr;

@@ -301,10 +301,32 @@ struct TridiagJob {
   double* snap;          // optional: X_{k0 + (j+1) snap_every}, complex n x ncols row-major
   int snap_every;        //   (block j at element j n ncols)
   int c64;               // x0, x_out and snap hold complex64 (else complex128)
+  // resident kernel: rows of every step (launch_tridiag_table; null: formed per
+  // column from the operators), nq = ceil(n / tridiag_chain_rows(n)), M the last
+  // step of the table
+  const double* tab;
+  long nq;
+  int M;
+  // nseg > 1 (x0 null): steps k0+1 .. k1 in nseg segments, the first rem of len0 + 1
+  // steps, each propagating the identity; with `planes` the result goes to
+  // state-major planes (row = column of the block, stride ld_planes; segment z
+  // at + z * bs, im plane at + bs / 2) instead of x_out
+  int len0, rem;
+  double* planes;
+  long ld_planes, bs;
+  // avg: the energy averages instead of x_out: avg[col] = avg_w sum over the steps s
+  // with s % spp == 0 of <x_s| H0 + f_grid[s / spp] Hmod |x_s> / <x_s|x_s>
+  double* avg;
+  const double* f_grid;
+  double avg_w;
+  int spp;
 };
 // Returns hipErrorInvalidValue when n exceeds what one workgroup can hold.
-hipError_t launch_tridiag_resident(const TridiagJob& job, hipStream_t s);
+hipError_t launch_tridiag_resident(const TridiagJob& job, int nseg, hipStream_t s);
 long tridiag_resident_max_n();
+int tridiag_chain_rows(long n);  // rows per lane
+// Step tables of all M steps: 4 nq tridiag_chain_rows(n) doubles each.
+hipError_t launch_tridiag_table(const TridiagJob& job, int M, double* out, hipStream_t s);
 
 // Longer columns: one launch runs terms [l0, l1) of step s on blocks of B owned
 // rows with K ghost rows per side (B + 2K = tridiag_stream_rows(G)), reading the

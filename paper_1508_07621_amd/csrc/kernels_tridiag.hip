@@ -36,9 +36,6 @@ __device__ __forceinline__ double from_next_lane(double v) {  // lane l <- lane 
   return __hiloint2double(hi, lo);
 }
 
-// coef, tape and snap come as separate restrict-qualified arguments so that the
-// checkpoint and snapshot stores inside the step loop cannot be taken to alias
-// the coefficient table, which then stays on scalar loads.
 // Complex state elements of the user blocks: complex128, or complex64 when c64.
 __device__ __forceinline__ void load_state(const void* base, long idx, int c64, double& re,
                                            double& im) {
@@ -189,30 +186,132 @@ __global__ __launch_bounds__(256) void tridiag_gauge_table_kernel(
   }
 }
 
-template <int R, int MAXT, bool MULTI>
-__global__ __launch_bounds__(MAXT) void tridiag_gauge_kernel(TridiagJob job, int G,
-                                                             const double2* __restrict__ coef,
-                                                             double* __restrict__ tape,
-                                                             double* __restrict__ snap) {
-  extern __shared__ double ysh[];  // [part][lane in part][r][2]
-  __shared__ double halo[2][2][2][kMaxWaves];  // [parity][part][0 first row, 1 last row][wave]
+// Row i of 2 Ht_s (zero outside the column) and the factor phase w_s [conj(w_{s+1})].
+struct TridiagRow {
+  double d2, g2;
+};
+__device__ __forceinline__ TridiagRow tridiag_row(const TridiagJob& job, int s, long i) {
+  TridiagRow row{0.0, 0.0};
+  if (i >= job.n) return row;
+  const double a = job.ab[2 * s], b = job.ab[2 * s + 1];
+  const double vi = job.v_diag[i];
+  row.d2 = 2.0 * (job.h0_diag[i] + a * vi - job.beta) * job.inv_dE;
+  if (i + 1 < job.n) {
+    const double2 h = reinterpret_cast<const double2*>(job.h0_off)[i];
+    const double q = b * (job.v_diag[i + 1] - vi);
+    row.g2 = 2.0 * sqrt((h.x * h.x + h.y * h.y) * (1.0 + q * q)) * job.inv_dE;
+  }
+  return row;
+}
+__device__ __forceinline__ double2 tridiag_rotation(const TridiagJob& job, int s, long i,
+                                                    bool next) {
+  const double2* gauge = reinterpret_cast<const double2*>(job.gauge);
+  const double2 ws = gauge[(long)s * job.n + i];
+  double rr = job.phr * ws.x - job.phi * ws.y, ri = job.phr * ws.y + job.phi * ws.x;
+  if (next) {
+    const double2 wn = gauge[(long)(s + 1) * job.n + i];
+    const double tr = rr * wn.x + ri * wn.y, ti = ri * wn.x - rr * wn.y;
+    rr = tr;
+    ri = ti;
+  }
+  return make_double2(rr, ri);
+}
+
+// Rows of every step in the lane order of the chain kernel: 2 d_i, 2 g_i, and the
+// rotation phase w_s conj(w_{s+1}) that ends step s (phase w_s after the last
+// one); row i at (i mod R) nq + i / R, so that the R rows a lane owns are
+// unit-stride loads across the wave. Rows from n on are zero.
+__global__ __launch_bounds__(256) void tridiag_table_kernel(TridiagJob job, int R, int M,
+                                                            double* __restrict__ out) {
+  const long n = job.n, nq = job.nq, nr = nq * R;
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  const int s = blockIdx.y;
+  if (i >= nr) return;
+  const TridiagRow row = tridiag_row(job, s, i);
+  double2 rot = make_double2(0.0, 0.0);
+  if (i < n) rot = tridiag_rotation(job, s, i, s + 1 < M);
+  double* t = out + (long)s * 4 * nr + (i % R) * nq + i / R;
+  t[0] = row.d2;
+  t[nr] = row.g2;
+  t[2 * nr] = rot.x;
+  t[3 * nr] = rot.y;
+}
+
+// The whole chain of one column (or one segment of it, blockIdx.y) in one
+// workgroup: G waves per part, lane pl of a part holding rows R pl .. R pl + R - 1.
+//
+// Bound by FP64 vector issue for many columns: per row and term three FMAs for
+// the stencil and one for the sum. 1000-state dimer, 500 steps of 68 terms, 2 waves
+// per SIMD: 11.5 ms, 76 TF/s at 26 flop per element and term and 60 % of the FMA issue at 2.4
+// GHz (17.0 ms when every column formed its rows, square roots included, from
+// strided operator loads in every step, and both halves of the sum went through
+// LDS). For few or short columns bound by the latency of one term after the other, which is why a
+// build with fewer columns than the chip has room for runs its segments side by
+// side, and why short columns take fewer rows per lane (R = 1 up to 64 rows): a
+// 21-state, 200-step build 653 -> 100 us. Per step a
+// lane reads its rows from the step table (R <= 8: loaded during the step
+// before; R = 16 has no registers to spare) and sends its half of the other
+// part's sum through LDS, one value per row and one barrier.
+//
+// ENERGY: avg[col] += w sum_s <x_s| H0 + f_s Hmod |x_s> / <x_s|x_s> over the steps
+// s with s % spp == 0, from the state in the gauge frame of step s, where
+// conj(x_i) h_i x_{i+1} = conj(x~_i) x~_{i+1} |h_i| (1 + i q) / sqrt(1 + q^2), q = b dv_i:
+// the real part of conj(x~_i) x~_{i+1} is a sum over the parts, the imaginary part
+// (q != 0) takes the other part's rows through LDS. All 1000 states of that
+// dimer: 15.9 ms, where a launch per step and two for its energies took 51 ms.
+template <int R, bool MULTI, bool ENERGY>
+__global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
+    TridiagJob job, int G, const double2* __restrict__ coef, const double* __restrict__ tab,
+    double* __restrict__ tape, double* __restrict__ snap) {
+  constexpr int PW = MULTI ? 256 : 64;                   // lanes per part, at most
+  constexpr int XB = MULTI ? 1 : 2;                      // buffers (LDS holds one of 4 waves)
+  __shared__ double xch[XB][2][R][PW];                   // [buffer][part][row][lane]
+  __shared__ double halo[2][2][2][MULTI ? kMaxWaves : 1];  // [parity][part][0 first row, 1 last row][wave]
+  __shared__ double esum[2][2][2 * (MULTI ? kMaxWaves : 1)];  // [parity][num, den][wave]
 
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int part = wid / G, w = wid % G;
+  const int part = MULTI ? wid / G : wid, w = MULTI ? wid % G : 0;
   const int pl = w * 64 + lane;  // lane index within its part
   const long col = blockIdx.x;
-  const long n = job.n;
+  const long n = job.n, nq = job.nq, nr = nq * R;
   const long base = (long)pl * R;
   const double sgn = part == 0 ? 1.0 : -1.0;
+  // this segment's steps
+  int k_lo = job.k0, k_hi = job.k1;
+  const int seg = blockIdx.y;
+  if (gridDim.y > 1) {
+    k_lo += seg * job.len0 + (seg < job.rem ? seg : job.rem);
+    k_hi = k_lo + job.len0 + (seg < job.rem ? 1 : 0);
+  }
   const double2* gauge = reinterpret_cast<const double2*>(job.gauge);
-  const double2* h0o = reinterpret_cast<const double2*>(job.h0_off);
 
   double pa[R], pb[R];  // the two most recent terms (roles alternate)
   double ys[R], yo[R];  // share of the sum: ys -> this part's component, yo -> the other one
   double d2[R], g2[R];  // 2 G: diagonal, coupling to the next row
   double gm2 = 0.0;     // 2 G coupling of row base-1 to row base
 
-  // X~ = D_{k0}^+ X, this part's component
+  auto rows_of = [&](int s, double* d, double* g, double& gm) {
+    if (tab) {
+      const double* t = tab + (long)s * 4 * nr;
+      const bool in = pl < nq;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        d[r] = in ? t[r * nq + pl] : 0.0;
+        g[r] = in ? t[nr + r * nq + pl] : 0.0;
+      }
+      gm = in && pl > 0 ? t[nr + (R - 1) * nq + pl - 1] : 0.0;
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const TridiagRow row = tridiag_row(job, s, base + r);
+        d[r] = row.d2;
+        g[r] = row.g2;
+      }
+      gm = base >= 1 ? tridiag_row(job, s, base - 1).g2 : 0.0;
+    }
+  };
+
+  // X~ = D_{k_lo}^+ X, this part's component
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const long i = base + r;
@@ -225,10 +324,10 @@ __global__ __launch_bounds__(MAXT) void tridiag_gauge_kernel(TridiagJob job, int
         xr = (i == col) ? 1.0 : 0.0;
         xi = 0.0;
       }
-      const double2 g = gauge[(long)job.k0 * n + i];
+      const double2 g = gauge[(long)k_lo * n + i];
       v = part == 0 ? g.x * xr + g.y * xi : g.x * xi - g.y * xr;  // conj(w) x
-      if (tape && job.k0 % job.ckpt == 0)  // checkpoint of X_{k0} (plain frame)
-        tape[2 * (((long)(job.k0 / job.ckpt) * job.ncols + col) * n + i) + part] =
+      if (tape && k_lo % job.ckpt == 0)  // checkpoint of X_{k_lo} (plain frame)
+        tape[2 * (((long)(k_lo / job.ckpt) * job.ncols + col) * n + i) + part] =
             part == 0 ? xr : xi;
     }
     pa[r] = v;
@@ -259,7 +358,7 @@ __global__ __launch_bounds__(MAXT) void tridiag_gauge_kernel(TridiagJob job, int
     {
       double t = fma(d2[0], v[0], -nw[0]);
       t = fma(gm2, up, t);
-      nw[0] = fma(g2[0], (R > 1) ? v[1] : dn, t);
+      nw[0] = fma(g2[0], (R > 1) ? v[R > 1 ? 1 : 0] : dn, t);
     }
     if constexpr (R > 1) {
       double t = fma(d2[R - 1], v[R - 1], -nw[R - 1]);
@@ -282,30 +381,106 @@ __global__ __launch_bounds__(MAXT) void tridiag_gauge_kernel(TridiagJob job, int
 #pragma unroll
     for (int r = 0; r < R; ++r) yo[r] = fma(c, p[r], yo[r]);
   };
-
-  const int L = job.L;
-  for (int s = job.k0; s < job.k1; ++s) {
-    const double a = job.ab[2 * s], b = job.ab[2 * s + 1];
+  // this part's share v of the other part's component goes to that part
+  int xp = 0;
+  auto trade = [&](const double* v, double* got) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const long i = base + r;
-      d2[r] = 0.0;
-      g2[r] = 0.0;
-      if (i < n) {
-        const double vi = job.v_diag[i];
-        d2[r] = 2.0 * (job.h0_diag[i] + a * vi - job.beta) * job.inv_dE;
-        if (i + 1 < n) {
-          const double2 h = h0o[i];
-          const double q = b * (job.v_diag[i + 1] - vi);
-          g2[r] = 2.0 * sqrt((h.x * h.x + h.y * h.y) * (1.0 + q * q)) * job.inv_dE;
+    for (int r = 0; r < R; ++r) xch[xp][part][r][pl] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) got[r] = xch[xp][1 - part][r][pl];
+    if constexpr (XB == 2)
+      xp ^= 1;
+    else
+      __syncthreads();
+  };
+
+  constexpr bool AHEAD = R <= 8;  // the next step's rows during this step
+  constexpr int RA = AHEAD ? R : 1;
+  double d2n[RA], g2n[RA], gmn = 0.0;
+  if constexpr (AHEAD) rows_of(k_lo, d2n, g2n, gmn);
+
+  double e_avg = 0.0;  // ENERGY: thread 0's sum of this column
+  const int L = job.L;
+  for (int s = k_lo; s < k_hi; ++s) {
+    const bool final_step = (s + 1 == k_hi);
+    double rr[R], ri[R];
+    auto rotation = [&]() {
+      const bool step_table = tab && (!final_step || s + 1 == job.M);
+      if (step_table) {
+        const double* t = tab + (long)s * 4 * nr + 2 * nr;
+        const bool in = pl < nq;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          rr[r] = in ? t[r * nq + pl] : 0.0;
+          ri[r] = in ? t[nr + r * nq + pl] : 0.0;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          double2 q = make_double2(0.0, 0.0);
+          if (base + r < n) q = tridiag_rotation(job, s, base + r, !final_step);
+          rr[r] = q.x;
+          ri[r] = q.y;
         }
       }
+    };
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        d2[r] = d2n[r];
+        g2[r] = g2n[r];
+      }
+      gm2 = gmn;
+      if (!final_step) rows_of(s + 1, d2n, g2n, gmn);
+      rotation();
+    } else {
+      rows_of(s, d2, g2, gm2);
     }
-    gm2 = 0.0;
-    if (base >= 1 && base < n) {
-      const double2 h = h0o[base - 1];
-      const double q = b * (job.v_diag[base] - job.v_diag[base - 1]);
-      gm2 = 2.0 * sqrt((h.x * h.x + h.y * h.y) * (1.0 + q * q)) * job.inv_dE;
+
+    if constexpr (ENERGY) {
+      const double b = job.ab[2 * s + 1];
+      const bool at = s % job.spp == 0, cross = at && b != 0.0;
+      if (at) {
+        double other[R], up, dn, on = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) other[r] = 0.0;
+        if (cross) {  // (b is the same for the whole workgroup)
+          trade(pa, other);
+          // the other part's row after this lane's last
+          const int q = pl + 1 < (MULTI ? G * 64 : 64) ? pl + 1 : pl;
+          on = xch[XB == 2 ? xp ^ 1 : 0][1 - part][0][q];
+        }
+        neighbours(pa, up, dn);
+        const double f = job.f_grid[s / job.spp];
+        const double2* h0o = reinterpret_cast<const double2*>(job.h0_off);
+        double num = 0.0, den = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const long i = base + r;
+          if (i >= n) continue;
+          const double x = pa[r], vi = job.v_diag[i];
+          num = fma((job.h0_diag[i] + f * vi) * x, x, num);
+          den = fma(x, x, den);
+          if (i + 1 >= n) continue;
+          const double2 h = h0o[i];
+          const double q = b * (job.v_diag[i + 1] - vi);
+          const double c = 2.0 * sqrt((h.x * h.x + h.y * h.y) / (1.0 + q * q));
+          const double xn = r + 1 < R ? pa[r + 1 < R ? r + 1 : 0] : dn;
+          num = fma(c * x, xn, num);
+          // - q Im: part 0 adds x_i * (other part's x_{i+1}), part 1 the mirrored term
+          if (cross) num = fma(-q * c * sgn * x, r + 1 < R ? other[r + 1 < R ? r + 1 : 0] : on, num);
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+          num += __shfl_xor(num, o);
+          den += __shfl_xor(den, o);
+        }
+        if (lane == 0) {
+          esum[(s / job.spp) & 1][0][wid] = num;
+          esum[(s / job.spp) & 1][1][wid] = den;
+        }
+      }
     }
 
     // l = 0, 1: P_0 = X~ (in pa), P_1 = G X~ (into pb)
@@ -330,69 +505,100 @@ __global__ __launch_bounds__(MAXT) void tridiag_gauge_kernel(TridiagJob job, int
       advance(pa, pb);  // P_{l+1} (odd) into pb
       acc_odd(pb, sgn * coef[l + 1].y);
     }
-    const bool last_in_a = (l <= L);
-    if (last_in_a) {
+    if (l <= L) {
       advance(pb, pa);
       acc_even(pa, coef[l].x);
     }
 
     // both halves of Y meet: X~_next = phase * w_s * conj(w_{s+1}) * Y (or
-    // phase * w_s * Y after the last step); this part keeps its component.
-    const bool final_step = (s + 1 == job.k1);
+    // phase * w_s * Y after the last step); this part keeps its component and
+    // sends its share of the other one.
+    if constexpr (!AHEAD) rotation();
     const bool ckpt_step = tape && !final_step && (s + 1) % job.ckpt == 0;
     const bool snap_step = snap && (s + 1 - job.k0) % job.snap_every == 0;
-    const long snap_j = snap_step ? (s + 1 - job.k0) / job.snap_every - 1 : 0;
+    // rotated sums: (rr + i ri)(Y_r + i Y_i) with Y = this part's shares
+    auto rotate = [&](const double* cr, const double* ci, double* out) {
+      double give[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      double* slot = ysh + (((long)part * G * 64 + pl) * R + r) * 2;
-      slot[0] = ys[r];
-      slot[1] = yo[r];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const long i = base + r;
-      const double* other = ysh + (((long)(1 - part) * G * 64 + pl) * R + r) * 2;
-      // component sums: this part's own component and the other component
-      const double own = ys[r] + other[1];
-      const double oth = yo[r] + other[0];
-      const double yr = part == 0 ? own : oth, yi = part == 0 ? oth : own;
-      double v = 0.0;
-      if (i < n) {
-        const double2 ws = gauge[(long)s * n + i];
-        // rot = phase * w_s [* conj(w_{s+1})]
-        double rr = job.phr * ws.x - job.phi * ws.y, ri = job.phr * ws.y + job.phi * ws.x;
-        const double plain = part == 0 ? rr * yr - ri * yi : rr * yi + ri * yr;  // X_{s+1}
-        if (ckpt_step)
-          tape[2 * (((long)((s + 1) / job.ckpt) * job.ncols + col) * n + i) + part] = plain;
-        if (snap_step) store_part(snap, (snap_j * n + i) * job.ncols + col, part, job.c64, plain);
-        if (!final_step) {
-          const double2 wn = gauge[(long)(s + 1) * n + i];
-          const double tr = rr * wn.x + ri * wn.y, ti = ri * wn.x - rr * wn.y;
-          rr = tr;
-          ri = ti;
-        }
-        v = part == 0 ? rr * yr - ri * yi : rr * yi + ri * yr;
+      for (int r = 0; r < R; ++r) {
+        give[r] = part == 0 ? fma(cr[r], yo[r], ci[r] * ys[r]) : fma(cr[r], yo[r], -ci[r] * ys[r]);
+        out[r] = part == 0 ? fma(cr[r], ys[r], -ci[r] * yo[r]) : fma(cr[r], ys[r], ci[r] * yo[r]);
       }
-      pa[r] = v;
+      double got[R];
+      trade(give, got);
+#pragma unroll
+      for (int r = 0; r < R; ++r) out[r] += got[r];
+    };
+    if (ckpt_step || snap_step) {  // X_{s+1} in the plain frame
+      double cr[R], ci[R], x[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        double2 q = make_double2(0.0, 0.0);
+        if (base + r < n) q = tridiag_rotation(job, s, base + r, false);
+        cr[r] = q.x;
+        ci[r] = q.y;
+      }
+      rotate(cr, ci, x);
+      const long snap_j = snap_step ? (s + 1 - job.k0) / job.snap_every - 1 : 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const long i = base + r;
+        if (i >= n) continue;
+        if (ckpt_step)
+          tape[2 * (((long)((s + 1) / job.ckpt) * job.ncols + col) * n + i) + part] = x[r];
+        if (snap_step) store_part(snap, (snap_j * n + i) * job.ncols + col, part, job.c64, x[r]);
+      }
     }
-    __syncthreads();
+    rotate(rr, ri, pa);
+    if constexpr (ENERGY) {  // (the step's barrier lies between these and the waves' sums)
+      if (s % job.spp == 0 && threadIdx.x == 0) {
+        const int nw = MULTI ? 2 * G : 2, e = (s / job.spp) & 1;
+        double num = 0.0, den = 0.0;
+        for (int i = 0; i < nw; ++i) {
+          num += esum[e][0][i];
+          den += esum[e][1][i];
+        }
+        e_avg += num / den;
+      }
+    }
   }
 
+  if constexpr (ENERGY) {
+    if (threadIdx.x == 0) job.avg[col] = job.avg_w * e_avg;
+    return;
+  }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const long i = base + r;
-    if (i < n) store_part(job.x_out, i * job.ld_out + col, part, job.c64, pa[r]);
+    if (i >= n) continue;
+    if (job.planes)  // state-major planes of this segment
+      job.planes[seg * job.bs + part * (job.bs / 2) + col * job.ld_planes + i] = pa[r];
+    else
+      store_part(job.x_out, i * job.ld_out + col, part, job.c64, pa[r]);
   }
 }
 
-template <int R, int MAXT, bool MULTI>
-hipError_t launch_r(const TridiagJob& job, int G, hipStream_t s) {
-  const size_t shmem = sizeof(double) * 2 * (size_t)G * 64 * R * 2;
-  hipLaunchKernelGGL((tridiag_gauge_kernel<R, MAXT, MULTI>), dim3((unsigned)job.ncols),
-                     dim3(2 * G * 64), shmem, s, job, G,
-                     reinterpret_cast<const double2*>(job.coef), job.tape, job.snap);
+// Rows per lane for columns of n rows.
+int chain_rows(long n) { return n <= 64 ? 1 : n <= 128 ? 2 : n <= 256 ? 4 : n <= 512 ? 8 : 16; }
+
+template <int R, bool MULTI, bool ENERGY>
+hipError_t launch_chain_r(const TridiagJob& job, int G, int nseg, hipStream_t s) {
+  hipLaunchKernelGGL((tridiag_chain_kernel<R, MULTI, ENERGY>),
+                     dim3((unsigned)job.ncols, (unsigned)nseg), dim3(2 * G * 64), 0, s, job, G,
+                     reinterpret_cast<const double2*>(job.coef), job.tab, job.tape, job.snap);
   return hipGetLastError();
+}
+
+template <bool ENERGY>
+hipError_t launch_chain(const TridiagJob& job, int nseg, hipStream_t s) {
+  switch (chain_rows(job.n)) {
+    case 1: return launch_chain_r<1, false, ENERGY>(job, 1, nseg, s);
+    case 2: return launch_chain_r<2, false, ENERGY>(job, 1, nseg, s);
+    case 4: return launch_chain_r<4, false, ENERGY>(job, 1, nseg, s);
+    case 8: return launch_chain_r<8, false, ENERGY>(job, 1, nseg, s);
+  }
+  if (job.n <= 1024) return launch_chain_r<16, false, ENERGY>(job, 1, nseg, s);
+  return launch_chain_r<16, true, ENERGY>(job, (int)((job.n + 1023) / 1024), nseg, s);
 }
 
 // ---- columns longer than one workgroup holds: k-term passes over HBM ----------------------------
@@ -1660,15 +1866,33 @@ hipError_t launch_tridiag_setup(long n, int M, const double* h0_diag, const void
 // 16 rows per lane and up to 4 waves per part (512 threads, <= 256 VGPRs).
 long tridiag_resident_max_n() { return 4L * 64 * 16; }
 
-hipError_t launch_tridiag_resident(const TridiagJob& job, hipStream_t s) {
-  if (job.n < 1 || job.ncols < 1) return hipErrorInvalidValue;
-  if (job.n <= 256) return launch_r<4, 128, false>(job, 1, s);
-  if (job.n <= 1024) return launch_r<16, 512, false>(job, 1, s);
-  if (job.n <= tridiag_resident_max_n()) {
-    const int G = (int)((job.n + 1023) / 1024);
-    return launch_r<16, 512, true>(job, G, s);
+int tridiag_chain_rows(long n) { return chain_rows(n); }
+
+hipError_t launch_tridiag_table(const TridiagJob& job, int M, double* out, hipStream_t s) {
+  const int R = chain_rows(job.n);
+  if (job.n < 1 || job.n > tridiag_resident_max_n() || M < 1 || job.nq != (job.n + R - 1) / R)
+    return hipErrorInvalidValue;
+  // (grid.y holds at most 65535 steps)
+  for (int k = 0; k < M; k += 65535) {
+    const int m = M - k < 65535 ? M - k : 65535;
+    TridiagJob j = job;
+    j.ab += 2L * k;
+    j.gauge += 2L * k * job.n;
+    hipLaunchKernelGGL(tridiag_table_kernel,
+                       dim3((unsigned)((job.nq * R + 255) / 256), (unsigned)m), dim3(256), 0, s, j, R,
+                       M - k, out + 4L * k * job.nq * R);
   }
-  return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_tridiag_resident(const TridiagJob& job, int nseg, hipStream_t s) {
+  const int R = chain_rows(job.n);
+  if (job.n < 1 || job.ncols < 1 || job.n > tridiag_resident_max_n() || nseg < 1 ||
+      nseg > 65535 || job.nq != (job.n + R - 1) / R ||
+      (nseg > 1 && (!job.planes || job.x0 || job.tape || job.snap ||
+                    (long)nseg * job.len0 + job.rem != (long)job.k1 - job.k0)))
+    return hipErrorInvalidValue;
+  return job.avg ? launch_chain<true>(job, nseg, s) : launch_chain<false>(job, nseg, s);
 }
 
 // ---- energy expectations of tridiagonal states -------------------------------------------------

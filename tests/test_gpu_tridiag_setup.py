@@ -82,3 +82,51 @@ def test_complex_couplings_through_the_gauge(fl, n):
     err = orc.column_error(U, ref)
     print("[case] e_col", err, flush=True)
     assert err < 1e-12
+
+
+# ---- the chain kernel at every number of rows per lane --------------------------------------------
+
+# 1, 2, 4, 8 and 16 rows per lane at their first and last sizes, two waves per part from
+# 1025 rows on; M = 40 steps make short columns run in segments
+@pytest.mark.parametrize("scheme", ["magnus4", "cf4"])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025])
+def test_chain_at_every_row_count(fl, n, scheme):
+    print("[case] chain", n, scheme, flush=True)
+    rng = np.random.default_rng(900 + n)
+    if n <= 129:                        # complex couplings, b_k != 0
+        d, e, v = _problem(n, 900 + n)
+        T, M = 2.0, 40
+    else:
+        d, e, v = dimer_tridiag(n - 1, 1.0, 0.01)
+        T, M = 0.05, 5
+    f = rng.uniform(-1, 1, (M, 2))
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=f, scheme=scheme)
+    U = ctx.build_ut().cpu().numpy()
+    rep = ctx.last_report
+    kw = dict(route="cheb", e_min=rep["e_min"], e_max=rep["e_max"], L=rep["L"], scheme=scheme)
+    cols = np.unique([0, n // 3, n - 1])
+    X0 = np.eye(n, dtype=complex)[:, cols]
+    ref = orc.build_ut_tridiag(d, e, v, f, T, M, X0=X0, **kw)
+    err = orc.column_error(U[:, cols], ref)
+    print("[case] build", err, "unitarity", rep["unitarity_max"], flush=True)
+    # every factor is bounded by 1: rounding of the order of L M eps
+    assert err < 1e-11
+    # a few states over a step range with snapshots, then the rest of the range
+    X = rng.standard_normal((n, min(n, 3))) + 1j * rng.standard_normal((n, min(n, 3)))
+    X /= np.linalg.norm(X, axis=0)
+    Y, snaps = ctx.propagate(X, 0, 3, snap_every=2)
+    Z = ctx.propagate(snaps[0].contiguous(), 2, M)
+    assert orc.column_error(Z.cpu().numpy(), U @ X) < 1e-11
+    assert orc.column_error(ctx.propagate(Y, 3, M).cpu().numpy(), U @ X) < 1e-11
+    # energies along the way (relative to the spectrum's scale)
+    fg = rng.uniform(-1, 1, M)
+    got = ctx.period_average(X, fg)
+    H0, V, _ = orc.tridiag_matrices(d, e, v)
+    want, Xk = 0.0, X
+    for k in range(M):
+        E = np.real(np.sum(Xk.conj() * (H0 @ Xk + fg[k] * (V @ Xk)), axis=0))
+        want = want + E / np.sum(np.abs(Xk) ** 2, axis=0) / M
+        Xk = orc.build_ut_tridiag(d, e, v, f, T, M, X0=Xk, k_range=(k, k + 1), **kw)
+    scale = max(abs(rep["e_min"]), abs(rep["e_max"]))
+    print("[case] average", np.max(np.abs(got - want)) / scale, flush=True)
+    assert np.max(np.abs(got - want)) < 1e-11 * scale
