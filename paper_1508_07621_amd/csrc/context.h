@@ -97,6 +97,11 @@ struct fq_ctx {
   double* d_ab = nullptr;             // 2*M
   double* d_coef = nullptr;           // 2*(L+1)
   double* d_gauge = nullptr;          // tridiagonal: M x n complex gauge factors
+  // tridiagonal gradient of resident columns: segments (their operators stay in
+  // pool after a build), how many at a time, steps of the store, theta' rows
+  int adj_seg = 0, adj_group = 0, adj_len = 0;
+  double* adj_store = nullptr;
+  double* d_theta = nullptr;
   double* d_tab = nullptr;            // tridiagonal: rows of every step (resident columns)
   double* d_fgrid = nullptr;          // tridiagonal: the period average's drive samples
   double* d_ext = nullptr;            // tridiagonal: extreme eigenvalues of every step

@@ -137,6 +137,12 @@ constexpr double kCf4Q = 0.5 - 0.57735026918962576451;  // 1/2 - sqrt(3)/3
 // Number of nested commutators in the sixth-order effective Hamiltonian.
 constexpr int kComm6 = 9;
 
+// Segments of the gradient of resident tridiagonal columns (one workgroup per
+// column and segment): nb of them, g at a time, the store holding len steps each.
+struct TridiagAdjPlan {
+  int nb = 0, g = 0, len = 0;
+};
+
 struct Layout {
   size_t total = 0;
   size_t zeroed = 0;  // bytes cleared by fq_create (the scratch matrices after them are not)
@@ -145,9 +151,10 @@ struct Layout {
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
          off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0,
-         off_ext = 0, off_tab = 0, off_fgrid = 0;
+         off_ext = 0, off_tab = 0, off_fgrid = 0, off_store = 0, off_theta = 0;
   long np = 0;
   int n_tape = 0;
+  TridiagAdjPlan tri_adj;
   int pool_mats = 0, n_extra = 0;
   size_t adj_mats = 0;
 };
@@ -185,6 +192,37 @@ bool streamed_adjoint(const fq_system* sys, const fq_params* par) {
   if (sys->n > fq::tridiag_adjoint_max_n()) return true;
   const char* e = std::getenv("FQ_TRIDIAG_STREAMED_ADJOINT");
   return e && e[0] == '1' && e[1] == 0;
+}
+
+constexpr size_t kTridiagStore = size_t(4) << 30;
+TridiagAdjPlan tridiag_adj_plan(long n, long M, long ckpt) {
+  TridiagAdjPlan p;
+  if (n > fq::tridiag_adj_chain_max_n()) return p;
+  const long R = fq::tridiag_chain_rows(n), np = pad_to(n, dense_tile(n));
+  const size_t step = 4 * 64 * sizeof(double) * (size_t)R * (size_t)n;  // store of one step
+  const double slots = 1024.0 * (R > 8 ? 1 : R > 4 ? 2 : 4);            // waves the chip holds
+  if (step * (size_t)M <= kTridiagStore) {
+    // all segments at once: rounds of the chip times steps (about 60 terms of 40 ns
+    // and 20 ns per row), and two products per segment for its X and Lambda
+    double best = 0.0;
+    for (int nb = 1; nb <= std::min<long>(32, M); ++nb) {
+      const double cost = std::ceil(2.0 * n * nb / slots) * std::ceil((double)M / nb) * 60.0 *
+                              (40e-9 + 20e-9 * R) +
+                          nb * (10e-6 + 16.0 * np * np * np / 5e13);
+      if (nb == 1 || cost < best) {
+        best = cost;
+        p.nb = nb;
+      }
+    }
+    p.g = p.nb;
+  } else {
+    const long len = std::max(ckpt, std::min(16L, M));
+    p.nb = (int)((M + len - 1) / len);
+    const long fit = (long)(kTridiagStore / (step * (size_t)len));
+    p.g = (int)std::max(1L, std::min<long>({p.nb, fit, (long)std::ceil(slots / n)}));
+  }
+  p.len = (int)((M + p.nb - 1) / p.nb);
+  return p;
 }
 
 Layout plan(const fq_system* sys, const fq_params* par) {
@@ -257,7 +295,17 @@ Layout plan(const fq_system* sys, const fq_params* par) {
     const size_t splane = sizeof(double) * n16 * (size_t)n;  // one state plane
     if (n > fq::tridiag_resident_max_n() || streamed_grad)  // two 8-plane states, per-step rows
       lay.off_stream = take(2 * 8 * splane + sizeof(double) * 6 * n16);
-    if (par->checkpoint_every > 0) {  // X_{j ckpt} per column; segment buffers
+    if (par->checkpoint_every > 0 && !streamed_grad)
+      lay.tri_adj = tridiag_adj_plan(n, Ms, cks);
+    if (lay.tri_adj.nb > 0) {
+      // the segments' operators and the products that multiply them up; these
+      // operators operator-major, X, Lambda^+ and X state-major
+      const int nb = lay.tri_adj.nb;
+      lay.pool_mats = nb + 2 * (nb / 2 + 1);
+      lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
+      lay.off_adj = take(plane2 * 4 * (size_t)nb);
+      lay.off_grad = take(2 * sizeof(double) * (size_t)Ms);
+    } else if (par->checkpoint_every > 0) {  // X_{j ckpt} per column; segment buffers
       const size_t vec = 2 * sizeof(double) * (size_t)n;
       lay.n_tape = (Ms + cks - 1) / cks + 1;
       lay.off_tape = take(vec * (size_t)n * (size_t)lay.n_tape);
@@ -294,9 +342,15 @@ Layout plan(const fq_system* sys, const fq_params* par) {
     }
     const long R = fq::tridiag_chain_rows(n), nr = pad_to(n, R);
     const size_t tab = 4 * sizeof(double) * (size_t)nr * (size_t)Ms;
-    if (tab <= left) lay.off_tab = take(tab);
+    if (tab <= left || lay.tri_adj.nb > 0) lay.off_tab = take(tab);
   }
   lay.zeroed = cur;
+  if (lay.tri_adj.nb > 0) {
+    const size_t R = (size_t)fq::tridiag_chain_rows(n);
+    lay.off_store = take(4 * 64 * sizeof(double) * R * (size_t)n * (size_t)lay.tri_adj.g *
+                         (size_t)lay.tri_adj.len);
+    lay.off_theta = take(sizeof(double) * (size_t)pad_to(n, (long)R) * (size_t)Ms);
+  }
   if (lay.adj_mats > 0)
     lay.off_seg = take(lay.adj_mats * 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np);
   if (dense_like(sys->layout) && par->precision == FQ_FP64) {
@@ -1112,9 +1166,10 @@ fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
   return FQ_OK;
 }
 
-// The product of cnt state-major operators at src (the first acts first), into
-// dst by pairs, ping-ponged with src; the result goes to the X planes.
-fq_status multiply_up(fq_ctx* c, double* src, double* dst, int cnt) {
+// The product of cnt state-major operators at src (the first acts first), by
+// pairs into dst and then back and forth with alt; the result goes to the X
+// planes.
+fq_status multiply_up(fq_ctx* c, double* src, double* dst, double* alt, int cnt) {
   const int np = (int)c->np;
   const long bs = 2 * c->np * c->np;
   const size_t bytes = sizeof(double) * (size_t)bs;
@@ -1128,7 +1183,8 @@ fq_status multiply_up(fq_ctx* c, double* src, double* dst, int cnt) {
       FQ_HIP(c, hipMemcpyAsync(dst + (size_t)pairs * bs, src + (size_t)(cnt - 1) * bs, bytes,
                                hipMemcpyDeviceToDevice, c->stream));
     cnt = pairs + cnt % 2;
-    std::swap(src, dst);
+    src = dst;
+    std::swap(dst, alt);
   }
   return FQ_OK;
 }
@@ -1168,7 +1224,7 @@ fq_status dense_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
                                hipMemcpyDeviceToDevice, c->stream));
     }
   }
-  return multiply_up(c, x, b[1], nb);
+  return multiply_up(c, x, b[1], x, nb);
 }
 
 // ---- mixed-precision builds: one format per Chebyshev term -----------------------------------
@@ -1447,7 +1503,7 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
       sc.xr = c->pool;
       sc.xi = c->pool + plane2 / 2;
       FQ_HIP(c, fq::launch_small_chain(sc, mrows, nseg, c->stream));
-      return multiply_up(c, c->pool, c->pool + (size_t)nseg * plane2, nseg);
+      return multiply_up(c, c->pool, c->pool + (size_t)nseg * plane2, c->pool, nseg);
     }
     FQ_HIP(c, fq::launch_small_chain(sc, mrows, 1, c->stream));
     return FQ_OK;
@@ -1582,6 +1638,7 @@ fq::TridiagJob tridiag_job(const fq_ctx* c) {
 // segments up costs a launch of about 6 us per level and 8 np^3 flop per
 // product at 50 TF/s.
 int tridiag_segments(const fq_ctx* c) {
+  if (c->adj_seg > 0) return c->adj_seg;  // the gradient's
   if (c->n > 1024 || c->pool_mats < 4 || c->tape) return 1;
   const double R = fq::tridiag_chain_rows(c->n), np = (double)c->np;
   int best = 1;
@@ -1612,7 +1669,15 @@ fq_status tridiag_build_segments(fq_ctx* c, int nseg) {
   job.bs = 2 * c->np * c->np;
   FQ_MARK(c, FQ_K_TRIDIAG);
   FQ_HIP(c, fq::launch_tridiag_resident(job, nseg, c->stream));
-  return multiply_up(c, c->pool, c->pool + (size_t)nseg * job.bs, nseg);
+  if (nseg == 1) {  // (a gradient context's single segment)
+    FQ_HIP(c, hipMemcpyAsync(c->xr, job.planes, sizeof(double) * (size_t)job.bs,
+                             hipMemcpyDeviceToDevice, c->stream));
+    return FQ_OK;
+  }
+  // (a gradient keeps the segments' operators: the products go elsewhere)
+  double* next = c->pool + (size_t)nseg * job.bs;
+  return multiply_up(c, job.planes, next, c->adj_seg ? next + (size_t)(nseg / 2 + 1) * job.bs : job.planes,
+                     nseg);
 }
 
 fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, void* x_out) {
@@ -2004,6 +2069,23 @@ AdjBuffers adj_carve(fq_ctx* c, const PolyPlan& p, int nb, double** next) {
   return b;
 }
 
+// From the first segment's X (X[0]) and the last one's Lambda^+ (D[nb - 1]) those of
+// every other: X_z = S_{z-1} X_{z-1}, D_z = D_{z+1} S_{z+1} with the segments' operators S
+// (all operator-major), one product of each chain per launch.
+fq_status segment_ends(fq_ctx* c, const std::function<double*(int)>& S, double* X, double* D,
+                       int nb) {
+  const int np = (int)c->np;
+  const long bs = 2 * c->np * c->np;
+  auto Xz = [&](int z) { return X + (size_t)z * bs; };
+  auto Dz = [&](int z) { return D + (size_t)z * bs; };
+  for (int i = 1; i < nb; ++i) {
+    FQ_MARK(c, FQ_K_LAST);
+    FQ_HIP(c, fq::launch_poly_apply(S(i - 1), Dz(nb - i) - S(i - 1), Xz(i - 1), S(nb - i) - Xz(i - 1),
+                                    true, Xz(i), Dz(nb - 1 - i) - Xz(i), np, np, 2, c->stream));
+  }
+  return FQ_OK;
+}
+
 // The whole gradient in nb segments, step t of all of them in one batch, from
 // nothing but the drive: P_0 = 1, then the segments' operators give every
 // segment's X (forwards) and Lambda^dagger (backwards).
@@ -2028,16 +2110,10 @@ fq_status adjoint_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
     FQ_HIP(c, fq::launch_poly_apply(w[0], bs, P[t], bs, true, P[t + 1], bs, np, np, act,
                                     c->stream));
   }
-  auto S = [&](int z) { return P[z < rem ? len0 + 1 : len0] + (size_t)z * bs; };
-  auto Xz = [&](int z) { return X + (size_t)z * bs; };
-  auto Dz = [&](int z) { return D + (size_t)z * bs; };
   FQ_HIP(c, fq::launch_identity_rows(X, X + bs / 2, c->n, np, np, c->stream));
-  FQ_HIP(c, fq::launch_conj_planar(c->lam, np, Dz(nb - 1), c->stream));
-  for (int i = 1; i < nb; ++i) {  // X_i = S_{i-1} X_{i-1} and D_j = D_{j+1} S_{j+1}, j = nb-1-i
-    FQ_MARK(c, FQ_K_LAST);
-    FQ_HIP(c, fq::launch_poly_apply(S(i - 1), Dz(nb - i) - S(i - 1), Xz(i - 1), S(nb - i) - Xz(i - 1),
-                                    true, Xz(i), Dz(nb - 1 - i) - Xz(i), np, np, 2, c->stream));
-  }
+  FQ_HIP(c, fq::launch_conj_planar(c->lam, np, D + (size_t)(nb - 1) * bs, c->stream));
+  FQ_TRY(segment_ends(c, [&](int z) { return P[z < rem ? len0 + 1 : len0] + (size_t)z * bs; }, X, D,
+                      nb));
   FQ_MARK(c, FQ_K_LAST);
   FQ_HIP(c, fq::launch_poly_apply(X, bs, D, bs, true, b.m[0], bs, np, np, nb, c->stream));
   for (int t = len - 1; t >= 0; --t)
@@ -2283,7 +2359,51 @@ fq_status tridiag_adjoint_streamed(fq_ctx* c, const void* U_bar, double* grad_f_
 // (each workgroup recomputes its column's segments from the tape), then the
 // chain rule to the node samples as in the dense case; streamed passes when
 // the context holds their buffers.
+// Resident columns: every segment's first X and last Lambda from the segments'
+// operators that the build left, then one workgroup per column and segment.
+fq_status tridiag_adjoint_chain(fq_ctx* c, const void* U_bar, double* grad_f_nodes) {
+  const int nb = c->adj_seg, np = (int)c->np, M = c->M;
+  const long bs = 2 * c->np * c->np;
+  const bool with_k = !c->pair_sums;
+  double* S = c->adj_pool;  // operator-major; then X, Lambda^+ and X state-major
+  double *X = S + (size_t)nb * bs, *D = X + (size_t)nb * bs, *Xs = D + (size_t)nb * bs;
+  FQ_HIP(c, zero_async(c->stream, c->d_grad, 2 * sizeof(double) * (size_t)M));
+  FQ_HIP(c, fq::launch_pack_planar_t(U_bar, c->n, c->n, c->n, c->xr, c->xi, c->np, c->np, c->c64,
+                                     c->stream));
+  FQ_HIP(c, fq::launch_conj_planar(c->xr, np, D + (size_t)(nb - 1) * bs, c->stream));
+  FQ_HIP(c, fq::launch_identity_rows(X, X + bs / 2, c->n, np, np, c->stream));
+  if (nb > 1) {
+    FQ_HIP(c, fq::launch_transpose_planar(c->pool, c->pool + bs / 2, S, S + bs / 2, np, bs, nb,
+                                          c->stream));
+    FQ_TRY(segment_ends(c, [&](int z) { return S + (size_t)z * bs; }, X, D, nb));
+  }
+  FQ_HIP(c, fq::launch_transpose_planar(X, X + bs / 2, Xs, Xs + bs / 2, np, bs, nb, c->stream));
+  fq::TridiagJob job = tridiag_job(c);
+  job.ncols = c->n;
+  fq::TridiagAdjChain aj{};
+  aj.len0 = M / nb;
+  aj.rem = M % nb;
+  aj.x = Xs;
+  aj.d = D;
+  aj.ld = np;
+  aj.bs = bs;
+  aj.store = c->adj_store;
+  aj.len = c->adj_len;
+  aj.theta = c->d_theta;
+  aj.dE = c->dE;
+  aj.grad = c->d_grad;
+  for (int z0 = 0; z0 < nb; z0 += c->adj_group)
+    FQ_HIP(c, fq::launch_tridiag_adj_chain(job, aj, with_k, z0, std::min(c->adj_group, nb - z0),
+                                           c->stream));
+  std::vector<double> g(2 * (size_t)M);
+  FQ_HIP(c, copy_sync(c->stream, g.data(), c->d_grad, g.size() * sizeof(double),
+                      hipMemcpyDeviceToHost));
+  grad_to_nodes(c, g, grad_f_nodes);
+  return FQ_OK;
+}
+
 fq_status tridiag_adjoint(fq_ctx* c, const void* U_bar, double* grad_f_nodes) {
+  if (c->adj_seg > 0) return tridiag_adjoint_chain(c, U_bar, grad_f_nodes);
   if (c->d_adj) return tridiag_adjoint_streamed(c, U_bar, grad_f_nodes);
   const int M = c->M;
   fq::TridiagAdjJob job{};
@@ -2679,6 +2799,15 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     c->d_ext = P(lay.off_ext);
     c->d_fgrid = P(lay.off_fgrid);
     if (lay.off_tab) c->d_tab = P(lay.off_tab);
+    if (lay.tri_adj.nb > 0) {
+      c->adj_seg = lay.tri_adj.nb;
+      c->adj_group = lay.tri_adj.g;
+      c->adj_len = lay.tri_adj.len;
+      c->adj_pool = P(lay.off_adj);
+      c->adj_store = P(lay.off_store);
+      c->d_theta = P(lay.off_theta);
+      c->d_grad = P(lay.off_grad);
+    }
     if (lay.pool_mats > 0) {
       c->pool = P(lay.off_pool);
       c->pool_mats = lay.pool_mats;
@@ -2845,13 +2974,14 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
       c->snap_ncols = c->n;
     }
     const int nseg = tridiag_segments(c);
-    st = nseg > 1 ? tridiag_build_segments(c, nseg) : tridiag_run(c, nullptr, c->n, 0, c->M, U_out);
+    const bool planes = nseg > 1 || c->adj_seg > 0;  // U_T ends in the X planes
+    st = planes ? tridiag_build_segments(c, nseg) : tridiag_run(c, nullptr, c->n, 0, c->M, U_out);
     c->snap = nullptr;
     if (st != FQ_OK) return st;
     FQ_MARK(c, -1);
     if (e1) FQ_HIP(c, hipEventRecord(e1, c->stream));
     c->tape_valid = c->ckpt > 0;
-    if (nseg > 1)
+    if (planes)
       FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, c->n, U_out, c->n, c->c64,
                                            c->stream));
     else

@@ -358,6 +358,24 @@ long tridiag_stream_rows(int G);
 hipError_t launch_tridiag_stream_step(const TridiagJob& job, const TridiagStream& st,
                                       double* stepc, hipStream_t s);
 
+// Gradient of resident columns of up to tridiag_adj_chain_max_n() rows, one
+// workgroup per (column, segment): segments z0 .. z0 + g - 1 of the steps (the first
+// rem of len0 + 1 steps, the others of len0). The job's step table is used.
+struct TridiagAdjChain {
+  int z0, len0, rem;
+  const double* x;   // X at every segment's first step, state-major planes (row = column
+  const double* d;   // of the block): stride ld, segment z at + z * bs, im plane at + bs / 2;
+  long ld, bs;       // Lambda^+ after its last step, operator-major planes
+  double* store;     // g * ncols * len * 4 * 64 tridiag_chain_rows(n) doubles
+  int len;           // steps the store holds per segment
+  double* theta;     // with_k: M nq tridiag_chain_rows(n) doubles (filled when z0 == 0)
+  double dE;
+  double* grad;      // 2 M accumulators, as below
+};
+long tridiag_adj_chain_max_n();
+hipError_t launch_tridiag_adj_chain(const TridiagJob& job, const TridiagAdjChain& aj, bool with_k,
+                                    int z0, int g, hipStream_t s);
+
 // Gradient of the tridiagonal chain, one workgroup per column (n <= 2048).
 struct TridiagAdjJob {
   long n, ncols;

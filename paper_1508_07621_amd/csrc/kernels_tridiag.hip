@@ -1225,6 +1225,355 @@ hipError_t launch_adj_r(const TridiagAdjJob& job, hipStream_t s) {
   return hipGetLastError();
 }
 
+// ---- reverse sweep of resident columns in the gauge frame ------------------------------------
+//
+// Columns of up to 1024 rows, one workgroup per (column, segment of steps): a wave
+// for the real and a wave for the imaginary part of every vector, in the row
+// layout and with the step tables of the chain kernel. The host hands in each
+// segment's first X and last Lambda, so the segments are independent. A
+// workgroup propagates its X through the segment, storing every step's last two
+// terms P_{L-1}, P_L, and then reverses the steps: per term
+//   Pbar_l  = (2 - delta_l0) G Pbar_{l+1} - Pbar_{l+2} + conj(c_l) Lambda',
+//   P_{l-1} = 2 G P_l - P_{l+1},
+//   S_V    += Pbar_{l+1} P_l per row (Hmod is diagonal),
+// with Lambda' = conj(phase) D^+ Lambda, of which a wave holds both parts (even c_l
+// are real, odd ones imaginary). Between steps Lambda changes frame by
+// conj(phase w_k) w_{k+1}.
+//
+// The derivative with respect to b (KC) splits. H = D G D^+ and E = D p(G) D^+,
+// also for the truncated series, so
+//   dE/db = i [Theta', E] + D (dp(G)/db) D^+,
+// Theta' = diag(d arg w_i / db), d arg w_{i+1} - d arg w_i = dv_i / (1 + q_i^2). The first
+// part is a boundary term: Re <Lambda, i [Theta', E] X> = sum_i theta'_i (Q_i(start) -
+// Q_i(end)), Q = Im conj(Lambda) X, a sum over the parts; the second contracts
+// with the real couplings' derivative |h| b dv^2 / sqrt(1 + q^2) and vanishes with b.
+// No term mixes the parts, so there is no exchange between the waves within a step.
+//
+// Bound by FP64 vector issue: 8 instructions per row, part and term backwards and
+// 4 forwards. 400-state dimer, 128 steps: 2.45 ms, where the sweep in complex values
+// with a barrier per term and all segments one after the other took 19.0 ms.
+template <int R, bool KC>
+__global__ __launch_bounds__(128, R > 8 ? 1 : 2) void tridiag_adj_chain_kernel(
+    TridiagJob job, TridiagAdjChain aj, const double2* __restrict__ coef,
+    const double* __restrict__ tab, double* __restrict__ store) {
+  __shared__ double xch[2][2][R][64];  // [buffer][part][row][lane]
+  const int part = threadIdx.x >> 6, pl = threadIdx.x & 63;
+  const long col = blockIdx.x;
+  const int z = aj.z0 + blockIdx.y;
+  const long n = job.n, nq = job.nq, nr = nq * R, base = (long)pl * R;
+  const double sgn = part == 0 ? 1.0 : -1.0;
+  const int k_lo = z * aj.len0 + (z < aj.rem ? z : aj.rem);
+  const int k_hi = k_lo + aj.len0 + (z < aj.rem ? 1 : 0);
+  const bool in = pl < nq;
+  const int L = job.L;
+  double* const st =
+      store + (((long)blockIdx.y * job.ncols + col) * aj.len * 2 + part) * 2 * (R * 64) + pl;
+  auto slot = [&](int k, int which, int r) { return ((long)(k - k_lo) * 4 + which) * (R * 64) + r * 64; };
+
+  double d2[R], g2[R], gm2 = 0.0;
+  auto rows_of = [&](int s) {
+    const double* t = tab + (long)s * 4 * nr;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      d2[r] = in ? t[r * nq + pl] : 0.0;
+      g2[r] = in ? t[nr + r * nq + pl] : 0.0;
+    }
+    gm2 = in && pl > 0 ? t[nr + (R - 1) * nq + pl - 1] : 0.0;
+  };
+  auto rotation = [&](int s, bool next, double* rr, double* ri) {  // phase w_s [conj(w_{s+1})]
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double2 q = make_double2(0.0, 0.0);
+      if (next && in) {
+        const double* t = tab + (long)s * 4 * nr + 2 * nr + r * nq + pl;
+        q = make_double2(t[0], t[nr]);
+      } else if (!next && base + r < n) {
+        q = tridiag_rotation(job, s, base + r, false);
+      }
+      rr[r] = q.x;
+      ri[r] = q.y;
+    }
+  };
+  int xp = 0;
+  auto trade = [&](const double* v, double* got) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) xch[xp][part][r][pl] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) got[r] = xch[xp][1 - part][r][pl];
+    xp ^= 1;
+  };
+  // nw = 2 G v - nw (the edge rows first, as in the chain kernel)
+  auto advance = [&](const double* v, double up, double dn, double* nw) {
+    {
+      double t = fma(d2[0], v[0], -nw[0]);
+      t = fma(gm2, up, t);
+      nw[0] = fma(g2[0], (R > 1) ? v[R > 1 ? 1 : 0] : dn, t);
+    }
+    if constexpr (R > 1) {
+      double t = fma(d2[R - 1], v[R - 1], -nw[R - 1]);
+      t = fma(g2[R - 2], v[R - 2], t);
+      nw[R - 1] = fma(g2[R - 1], dn, t);
+    }
+#pragma unroll
+    for (int r = 1; r < R - 1; ++r) {
+      double t = fma(d2[r], v[r], -nw[r]);
+      t = fma(g2[r - 1], v[r - 1], t);
+      nw[r] = fma(g2[r], v[r + 1], t);
+    }
+  };
+
+  double xa[R], xb[R];  // P terms
+  double pa[R], pb[R];  // forwards: shares of the sum; backwards: Pbar terms
+  double lo[R], lx[R];  // Lambda': this part, the other part
+
+  // ---- forwards ----
+  {
+    double rr[R], ri[R];
+    const double* xre = aj.x + (long)z * aj.bs + col * aj.ld;
+    const double2* gauge = reinterpret_cast<const double2*>(job.gauge) + (long)k_lo * n;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const long i = base + r;
+      xa[r] = 0.0;
+      if (i < n) {
+        const double xr = xre[i], xi = xre[aj.bs / 2 + i];
+        const double2 g = gauge[i];
+        xa[r] = part == 0 ? g.x * xr + g.y * xi : g.x * xi - g.y * xr;  // conj(w) x
+      }
+    }
+    for (int s = k_lo; s < k_hi; ++s) {
+      const bool final_step = s + 1 == k_hi;
+      rows_of(s);
+      const double c0 = coef[0].x, c1 = sgn * coef[1].y;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        xb[r] = 0.0;
+        pa[r] = c0 * xa[r];
+      }
+      advance(xa, from_prev_lane(xa[R - 1]), from_next_lane(xa[0]), xb);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        xb[r] *= 0.5;
+        pb[r] = c1 * xb[r];
+      }
+      int l = 2;
+      for (; l + 1 <= L; l += 2) {
+        const double ce = coef[l].x, co = sgn * coef[l + 1].y;
+        advance(xb, from_prev_lane(xb[R - 1]), from_next_lane(xb[0]), xa);
+#pragma unroll
+        for (int r = 0; r < R; ++r) pa[r] = fma(ce, xa[r], pa[r]);
+        advance(xa, from_prev_lane(xa[R - 1]), from_next_lane(xa[0]), xb);
+#pragma unroll
+        for (int r = 0; r < R; ++r) pb[r] = fma(co, xb[r], pb[r]);
+      }
+      if (l <= L) {
+        const double ce = coef[l].x;
+        advance(xb, from_prev_lane(xb[R - 1]), from_next_lane(xb[0]), xa);
+#pragma unroll
+        for (int r = 0; r < R; ++r) pa[r] = fma(ce, xa[r], pa[r]);
+      }
+      // (even terms are in xa, odd ones in xb)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        st[slot(s, 0, r)] = xa[r];
+        st[slot(s, 1, r)] = xb[r];
+      }
+      if (final_step && !KC) break;
+      rotation(s, !final_step, rr, ri);  // the last X in the plain frame
+      double give[R], got[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        give[r] = part == 0 ? fma(rr[r], pb[r], ri[r] * pa[r]) : fma(rr[r], pb[r], -ri[r] * pa[r]);
+        xa[r] = part == 0 ? fma(rr[r], pa[r], -ri[r] * pb[r]) : fma(rr[r], pa[r], ri[r] * pb[r]);
+      }
+      trade(give, got);
+#pragma unroll
+      for (int r = 0; r < R; ++r) xa[r] += got[r];
+    }
+  }
+
+  // theta' of step s against this part's share of Q
+  double bnd = 0.0;  // boundary term of the step being reversed
+  auto against_theta = [&](int s, const double* q) {
+    const double* t = aj.theta + (long)s * nr;
+    double sum = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum = fma(in ? t[r * nq + pl] : 0.0, q[r], sum);
+    return sum;
+  };
+  // ---- Lambda at the segment's end: D = Lambda^+ ----
+  {
+    const double* dre = aj.d + (long)z * aj.bs + col * aj.ld;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const long i = base + r;
+      const double re = i < n ? dre[i] : 0.0, im = i < n ? -dre[aj.bs / 2 + i] : 0.0;
+      lo[r] = part == 0 ? re : im;
+      lx[r] = part == 0 ? im : re;
+    }
+    if constexpr (KC) {
+      double q[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) q[r] = -sgn * lx[r] * xa[r];
+      bnd = -against_theta(k_hi - 1, q);
+    }
+  }
+  for (int k = k_hi - 1; k >= k_lo; --k) {
+    rows_of(k);
+    {  // Lambda' = conj(phase w_k [conj(w_{k+1})]) Lambda
+      double rr[R], ri[R];
+      rotation(k, k != k_hi - 1, rr, ri);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // (rr - i ri)(own, other): real = rr re + ri im, imag = rr im - ri re
+        const double o = fma(rr[r], lo[r], sgn * ri[r] * lx[r]);
+        const double x = fma(rr[r], lx[r], -sgn * ri[r] * lo[r]);
+        lo[r] = o;
+        lx[r] = x;
+      }
+    }
+    double sv[R], sk[KC ? R : 1];
+    const double b = job.ab[2 * k + 1];
+    const bool couplings = KC && b != 0.0;
+    // source of term l: conj(c_l) Lambda'
+#define FQ_SOURCE(l, r) (((l) & 1) ? sgn * coef[l].y * lx[r] : coef[l].x * lo[r])
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      xa[r] = st[slot(k, 0, r)];
+      xb[r] = st[slot(k, 1, r)];
+      // Pbar_L (by its parity: even terms in pa, odd ones in pb), Pbar_{L+1} = 0
+      const double src = FQ_SOURCE(L, r);
+      pa[r] = (L & 1) ? 0.0 : src;
+      pb[r] = (L & 1) ? src : 0.0;
+      sv[r] = 0.0;
+      if (KC) sk[KC ? r : 0] = 0.0;
+    }
+#undef FQ_SOURCE
+    // one term: x = P_l, y = P_{l+1} -> P_{l-1}, p = Pbar_{l+1}, o = Pbar_{l+2} -> Pbar_l
+    auto down = [&](const double* x, double* y, const double* p, double* o, double c,
+                    const double* lam, bool more) {
+      const double pu = from_prev_lane(p[R - 1]), pd = from_next_lane(p[0]);
+      const double xu = from_prev_lane(x[R - 1]), xd = from_next_lane(x[0]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) sv[r] = fma(p[r], x[r], sv[r]);
+      if (couplings) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          double& a = sk[KC ? r : 0];
+          a = fma(p[r], r + 1 < R ? x[r + 1 < R ? r + 1 : 0] : xd, a);
+          a = fma(r + 1 < R ? p[r + 1 < R ? r + 1 : 0] : pd, x[r], a);
+        }
+      }
+      advance(p, pu, pd, o);
+#pragma unroll
+      for (int r = 0; r < R; ++r) o[r] = fma(c, lam[r], o[r]);
+      if (more) advance(x, xu, xd, y);
+    };
+    int l = L - 1;
+    // even l: x = xa, p = pb; odd l: x = xb, p = pa
+    if (l >= 1 && (l & 1)) {
+      down(xb, xa, pa, pb, sgn * coef[l].y, lx, true);
+      --l;
+    }
+    for (; l >= 2; l -= 2) {
+      const double ce = coef[l].x, co = sgn * coef[l - 1].y;
+      down(xa, xb, pb, pa, ce, lo, true);
+      down(xb, xa, pa, pb, co, lx, true);
+    }
+    // l = 0: half the weight of the other terms; Pbar_0 = G Pbar_1 - Pbar_2 + c_0 Lambda'
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      sv[r] *= 2.0;
+      pa[r] *= 2.0;
+      if (KC) sk[KC ? r : 0] *= 2.0;
+    }
+    down(xa, xb, pb, pa, 2.0 * coef[0].x, lo, false);
+#pragma unroll
+    for (int r = 0; r < R; ++r) pa[r] *= 0.5;
+    // Lambda of the step before, both parts, in the frame of step k; X_k is in xa
+#pragma unroll
+    for (int r = 0; r < R; ++r) lo[r] = pa[r];
+    trade(lo, lx);
+    double gv = 0.0, gk = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const long i = base + r;
+      if (i >= n) continue;
+      const double vi = job.v_diag[i];
+      gv = fma(vi, sv[r], gv);
+      if (couplings && i + 1 < n) {
+        const double2 h = reinterpret_cast<const double2*>(job.h0_off)[i];
+        const double dv = job.v_diag[i + 1] - vi, q = b * dv;
+        const double dg = b * dv * dv * sqrt((h.x * h.x + h.y * h.y) / (1.0 + q * q));
+        gk = fma(dg, sk[KC ? r : 0], gk);
+      }
+    }
+    if constexpr (KC) {
+      double q[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) q[r] = -sgn * lx[r] * xa[r];
+      gk += aj.dE * (bnd + against_theta(k, q));
+      if (k > k_lo) bnd = -against_theta(k - 1, q);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      gv += __shfl_xor(gv, o);
+      if (KC) gk += __shfl_xor(gk, o);
+    }
+    if (pl == 0) {
+      atomicAdd(aj.grad + 2 * k, gv);
+      if (KC) atomicAdd(aj.grad + 2 * k + 1, gk);
+    }
+  }
+}
+
+// theta'_i of every step (see above) in the lane order of the step tables.
+__global__ __launch_bounds__(256) void tridiag_theta_kernel(TridiagJob job, int R,
+                                                            double* __restrict__ out) {
+  __shared__ double run[2][256];
+  const int t = threadIdx.x;
+  const long n = job.n, nq = job.nq;
+  const double b = job.ab[2 * blockIdx.x + 1];
+  const long c = (n + 255) / 256, i0 = t * c < n ? t * c : n, i1 = i0 + c < n ? i0 + c : n;
+  double* o = out + (long)blockIdx.x * nq * R;
+  auto inc = [&](long i) {
+    if (i + 1 >= n) return 0.0;
+    const double dv = job.v_diag[i + 1] - job.v_diag[i], q = b * dv;
+    return dv / (1.0 + q * q);
+  };
+  double s = 0.0;
+  for (long i = i0; i < i1; ++i) s += inc(i);
+  run[0][t] = s;
+  __syncthreads();
+  int cur = 0;
+  for (int d = 1; d < 256; d <<= 1) {
+    run[cur ^ 1][t] = run[cur][t] + (t >= d ? run[cur][t - d] : 0.0);
+    __syncthreads();
+    cur ^= 1;
+  }
+  double th = t > 0 ? run[cur][t - 1] : 0.0;
+  for (long i = i0; i < i1; ++i) {
+    o[(i % R) * nq + i / R] = th;
+    th += inc(i);
+  }
+  for (long i = n + t; i < nq * R; i += 256) o[(i % R) * nq + i / R] = 0.0;
+}
+
+template <int R>
+hipError_t launch_adj_chain_r(const TridiagJob& job, const TridiagAdjChain& aj, bool with_k, int g,
+                              hipStream_t s) {
+  const dim3 grid((unsigned)job.ncols, (unsigned)g);
+  const double2* coef = reinterpret_cast<const double2*>(job.coef);
+  if (with_k)
+    hipLaunchKernelGGL((tridiag_adj_chain_kernel<R, true>), grid, dim3(128), 0, s, job, aj, coef,
+                       job.tab, aj.store);
+  else
+    hipLaunchKernelGGL((tridiag_adj_chain_kernel<R, false>), grid, dim3(128), 0, s, job, aj, coef,
+                       job.tab, aj.store);
+  return hipGetLastError();
+}
+
 // ---- streamed reverse sweep ------------------------------------------------------------------
 //
 // For columns longer than one workgroup holds, the reverse recurrences run one
@@ -2004,10 +2353,33 @@ hipError_t launch_tridiag_adjoint(const TridiagAdjJob& job, hipStream_t s) {
   if (job.n < 1 || job.ncols < 1 || job.L < 1 || job.M < 1 || job.ckpt < 1 ||
       job.ncols > 0x7fffffffL)
     return hipErrorInvalidValue;
-  if (job.n <= 256) return launch_adj_r<4, 1>(job, s);
-  if (job.n <= 1024) return launch_adj_r<4, 4>(job, s);
   if (job.n <= tridiag_adjoint_max_n()) return launch_adj_r<4, 8>(job, s);
   return hipErrorInvalidValue;
+}
+
+long tridiag_adj_chain_max_n() { return 1024; }
+
+hipError_t launch_tridiag_adj_chain(const TridiagJob& job, const TridiagAdjChain& aj, bool with_k,
+                                    int z0, int g, hipStream_t s) {
+  const int R = chain_rows(job.n);
+  TridiagAdjChain a = aj;
+  a.z0 = z0;
+  const long n_seg = aj.len0 > 0 ? ((long)job.M - aj.rem) / aj.len0 : 0;
+  if (job.n < 1 || job.n > tridiag_adj_chain_max_n() || !job.tab || job.nq != (job.n + R - 1) / R ||
+      job.L < 1 || g < 1 || g > 65535 || z0 < 0 || z0 + g > n_seg ||
+      n_seg * aj.len0 + aj.rem != job.M || aj.len < aj.len0 + (aj.rem ? 1 : 0) ||
+      (with_k && !aj.theta))
+    return hipErrorInvalidValue;
+  if (with_k && z0 == 0)
+    hipLaunchKernelGGL(tridiag_theta_kernel, dim3((unsigned)job.M), dim3(256), 0, s, job, R,
+                       a.theta);
+  switch (R) {
+    case 1: return launch_adj_chain_r<1>(job, a, with_k, g, s);
+    case 2: return launch_adj_chain_r<2>(job, a, with_k, g, s);
+    case 4: return launch_adj_chain_r<4>(job, a, with_k, g, s);
+    case 8: return launch_adj_chain_r<8>(job, a, with_k, g, s);
+  }
+  return launch_adj_chain_r<16>(job, a, with_k, g, s);
 }
 
 hipError_t launch_tridiag_adj_table(const TridiagAdjStream& p, int k, bool plain_lambda,

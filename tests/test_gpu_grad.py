@@ -568,3 +568,40 @@ def test_dense_gradient_of_every_order(fl, n, M, ckpt, L, T):
     fd = (vals[0] - vals[1]) / (2 * eps)
     _say("direction", np.sum(g * u), "difference", fd)
     assert abs(np.sum(g * u) - fd) < 1e-8 * max(1.0, abs(fd))
+
+
+# ---- resident sweep in the gauge frame: every row count, segments, both drives ------------------
+
+@pytest.mark.parametrize("pair", [True, False])
+@pytest.mark.parametrize("n,L", [(2, 0), (64, 0), (65, 1), (128, 2), (129, 3), (256, 0), (257, 0),
+                                 (512, 0), (513, 0), (1024, 0)])
+def test_tridiag_resident_sweep_at_every_row_count(fl, monkeypatch, n, L, pair):
+    """1, 2, 4, 8 and 16 rows per lane at their first and last sizes, unequal
+    segments, one to three terms, against the streamed sweep, which contracts
+    with the commutator term by term instead of at the step's ends: complex
+    couplings with one zero among them, a drive with b_k != 0 and a step with
+    b_k = 0. Both sum some n M L products of order one in FP64."""
+    _say("resident sweep", n, L, "pair sums", pair)
+    rng = np.random.default_rng(600 + n)
+    d = rng.standard_normal(n)
+    e = rng.standard_normal(n - 1) + 1j * rng.standard_normal(n - 1)
+    if n > 4:
+        e[n // 2] = 0.0
+    v = rng.standard_normal(n)
+    T, M = (0.02 if L else 1.5), 9
+    nodes = rng.uniform(-1, 1, (M, 2))
+    nodes[4, 1] = nodes[4, 0]
+    kw = dict(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=nodes, checkpoint_every=2, L=L,
+              grad_pair_sums=pair)
+    res = fl.FloquetContext(**kw)
+    monkeypatch.setenv("FQ_TRIDIAG_STREAMED_ADJOINT", "1")
+    streamed = fl.FloquetContext(**kw)
+    monkeypatch.delenv("FQ_TRIDIAG_STREAMED_ADJOINT")
+    U = res.build_ut().cpu().numpy()
+    Us = streamed.build_ut().cpu().numpy()
+    assert np.max(np.abs(U - Us)) < 1e-12
+    w = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+    g1, g2 = res.grad(w), streamed.grad(w)
+    err = np.max(np.abs(g1 - g2)) / np.max(np.abs(g2))
+    _say("rel diff", err, "max|g|", np.max(np.abs(g2)))
+    assert err < 1e-10
