@@ -151,7 +151,7 @@ struct Layout {
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
          off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0,
-         off_ext = 0, off_tab = 0, off_fgrid = 0, off_store = 0, off_theta = 0;
+         off_ext = 0, off_tab = 0, off_fgrid = 0, off_store = 0, off_theta = 0, off_adj_mats = 0;
   long np = 0;
   int n_tape = 0;
   TridiagAdjPlan tri_adj;
@@ -199,7 +199,7 @@ TridiagAdjPlan tridiag_adj_plan(long n, long M, long ckpt) {
   TridiagAdjPlan p;
   if (n > fq::tridiag_adj_chain_max_n()) return p;
   const long R = fq::tridiag_chain_rows(n), np = pad_to(n, dense_tile(n));
-  const size_t step = 4 * 64 * sizeof(double) * (size_t)R * (size_t)n;  // store of one step
+  const size_t step = 4 * sizeof(double) * (size_t)pad_to(n, R) * (size_t)n;  // store of one step
   const double slots = 1024.0 * (R > 8 ? 1 : R > 4 ? 2 : 4);            // waves the chip holds
   if (step * (size_t)M <= kTridiagStore) {
     // all segments at once: rounds of the chip times steps (about 60 terms of 40 ns
@@ -295,17 +295,17 @@ Layout plan(const fq_system* sys, const fq_params* par) {
     const size_t splane = sizeof(double) * n16 * (size_t)n;  // one state plane
     if (n > fq::tridiag_resident_max_n() || streamed_grad)  // two 8-plane states, per-step rows
       lay.off_stream = take(2 * 8 * splane + sizeof(double) * 6 * n16);
-    if (par->checkpoint_every > 0 && !streamed_grad)
-      lay.tri_adj = tridiag_adj_plan(n, Ms, cks);
+    // (the environment's switch adds the streamed sweep's buffers to these)
+    if (par->checkpoint_every > 0) lay.tri_adj = tridiag_adj_plan(n, Ms, cks);
     if (lay.tri_adj.nb > 0) {
-      // the segments' operators and the products that multiply them up; these
-      // operators operator-major, X, Lambda^+ and X state-major
-      const int nb = lay.tri_adj.nb;
-      lay.pool_mats = nb + 2 * (nb / 2 + 1);
+      // the segments' operators; these operator-major and X state-major, X, Lambda^+
+      // (a build multiplies the operators up there)
+      lay.pool_mats = lay.tri_adj.nb;
       lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
-      lay.off_adj = take(plane2 * 4 * (size_t)nb);
+      lay.off_adj_mats = take(plane2 * 3 * (size_t)lay.tri_adj.nb);
       lay.off_grad = take(2 * sizeof(double) * (size_t)Ms);
-    } else if (par->checkpoint_every > 0) {  // X_{j ckpt} per column; segment buffers
+    }
+    if (par->checkpoint_every > 0 && (streamed_grad || lay.tri_adj.nb == 0)) {  // X_{j ckpt} per column; segment buffers
       const size_t vec = 2 * sizeof(double) * (size_t)n;
       lay.n_tape = (Ms + cks - 1) / cks + 1;
       lay.off_tape = take(vec * (size_t)n * (size_t)lay.n_tape);
@@ -346,10 +346,10 @@ Layout plan(const fq_system* sys, const fq_params* par) {
   }
   lay.zeroed = cur;
   if (lay.tri_adj.nb > 0) {
-    const size_t R = (size_t)fq::tridiag_chain_rows(n);
-    lay.off_store = take(4 * 64 * sizeof(double) * R * (size_t)n * (size_t)lay.tri_adj.g *
+    const size_t nr = (size_t)pad_to(n, fq::tridiag_chain_rows(n));
+    lay.off_store = take(4 * sizeof(double) * nr * (size_t)n * (size_t)lay.tri_adj.g *
                          (size_t)lay.tri_adj.len);
-    lay.off_theta = take(sizeof(double) * (size_t)pad_to(n, (long)R) * (size_t)Ms);
+    lay.off_theta = take(sizeof(double) * nr * (size_t)Ms);
   }
   if (lay.adj_mats > 0)
     lay.off_seg = take(lay.adj_mats * 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np);
@@ -1674,10 +1674,10 @@ fq_status tridiag_build_segments(fq_ctx* c, int nseg) {
                              hipMemcpyDeviceToDevice, c->stream));
     return FQ_OK;
   }
-  // (a gradient keeps the segments' operators: the products go elsewhere)
-  double* next = c->pool + (size_t)nseg * job.bs;
-  return multiply_up(c, job.planes, next, c->adj_seg ? next + (size_t)(nseg / 2 + 1) * job.bs : job.planes,
-                     nseg);
+  if (c->adj_seg)  // a gradient keeps the segments' operators: the products go elsewhere
+    return multiply_up(c, job.planes, c->adj_pool, c->adj_pool + (size_t)(nseg / 2 + 1) * job.bs,
+                       nseg);
+  return multiply_up(c, job.planes, c->pool + (size_t)nseg * job.bs, job.planes, nseg);
 }
 
 fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, void* x_out) {
@@ -2365,8 +2365,8 @@ fq_status tridiag_adjoint_chain(fq_ctx* c, const void* U_bar, double* grad_f_nod
   const int nb = c->adj_seg, np = (int)c->np, M = c->M;
   const long bs = 2 * c->np * c->np;
   const bool with_k = !c->pair_sums;
-  double* S = c->adj_pool;  // operator-major; then X, Lambda^+ and X state-major
-  double *X = S + (size_t)nb * bs, *D = X + (size_t)nb * bs, *Xs = D + (size_t)nb * bs;
+  double* S = c->adj_pool;  // operator-major, then X state-major in their place
+  double *X = S + (size_t)nb * bs, *D = X + (size_t)nb * bs, *Xs = S;
   FQ_HIP(c, zero_async(c->stream, c->d_grad, 2 * sizeof(double) * (size_t)M));
   FQ_HIP(c, fq::launch_pack_planar_t(U_bar, c->n, c->n, c->n, c->xr, c->xi, c->np, c->np, c->c64,
                                      c->stream));
@@ -2799,11 +2799,11 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     c->d_ext = P(lay.off_ext);
     c->d_fgrid = P(lay.off_fgrid);
     if (lay.off_tab) c->d_tab = P(lay.off_tab);
-    if (lay.tri_adj.nb > 0) {
+    if (lay.tri_adj.nb > 0 && !lay.off_adj) {
       c->adj_seg = lay.tri_adj.nb;
       c->adj_group = lay.tri_adj.g;
       c->adj_len = lay.tri_adj.len;
-      c->adj_pool = P(lay.off_adj);
+      c->adj_pool = P(lay.off_adj_mats);
       c->adj_store = P(lay.off_store);
       c->d_theta = P(lay.off_theta);
       c->d_grad = P(lay.off_grad);

@@ -366,7 +366,7 @@ struct TridiagAdjChain {
   const double* x;   // X at every segment's first step, state-major planes (row = column
   const double* d;   // of the block): stride ld, segment z at + z * bs, im plane at + bs / 2;
   long ld, bs;       // Lambda^+ after its last step, operator-major planes
-  double* store;     // g * ncols * len * 4 * 64 tridiag_chain_rows(n) doubles
+  double* store;     // g * ncols * len * 4 * nq tridiag_chain_rows(n) doubles
   int len;           // steps the store holds per segment
   double* theta;     // with_k: M nq tridiag_chain_rows(n) doubles (filled when z0 == 0)
   double dE;

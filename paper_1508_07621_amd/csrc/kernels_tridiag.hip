@@ -1266,9 +1266,8 @@ __global__ __launch_bounds__(128, R > 8 ? 1 : 2) void tridiag_adj_chain_kernel(
   const int k_hi = k_lo + aj.len0 + (z < aj.rem ? 1 : 0);
   const bool in = pl < nq;
   const int L = job.L;
-  double* const st =
-      store + (((long)blockIdx.y * job.ncols + col) * aj.len * 2 + part) * 2 * (R * 64) + pl;
-  auto slot = [&](int k, int which, int r) { return ((long)(k - k_lo) * 4 + which) * (R * 64) + r * 64; };
+  double* const st = store + (((long)blockIdx.y * job.ncols + col) * aj.len * 2 + part) * 2 * nr + pl;
+  auto slot = [&](int k, int which, int r) { return ((long)(k - k_lo) * 4 + which) * nr + r * nq; };
 
   double d2[R], g2[R], gm2 = 0.0;
   auto rows_of = [&](int s) {
@@ -1374,10 +1373,12 @@ __global__ __launch_bounds__(128, R > 8 ? 1 : 2) void tridiag_adj_chain_kernel(
         for (int r = 0; r < R; ++r) pa[r] = fma(ce, xa[r], pa[r]);
       }
       // (even terms are in xa, odd ones in xb)
+      if (in) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        st[slot(s, 0, r)] = xa[r];
-        st[slot(s, 1, r)] = xb[r];
+        for (int r = 0; r < R; ++r) {
+          st[slot(s, 0, r)] = xa[r];
+          st[slot(s, 1, r)] = xb[r];
+        }
       }
       if (final_step && !KC) break;
       rotation(s, !final_step, rr, ri);  // the last X in the plain frame
@@ -1440,8 +1441,8 @@ __global__ __launch_bounds__(128, R > 8 ? 1 : 2) void tridiag_adj_chain_kernel(
 #define FQ_SOURCE(l, r) (((l) & 1) ? sgn * coef[l].y * lx[r] : coef[l].x * lo[r])
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      xa[r] = st[slot(k, 0, r)];
-      xb[r] = st[slot(k, 1, r)];
+      xa[r] = in ? st[slot(k, 0, r)] : 0.0;
+      xb[r] = in ? st[slot(k, 1, r)] : 0.0;
       // Pbar_L (by its parity: even terms in pa, odd ones in pb), Pbar_{L+1} = 0
       const double src = FQ_SOURCE(L, r);
       pa[r] = (L & 1) ? 0.0 : src;
