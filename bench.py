@@ -403,9 +403,9 @@ TERM_KERNEL_X4 = {
 
 def x4_tiles(n: int) -> bool:
     """Whether the split-BF16 products of an n-state build run on 128 x 128 output
-    tiles (states padded to 128 from n = 1024 on, to 64 below), where the one- and
+    tiles (states padded to 128 beyond n = 1984, to 64 below), where the one- and
     two-piece products use cheb_x4_kernel."""
-    t = 128 if n >= 1024 else 64
+    t = 128 if n > 1984 else 64
     npad = (n + t - 1) // t * t
     return npad % 128 == 0 and npad * npad >= BIG_TILE_ELEMS
 

@@ -803,6 +803,122 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// One- to three-piece products on 64 x 64 tiles (N < 2048), four waves of 32 x 32 and
+// the four real products. With about one workgroup per CU the time of a k-block is
+// the latency of its loads unless they are issued far ahead, so every thread
+// keeps its chunks of the next D = 4 k-blocks in registers (each iteration
+// writes the next one to LDS and loads the one four ahead in its place); with
+// the Gauss form, loaded one k-block ahead, a k-block took 0.6 us (one
+// piece) to 1.5 us (three). Four real products instead of Gauss's three leave
+// no sums to form and split while staging.
+// ---------------------------------------------------------------------------------------------
+template <int KIND, bool P_F64, int NPC>
+__global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
+  constexpr int BM = 64, BN = 64, NT = 256, D = 4;
+  constexpr int NL = 2 * NPC;                // stored planes read per operand
+  constexpr int SA = BM * 32, SB = BN * 32;  // bytes per plane and k-block
+  constexpr int STAGE = NL * (SA + SB);
+  constexpr int EPI = 2 * BM * BN * 4;       // FP32 Re, Im in k-blocked order
+  constexpr int SMEM = (2 * STAGE > EPI) ? 2 * STAGE : EPI;
+  constexpr bool FIRST = KIND == CHEB_FIRST || KIND == CHEB_FIRST_LAST;
+  static_assert(!FIRST || P_F64, "the first product reads X in FP64");
+  static_assert(2 * (BM + BN) == NT, "one 16-byte chunk of A or of B per thread");
+
+  __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+
+  int tm, tn;
+  tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+  if (tm >= g.tiles_m) return;  // grid padding
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int wm = wid >> 1, wn = wid & 1;
+  const long np = g.np, plane = g.plane;
+  const int nk = g.np / 16;      // a multiple of D (np of 64)
+  const long kstride = np * 16;  // words between consecutive k-blocks of a plane
+
+  const bool is_a = tid < 2 * BM;  // whole waves
+  const int cq = is_a ? tid : tid - 2 * BM;
+  const u16* src = is_a ? g.a + (long)m0 * 16 + cq * 8 : g.b + (long)n0 * 16 + cq * 8;
+  const int ldst = is_a ? cq * 16 : NL * SA + cq * 16;
+  static_assert(SA == SB, "one plane step for both operands");
+  u32x4 st[D][NL];
+  auto gload = [&](int kb, u32x4 (&v)[NL]) {
+    const long k = (long)(kb < nk ? kb : nk - 1) * kstride;
+#pragma unroll
+    for (int q = 0; q < NL; ++q)
+      v[q] = *reinterpret_cast<const u32x4*>(src + (q < NPC ? q : 3 + q - NPC) * plane + k);
+  };
+  auto lstore = [&](int buf, const u32x4 (&v)[NL]) {
+    unsigned char* d = smem + buf * STAGE + ldst;
+#pragma unroll
+    for (int q = 0; q < NL; ++q) *reinterpret_cast<u32x4*>(d + q * SA) = v[q];
+  };
+  const int arow = wm * 32 + (lane & 31), brow = wn * 32 + (lane & 31);
+  const int aoff = arow * 32 + 16 * ((lane >> 5) ^ ((arow >> 3) & 1));
+  const int boff = NL * SA + brow * 32 + 16 * ((lane >> 5) ^ ((brow >> 3) & 1));
+
+  f16v cre, cim;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) cre[r] = cim[r] = 0.f;
+
+  gload(0, st[0]);
+#pragma unroll
+  for (int d = 1; d < D; ++d) gload(d, st[d]);
+  lstore(0, st[0]);
+  gload(D, st[0]);
+  __syncthreads();
+  for (int kb0 = 0; kb0 < nk; kb0 += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      const int kb = kb0 + u;
+      const unsigned char* sb = smem + (u & 1) * STAGE;  // (D is even)
+      bf8 fa[NL], fb[NL], ma[NPC];
+#pragma unroll
+      for (int q = 0; q < NL; ++q) {
+        fa[q] = *reinterpret_cast<const bf8*>(sb + q * SA + aoff);
+        fb[q] = *reinterpret_cast<const bf8*>(sb + q * SB + boff);
+      }
+#pragma unroll
+      for (int q = 0; q < NPC; ++q) {  // -Ai pieces: flipped sign bits
+        u32x4 w = __builtin_bit_cast(u32x4, fa[NPC + q]);
+        w ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+        ma[q] = __builtin_bit_cast(bf8, w);
+      }
+      // piece pairs i + j < NPC, the smallest first
+#pragma unroll
+      for (int w = NPC - 1; w >= 0; --w)
+#pragma unroll
+        for (int i = w; i >= 0; --i) {
+          const int j = w - i;
+          cre = mfma32_bf16(fa[i], fb[j], cre);
+          cim = mfma32_bf16(fa[i], fb[NPC + j], cim);
+          cre = mfma32_bf16(ma[i], fb[NPC + j], cre);
+          cim = mfma32_bf16(fa[NPC + i], fb[j], cim);
+        }
+      // the next k-block into the other buffer (last read before the previous
+      // barrier), the one D further into its registers
+      lstore((u & 1) ^ 1, st[(u + 1) % D]);
+      gload(kb + 1 + D, st[(u + 1) % D]);
+      __syncthreads();
+    }
+  }
+
+  float* ere = reinterpret_cast<float*>(smem);
+  float* eim = ere + BM * BN;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    const int col = wn * 32 + (lane & 31);
+    const int slot = ((col >> 3) & 1) ^ ((row >> 3) & 1);
+    const int f = ((col >> 4) * BM + row) * 16 + 8 * slot + (col & 7);
+    ere[f] = cre[r];
+    eim[f] = cim[r];
+  }
+  __syncthreads();
+  bf3_tile_epilogue<BM, BN, NT, KIND, P_F64>(g, ere, eim, m0, n0, tid);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Split-BF16 product with FP64 accumulation, for the terms whose Bessel weight
 // is too large for FP32 accumulators (P_1 of every step, and any term with a
 // comparable weight). Each operand is split into three BF16 pieces; per FLUSH
@@ -999,8 +1115,8 @@ hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
   } else if (mrows % 64 == 0 && np % 64 == 0) {
     g.tiles_m = mrows / 64;
     g.tiles_n = np / 64;
-    hipLaunchKernelGGL((cheb_bf3_kernel<64, 64, 2, 2, KIND, P_F64, NPC>),
-                       dim3(grid_rows(g.tiles_m) * g.tiles_n), dim3(256), 0, s, g);
+    hipLaunchKernelGGL((cheb_s4_kernel<KIND, P_F64, NPC>), dim3(grid_rows(g.tiles_m) * g.tiles_n),
+                       dim3(256), 0, s, g);
   } else {
     return hipErrorInvalidValue;
   }
