@@ -209,11 +209,31 @@ inline bool take_tile64(long t64, long t32) {
   return c64 <= c32;
 }
 
+// Products of mrows x ncols (multiples of 16) per batch member that fit one
+// round of one workgroup per CU in blocks of 16 x 16 or 32 x 16 share their
+// reduction between waves instead of taking tiles: 16 rows first (N = 512: 128 rows
+// 9.4 us, 13.1 us in blocks of 32, 23.7 us in 32 x 32 tiles), 32 while those fit
+// (256 rows 13.4, 16.8 and 24.1 us). Beyond one round tiles are as good or better
+// (N = 512, 512 rows: 24.5 us in each form; N = 768, 768 rows: 76 us in tiles, 81).
+inline int split_rows(long m16, long n16, long batch) {
+  if (m16 * n16 * batch <= 256) return 16;
+  return (m16 + 1) / 2 * n16 * batch <= 256 ? 32 : 0;
+}
+
+template <int FM, bool CONJ_A, bool CONJ_B, bool TRANS_B, class Epi>
+hipError_t launch_split(const Operands& op, int mrows, int ncols, int batch, Epi epi,
+                        hipStream_t s) {
+  hipLaunchKernelGGL((zgemm_split_kernel<FM, 8, CONJ_A, CONJ_B, TRANS_B, false, Epi>),
+                     dim3(ncols / 16, (mrows + 16 * FM - 1) / (16 * FM), batch), dim3(512), 0, s,
+                     op, epi);
+  return hipGetLastError();
+}
+
 // Few rows of A: 1, 2, 4, 8 or 16 of them on the vector units, 32, 48 or 64 on
-// the matrix cores with one block of 16 rows per workgroup, or two once those
-// fill the chip (N = 2048, 64 rows: 58 us against 97 us with four blocks and 89 us
-// with 32 x 32 tiles; N = 4096: 186 us with two, 247 us with one). 16 rows as two
-// blocks of 8: 14 us at N = 1024 (17 us on the matrix cores), equal at 2048.
+// the matrix cores, in blocks of 16 rows or two once those take more than one
+// round (N = 1536, 64 rows: 34 us against 45 us; N = 4096: 186 against 247 us; 32 x 32
+// tiles 66 and 190 us). 16 rows as two blocks of 8: 14 us at N = 1024 (17 us on the
+// matrix cores), equal at 2048.
 template <class Epi>
 hipError_t launch_few(const Operands& op, int mrows, int ncols, Epi epi, hipStream_t s) {
   const dim3 gs(ncols / 4, mrows > 8 ? mrows / 8 : 1);
@@ -225,14 +245,10 @@ hipError_t launch_few(const Operands& op, int mrows, int ncols, Epi epi, hipStre
     case 16: hipLaunchKernelGGL((zgemm_few_states_kernel<8, Epi>), gs, dim3(256), 0, s, op, epi); break;
     case 32:
     case 48:
-    case 64:
-      if ((long)(mrows / 16) * (ncols / 16) < 512)
-        hipLaunchKernelGGL((zgemm_few_rows_kernel<1, 16, Epi>), dim3(ncols / 16, mrows / 16),
-                           dim3(1024), 0, s, op, epi);
-      else  // (48 rows: the second block's upper half is scratch rows below 64)
-        hipLaunchKernelGGL((zgemm_few_rows_kernel<2, 8, Epi>), dim3(ncols / 16, (mrows + 16) / 32),
-                           dim3(512), 0, s, op, epi);
-      break;
+    case 64:  // (48 rows: the second block's upper half is scratch rows below 64)
+      return split_rows(mrows / 16, ncols / 16, 1) == 16
+                 ? launch_split<1, false, false, false>(op, mrows, ncols, 1, epi, s)
+                 : launch_split<2, false, false, false>(op, mrows, ncols, 1, epi, s);
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -247,6 +263,10 @@ hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi
   if constexpr (!CONJ_A && !CONJ_B && !TRANS_B)
     if (op0.few) return batch == 1 ? launch_few(op0, mrows, ncols, epi, s) : hipErrorInvalidValue;
   if (mrows % 64 != 0) return hipErrorInvalidValue;
+  switch (split_rows(mrows / 16, ncols / 16, batch)) {
+    case 16: return launch_split<1, CONJ_A, CONJ_B, TRANS_B>(op0, mrows, ncols, batch, epi, s);
+    case 32: return launch_split<2, CONJ_A, CONJ_B, TRANS_B>(op0, mrows, ncols, batch, epi, s);
+  }
   Operands op = op0;
   const long t64 = (long)(mrows / 64) * (ncols / 64) * batch;
   if (take_tile64(t64, 4 * t64)) {
@@ -271,9 +291,12 @@ template <bool CONJ_A, bool CONJ_B, class Epi>
 hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hipStream_t s) {
   if (np % 64 != 0 || op0.kdim % 16 != 0 || batch < 1 || batch > 65535)
     return hipErrorInvalidValue;
-  const long a = np / 64, b = np / 32;
-  const long t64 = a * (a + 1) / 2, t32 = b * (b + 1) / 2;
-  if (take_tile64(t64 * batch, t32 * batch))
+  const long a = np / 64, b = np / 32, c = np / 16;
+  const long t64 = a * (a + 1) / 2, t32 = b * (b + 1) / 2, t16 = c * (c + 1) / 2;
+  if (t16 * batch <= 256)
+    hipLaunchKernelGGL((zgemm_split_kernel<1, 8, CONJ_A, CONJ_B, false, true, Epi>),
+                       dim3(t16, 1, batch), dim3(512), 0, s, op0, epi);
+  else if (take_tile64(t64 * batch, t32 * batch))
     hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, false, true, true, 4,
                                             Epi>),
                        dim3(t64, batch), dim3(512), 0, s, op0, epi);

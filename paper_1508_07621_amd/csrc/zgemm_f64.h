@@ -248,38 +248,54 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   epi.finish();
 }
 
-// The same product for 17 to 64 rows m (a few propagated states against a large
-// operator): a workgroup takes 16 FM rows of A and 16 rows of B, its W waves
-// share the reduction in steps of 8 k and meet in LDS, and fragments go straight
-// from global memory to registers. What bounds it is the vector memory path: a
-// fragment load touches 16 rows of 64 bytes (N = 2048, 16 rows: 31.8 us, the
-// same without the MFMAs, 18 us without the loads of A). Splitting the reduction over
-// workgroups as well loses to the device-scope fences that takes (124 us).
-template <int FM, int W, class Epi>
-__global__ __launch_bounds__(W * 64) void zgemm_few_rows_kernel(Operands op, Epi epi) {
+// The same product where tiles would leave most of the chip idle (few rows m
+// against a large operator, small N): a workgroup takes 16 FM rows of A and 16
+// rows of B, its W waves share the reduction in steps of 8 k and meet in LDS, and
+// fragments go straight from global memory to registers. Against 32 x 32 tiles,
+// whose four waves each walk the whole reduction behind a barrier per 16 k: N =
+// 256, all rows, 13.1 -> 5.8 us; N = 512, 192 rows, 23.7 -> 13.2 us; N = 128 7.6
+// -> 3.9 us. What bounds it is the vector memory path: a fragment load touches 16
+// rows of 64 bytes (N = 2048, 16 rows: 31.8 us, the same without the MFMAs, 18 us
+// without the loads of A). Splitting the reduction over workgroups as well loses
+// to the device-scope fences that takes (124 us). HERM and TRANS_B as above.
+template <int FM, int W, bool CONJ_A, bool CONJ_B, bool TRANS_B, bool HERM, class Epi>
+__global__ __launch_bounds__(W * 64) void zgemm_split_kernel(Operands op, Epi epi) {
+  static_assert(!HERM || FM == 1, "Hermitian products take square tiles");
   __shared__ double red[W][FM * 8][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * 16 * FM, n0 = blockIdx.x * 16;
+  int tm = blockIdx.y, tn = blockIdx.x;
+  if constexpr (HERM) tri_coords(blockIdx.x, tm, tn);
+  const int m0 = tm * 16 * FM, n0 = tn * 16;
   const int rr = lane & 15, kp = 2 * (lane >> 4);
   const long ld = op.ld;
   const int units = op.kdim / 8;
-  const double* br = op.br + (long)(n0 + rr) * ld + kp;
-  const double* bi = op.bi + (long)(n0 + rr) * ld + kp;
-  const double* ar = op.ar + (long)(m0 + rr) * ld + kp;
-  const double* ai = op.ai + (long)(m0 + rr) * ld + kp;
+  const long bo = blockIdx.z * op.b_bs + (TRANS_B ? kp * ld + n0 + rr : (n0 + rr) * ld + kp);
+  const double* br = op.br + bo;
+  const double* bi = op.bi + bo;
+  const long ao = blockIdx.z * op.a_bs + (m0 + rr) * ld + kp;
+  const double* ar = op.ar + ao;
+  const double* ai = op.ai + ao;
   d4 a1[FM], a2[FM], a3[FM];  // T1, T2, T3 of Gauss's three products
 #pragma unroll
   for (int i = 0; i < FM; ++i) a1[i] = a2[i] = a3[i] = d4{0, 0, 0, 0};
 #pragma unroll 8 / FM
   for (int u = wave; u < units; u += W) {
     const long k = 8L * u;
-    const d2 fbr = *reinterpret_cast<const d2*>(br + k);
-    const d2 fbi = *reinterpret_cast<const d2*>(bi + k);
+    d2 fbr, fbi;
+    if constexpr (TRANS_B) {
+      fbr = d2{br[k * ld], br[(k + 1) * ld]};
+      fbi = d2{bi[k * ld], bi[(k + 1) * ld]};
+    } else {
+      fbr = *reinterpret_cast<const d2*>(br + k);
+      fbi = *reinterpret_cast<const d2*>(bi + k);
+    }
+    if constexpr (CONJ_B) fbi = -fbi;
     const d2 fbs = fbr + fbi;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const d2 fr = *reinterpret_cast<const d2*>(ar + 16L * i * ld + k);
-      const d2 fi = *reinterpret_cast<const d2*>(ai + 16L * i * ld + k);
+      d2 fi = *reinterpret_cast<const d2*>(ai + 16L * i * ld + k);
+      if constexpr (CONJ_A) fi = -fi;
       const d2 fs = fr + fi;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -297,7 +313,7 @@ __global__ __launch_bounds__(W * 64) void zgemm_few_rows_kernel(Operands op, Epi
       red[wave][8 * i + 4 + r][lane] = a3[i][r] - a1[i][r] - a2[i][r];
     }
   __syncthreads();
-  epi.batch(0);
+  epi.batch(blockIdx.z);
   for (int q = threadIdx.x; q < FM * 256; q += W * 64) {
     const int l = q & 63, i = q >> 8, r = (q >> 6) & 3, v = 8 * i + r;
     double re = 0.0, im = 0.0;
@@ -306,8 +322,13 @@ __global__ __launch_bounds__(W * 64) void zgemm_few_rows_kernel(Operands op, Epi
       re += red[w][v][l];
       im += red[w][v + 4][l];
     }
-    epi(m0 + 16 * i + 4 * r + (l >> 4), n0 + (l & 15), re, im);
+    const int m = m0 + 16 * i + 4 * r + (l >> 4), n = n0 + (l & 15);
+    if constexpr (HERM)
+      epi.herm(m, n, re, im, tm != tn);
+    else
+      epi(m, n, re, im);
   }
+  epi.finish();
 }
 
 // Sums over the 64 lanes of N values per lane (N a power of two up to 64), by

@@ -128,3 +128,35 @@ def test_few_states(fl, n, ncols):
         w, Q = np.linalg.eigh(H0 + a[k] * V + b[k] * K)
         Y = Q @ (np.exp(-1j * (T / M) * w)[:, None] * (Q.conj().T @ Y))
     assert np.max(np.abs(e - ref / M)) < 1e-11
+
+
+# products that share their reduction between waves: blocks of 16 rows up to one
+# per CU (128 rows at 512 padded states), of 32 rows up to one per CU (256 rows at
+# 512), tiles beyond; conjugated, transposed and Hermitian operands through a
+# whole block's step polynomials and the segments of a build (16 rows up to 256
+# padded states, Hermitian up to 320, 32 rows up to 320); two members in a batch
+@pytest.mark.parametrize("n,ncols", [(128, 128), (256, 65), (256, 256), (300, 300), (320, 320),
+                                     (321, 321), (500, 128), (500, 129), (500, 250), (500, 300),
+                                     (700, 100), (1000, 128), (1000, 129)])
+def test_products_with_shared_reduction(fl, n, ncols):
+    print("[case] shared reduction", n, ncols, flush=True)
+    rng = np.random.default_rng(3 * n + ncols)
+    H0, V = gue(n, rng), gue(n, rng)
+    T, M = 0.4, 3
+    f = np.cos(fl.node_times(T, M))
+    X0 = rng.standard_normal((n, ncols)) + 1j * rng.standard_normal((n, ncols))
+    X0 /= np.linalg.norm(X0, axis=0)
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f)
+    U = ctx.build_ut().cpu().numpy()
+    X = ctx.propagate(X0).cpu().numpy()
+    a, b = orc.magnus4_weights(f, T / M)
+    K = orc.commutator(H0, V)
+    R, Y = np.eye(n, dtype=complex), X0
+    for k in range(M):
+        w, Q = np.linalg.eigh(H0 + a[k] * V + b[k] * K)
+        E = (Q * np.exp(-1j * (T / M) * w)) @ Q.conj().T
+        R, Y = E @ R, E @ Y
+    eu, ex = orc.column_error(U, R), orc.column_error(X, Y)
+    print("[case] build", eu, "block", ex, flush=True)
+    # truncation 1e-12 a step beside rounding
+    assert eu < M * 1e-12 + 1e-13 and ex < M * 1e-12 + 1e-13
