@@ -1365,6 +1365,7 @@ fq_status dense_cheb_step_mixed(fq_ctx* c, int mrows) {
       t.o_re = o.p; t.o_im = o.p + plane;
       t.c0r = C(0).real(); t.c0i = C(0).imag(); t.cr = C(l).real(); t.ci = C(l).imag();
       t.phr = c->phr; t.phi = c->phi;
+      t.tiles = true;
       FQ_HIP(c, fq::launch_cheb_f64(t, mrows, np, c->stream));
       return FQ_OK;
     }

@@ -51,6 +51,9 @@ struct ChebTerm {
   double phr, phi;          // exp(-i beta h)
   double* save_re;          // optional: the last product also stores P_L here
   double* save_im;
+  // A mixed step rounds its FP64 terms to the low format next: their last bits
+  // then decide which way, so shares of a build sum over k in the build's order.
+  bool tiles;
 };
 
 // ---- adjoint products (kernels_dense.hip) ---------------------------------------------------

@@ -263,7 +263,7 @@ hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi
   if constexpr (!CONJ_A && !CONJ_B && !TRANS_B)
     if (op0.few) return batch == 1 ? launch_few(op0, mrows, ncols, epi, s) : hipErrorInvalidValue;
   if (mrows % 64 != 0) return hipErrorInvalidValue;
-  switch (split_rows(mrows / 16, ncols / 16, batch)) {
+  switch (op0.tiles ? 0 : split_rows(mrows / 16, ncols / 16, batch)) {
     case 16: return launch_split<1, CONJ_A, CONJ_B, TRANS_B>(op0, mrows, ncols, batch, epi, s);
     case 32: return launch_split<2, CONJ_A, CONJ_B, TRANS_B>(op0, mrows, ncols, batch, epi, s);
   }
@@ -820,7 +820,7 @@ __global__ __launch_bounds__(256) void transpose_planar_kernel(const double* __r
 }  // namespace
 
 hipError_t launch_cheb_f64(const ChebTerm& t, int mrows, int np, hipStream_t s) {
-  Operands op{t.a_re, t.a_im, t.b_re, t.b_im, np, np, 0, 0, 0, 0, mrows <= 64 && mrows < np};
+  Operands op{t.a_re, t.a_im, t.b_re, t.b_im, np, np, 0, 0, 0, 0, mrows <= 64 && mrows < np, t.tiles};
   switch (t.kind) {
     case CHEB_FIRST:
       return launch_gemm<false, false>(op, mrows, np, 1, EpiCheb<CHEB_FIRST>{t, np}, s);

@@ -33,6 +33,7 @@ struct Operands {
   long a_bs;    // batch strides (elements) of A and B: operand z at + z * stride
   long b_bs;
   bool few = false;  // few rows of A: take the kernels below rather than tiles
+  bool tiles = false;  // tiles for more rows: sums over k in the same order in any block
 };
 
 // Tile (tm, tn), tm <= tn, number t of the upper triangle of a tiles x tiles
