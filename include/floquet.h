@@ -86,7 +86,9 @@ typedef enum { FQ_DENSE = 0, FQ_TRIDIAG = 1, FQ_DENSE_EIGEN = 2 } fq_layout;
  * FQ_BF16X3: products on BF16 matrix cores with operands split into BF16
  * pieces, each term in its own fq_term_format chosen from its Bessel weight;
  * P_l stored as three BF16 pieces (about 24 bits); X and the Chebyshev sum
- * float64. Setup, coefficients and checks are always float64. */
+ * float64. Setup, coefficients and checks are always float64. FQ_FP32 and
+ * FQ_BF16X3 allow these products; calls that run faster in FP64 (small N, few
+ * states, most FQ_FP32 builds) run there, unless fq_params.term_formats is set. */
 typedef enum { FQ_FP64 = 0, FQ_FP32 = 1, FQ_BF16X3 = 2 } fq_precision;
 
 /* Format of one Chebyshev product P_l = 2 Ht P_{l-1} - P_{l-2} (P_1 = Ht X) of
@@ -271,8 +273,10 @@ typedef struct fq_report {
   int32_t n_kernel[FQ_K_SLOTS];   /* profile mode: launches per kind */
   int32_t term_format[FQ_TERM_SLOTS];  /* FQ_BF16X3 and FQ_FP32: fq_term_format
                                           of terms 1 .. min(L, 16) (later terms
-                                          are not listed); FQ_FP64 builds and
-                                          unused entries: -1 */
+                                          are not listed), the schedule of the
+                                          drive or, after a build that ran in
+                                          FP64, FQ_TERM_FP64; FQ_FP64 builds
+                                          and unused entries: -1 */
   double mixed_err_est;           /* FQ_BF16X3 and FQ_FP32: the error estimate
                                      the schedule was chosen for (0 otherwise) */
   int32_t diverged;               /* 1 when the last build's max |(U^dagger U -

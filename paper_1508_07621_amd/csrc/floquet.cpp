@@ -161,6 +161,9 @@ struct Layout {
   size_t adj_mats = 0;
 };
 
+// Split-BF16 contexts up to this padded size run in FP64 (see runs_f64).
+constexpr long kBf16F64Np = 512;
+
 // Scratch matrices of the FP64 step operators (see PolyPlan). Below 1024 padded
 // states one product leaves most of the chip idle, so a build cuts the chain
 // into segments and runs one step of each as a batch: up to two 64 x 64-tile
@@ -355,7 +358,8 @@ Layout plan(const fq_system* sys, const fq_params* par) {
   }
   if (lay.adj_mats > 0)
     lay.off_seg = take(lay.adj_mats * 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np);
-  if (dense_like(sys->layout) && par->precision == FQ_FP64) {
+  if (dense_like(sys->layout) && par->n_term_formats == 0 &&
+      (par->precision != FQ_BF16X3 || lay.np <= kBf16F64Np)) {
     const size_t plane2 = 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np;
     // (a gradient tape is never in the static scratch)
     const size_t left = par->checkpoint_every > 0 ? kPoolBudget
@@ -365,7 +369,7 @@ Layout plan(const fq_system* sys, const fq_params* par) {
       lay.pool_mats = (int)std::min<size_t>(kPoolBufs * (size_t)pool_segments(lay.np),
                                             std::min(left, kPoolBytes) / plane2);
       if (lay.pool_mats > 0) lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
-    } else {
+    } else if (par->precision == FQ_FP64) {  // (others have two matrices more already)
       lay.n_extra = left == 0 || par->checkpoint_every > 0
                         ? kExtraBufs
                         : (int)std::min<size_t>(kExtraBufs, left / plane2);
@@ -980,13 +984,46 @@ fq_status cheb_launch(fq_ctx* c, int kind, int mrows, double* a, double* p, doub
   return FQ_OK;
 }
 
+PolyPlan poly_plan(const fq_ctx* c, int nbuf, double apply);
+
+// Whether the steps on mrows rows run in FP64 in a context that allows FP32 or
+// split-BF16 products: where the FP64 form is the faster one (no caller's
+// formats). Milliseconds a step, L = 8, FP64 against BF16 and FP32:
+//   builds         N = 256  0.019, 0.096, 0.23   N = 512 0.082, 0.138, 0.39
+//                  N = 960  0.47,  0.26,  0.77   N = 4096 26.1, 9.0,  37.6
+//   150 states     N = 256  0.045, 0.092, 0.22   N = 512 0.125, 0.132, 0.37
+//   64 states      N = 960  0.144, 0.192, 0.60   N = 2048 0.41, 0.41, 1.32
+//   32 states      N = 2048 0.29,  0.41,  1.32   N = 4096 1.05, 0.88, 2.7
+//   8 states       N = 3000 0.56,  0.63,  2.0    N = 8000 2.7,  2.4,  6.1
+//   100 states     N = 3000 1.87,  0.63,  2.02   N = 4096 2.57, 0.88, 2.73
+//   400 states     N = 960  -      -      -      N = 2048 1.97, 0.48, 1.48
+// Against BF16: small N, where batched step polynomials and products in one round
+// win over L launches, and few states, whose product streams the matrix. Against
+// FP32 also builds and whatever else the step polynomials make cheaper, at 0.68
+// of an FP64 product per FP32 one (its first is in FP64).
+bool runs_f64(const fq_ctx* c, long mrows) {
+  if (c->precision == FQ_FP64) return true;
+  if (!c->term_formats.empty()) return false;
+  if (c->precision == FQ_BF16X3)
+    return c->np <= kBf16F64Np || (c->np <= 3072 && mrows * c->np <= 65536);
+  if (c->np < 1024 || mrows * c->np <= 1L << 18) return true;
+  const double apply = (double)mrows / (double)c->np;
+  if (apply < 0.25) return false;
+  const PolyPlan p = poly_plan(c, 6, apply);
+  return p.s && 0.6 * (p.s - 1) + (p.J - 1) + apply < (1.0 + 0.68 * (c->L - 1)) * apply;
+}
+
 // Rows of the state-major block the products of ncols states run on: FP64
 // products of up to 64 states take 1, 2, 4, 8 or blocks of 16 rows, the others
 // whole tiles (as does the one-launch chain at np = 64, in blocks of 16).
 long product_rows(const fq_ctx* c, long ncols) {
-  if (c->precision != FQ_FP64 || ncols > 64) return pad_to(ncols, dense_tile(c->n));
-  if (ncols > 8 || c->np == 64) return pad_to(ncols, 16);
-  return ncols > 4 ? 8 : (ncols > 2 ? 4 : ncols);
+  const long tile = pad_to(ncols, dense_tile(c->n));
+  if (ncols > 64) return tile;
+  const long few = ncols > 8 || c->np == 64 ? pad_to(ncols, 16)
+                   : ncols > 4              ? 8
+                   : ncols > 2              ? 4
+                                            : ncols;
+  return runs_f64(c, few) ? few : tile;
 }
 
 fq_status dense_cheb_step_mixed(fq_ctx* c, int mrows);
@@ -1150,11 +1187,18 @@ fq_status poly_form_in_place(fq_ctx* c, const PolyPlan& p, const std::vector<dou
   return poly_form(c, p, b, w, batch);
 }
 
+// Matrices beside Ht, Y and the two P's that an FP64 step may use.
+int extra_mats(const fq_ctx* c) { return c->n_extra + (c->htx ? 2 : 0); }
+
 // One FP64 step X <- E_k X through E_k (Ht formed here).
 fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
   std::vector<double*> b{c->htr, c->par, c->pbr, c->yr};
   const size_t plane2 = 2 * (size_t)c->np * (size_t)c->np;
   for (int i = 0; i < c->n_extra; ++i) b.push_back(c->extra + (size_t)i * plane2);
+  if (c->htx) {  // a mixed context's buffers, not in use in an FP64 step
+    b.push_back(static_cast<double*>(c->htx));
+    b.push_back(c->pcr);
+  }
   FQ_TRY(dense_heff(c, k));
   FQ_TRY(poly_form_in_place(c, p, b, 1));
   FQ_MARK(c, FQ_K_LAST);
@@ -1478,6 +1522,12 @@ bool small_chain_ok(const fq_ctx* c, bool record_tape) {
 
 fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
   const size_t plane2 = 2 * (size_t)c->np * (size_t)c->np;
+  struct Restore {
+    fq_ctx* c;
+    int prec;
+    ~Restore() { c->precision = prec; }
+  } restore{c, c->precision};
+  if (runs_f64(c, mrows)) c->precision = FQ_FP64;
   if (small_chain_ok(c, record_tape)) {
     fq::SmallChain sc{};
     sc.h0r = c->h0r; sc.h0i = c->h0i;
@@ -1518,7 +1568,7 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
       const int nb = poly.s ? poly_segments(c, poly) : 0;
       if (nb > 1) return dense_poly_segments(c, poly, nb);
     }
-    poly = poly_plan(c, 4 + c->n_extra, (double)mrows / (double)c->np);
+    poly = poly_plan(c, 4 + extra_mats(c), (double)mrows / (double)c->np);
   }
   if (record_tape && k0 == 0)
     FQ_HIP(c, hipMemcpyAsync(c->tape, c->xr, plane2 / 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -2958,6 +3008,11 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
     st = dense_steps(c, 0, c->M, (int)c->np, c->ckpt > 0 && adj_mode(c, &gp, &gnb) != 1);
     c->from_identity = false;
     if (st != FQ_OK) return st;
+    if (c->precision != FQ_FP64 && runs_f64(c, c->np)) {  // the formats that ran
+      for (int l = 0; l < std::min(c->L, FQ_TERM_SLOTS); ++l)
+        c->last.term_format[l] = FQ_TERM_FP64;
+      c->last.mixed_err_est = 0.0;
+    }
     FQ_MARK(c, -1);
     if (e1) FQ_HIP(c, hipEventRecord(e1, c->stream));
     FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, c->n, U_out, c->n, c->c64,
