@@ -582,52 +582,12 @@ fq_status drive_sum(fq_ctx* c, int k, bool with_base, double* outr, double* outi
 using cd = std::complex<double>;
 using Matvec = std::function<fq_status(const std::vector<cd>&, std::vector<cd>&)>;
 
-// y = A x for a dense complex128 device matrix, through the device scratch
-// (the Y planes are free during setup).
-fq_status device_matvec(fq_ctx* ctx, const void* A, const std::vector<cd>& x, std::vector<cd>& y) {
-  const long n = ctx->n;
-  void* dx = ctx->yr;
-  void* dy = ctx->yr + 2 * n;
-  y.resize(n);
-  FQ_HIP(ctx, hipMemcpyAsync(dx, x.data(), n * sizeof(cd), hipMemcpyHostToDevice, ctx->stream));
-  FQ_HIP(ctx, fq::launch_zgemv(A, n, dx, dy, ctx->stream));
-  FQ_HIP(ctx, hipMemcpyAsync(y.data(), dy, n * sizeof(cd), hipMemcpyDeviceToHost, ctx->stream));
-  FQ_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  return FQ_OK;
-}
-
-// y = A x for a planar (re, im) device matrix with row stride np.
-fq_status device_matvec_planar(fq_ctx* ctx, const double* ar, const double* ai,
-                               const std::vector<cd>& x, std::vector<cd>& y) {
-  const long n = ctx->n;
-  void* dx = ctx->yr;
-  void* dy = ctx->yr + 2 * n;
-  y.resize(n);
-  FQ_HIP(ctx, hipMemcpyAsync(dx, x.data(), n * sizeof(cd), hipMemcpyHostToDevice, ctx->stream));
-  FQ_HIP(ctx, fq::launch_zgemv_planar(ar, ai, n, ctx->np, dx, dy, ctx->stream));
-  FQ_HIP(ctx, hipMemcpyAsync(y.data(), dy, n * sizeof(cd), hipMemcpyDeviceToHost, ctx->stream));
-  FQ_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  return FQ_OK;
-}
-
-// Extreme Ritz values of a Hermitian operator after k Lanczos steps. The start
-// vector is drawn from a generator seeded with a hash of A x0 for a fixed x0,
-// so it is not fixed in advance of the operator (no operator can be chosen with
-// its extreme eigenvector orthogonal to a known start) and the same operator
-// always gets the same start (reproducible covers). Ritz values lie inside
-// [lambda_min, lambda_max] and converge to its ends fastest; the probability
-// bound above applies to starts uniform on the sphere, which complex Gaussian
-// components give after normalisation.
-fq_status lanczos_extremes(long n, const Matvec& mv, double* lo, double* hi) {
-  std::vector<cd> q(n), qp(n, 0.0), w(n);
-  // hash of A x0, x0 = (1, 1, ..., 1) / sqrt(n)
-  for (long i = 0; i < n; ++i) q[i] = cd(1.0 / std::sqrt((double)n), 0.0);
-  fq_status st = mv(q, w);
-  if (st != FQ_OK) return st;
+// The start vector from ax0 = A x0, x0 = (1, 1, ..., 1) / sqrt(n) (see below).
+void lanczos_start(long n, const cd* ax0, std::vector<cd>& q) {
   uint64_t s = 0x9E3779B97F4A7C15ull ^ (uint64_t)n;
   for (long i = 0; i < n; ++i) {
     uint64_t bits[2];
-    std::memcpy(bits, &w[i], sizeof bits);
+    std::memcpy(bits, &ax0[i], sizeof bits);
     for (uint64_t b : bits) {
       s ^= b + 0x9E3779B97F4A7C15ull + (s << 6) + (s >> 2);
       s *= 0xBF58476D1CE4E5B9ull;
@@ -649,6 +609,22 @@ fq_status lanczos_extremes(long n, const Matvec& mv, double* lo, double* hi) {
   }
   nrm = std::sqrt(nrm);
   for (auto& v : q) v /= nrm;
+}
+
+// Extreme Ritz values of a Hermitian operator after k Lanczos steps. The start
+// vector is drawn from a generator seeded with a hash of A x0 for a fixed x0,
+// so it is not fixed in advance of the operator (no operator can be chosen with
+// its extreme eigenvector orthogonal to a known start) and the same operator
+// always gets the same start (reproducible covers). Ritz values lie inside
+// [lambda_min, lambda_max] and converge to its ends fastest; the probability
+// bound above applies to starts uniform on the sphere, which complex Gaussian
+// components give after normalisation.
+fq_status lanczos_extremes(long n, const Matvec& mv, double* lo, double* hi) {
+  std::vector<cd> q(n), qp(n, 0.0), w(n);
+  for (long i = 0; i < n; ++i) q[i] = cd(1.0 / std::sqrt((double)n), 0.0);
+  fq_status st = mv(q, w);
+  if (st != FQ_OK) return st;
+  lanczos_start(n, w.data(), q);
   const int ksteps = (int)std::min<long>(n, kLanczosSteps);
   std::vector<double> alpha, beta;
   double bprev = 0.0;
@@ -676,21 +652,73 @@ fq_status lanczos_extremes(long n, const Matvec& mv, double* lo, double* hi) {
   return FQ_OK;
 }
 
-fq_status lanczos_ritz(fq_ctx* ctx, const Matvec& mv, double* lo, double* hi) {
-  return lanczos_extremes(ctx->n, mv, lo, hi);
+// The same on the device for planar operators (row stride np), all of them in
+// each launch, in the Y planes (free during setup).
+struct PlanarOp {
+  const double *re, *im;
+};
+fq_status lanczos_device(fq_ctx* ctx, const std::vector<PlanarOp>& ops, std::vector<double>& lo,
+                         std::vector<double>& hi) {
+  const long n = ctx->n;
+  const int cnt = (int)ops.size(), ksteps = (int)std::min<long>(n, kLanczosSteps);
+  lo.resize(cnt);
+  hi.resize(cnt);
+  if (cnt == 0) return FQ_OK;
+  fq::LanczosBatch b{};
+  for (int z = 0; z < cnt; ++z) {
+    b.re[z] = ops[z].re;
+    b.im[z] = ops[z].im;
+  }
+  b.n = n;
+  b.ld = ctx->np;
+  b.stride = fq::lanczos_state(n, ksteps);
+  b.state = ctx->yr;
+  b.count = cnt;
+  std::vector<double> st((size_t)b.stride * cnt, 0.0);
+  const size_t bytes = st.size() * sizeof(double);
+  auto vec = [&](int z, int i) { return reinterpret_cast<cd*>(&st[(size_t)b.stride * z]) + n * i; };
+  for (int z = 0; z < cnt; ++z)
+    for (long i = 0; i < n; ++i) vec(z, 2)[i] = cd(1.0 / std::sqrt((double)n), 0.0);
+  FQ_HIP(ctx, copy_sync(ctx->stream, b.state, st.data(), bytes, hipMemcpyHostToDevice));
+  FQ_HIP(ctx, fq::launch_lanczos_step(b, 0, ksteps, ctx->stream));  // A x0
+  FQ_HIP(ctx, copy_sync(ctx->stream, st.data(), b.state, bytes, hipMemcpyDeviceToHost));
+  std::vector<cd> q(n);
+  for (int z = 0; z < cnt; ++z) {
+    lanczos_start(n, vec(z, 0), q);
+    std::copy(q.begin(), q.end(), vec(z, 2));
+  }
+  FQ_HIP(ctx, copy_sync(ctx->stream, b.state, st.data(), bytes, hipMemcpyHostToDevice));
+  for (int j = 0; j <= ksteps; ++j)
+    FQ_HIP(ctx, fq::launch_lanczos_step(b, j, ksteps, ctx->stream));
+  FQ_HIP(ctx, copy_sync(ctx->stream, st.data(), b.state, bytes, hipMemcpyDeviceToHost));
+  for (int z = 0; z < cnt; ++z) {
+    const double* alpha = &st[(size_t)b.stride * z + 10 * n];
+    const long k = std::max(1L, (long)alpha[2 * ksteps]);
+    fq::tridiag_extremes(k, alpha, alpha + ksteps, &lo[z], &hi[z]);
+  }
+  return FQ_OK;
 }
 
-// Ritz extremes of one of the context's fixed operators (key: its device
-// pointer), computed once per context: fq_set_drive reuses them.
-fq_status cached_ritz(fq_ctx* ctx, const void* key, const Matvec& mv, double* lo, double* hi) {
-  for (const auto& e : ctx->ritz_cache)
-    if (e.first == key) {
-      *lo = e.second.first;
-      *hi = e.second.second;
-      return FQ_OK;
-    }
-  FQ_TRY(lanczos_ritz(ctx, mv, lo, hi));
-  ctx->ritz_cache.push_back({key, {*lo, *hi}});
+// Ritz extremes of the context's fixed operators (key: their first plane),
+// computed once per context: fq_set_drive reuses them.
+fq_status cached_ritz(fq_ctx* ctx, const std::vector<PlanarOp>& ops, std::vector<double>& lo,
+                      std::vector<double>& hi) {
+  lo.resize(ops.size());
+  hi.resize(ops.size());
+  auto known = [&](const double* key) {
+    return std::find_if(ctx->ritz_cache.begin(), ctx->ritz_cache.end(),
+                        [&](const auto& e) { return e.first == key; });
+  };
+  std::vector<PlanarOp> todo;
+  for (const PlanarOp& o : ops)
+    if (known(o.re) == ctx->ritz_cache.end()) todo.push_back(o);
+  std::vector<double> l, h;
+  FQ_TRY(lanczos_device(ctx, todo, l, h));
+  for (size_t i = 0; i < todo.size(); ++i) ctx->ritz_cache.push_back({todo[i].re, {l[i], h[i]}});
+  for (size_t i = 0; i < ops.size(); ++i) {
+    lo[i] = known(ops[i].re)->second.first;
+    hi[i] = known(ops[i].re)->second.second;
+  }
   return FQ_OK;
 }
 
@@ -699,9 +727,12 @@ fq_status cached_ritz(fq_ctx* ctx, const void* key, const Matvec& mv, double* lo
 // Ritz values approach the ends from inside) and ||K||_2 <= 2 ||H0|| ||Hmod||.
 fq_status dense_cover(fq_ctx* ctx, double* lo_out, double* hi_out, double margin) {
   double l0, h0, lv, hv;
-  Matvec mh0 = [&](const std::vector<cd>& x, std::vector<cd>& y) { return device_matvec(ctx, ctx->sys.h0, x, y); };
-  Matvec mv = [&](const std::vector<cd>& x, std::vector<cd>& y) { return device_matvec(ctx, ctx->sys.hmod, x, y); };
-  fq_status st = FQ_OK;
+  const size_t plane = (size_t)ctx->np * (size_t)ctx->np;
+  std::vector<PlanarOp> ops;  // the drive matrices, and H0 unless its spectrum is given
+  for (int d = 0; d < ctx->S; ++d) ops.push_back({ctx->vr + d * plane, ctx->vi + d * plane});
+  if (!ctx->h0_eigen) ops.push_back({ctx->h0r, ctx->h0i});
+  std::vector<double> ls, hs;
+  FQ_TRY(cached_ritz(ctx, ops, ls, hs));
   if (ctx->h0_eigen) {  // the extremes of diag(E) are exact
     std::vector<double> e(ctx->n);
     FQ_HIP(ctx, copy_sync(ctx->stream, e.data(), ctx->sys.h0_diag, ctx->n * sizeof(double),
@@ -709,8 +740,8 @@ fq_status dense_cover(fq_ctx* ctx, double* lo_out, double* hi_out, double margin
     l0 = *std::min_element(e.begin(), e.end());
     h0 = *std::max_element(e.begin(), e.end());
   } else {
-    st = cached_ritz(ctx, ctx->sys.h0, mh0, &l0, &h0);
-    if (st != FQ_OK) return st;
+    l0 = ls.back();
+    h0 = hs.back();
   }
   if (ctx->S > 1) {
     // Weyl over the drive terms with their Lanczos extremes; ||K_s|| <= 2 ||H0|| ||Hmod_s||,
@@ -720,12 +751,8 @@ fq_status dense_cover(fq_ctx* ctx, double* lo_out, double* hi_out, double margin
     l0 -= margin * w0;
     h0 += margin * w0;
     const double n0 = std::max(std::fabs(l0), std::fabs(h0));
-    std::vector<double> ls(S), hs(S), nb(J, 0.0);
+    std::vector<double> nb(J, 0.0);
     for (int d = 0; d < S; ++d) {
-      Matvec md = [&](const std::vector<cd>& x, std::vector<cd>& y) {
-        return device_matvec(ctx, ctx->sys.hmods[d], x, y);
-      };
-      FQ_TRY(cached_ritz(ctx, ctx->sys.hmods[d], md, &ls[d], &hs[d]));
       const double wd = hs[d] - ls[d];
       ls[d] -= margin * wd;
       hs[d] += margin * wd;
@@ -757,8 +784,8 @@ fq_status dense_cover(fq_ctx* ctx, double* lo_out, double* hi_out, double margin
     *hi_out = hi;
     return FQ_OK;
   }
-  st = cached_ritz(ctx, ctx->sys.hmod, mv, &lv, &hv);
-  if (st != FQ_OK) return st;
+  lv = ls[0];
+  hv = hs[0];
   const double w0 = h0 - l0, wv = hv - lv;
   l0 -= margin * w0;
   h0 += margin * w0;
@@ -814,49 +841,31 @@ fq_status dense_inner_bounds(fq_ctx* ctx, double* lo_out, double* hi_out) {
     if (ak < amin) kmin = k;
     if (ak > amax) kmax = k;
   }
-  double lo = std::numeric_limits<double>::infinity(), hi = -lo;
+  // H_eff of both steps in the Ht and P planes (free between builds)
+  const size_t plane = (size_t)ctx->np * (size_t)ctx->np;
+  std::vector<PlanarOp> ops;
   for (int k : {kmin, kmax}) {
-    const double a = ctx->a[k], b = ctx->b[k];
-    if (ctx->scheme == FQ_MAGNUS6 || ctx->S > 1) {  // H_eff,k formed on the device
-      if (ctx->S > 1)
-        FQ_TRY(drive_sum(ctx, k, true, ctx->htr, ctx->hti));  // (Ht planes are free)
-      else
-        FQ_TRY(magnus6_sum(ctx, k, true, ctx->htr, ctx->hti));
-      Matvec mz = [&](const std::vector<cd>& x, std::vector<cd>& y) {
-        return device_matvec_planar(ctx, ctx->htr, ctx->hti, x, y);
-      };
-      double l, h;
-      FQ_TRY(lanczos_ritz(ctx, mz, &l, &h));
-      lo = std::min(lo, l);
-      hi = std::max(hi, h);
-      if (kmin == kmax) break;
-      continue;
+    double* re = k == kmin ? ctx->htr : ctx->par;
+    double* im = re + plane;
+    if (ctx->S > 1) {
+      FQ_TRY(drive_sum(ctx, k, true, re, im));
+    } else if (ctx->scheme == FQ_MAGNUS6) {
+      FQ_TRY(magnus6_sum(ctx, k, true, re, im));
+    } else {
+      fq::WeightedSum ws{};
+      ws.re[0] = ctx->h0r; ws.im[0] = ctx->h0i; ws.w[0] = 1.0;
+      ws.re[1] = ctx->vr;  ws.im[1] = ctx->vi;  ws.w[1] = ctx->a[k];
+      ws.re[2] = ctx->kr;  ws.im[2] = ctx->ki;  ws.w[2] = ctx->b[k];
+      ws.count = ctx->b[k] != 0.0 ? 3 : 2;
+      FQ_HIP(ctx, fq::launch_weighted_sum(ws, (long)plane, re, im, ctx->stream));
     }
-    Matvec mv = [&](const std::vector<cd>& x, std::vector<cd>& y) {
-      // H0 x + a Hmod x + b K x with K x = -i (H0 (Hmod x) - Hmod (H0 x))
-      std::vector<cd> u1, u2, u3, u4;
-      fq_status st = ctx->h0_eigen ? device_matvec_planar(ctx, ctx->h0r, ctx->h0i, x, u1)
-                                   : device_matvec(ctx, ctx->sys.h0, x, u1);
-      if (st == FQ_OK) st = device_matvec(ctx, ctx->sys.hmod, x, u2);
-      if (st == FQ_OK && b != 0.0)
-        st = ctx->h0_eigen ? device_matvec_planar(ctx, ctx->h0r, ctx->h0i, u2, u3)
-                           : device_matvec(ctx, ctx->sys.h0, u2, u3);
-      if (st == FQ_OK && b != 0.0) st = device_matvec(ctx, ctx->sys.hmod, u1, u4);
-      if (st != FQ_OK) return st;
-      y.resize(x.size());
-      for (size_t i = 0; i < x.size(); ++i) {
-        y[i] = u1[i] + a * u2[i];
-        if (b != 0.0) y[i] += b * cd(0.0, -1.0) * (u3[i] - u4[i]);
-      }
-      return FQ_OK;
-    };
-    double l, h;
-    fq_status st = lanczos_ritz(ctx, mv, &l, &h);
-    if (st != FQ_OK) return st;
-    lo = std::min(lo, l);
-    hi = std::max(hi, h);
+    ops.push_back({re, im});
     if (kmin == kmax) break;
   }
+  std::vector<double> ls, hs;
+  FQ_TRY(lanczos_device(ctx, ops, ls, hs));
+  const double lo = *std::min_element(ls.begin(), ls.end());
+  const double hi = *std::max_element(hs.begin(), hs.end());
   *lo_out = lo;
   *hi_out = hi;
   return FQ_OK;
@@ -3008,11 +3017,6 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
     st = dense_steps(c, 0, c->M, (int)c->np, c->ckpt > 0 && adj_mode(c, &gp, &gnb) != 1);
     c->from_identity = false;
     if (st != FQ_OK) return st;
-    if (c->precision != FQ_FP64 && runs_f64(c, c->np)) {  // the formats that ran
-      for (int l = 0; l < std::min(c->L, FQ_TERM_SLOTS); ++l)
-        c->last.term_format[l] = FQ_TERM_FP64;
-      c->last.mixed_err_est = 0.0;
-    }
     FQ_MARK(c, -1);
     if (e1) FQ_HIP(c, hipEventRecord(e1, c->stream));
     FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, c->n, U_out, c->n, c->c64,
@@ -3058,6 +3062,10 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
   st = collect_profile(c);
   if (st != FQ_OK) return st;
   fill_report(c);
+  if (c->layout == FQ_DENSE && c->precision != FQ_FP64 && runs_f64(c, c->np)) {  // what ran
+    for (int l = 0; l < std::min(c->L, FQ_TERM_SLOTS); ++l) c->last.term_format[l] = FQ_TERM_FP64;
+    c->last.mixed_err_est = 0.0;
+  }
   if (rep) *rep = c->last;
   return FQ_OK;
 }

@@ -245,11 +245,21 @@ hipError_t launch_transpose_planar(const double* sr, const double* si, double* d
 // t = d * s elementwise on count planar complex elements.
 hipError_t launch_scale_planar(const double* sr, const double* si, double dr, double di,
                                double* tr, double* ti, long count, hipStream_t s);
-// y = A x for a dense complex128 row-major matrix (n x n) and vectors x, y (complex128).
-hipError_t launch_zgemv(const void* A, long n, const void* x, void* y, hipStream_t s);
-// y = A x for a planar (re, im) matrix with row stride ld; x, y interleaved complex, n rows.
-hipError_t launch_zgemv_planar(const double* ar, const double* ai, long n, long ld, const void* x,
-                               void* y, hipStream_t s);
+// Lanczos on up to kLanczosOps planar Hermitian operators at once (row stride ld).
+// State of operator z at state + z * stride (doubles): 5 vectors of n complex
+// numbers, ksteps alphas, ksteps betas, and the number of alphas (0 until known);
+// the start vector is vector 2. Launch j = 0 .. ksteps ends step j - 1 (its alpha
+// and beta) and forms A q of step j.
+constexpr int kLanczosOps = 5;
+struct LanczosBatch {
+  const double* re[kLanczosOps];
+  const double* im[kLanczosOps];
+  long n, ld, stride;
+  double* state;
+  int count;
+};
+inline long lanczos_state(long n, int ksteps) { return 10 * n + 2 * (long)ksteps + 2; }
+hipError_t launch_lanczos_step(const LanczosBatch& b, int j, int ksteps, hipStream_t s);
 
 // out = sum_j w_j M_j over planar matrices of `total` elements each (real weights).
 constexpr int kMaxSumTerms = 16;

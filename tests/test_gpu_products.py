@@ -160,3 +160,79 @@ def test_products_with_shared_reduction(fl, n, ncols):
     print("[case] build", eu, "block", ex, flush=True)
     # truncation 1e-12 a step beside rounding
     assert eu < M * 1e-12 + 1e-13 and ex < M * 1e-12 + 1e-13
+
+
+# the cover's Lanczos on the device: one, four and sixteen elements per thread
+# (up to 256, 1024 and 4096 states) and vectors in memory beyond; fewer states
+# than steps; one row per workgroup and blocks of four. With a zero drive the
+# cover is H0's Ritz hull widened by 1 % of its spread, and 200 steps leave an
+# extreme Ritz value less than 1 % of the spread inside the spectrum.
+@pytest.mark.parametrize("n", [1, 2, 7, 200, 256, 257, 515, 1024, 1025, 4096, 4100])
+def test_cover_of_a_known_spectrum(fl, n):
+    print("[case] cover", n, flush=True)
+    rng = np.random.default_rng(n)
+    lam = np.sort(rng.uniform(-3.0, 5.0, n))
+    # Householder reflection of diag(lam): dense, spectrum known
+    v = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    v /= np.linalg.norm(v)
+    lv = lam * v
+    H0 = np.diag(lam).astype(complex) - 2.0 * np.outer(v, lv.conj()) - 2.0 * np.outer(lv, v.conj()) \
+        + 4.0 * np.real(np.vdot(v, lv)) * np.outer(v, v.conj())
+    H0 = 0.5 * (H0 + H0.conj().T)
+    Hm = np.diag(rng.uniform(-1.0, 1.0, n)).astype(complex)
+    ctx = fl.FloquetContext(h0=H0, hmod=Hm, T=0.1, M=1, f_nodes=np.zeros((1, 2)))
+    rep = ctx.report
+    w = lam[-1] - lam[0]
+    print("[case] interval", rep["e_min"], rep["e_max"], "spectrum", lam[0], lam[-1], flush=True)
+    slack = 1e-7 if w == 0.0 else 1e-12 * w
+    assert lam[0] - 0.01 * w - slack <= rep["e_min"] <= lam[0] + slack
+    assert lam[-1] - slack <= rep["e_max"] <= lam[-1] + 0.01 * w + slack
+    # the same interval given by hand passes its check, one that cuts the spectrum fails
+    kw = dict(h0=H0, hmod=Hm, T=0.1, M=1, f_nodes=np.zeros((1, 2)))
+    fl.FloquetContext(e_min=rep["e_min"], e_max=rep["e_max"], **kw)
+    if w > 0.0:
+        from paper_1508_07621_amd._abi import FQ_ERR_SPECTRUM, FloquetError
+        with pytest.raises(FloquetError) as e:
+            fl.FloquetContext(e_min=lam[0] - 0.01 * w, e_max=lam[0] + 0.5 * w, **kw)
+        assert e.value.status == FQ_ERR_SPECTRUM
+
+
+# which precision a mixed context's calls run in, on both sides of every rule:
+# FP64 up to 512 padded states and for few states, else the context's own
+# products; FP32 also runs builds in FP64. Errors: truncation 1e-12 a step for
+# FP64 runs, the library's bar of 1e-6 for the others.
+@pytest.mark.parametrize("precision,n,ncols,f64", [
+    ("bf16x3", 64, 0, True), ("bf16x3", 512, 0, True), ("bf16x3", 512, 200, True),
+    ("bf16x3", 513, 0, False), ("bf16x3", 513, 65, False), ("bf16x3", 1100, 48, True),
+    ("bf16x3", 1100, 64, False), ("bf16x3", 2000, 32, True), ("bf16x3", 2000, 33, False),
+    ("fp32", 513, 0, True), ("fp32", 1100, 0, True), ("fp32", 1100, 1000, True),
+    ("fp32", 1100, 192, True), ("fp32", 1100, 257, False), ("fp32", 2000, 128, True)])
+def test_mixed_context_runs_in_fp64_where_faster(fl, precision, n, ncols, f64):
+    print("[case] route", precision, n, ncols, flush=True)
+    rng = np.random.default_rng(n + ncols)
+    H0, V = gue(n, rng), gue(n, rng)
+    T, M = 0.4, 2
+    f = np.cos(fl.node_times(T, M))
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f, precision=precision)
+    cols = np.arange(min(n, ncols)) if ncols else np.array([0, n // 2, n - 1])
+    if ncols:
+        X = ctx.propagate(np.eye(n, ncols, dtype=complex)).cpu().numpy()
+    else:
+        X = ctx.build_ut().cpu().numpy()[:, cols]
+        rep = ctx.last_report
+        assert all(t == 0 for t in rep["term_format"][:rep["L"]]) == f64
+        assert (rep["mixed_err_est"] == 0.0) == f64
+    a, b = orc.magnus4_weights(f, T / M)
+    K = orc.commutator(H0, V)
+    Y = np.eye(n, dtype=complex)[:, cols]
+    for k in range(M):
+        w, Q = np.linalg.eigh(H0 + a[k] * V + b[k] * K)
+        Y = Q @ (np.exp(-1j * (T / M) * w)[:, None] * (Q.conj().T @ Y))
+    err = orc.column_error(X, Y)
+    print("[case] e_col", err, flush=True)
+    if f64:
+        assert err < M * 1e-12 + 1e-13
+    else:
+        assert err < 1e-6
+        if precision == "bf16x3":   # not in FP64
+            assert err > 1e-11
