@@ -275,8 +275,12 @@ typedef struct fq_report {
                                           of terms 1 .. min(L, 16) (later terms
                                           are not listed), the schedule of the
                                           drive or, after a build that ran in
-                                          FP64, FQ_TERM_FP64; FQ_FP64 builds
-                                          and unused entries: -1 */
+                                          FP64, FQ_TERM_FP64. After a split-BF16
+                                          build by step polynomials: entry 0 the
+                                          product with X, entries 1 .. those of
+                                          T_2, T_3 .., later terms that of their
+                                          block. FQ_FP64 builds and unused
+                                          entries: -1 */
   double mixed_err_est;           /* FQ_BF16X3 and FQ_FP32: the error estimate
                                      the schedule was chosen for (0 otherwise) */
   int32_t diverged;               /* 1 when the last build's max |(U^dagger U -

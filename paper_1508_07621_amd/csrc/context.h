@@ -12,6 +12,17 @@ struct PolyPlan {
   std::vector<double> gr, gi;
 };
 
+// The same in split BF16 (see choose_mixed_poly): formats of T_l (index l), of the
+// product that completes block j, and of the product with X; E = c0 + the plan's sum.
+struct MixedPoly {
+  PolyPlan plan;
+  std::vector<int> t_fmt, b_fmt;
+  int x_fmt = 0;
+  std::complex<double> c0;
+  double form = 0.0;  // cost of E, in units of a product's matrix instructions
+  double err = 0.0;   // estimate of the error that the formats add to U_T
+};
+
 // ---- the context ---------------------------------------------------------------------------
 struct fq_ctx {
   // system
@@ -69,6 +80,7 @@ struct fq_ctx {
   double* pcr = nullptr;              // mixed builds: a third P buffer (format changes)
   std::vector<int> term_fmt;          // mixed builds: TermFmt of terms 1..L (index 0 unused)
   double mixed_err_est = 0.0;         // the schedule's estimate of the error it adds to U_T
+  MixedPoly mpoly;                    // split-BF16 step polynomial (s = 0: none)
   double* tape = nullptr;             // checkpoints, each 2 planes
   int n_tape = 0;
   // gradient: per segment step X_{k-1}, P_{L-1}, P_L; two stacks; Lambda; d/da, d/db per step

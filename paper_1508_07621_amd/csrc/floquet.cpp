@@ -950,7 +950,7 @@ fq_status heff_f64(fq_ctx* c, int t, int batch, int len0, int rem, double* out) 
   return FQ_OK;
 }
 
-fq_status dense_heff(fq_ctx* c, int k) {
+fq_status dense_heff(fq_ctx* c, int k, bool f64 = true) {  // mixed: FP64 planes too
   FQ_MARK(c, FQ_K_HEFF);
   if (c->precision == FQ_FP64) return heff_f64(c, k, 1, 0, 0, c->htr);
   if (c->scheme == FQ_MAGNUS6) FQ_TRY(magnus6_sum(c, k, false, c->kr, c->ki));  // K slot
@@ -963,8 +963,8 @@ fq_status dense_heff(fq_ctx* c, int k) {
     h0i = c->pai;
   }
   FQ_HIP(c, fq::launch_heff_mixed(h0r, h0i, c->vr, c->vi, c->kr, c->ki, c->a[k],
-                                  c->b[k], c->beta, c->dE, c->n, c->np, c->htr, c->hti, c->htx,
-                                  c->precision, c->stream));
+                                  c->b[k], c->beta, c->dE, c->n, c->np, f64 ? c->htr : nullptr,
+                                  c->hti, c->htx, c->precision, c->stream));
   return FQ_OK;
 }
 
@@ -1319,6 +1319,8 @@ double term_error(int tf, long nk) {
   }
 }
 
+void choose_mixed_poly(fq_ctx* c, double tol);
+
 // Formats of terms 1..L of a mixed build: the caller's, or the cheapest
 // schedule found as follows. Random rounding errors of the terms add in
 // quadrature over terms and steps, so the estimate for U_T is
@@ -1378,6 +1380,203 @@ void choose_schedule(fq_ctx* c) {
     }
   }
   c->mixed_err_est = total();
+  c->mpoly = MixedPoly();
+  if (nf == 0 && !f32) choose_mixed_poly(c, tol);
+}
+
+// ---- split-BF16 steps as matrix polynomials ------------------------------------------------------
+//
+// The step polynomials of the FP64 path in k-blocked BF16X3 matrices: T_2 .. T_s
+// (Hermitian, tiles on and above the diagonal) and the blocks in the formats that
+// their weight in the sum allows, then X <- c_0 X + F X with F = E - c_0, whose
+// product carries the weight |c_1| of the first term and its format. Term by term a
+// step of L = 8 takes one product in FP64-sum (24 matrix instructions per tile and
+// k-block), two in two-piece (12) and five in one-piece format (4) and passes the
+// FP64 sum eight times; its polynomial with s = 4 takes the first one, half of two
+// two-piece and of a one-piece product, one one-piece product, and a pass over four
+// matrices. A step of L = 8, before and after: N = 1030 0.37 -> 0.25 ms, N = 2500 2.76
+// -> 1.75 ms; L = 7 at N = 4096 7.7 -> 5.9 ms (5.3 ms of it MFMA-bound products: the
+// one with X 2.2, four others 0.7 on average); errors as before (e_col 1.1 .. 3.6e-7).
+
+// Units of a product: matrix instructions per tile and k-block, and its pass over
+// the operands.
+double product_units(int tf) {
+  return (tf == fq::TF_ACC ? 24 : tf == fq::TF_X3 ? 18 : tf == fq::TF_X2 ? 12 : 4) + 5.0;
+}
+
+// Formats and cost of the polynomial with blocks of length s: each product takes the
+// cheapest format whose own contribution to the error of the build is within an
+// allowance that shrinks until the root sum of squares meets the target, as for the
+// terms. false if a T needs more than three pieces or a block more than two.
+bool mixed_poly_formats(const fq_ctx* c, int s, double tol, MixedPoly* out) {
+  MixedPoly m;
+  m.plan = poly_blocks(c, s);
+  const int J = m.plan.J;
+  auto G = [&](int j, int l) {
+    const size_t i = (size_t)j * (s + 1) + l;
+    return std::hypot(m.plan.gr[i], m.plan.gi[i]);
+  };
+  // T_2 is kept as S = T_2 + 1 (see mixed_poly_step): its coefficients' numbers go to
+  // block 0 of T_0. A number g in a block j >= 1 would pass a product as g times the
+  // identity, whose rounding is the same in every step and adds up: g T_s goes to
+  // block j - 1, -g to block j - 2 instead. The number in block 0 multiplies X in FP64.
+  auto move = [&](std::vector<double>& g) {
+    for (int j = J - 1; j >= 0; --j) {
+      double& v = g[(size_t)j * (s + 1)];
+      v -= g[(size_t)j * (s + 1) + 2];
+      if (j == 0) break;
+      g[(size_t)(j - 1) * (s + 1) + s] += (j > 1 ? 2.0 : 1.0) * v;
+      if (j > 1) g[(size_t)(j - 2) * (s + 1)] -= v;
+      v = 0.0;
+    }
+  };
+  move(m.plan.gr);
+  move(m.plan.gi);
+  m.c0 = {m.plan.gr[0], m.plan.gi[0]};
+  m.plan.gr[0] = m.plan.gi[0] = 0.0;
+  // norms of the blocks and of Clenshaw's partial sums; E's sensitivity to each T_l
+  std::vector<double> q(J, 0.0), w(J + 1, 0.0), d(s + 1, 0.0);
+  for (int j = 0; j < J; ++j)
+    for (int l = 0; l <= s; ++l) {
+      q[j] += G(j, l);
+      if (l > 0) d[l] += G(j, l);
+    }
+  for (int j = 0; j < J; ++j)
+    for (int i = j; i < J; ++i) w[j] += (i - j + 1) * q[i];
+  for (int j = 1; j < J; ++j) d[s] += (double)j * j * q[j];
+  for (int l = s; l >= 2; --l) {  // (S enters T_3 and T_4 once more, T_1 enters T_3)
+    d[l / 2] += 2.0 * d[l];
+    d[(l + 1) / 2] += 2.0 * d[l];
+    if (l == 3) d[1] += 3.0 * d[l];
+    if (l == 4) d[2] += 4.0 * d[l];
+  }
+  const double sm = std::sqrt((double)c->M);
+  const long nk = c->np / 16;
+  m.t_fmt.assign(s + 1, fq::TF_X3);
+  m.b_fmt.assign(J, fq::TF_X3);
+  double allowance = tol;
+  for (int pass = 0; pass < 64; ++pass, allowance *= 0.7) {
+    double e2 = 0.0;
+    bool ok = true;
+    auto pick = [&](double weight, std::initializer_list<int> formats) {
+      for (int f : formats) {
+        const double e = weight * sm * term_error(f, nk);
+        if (e > allowance) continue;
+        e2 += e * e;
+        return f;
+      }
+      ok = false;
+      return (int)fq::TF_X1;
+    };
+    for (int l = 2; l <= s; ++l) m.t_fmt[l] = pick(d[l], {fq::TF_X1, fq::TF_X2, fq::TF_X3});
+    for (int j = 0; j + 1 < J; ++j)
+      m.b_fmt[j] = pick((j ? 2.0 : 1.0) * w[j + 1], {fq::TF_X1, fq::TF_X2});
+    m.x_fmt = pick(w[0], {fq::TF_X1, fq::TF_X2, fq::TF_X3, fq::TF_ACC});
+    if (!ok) return false;
+    m.err = std::sqrt(e2);
+    if (m.err <= tol) break;
+  }
+  if (m.err > tol) return false;
+  m.form = 2.0;  // the combination
+  for (int l = 2; l <= s; ++l)
+    m.form += 0.65 * product_units(m.t_fmt[l]);
+  for (int j = 0; j + 1 < J; ++j) m.form += product_units(m.b_fmt[j]);
+  *out = m;
+  return true;
+}
+
+// The cheapest polynomial for the present drive (empty when none meets the target
+// or the caller fixed the formats).
+void choose_mixed_poly(fq_ctx* c, double tol) {
+  c->mpoly = MixedPoly();
+  for (int s = 2; s <= std::min(4, c->L); ++s) {
+    const int J = (c->L + s - 1) / s;
+    if (J > 4 || (s == 2 && J > 1)) continue;  // (a block needs T_s itself)
+    MixedPoly m;
+    if (!mixed_poly_formats(c, s, tol, &m)) continue;
+    if (c->mpoly.plan.s == 0 || m.form + product_units(m.x_fmt) <
+                                    c->mpoly.form + product_units(c->mpoly.x_fmt))
+      c->mpoly = m;
+  }
+}
+
+// Whether steps on mrows rows take it: its products of matrices cost the same for
+// any number of rows, the terms do not.
+bool takes_mixed_poly(const fq_ctx* c, long mrows) {
+  if (c->precision != FQ_BF16X3 || c->mpoly.plan.s == 0) return false;
+  const double apply = (double)mrows / (double)c->np;
+  double terms = 0.0;
+  for (int l = 1; l <= c->L; ++l)
+    terms += c->term_fmt[l] == fq::TF_F64 ? 60.0 : product_units(c->term_fmt[l]);
+  return c->mpoly.form + product_units(c->mpoly.x_fmt) * apply < terms * apply;
+}
+
+fq_status mixed_poly_step(fq_ctx* c, int k, int mrows) {
+  const MixedPoly& m = c->mpoly;
+  const int s = m.plan.s, J = m.plan.J, np = (int)c->np, n = (int)c->n;
+  const long plane = c->np * c->np;
+  // T_1, S = T_2 + 1, T_3, T_4; the blocks take the places of those no longer needed
+  // (T_s stays). T_2 itself is nearly a multiple of the identity where the spectrum
+  // fills little of the interval: the rounding of its diagonal would be the same in
+  // every column and step.
+  double* t[5] = {static_cast<double*>(c->htx), c->par, c->pbr, c->pcr, c->htr};
+  double* w[4];
+  for (int j = 0, at = 0; j < J; ++j, ++at) {
+    if (J > 1 && at == s - 1) ++at;
+    w[j] = t[at];
+  }
+  FQ_TRY(dense_heff(c, k, false));
+  for (int l = 2; l <= s; ++l) {
+    FQ_MARK(c, FQ_K_POLY);
+    // S = 2 T_1^2, T_3 = 2 T_1 S - 3 T_1, T_4 = 2 S^2 - 4 S + 1. The diagonal of S, a
+    // sum of squares, would collect what dropped piece pairs and FP32 sums lose on one
+    // side, the same in every step: it is the rows' norms in FP64 (1030 states, 100
+    // steps: e_col 8.2e-7 and 4.2e-7 with two and three pieces without them).
+    const double* norms = l == 2 ? c->yr : nullptr;
+    if (norms) FQ_HIP(c, fq::launch_bf3_norms(t[0], np, c->yr, c->stream));
+    FQ_HIP(c, fq::launch_bf3_poly(true, m.t_fmt[l], t[l / 2 - 1], t[(l + 1) / 2 - 1], 2.0,
+                                  l == 2 ? nullptr : (l == 3 ? t[0] : t[1]), l == 3 ? 3.0 : 4.0,
+                                  l == 4 ? 1.0 : 0.0, norms, false, t[l - 1], n, np, c->stream));
+  }
+  fq::PolyCombine q{};
+  q.s = s;
+  q.J = J;
+  for (int l = 0; l < s; ++l) q.t[l] = t[l];
+  for (int j = 0; j < J; ++j) {
+    q.q[j] = w[j];
+    for (int l = 0; l <= s; ++l) {
+      q.gr[j][l] = m.plan.gr[(size_t)j * (s + 1) + l];
+      q.gi[j][l] = m.plan.gi[(size_t)j * (s + 1) + l];
+    }
+  }
+  FQ_MARK(c, FQ_K_HEFF);
+  FQ_HIP(c, fq::launch_poly_combine_bf3(q, n, np, c->stream));
+  for (int j = J - 2; j >= 0; --j) {
+    FQ_MARK(c, FQ_K_POLY);
+    FQ_HIP(c, fq::launch_bf3_poly(false, m.b_fmt[j], w[j + 1], t[s - 1], j >= 1 ? 2.0 : 1.0,
+                                  j + 2 < J ? w[j + 2] : nullptr, 1.0, 0.0, nullptr, true, w[j], n,
+                                  np, c->stream));
+  }
+  // X <- c_0 X + F X (F = w[0] in T_1's place, a BF16X3 copy of X in T_2's)
+  FQ_MARK(c, FQ_K_CONVERT);
+  FQ_HIP(c, fq::launch_to_product(c->xr, c->xi, t[1], fq::FMT_BF16X3, mrows, np, c->stream));
+  FQ_MARK(c, FQ_K_TERM_FP64 + m.x_fmt);
+  fq::ChebTermX x{};
+  x.kind = fq::CHEB_FIRST_LAST;
+  x.a_fmt = fq::FMT_BF16X3;
+  x.p_fmt = x.o_fmt = fq::FMT_F64;
+  x.plane = plane;
+  x.a = t[1];
+  x.b = w[0];
+  x.p = x.o = c->xr;
+  x.y_re = c->yr;
+  x.y_im = c->yi;
+  x.c0r = m.c0.real();
+  x.c0i = m.c0.imag();
+  x.cr = 1.0;
+  x.phr = 1.0;
+  FQ_HIP(c, fq::launch_cheb_bf16(x, m.x_fmt, mrows, np, c->stream));
+  return FQ_OK;
 }
 
 // One mixed-precision step on the state-major block in the X planes:
@@ -1579,6 +1778,7 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
     }
     poly = poly_plan(c, 4 + extra_mats(c), (double)mrows / (double)c->np);
   }
+  const bool mixed_poly = takes_mixed_poly(c, mrows);
   if (record_tape && k0 == 0)
     FQ_HIP(c, hipMemcpyAsync(c->tape, c->xr, plane2 / 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   if (record_tape && k0 == 0)
@@ -1587,6 +1787,8 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
   for (int k = k0; k < k1; ++k) {
     if (poly.s) {
       FQ_TRY(dense_poly_step(c, poly, k, mrows));
+    } else if (mixed_poly) {
+      FQ_TRY(mixed_poly_step(c, k, mrows));
     } else {
       FQ_TRY(dense_heff(c, k));
       FQ_TRY(dense_cheb_step(c, mrows));
@@ -2782,9 +2984,9 @@ fq_status apply_drive(fq_ctx* c, const double* f_nodes) {
     c->coef[2 * l] = (q == 0) ? w : (q == 2 ? -w : 0.0);
     c->coef[2 * l + 1] = (q == 1) ? -w : (q == 3 ? w : 0.0);
   }
-  if (c->precision != FQ_FP64 && c->layout == FQ_DENSE) choose_schedule(c);
   c->phr = std::cos(c->beta * c->h);
   c->phi = -std::sin(c->beta * c->h);
+  if (c->precision != FQ_FP64 && c->layout == FQ_DENSE) choose_schedule(c);
   if (c->layout == FQ_DENSE) FQ_TRY(upload_heff_weights(c));
   if (c->d_tab) FQ_HIP(c, fq::launch_tridiag_table(tridiag_job(c), c->M, c->d_tab, c->stream));
   if (copy_sync(c->stream, c->d_coef, c->coef.data(), c->coef.size() * sizeof(double),
@@ -3065,6 +3267,13 @@ fq_status floquet_build_UT(fq_ctx* c, void* U_out, fq_report* rep) {
   if (c->layout == FQ_DENSE && c->precision != FQ_FP64 && runs_f64(c, c->np)) {  // what ran
     for (int l = 0; l < std::min(c->L, FQ_TERM_SLOTS); ++l) c->last.term_format[l] = FQ_TERM_FP64;
     c->last.mixed_err_est = 0.0;
+  } else if (c->layout == FQ_DENSE && takes_mixed_poly(c, c->np)) {
+    const MixedPoly& m = c->mpoly;
+    for (int l = 0; l < std::min(c->L, FQ_TERM_SLOTS); ++l)
+      c->last.term_format[l] = l == 0              ? m.x_fmt
+                               : l < m.plan.s      ? m.t_fmt[l + 1]
+                                                   : m.b_fmt[l / m.plan.s - 1];
+    c->last.mixed_err_est = m.err;
   }
   if (rep) *rep = c->last;
   return FQ_OK;

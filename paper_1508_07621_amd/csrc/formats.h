@@ -35,6 +35,16 @@ __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, i
   }
 }
 
+// Tile (tm, tn), tm <= tn, number t of the upper triangle of a tiles x tiles
+// grid, column by column.
+__device__ __forceinline__ void tri_coords(int t, int& tm, int& tn) {
+  int c = (int)((__builtin_sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while ((c + 1) * (c + 2) / 2 <= t) ++c;
+  while (c * (c + 1) / 2 > t) --c;
+  tn = c;
+  tm = t - c * (c + 1) / 2;
+}
+
 // 128 x 128 output tiles only when they make at least 256 workgroups (one per
 // CU); smaller products take 64 x 64 tiles so that every CU has work.
 constexpr long kBigTileElems = 256L * 128 * 128;

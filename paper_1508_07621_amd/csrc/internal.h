@@ -221,6 +221,18 @@ struct PolyCombine {
 };
 hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, int batch,
                                hipStream_t s);
+// On k-blocked BF16X3 matrices, in term format tf (TF_X2, TF_X1, herm also TF_X3) and
+// with a Hermitian B: o = [o +] f A B - fs sub (optional) + one on the diagonal; herm: the result is
+// Hermitian. For the combination t and q are BF16X3 matrices, at most 4 q's.
+hipError_t launch_bf3_poly(bool herm, int tf, const void* a, const void* b, double f,
+                           const void* sub, double fs, double one, const double* norms, bool add,
+                           void* o, int n, int np, hipStream_t s);
+// Squared row norms of such a matrix in kNormParts partial sums (part p at out + p np),
+// for launch_bf3_poly's norms (null: none): its result then has f times the norm on the
+// diagonal in place of the product's.
+constexpr int kNormParts = 16;
+hipError_t launch_bf3_norms(const void* a, int np, double* out, hipStream_t s);
+hipError_t launch_poly_combine_bf3(const PolyCombine& p, long n, long np, hipStream_t s);
 // out = [out +] f A B - sub (sub optional, with out's stride); b_herm: B is Hermitian.
 hipError_t launch_poly_block(const double* a, long a_bs, const double* b, long b_bs, bool b_herm,
                              double f, const double* sub, bool add, double* out, long o_bs, int np,

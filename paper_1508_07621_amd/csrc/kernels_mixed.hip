@@ -16,6 +16,7 @@
 // and the last one applies the step phase in FP64.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -282,7 +283,19 @@ struct Bf3Args {
   int np;
   int tiles_m, tiles_n;
   double c0r, c0i, cr, ci, phr, phi;
+  // step polynomials (BF3_T, BF3_BLOCK): o = [o +] f A B - fs sub + one on the n x n
+  // block; all k-blocked BF16X3. norms (the square of one matrix): f times the rows'
+  // squared norms, in kNormParts partial sums, are the diagonal of f A B.
+  const u16* sub;
+  const double* norms;
+  double f, fs, one;
+  int add, n;
 };
+
+// Kinds beside the CHEB_* ones. Both take a Hermitian B as (A B)(m, c) = sum_k
+// A(m, k) conj(B(c, k)); the result of BF3_T is Hermitian and its grid holds the
+// tiles on and above the diagonal.
+constexpr int BF3_T = 4, BF3_BLOCK = 5;
 
 // The leading `npc` pieces of x (fp32): hi, or hi and mid, or all three.
 template <int NPC>
@@ -456,6 +469,93 @@ __device__ __forceinline__ void bf3_tile_epilogue(const Bf3Args& g, const float*
   }
 }
 
+// Epilogue of the step polynomials' products, from the same LDS order. TR: the
+// mirror image of the tile, whose row is a tile column (elements conjugated).
+template <int BM, int BN, int NT, bool TR>
+__device__ __forceinline__ void bf3_poly_epilogue(const Bf3Args& g, const float* cre,
+                                                  const float* cim, int m0, int n0, int tid) {
+  constexpr int NS = BF3_PLANES;
+  constexpr int ROWS = TR ? BN : BM;  // rows of the image
+  const long np = g.np, plane = g.plane;
+  const long mb = TR ? n0 : m0, nb = TR ? m0 : n0;
+  auto decode = [](const u32x4* w, int e, double& re, double& im) {
+    float s[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      const uint32_t word = w[k][e >> 1];
+      s[k] = bf16_val((u16)((e & 1) ? (word >> 16) : (word & 0xffffu)));
+    }
+    re = (double)(s[0] + s[1] + s[2]);
+    im = (double)(s[3] + s[4] + s[5]);
+  };
+#pragma unroll 2
+  for (int q = tid; q < BM * BN / 8; q += NT) {
+    const int kbl = q / (2 * ROWS), rem = q % (2 * ROWS);
+    const int row = rem >> 1, slot = rem & 1;
+    const int c = kbl * 16 + 8 * (slot ^ ((row >> 3) & 1));  // first of 8 columns
+    const long m = mb + row, nc = nb + c;
+    const long chunk = ((nb / 16 + kbl) * np + m) * 16 + 8 * slot;
+    u32x4 ow[NS], sw[NS];
+    u16* o = static_cast<u16*>(g.o) + chunk;
+    if (g.add) {
+#pragma unroll
+      for (int k = 0; k < NS; ++k) ow[k] = *reinterpret_cast<const u32x4*>(o + k * plane);
+    }
+    if (g.sub) {
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+        sw[k] = *reinterpret_cast<const u32x4*>(g.sub + chunk + k * plane);
+    }
+    float ar[8], ai[8];
+    if constexpr (TR) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {  // tile element (c + e, row)
+        const int t = ((row >> 4) * BM + c + e) * 16 + 8 * (((row >> 3) ^ (c >> 3)) & 1) + (row & 7);
+        ar[e] = cre[t];
+        ai[e] = -cim[t];
+      }
+    } else {
+      *reinterpret_cast<f4*>(ar) = *reinterpret_cast<const f4*>(cre + q * 8);
+      *reinterpret_cast<f4*>(ar + 4) = *reinterpret_cast<const f4*>(cre + q * 8 + 4);
+      *reinterpret_cast<f4*>(ai) = *reinterpret_cast<const f4*>(cim + q * 8);
+      *reinterpret_cast<f4*>(ai + 4) = *reinterpret_cast<const f4*>(cim + q * 8 + 4);
+    }
+    u32x4 w[NS];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      double re = g.f * (double)ar[e], im = g.f * (double)ai[e], xr, xi;
+      if (g.norms && m == nc + e) {
+        re = im = 0.0;
+        for (int u = 0; u < kNormParts; ++u) re += g.norms[u * np + m];
+        re *= g.f;
+      }
+      if (g.add) {
+        decode(ow, e, xr, xi);
+        re += xr;
+        im += xi;
+      }
+      if (g.sub) {
+        decode(sw, e, xr, xi);
+        re -= g.fs * xr;
+        im -= g.fs * xi;
+      }
+      if (m == nc + e && m < g.n) re += g.one;
+      u16 hs[NS];
+      split3((float)re, hs[0], hs[1], hs[2]);
+      split3((float)im, hs[3], hs[4], hs[5]);
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        if (e & 1)
+          w[k][e >> 1] |= (uint32_t)hs[k] << 16;
+        else
+          w[k][e >> 1] = hs[k];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) *reinterpret_cast<u32x4*>(o + k * plane) = w[k];
+  }
+}
+
 // Split-BF16 product on 32x32x16 matrix cores with NPC = 1, 2 or 3 pieces per
 // operand: the piece pairs of weight at least 2^-8 (NPC - 1) of the leading one
 // ((hh); (hh, hm, mh); (hh, hm, mh, hl, mm, lh)), so the product carries about
@@ -476,7 +576,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
   constexpr int EPI = 2 * BM * BN * 4;       // FP32 Re, Im in k-blocked order
   constexpr int SMEM = (2 * STAGE > EPI) ? 2 * STAGE : EPI;
   constexpr bool FIRST = KIND == CHEB_FIRST || KIND == CHEB_FIRST_LAST;
-  constexpr bool TO_X = KIND == CHEB_LAST || KIND == CHEB_FIRST_LAST;  // FP64 X_k out
+  constexpr bool POLY = KIND >= BF3_T;
   static_assert(2 * (BM + BN) == NT, "one 16-byte chunk column of A or B per thread");
   static_assert(FM >= 1 && FN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
   static_assert(NPC >= 1 && NPC <= 3, "pieces");
@@ -485,8 +585,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
   int tm, tn;
-  tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
-  if (tm >= g.tiles_m) return;  // grid padding
+  if constexpr (KIND == BF3_T) {
+    tri_coords(blockIdx.x, tm, tn);
+  } else {
+    tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+    if (tm >= g.tiles_m) return;  // grid padding
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid / WGN, wn = wid % WGN;
@@ -529,7 +633,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
           im += piece(NPC + p);
         }
         u16 hs[NPC];
-        split_n<NPC>(re + im, hs);
+        split_n<NPC>(POLY && !is_a ? re - im : re + im, hs);
 #pragma unroll
         for (int q = 0; q < NPC; ++q) o[q] |= (uint32_t)hs[q] << sh;
       }
@@ -626,12 +730,19 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
         const int col = wn * WTN + j * 32 + (lane & 31);
         const int slot = ((col >> 3) & 1) ^ ((row >> 3) & 1);
         const int f = ((col >> 4) * BM + row) * 16 + 8 * slot + (col & 7);
-        cre[f] = t1[i][j][r] - t2[i][j][r];
-        cim[f] = t3[i][j][r] - t1[i][j][r] - t2[i][j][r];
+        // (conjugated B: T2 = -Ai Bi, T3 = (Ar + Ai)(Br - Bi))
+        const float t2s = POLY ? -t2[i][j][r] : t2[i][j][r];
+        cre[f] = t1[i][j][r] - t2s;
+        cim[f] = t3[i][j][r] - t1[i][j][r] - t2s;
       }
   __syncthreads();
 
-  bf3_tile_epilogue<BM, BN, NT, KIND, P_F64>(g, cre, cim, m0, n0, tid);
+  if constexpr (POLY) {
+    bf3_poly_epilogue<BM, BN, NT, false>(g, cre, cim, m0, n0, tid);
+    if (KIND == BF3_T && tm != tn) bf3_poly_epilogue<BM, BN, NT, true>(g, cre, cim, m0, n0, tid);
+  } else {
+    bf3_tile_epilogue<BM, BN, NT, KIND, P_F64>(g, cre, cim, m0, n0, tid);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -655,6 +766,7 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
   constexpr int EPI = 2 * 128 * 64 * 4;      // FP32 Re, Im of one half, k-blocked order
   constexpr int SMEM = (2 * STAGE > EPI) ? 2 * STAGE : EPI;
   constexpr int NPAIR = NPC == 1 ? 1 : 3;
+  constexpr bool POLY = KIND >= BF3_T;  // B conjugated: cre = Ar Br + Ai Bi, cim = Ai Br - Ar Bi
   constexpr bool FIRST = KIND == CHEB_FIRST || KIND == CHEB_FIRST_LAST;
   static_assert(NPC == 1 || NPC == 2, "pieces (three take the Gauss kernel)");
   static_assert(!FIRST || P_F64, "the first product reads X in FP64");
@@ -664,8 +776,12 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
   int tm, tn;
-  tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
-  if (tm >= g.tiles_m) return;  // grid padding
+  if constexpr (KIND == BF3_T) {
+    tri_coords(blockIdx.x, tm, tn);
+  } else {
+    tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+    if (tm >= g.tiles_m) return;  // grid padding
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid >> 1, wn = wid & 1;
@@ -735,12 +851,12 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
   __syncthreads();
   for (int kb = 0; kb < nk; ++kb) {
     fload(kb & 1, fa, fb);
-    bf8 ma[NPC][FM];  // -Ai pieces: flipped sign bits
+    bf8 ma[NPC][FM];  // -Ai pieces (POLY: -Ar): flipped sign bits
 #pragma unroll
     for (int q = 0; q < NPC; ++q)
 #pragma unroll
       for (int i = 0; i < FM; ++i) {
-        u32x4 w = __builtin_bit_cast(u32x4, fa[NPC + q][i]);
+        u32x4 w = __builtin_bit_cast(u32x4, fa[POLY ? q : NPC + q][i]);
         w ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
         ma[q][i] = __builtin_bit_cast(bf8, w);
       }
@@ -754,13 +870,13 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
           cre[i][j] = mfma32_bf16(fa[pa][i], fb[pb][j], cre[i][j]);
-          cim[i][j] = mfma32_bf16(fa[pa][i], fb[NPC + pb][j], cim[i][j]);
+          cim[i][j] = mfma32_bf16(POLY ? ma[pa][i] : fa[pa][i], fb[NPC + pb][j], cim[i][j]);
         }
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          cre[i][j] = mfma32_bf16(ma[pa][i], fb[NPC + pb][j], cre[i][j]);
+          cre[i][j] = mfma32_bf16(POLY ? fa[NPC + pa][i] : ma[pa][i], fb[NPC + pb][j], cre[i][j]);
           cim[i][j] = mfma32_bf16(fa[NPC + pa][i], fb[pb][j], cim[i][j]);
         }
     }
@@ -780,8 +896,8 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
   // with slot = ((col / 8) & 1) ^ ((row / 8) & 1); real parts, then imaginary.
   float* ere = reinterpret_cast<float*>(smem);
   float* eim = ere + 2 * 128 * 32;  // two groups of 128 x 32 each
-#pragma unroll
-  for (int h = 0; h < FN; ++h) {
+  auto half = [&](auto hc) {  // (unrolled by hand: h indexes registers)
+    constexpr int h = decltype(hc)::value;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -795,11 +911,20 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
       }
     __syncthreads();
 #pragma unroll
-    for (int sgrp = 0; sgrp < 2; ++sgrp)
-      bf3_tile_epilogue<128, 32, NT, KIND, P_F64, 1>(
-          g, ere + sgrp * 4096, eim + sgrp * 4096, m0, n0 + 64 * sgrp + 32 * h, tid);
+    for (int sgrp = 0; sgrp < 2; ++sgrp) {
+      const float *gre = ere + sgrp * 4096, *gim = eim + sgrp * 4096;
+      const int nh = n0 + 64 * sgrp + 32 * h;
+      if constexpr (POLY) {
+        bf3_poly_epilogue<128, 32, NT, false>(g, gre, gim, m0, nh, tid);
+        if (KIND == BF3_T && tm != tn) bf3_poly_epilogue<128, 32, NT, true>(g, gre, gim, m0, nh, tid);
+      } else {
+        bf3_tile_epilogue<128, 32, NT, KIND, P_F64, 1>(g, gre, gim, m0, nh, tid);
+      }
+    }
     __syncthreads();
-  }
+  };
+  half(std::integral_constant<int, 0>{});
+  half(std::integral_constant<int, 1>{});
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -815,6 +940,7 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
 template <int KIND, bool P_F64, int NPC>
 __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
   constexpr int BM = 64, BN = 64, NT = 256, D = 4;
+  constexpr bool POLY = KIND >= BF3_T;  // B conjugated, as above
   constexpr int NL = 2 * NPC;                // stored planes read per operand
   constexpr int SA = BM * 32, SB = BN * 32;  // bytes per plane and k-block
   constexpr int STAGE = NL * (SA + SB);
@@ -827,8 +953,12 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
   int tm, tn;
-  tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
-  if (tm >= g.tiles_m) return;  // grid padding
+  if constexpr (KIND == BF3_T) {
+    tri_coords(blockIdx.x, tm, tn);
+  } else {
+    tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+    if (tm >= g.tiles_m) return;  // grid padding
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid >> 1, wn = wid & 1;
@@ -879,8 +1009,8 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
         fb[q] = *reinterpret_cast<const bf8*>(sb + q * SB + boff);
       }
 #pragma unroll
-      for (int q = 0; q < NPC; ++q) {  // -Ai pieces: flipped sign bits
-        u32x4 w = __builtin_bit_cast(u32x4, fa[NPC + q]);
+      for (int q = 0; q < NPC; ++q) {  // -Ai pieces (POLY: -Ar): flipped sign bits
+        u32x4 w = __builtin_bit_cast(u32x4, fa[POLY ? q : NPC + q]);
         w ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
         ma[q] = __builtin_bit_cast(bf8, w);
       }
@@ -891,8 +1021,8 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
         for (int i = w; i >= 0; --i) {
           const int j = w - i;
           cre = mfma32_bf16(fa[i], fb[j], cre);
-          cim = mfma32_bf16(fa[i], fb[NPC + j], cim);
-          cre = mfma32_bf16(ma[i], fb[NPC + j], cre);
+          cim = mfma32_bf16(POLY ? ma[i] : fa[i], fb[NPC + j], cim);
+          cre = mfma32_bf16(POLY ? fa[NPC + i] : ma[i], fb[NPC + j], cre);
           cim = mfma32_bf16(fa[NPC + i], fb[j], cim);
         }
       // the next k-block into the other buffer (last read before the previous
@@ -915,7 +1045,12 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
     eim[f] = cim[r];
   }
   __syncthreads();
-  bf3_tile_epilogue<BM, BN, NT, KIND, P_F64>(g, ere, eim, m0, n0, tid);
+  if constexpr (POLY) {
+    bf3_poly_epilogue<BM, BN, NT, false>(g, ere, eim, m0, n0, tid);
+    if (KIND == BF3_T && tm != tn) bf3_poly_epilogue<BM, BN, NT, true>(g, ere, eim, m0, n0, tid);
+  } else {
+    bf3_tile_epilogue<BM, BN, NT, KIND, P_F64>(g, ere, eim, m0, n0, tid);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1100,6 +1235,11 @@ template <int KIND, bool P_F64, int NPC>
 hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
   Bf3Args g = g0;
   const int np = g.np;
+  auto grid = [&]() {
+    const int t = g.tiles_n;
+    return dim3(KIND == BF3_T ? t * (t + 1) / 2 : grid_rows(g.tiles_m) * t);
+  };
+  if (KIND == BF3_T && mrows != np) return hipErrorInvalidValue;
   if (mrows % 128 == 0 && np % 128 == 0 && (long)mrows * np >= kBigTileElems) {
     g.tiles_m = mrows / 128;
     g.tiles_n = np / 128;
@@ -1107,16 +1247,14 @@ hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
     // workgroups per CU; three pieces: the Gauss form on 64 x 32 wave tiles
     // (measured faster there: the four-product form needs 96 KiB of LDS)
     if constexpr (NPC <= 2)
-      hipLaunchKernelGGL((cheb_x4_kernel<KIND, P_F64, NPC>),
-                         dim3(grid_rows(g.tiles_m) * g.tiles_n), dim3(256), 0, s, g);
+      hipLaunchKernelGGL((cheb_x4_kernel<KIND, P_F64, NPC>), grid(), dim3(256), 0, s, g);
     else
-      hipLaunchKernelGGL((cheb_bf3_kernel<128, 128, 2, 4, KIND, P_F64, NPC>),
-                         dim3(grid_rows(g.tiles_m) * g.tiles_n), dim3(512), 0, s, g);
+      hipLaunchKernelGGL((cheb_bf3_kernel<128, 128, 2, 4, KIND, P_F64, NPC>), grid(), dim3(512), 0,
+                         s, g);
   } else if (mrows % 64 == 0 && np % 64 == 0) {
     g.tiles_m = mrows / 64;
     g.tiles_n = np / 64;
-    hipLaunchKernelGGL((cheb_s4_kernel<KIND, P_F64, NPC>), dim3(grid_rows(g.tiles_m) * g.tiles_n),
-                       dim3(256), 0, s, g);
+    hipLaunchKernelGGL((cheb_s4_kernel<KIND, P_F64, NPC>), grid(), dim3(256), 0, s, g);
   } else {
     return hipErrorInvalidValue;
   }
@@ -1277,12 +1415,114 @@ __global__ void heff_bf3_kernel(const double* __restrict__ h0r, const double* __
 #pragma unroll
         for (int p = 0; p < BF3_PLANES; ++p) wd[p] |= (uint32_t)hs[p] << (16 * e);
       }
-      *reinterpret_cast<d2*>(hr + idx) = re2;
-      *reinterpret_cast<d2*>(hi + idx) = im2;
+      if (hr) {
+        *reinterpret_cast<d2*>(hr + idx) = re2;
+        *reinterpret_cast<d2*>(hi + idx) = im2;
+      }
     }
     u16* o = out + bf3_offset(i, k, np);  // columns k, k + 1: adjacent words
 #pragma unroll
     for (int p = 0; p < BF3_PLANES; ++p) *reinterpret_cast<uint32_t*>(o + p * plane) = wd[p];
+  }
+}
+
+// Squared norms of the rows of a BF16X3 matrix, part blockIdx.y of the columns into
+// out[blockIdx.y * np + row]: 64 rows per workgroup, a thread one 16-byte chunk of
+// every second k-block's row. One read of the matrix.
+__global__ __launch_bounds__(256) void bf3_norms_kernel(const u16* __restrict__ a, long np,
+                                                        double* __restrict__ out) {
+  __shared__ double red[256];
+  const long plane = np * np, nk = np / 16;
+  const int t = threadIdx.x & 127, half = threadIdx.x >> 7;
+  const long lo = blockIdx.y * nk / kNormParts, hi = (blockIdx.y + 1) * nk / kNormParts;
+  double s = 0.0;
+  for (long kb = lo + half; kb < hi; kb += 2) {
+    const u16* p = a + (kb * np + 64L * blockIdx.x) * 16 + t * 8;
+    u32x4 w[BF3_PLANES];
+#pragma unroll
+    for (int k = 0; k < BF3_PLANES; ++k) w[k] = *reinterpret_cast<const u32x4*>(p + k * plane);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float v[BF3_PLANES];
+#pragma unroll
+      for (int k = 0; k < BF3_PLANES; ++k) {
+        const uint32_t word = w[k][e >> 1];
+        v[k] = bf16_val((u16)((e & 1) ? (word >> 16) : (word & 0xffffu)));
+      }
+      const double re = (double)(v[0] + v[1] + v[2]), im = (double)(v[3] + v[4] + v[5]);
+      s += re * re + im * im;
+    }
+  }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  const int r = threadIdx.x;  // row r: chunks 2 r and 2 r + 1 of both halves
+  if (r < 64)
+    out[blockIdx.y * np + 64L * blockIdx.x + r] =
+        red[2 * r] + red[2 * r + 1] + red[128 + 2 * r] + red[128 + 2 * r + 1];
+}
+
+// Q_q = sum_{l = 0 .. s} g_ql T_l for q < J <= NJ on BF16X3 matrices (T_0 = 1 on the
+// n x n block), one 16-byte chunk (8 columns of a row) of every plane per thread; a
+// Q may take the place of a T. Bound by HBM: each T read and each Q written once.
+template <int NJ>
+__global__ __launch_bounds__(256) void poly_combine_bf3_kernel(PolyCombine p, long n, long np) {
+  const long plane = np * np, chunks = plane / 8;
+  for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < chunks;
+       q += (long)gridDim.x * blockDim.x) {
+    const long kb = q / (2 * np), rem = q % (2 * np), row = rem >> 1;
+    const int slot = (int)(rem & 1);
+    const long col = kb * 16 + 8 * (slot ^ ((row >> 3) & 1));
+    double qr[NJ][8], qi[NJ][8];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool one = row == col + e && row < n;
+        qr[j][e] = one ? p.gr[j][0] : 0.0;
+        qi[j][e] = one ? p.gi[j][0] : 0.0;
+      }
+    for (int l = 1; l <= p.s; ++l) {
+      const u16* t = reinterpret_cast<const u16*>(p.t[l - 1]) + q * 8;
+      u32x4 w[BF3_PLANES];
+#pragma unroll
+      for (int k = 0; k < BF3_PLANES; ++k) w[k] = *reinterpret_cast<const u32x4*>(t + k * plane);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float s[BF3_PLANES];
+#pragma unroll
+        for (int k = 0; k < BF3_PLANES; ++k) {
+          const uint32_t word = w[k][e >> 1];
+          s[k] = bf16_val((u16)((e & 1) ? (word >> 16) : (word & 0xffffu)));
+        }
+        const double re = (double)(s[0] + s[1] + s[2]), im = (double)(s[3] + s[4] + s[5]);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          qr[j][e] += p.gr[j][l] * re - p.gi[j][l] * im;
+          qi[j][e] += p.gr[j][l] * im + p.gi[j][l] * re;
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      if (j >= p.J) break;
+      u32x4 w[BF3_PLANES];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        u16 hs[BF3_PLANES];
+        split3((float)qr[j][e], hs[0], hs[1], hs[2]);
+        split3((float)qi[j][e], hs[3], hs[4], hs[5]);
+#pragma unroll
+        for (int k = 0; k < BF3_PLANES; ++k) {
+          if (e & 1)
+            w[k][e >> 1] |= (uint32_t)hs[k] << 16;
+          else
+            w[k][e >> 1] = hs[k];
+        }
+      }
+      u16* o = reinterpret_cast<u16*>(p.q[j]) + q * 8;
+#pragma unroll
+      for (int k = 0; k < BF3_PLANES; ++k) *reinterpret_cast<u32x4*>(o + k * plane) = w[k];
+    }
   }
 }
 
@@ -1321,6 +1561,47 @@ __global__ void to_product_kernel(const double* __restrict__ re, const double* _
 
 hipError_t launch_cheb_bf16(const ChebTermX& t, int term_fmt, int mrows, int np, hipStream_t s) {
   return dispatch_bf3(t, term_fmt, mrows, np, s);
+}
+
+hipError_t launch_bf3_poly(bool herm, int tf, const void* a, const void* b, double f,
+                           const void* sub, double fs, double one, const double* norms, bool add,
+                           void* o, int n, int np, hipStream_t s) {
+  Bf3Args g{};
+  g.a = static_cast<const u16*>(a);
+  g.b = static_cast<const u16*>(b);
+  g.o = o;
+  g.plane = (long)np * np;
+  g.np = np;
+  g.sub = static_cast<const u16*>(sub);
+  g.f = f;
+  g.fs = fs;
+  g.one = one;
+  g.norms = norms;
+  g.add = add;
+  g.n = n;
+  switch (tf) {
+    case TF_X3: return herm ? launch_bf3<BF3_T, false, 3>(g, np, s) : hipErrorInvalidValue;
+    case TF_X2: return herm ? launch_bf3<BF3_T, false, 2>(g, np, s) : launch_bf3<BF3_BLOCK, false, 2>(g, np, s);
+    case TF_X1: return herm ? launch_bf3<BF3_T, false, 1>(g, np, s) : launch_bf3<BF3_BLOCK, false, 1>(g, np, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_bf3_norms(const void* a, int np, double* out, hipStream_t s) {
+  if (np < 64 || np % 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(bf3_norms_kernel, dim3(np / 64, kNormParts), dim3(256), 0, s,
+                     static_cast<const u16*>(a), (long)np, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_poly_combine_bf3(const PolyCombine& p, long n, long np, hipStream_t s) {
+  if (p.s < 1 || p.s > kPolyMaxS || p.J < 1 || p.J > 4 || np % 64) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)std::min<long>((np * np / 8 + 255) / 256, 65536));
+  if (p.J <= 2)
+    hipLaunchKernelGGL(poly_combine_bf3_kernel<2>, grid, dim3(256), 0, s, p, n, np);
+  else
+    hipLaunchKernelGGL(poly_combine_bf3_kernel<4>, grid, dim3(256), 0, s, p, n, np);
+  return hipGetLastError();
 }
 
 hipError_t launch_cheb_mixed(const ChebTermX& t, int precision, int mrows, int np, hipStream_t s) {

@@ -36,16 +36,6 @@ struct Operands {
   bool tiles = false;  // tiles for more rows: sums over k in the same order in any block
 };
 
-// Tile (tm, tn), tm <= tn, number t of the upper triangle of a tiles x tiles
-// grid, column by column.
-__device__ __forceinline__ void tri_coords(int t, int& tm, int& tn) {
-  int c = (int)((__builtin_sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
-  while ((c + 1) * (c + 2) / 2 <= t) ++c;
-  while (c * (c + 1) / 2 > t) --c;
-  tn = c;
-  tm = t - c * (c + 1) / 2;
-}
-
 // One workgroup computes a BM x BN complex tile with WGM x WGN waves. K is
 // consumed in BK-wide stages through two LDS stages with one barrier each: the
 // next stage is written from registers (loaded one stage earlier) while the

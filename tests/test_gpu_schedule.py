@@ -124,3 +124,42 @@ def test_forced_schedule_large_tiles(fl, L, sched):
     """n = 2049 (17 x 17 tiles of 128): the split-BF16 products take their
     128 x 128 tiles, the FP64-sum product its 128-row tiles."""
     test_forced_schedule_matches_oracle(fl, 2049, L, sched)
+
+
+# split-BF16 steps as matrix polynomials: every block length and count (L = 2 .. 16),
+# one to three pieces (error targets, step sizes), 64 x 64 tiles with odd and even counts and
+# 128 x 128 tiles (2049 states: 17 x 17, 2048: 16 x 16), blocks of states, a block
+# too narrow for it. The bound is the forced schedules': ten times the estimated error.
+@pytest.mark.parametrize("n,L,tol,ncols,T", [
+    (600, 2, 0.0, 0, 0.3), (600, 3, 0.0, 0, 0.3), (600, 4, 0.0, 0, 0.3), (600, 5, 0.0, 0, 0.3),
+    (600, 8, 0.0, 0, 0.3), (600, 9, 0.0, 0, 0.3), (600, 12, 0.0, 0, 0.3), (600, 13, 0.0, 0, 0.3),
+    (600, 16, 0.0, 0, 0.3), (600, 7, 1e-4, 0, 0.3), (600, 7, 1e-5, 0, 0.3),
+    (600, 7, 2e-8, 0, 0.3), (700, 7, 0.0, 0, 0.3), (700, 7, 0.0, 600, 0.3),
+    (700, 7, 0.0, 300, 0.3), (2048, 6, 0.0, 0, 0.3), (2049, 3, 1e-4, 0, 0.3),
+    (2049, 6, 0.0, 0, 0.3), (2049, 7, 3e-8, 0, 0.3), (2049, 9, 0.0, 1990, 0.3),
+    (600, 7, 1.5e-7, 0, 0.3), (2049, 6, 1.5e-7, 0, 0.3), (600, 12, 0.0, 0, 0.9),
+    (600, 12, 3e-6, 0, 0.9), (2049, 12, 0.0, 0, 0.9), (2049, 12, 3e-6, 0, 0.9),
+    (600, 16, 1.5e-6, 0, 2.0), (2049, 16, 2e-6, 0, 2.0)])
+def test_step_polynomials_of_matrices(fl, n, L, tol, ncols, T):
+    _say("polynomial", n, "L", L, "mixed_tol", tol, "columns", ncols, "T", T)
+    M = 3
+    H0, V, f, lo, hi = _case(n, M, 200 + L, T)
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f, e_min=lo, e_max=hi, L=L,
+                            precision="bf16x3", mixed_tol=tol)
+    eye = np.eye(n, dtype=complex)
+    U = ctx.build_ut().cpu().numpy()
+    rep = ctx.last_report
+    _say("formats", rep["term_format"][:L], "estimate", rep["mixed_err_est"], "R", rep["R"])
+    cols = [0, 1, n // 2, n - 2, n - 1]
+    Uref = orc.build_ut(H0, V, f, T, M, route="cheb", e_min=lo, e_max=hi, L=L, X0=eye[:, cols])
+    bound = 10.0 * rep["mixed_err_est"] + 1e-11
+    err = orc.column_error(U[:, cols], Uref)
+    _say("e_col", err, "bound", bound)
+    assert err < bound
+    if ncols:
+        X = ctx.propagate(eye[:, :ncols]).cpu().numpy()
+        sub = [0, 1, ncols // 2, ncols - 1]
+        Xref = orc.build_ut(H0, V, f, T, M, route="cheb", e_min=lo, e_max=hi, L=L, X0=eye[:, sub])
+        err = orc.column_error(X[:, sub], Xref)
+        _say("block e_col", err)
+        assert err < 10.0 * max(rep["mixed_err_est"], 5e-7) + 1e-11
