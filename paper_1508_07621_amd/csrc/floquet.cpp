@@ -87,7 +87,7 @@ long dense_tile(long n) { return n > 1984 ? 128 : 64; }
 long pad_to(long x, long t) { return (x + t - 1) / t * t; }
 
 // Terms per pass of the streamed tridiagonal gradient (a multiple of 16;
-// windows of tridiag_stream_rows(1) rows hold 2K ghost and B = rows - 2K owned
+// windows of tridiag_stream_rows(16) rows hold 2K ghost and B = rows - 2K owned
 // rows): the K that minimises passes x windows x (overhead + terms per pass)
 // for `terms` terms per step over columns of n rows. The overhead is a pass
 // window's cost beyond its terms, in terms, measured on the 10^4-row dimer
@@ -96,7 +96,7 @@ long pad_to(long x, long t) { return (x + t - 1) / t * t; }
 // with 16 owned rows) lost 3 % against K = 144 there. kmax: the reverse pass
 // with the K contraction stages at most 128 of its coefficients in LDS.
 int stream_pass_terms(long n, int terms, double overhead, int kmax) {
-  const long rows = fq::tridiag_stream_rows(1);
+  const long rows = fq::tridiag_stream_rows(16);
   int best = 64;
   double best_cost = 0.0;
   for (int K = 64; K <= kmax && rows - 2L * K >= 256; K += 16) {
@@ -1944,6 +1944,38 @@ fq_status tridiag_build_segments(fq_ctx* c, int nseg) {
   return multiply_up(c, job.planes, c->pool + (size_t)nseg * job.bs, job.planes, nseg);
 }
 
+// Rows per lane and terms per pass of streamed columns. A pass costs its launch and
+// start (6 us), its state's way through memory (8 planes in and out) and K terms:
+// 45 ns and 6.7 ns per row of a lane for a wave alone on its SIMD (a fifth more once
+// the whole chip is busy), 9.5 ns per row for each of several (measured with R = 8
+// and 16, K = 64 .. 368, 1 .. 200 states of 4100, 6000 and 8000 rows); 64 R - 2 K rows of
+// a wave are its own. 16 states of 6000 rows, 721 terms a step: 159 ns a term in 5
+// passes with R = 8 (217 ns with R = 16, K = 128); from about 50 states on R = 16.
+struct TridiagPasses {
+  int R, K;
+};
+TridiagPasses tridiag_passes(long n, long ncols, int L) {
+  TridiagPasses best{16, 128};
+  double best_cost = 0.0;
+  for (int R : {16, 8})
+    for (int p = 1; p <= 64; ++p) {
+      // terms of a pass, at least 16 of them (an exact share of the L + 1 terms)
+      const long K = pad_to(std::max(16L, (L + 1L + p - 1) / p), R), B = 64L * R - 2 * K;
+      if (B < 4L * R) continue;
+      const long nblk = (n + B - 1) / B, passes = (L + 1L + K - 1) / K;
+      const double waves = 2.0 * (double)ncols * (double)nblk / 1024.0;
+      const double term = std::max((45e-9 + 6.7e-9 * R) * (1.0 + 0.2 * std::min(1.0, waves)),
+                                   waves > 1.0 ? std::ceil(waves) * 9.5e-9 * R : 0.0);
+      const double cost = (double)passes * (6e-6 + 128.0 * (double)n * (double)ncols / 4.7e12 +
+                                            (double)std::min<long>(K, L + 1) * term);
+      if (best_cost == 0.0 || cost < best_cost) {
+        best_cost = cost;
+        best = {R, (int)K};
+      }
+    }
+  return best;
+}
+
 fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, void* x_out) {
   fq::TridiagJob job = tridiag_job(c);
   job.ncols = ncols;
@@ -1968,7 +2000,8 @@ fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, voi
     return FQ_OK;
   }
   // Longer columns: k-term passes with ghost rows, state ping-ponged through HBM.
-  const int K = 128, G = 1;  // 768 owned rows per workgroup
+  const TridiagPasses tp = tridiag_passes(c->n, ncols, c->L);
+  const int K = tp.K;
   if (x0 && x0 == x_out && k1 - k0 == 1 && c->L + 1 <= K) {
     // One pass both reads X0 (with ghost rows) and writes X_out (owned rows):
     // in place, a workgroup could overwrite rows its neighbour still reads.
@@ -1978,11 +2011,11 @@ fq_status tridiag_run(fq_ctx* c, const void* x0, long ncols, int k0, int k1, voi
     job.x0 = c->d_stream;
   }
   fq::TridiagStream st{};
-  st.G = G;
+  st.R = tp.R;
   st.n16 = (c->n + 15) / 16 * 16;
   st.plane = st.n16 * ncols;
   st.K = K;
-  st.B = fq::tridiag_stream_rows(G) - 2L * K;
+  st.B = fq::tridiag_stream_rows(tp.R) - 2L * K;
   st.nblk = (c->n + st.B - 1) / st.B;
   const size_t state = 8 * (size_t)st.n16 * (size_t)c->n;
   double* buf[2] = {c->d_stream, c->d_stream + state};
@@ -2496,11 +2529,11 @@ fq_status tridiag_adjoint_streamed(fq_ctx* c, const void* U_bar, double* grad_f_
   job.ncols = n;
   job.ld_x0 = n;
   fq::TridiagStream st{};
-  st.G = 1;
+  st.R = 16;
   st.n16 = n16;
   st.plane = (long)plane;
   st.K = K;
-  st.B = fq::tridiag_stream_rows(1) - 2L * K;
+  st.B = fq::tridiag_stream_rows(16) - 2L * K;
   st.nblk = (n + st.B - 1) / st.B;
   double* fbuf[2] = {c->d_stream, c->d_stream + 8 * plane};
   double* stepc = c->d_stream + 16 * plane;

@@ -354,7 +354,7 @@ int tridiag_chain_rows(long n);  // rows per lane
 hipError_t launch_tridiag_table(const TridiagJob& job, int M, double* out, hipStream_t s);
 
 // Longer columns: one launch runs terms [l0, l1) of step s on blocks of B owned
-// rows with K ghost rows per side (B + 2K = tridiag_stream_rows(G)), reading the
+// rows with K ghost rows per side (B + 2K = tridiag_stream_rows(R)), reading the
 // state from `in` and writing it to `out` (8 planes of ncols x n16 doubles each),
 // or, at the end of the last step (last_step and l1 == L + 1), X to job.x_out.
 // first_step with l0 == 0 takes X from job.x0 (identity when null) instead of in.
@@ -375,11 +375,11 @@ struct TridiagStream {
   double* save;     // nullable: at the step's end, its last two terms P_{L-1}, P_L
                     // (4 planes [l & 1][part] in the state-plane layout)
   int K;            // ghost rows per side
-  int G;            // waves per part: 1024 G rows per workgroup (the launcher takes G = 1)
+  int R;            // rows per lane, 8 or 16: 64 R rows per workgroup
   long B;           // owned rows per block
   long nblk;        // blocks per column = ceil(n / B)
 };
-long tridiag_stream_rows(int G);
+long tridiag_stream_rows(int R);
 hipError_t launch_tridiag_stream_step(const TridiagJob& job, const TridiagStream& st,
                                       double* stepc, hipStream_t s);
 
@@ -423,7 +423,7 @@ hipError_t launch_tridiag_adjoint(const TridiagAdjJob& job, hipStream_t s);
 
 // One launch of the streamed reverse sweep for columns longer than one
 // workgroup holds: terms l = hi .. lo of one step on the windows of the forward
-// passes (B owned rows, K ghost rows per side, B + 2K = tridiag_stream_rows(1);
+// passes (B owned rows, K ghost rows per side, B + 2K = tridiag_stream_rows(16);
 // both multiples of 16), in the gauge frame of the step. Vectors are planes of
 // ncols x n16 doubles in the interleaved row layout of TridiagStream.
 constexpr int kAdjSlots = 64;  // accumulator slots per step (workgroup b adds to b mod 64)

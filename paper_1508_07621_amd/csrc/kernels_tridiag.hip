@@ -603,20 +603,22 @@ hipError_t launch_chain(const TridiagJob& job, int nseg, hipStream_t s) {
 
 // ---- columns longer than one workgroup holds: k-term passes over HBM ----------------------------
 //
-// A column is cut into blocks of B owned rows; a workgroup loads its block with
-// K ghost rows on each side (1024 G rows: 16 per lane, G waves per part), runs
-// at most K terms of one step in registers exactly as above, and writes back
-// only its owned rows: after t terms the rows within t of a cut are stale, the
-// owned ones are not. One wave per part (G = 1) is what the library launches:
-// its waves never wait for each other inside a pass, and the third of the rows
-// that are ghosts costs less than a barrier per term does with G = 2 or 4. Between launches the state lives in HBM in the gauge frame of
+// A column is cut into blocks of B owned rows; two waves, one per part, load a
+// block with K ghost rows on each side (64 R rows, R per lane), run
+// at most K terms of one step in registers exactly as above, and write back
+// only the owned rows: after t terms the rows within t of a cut are stale, the
+// owned ones are not. The waves never wait for each other inside a pass, and the
+// ghosts cost less than a barrier per term would. R and K by a cost model where
+// the passes are set up: 8 rows per lane for few columns, whose terms wait for the
+// lane's chain. A workgroup takes two such windows: workgroups of two waves leave
+// two of a CU's four SIMDs idle (16 states of 6000 rows: 196 against 159 ns a term;
+// still 5 % with 200 states). Between launches the state lives in HBM in the gauge frame of
 // the current step, as 8 planes of ncols x n16 doubles: role 0 = latest even
 // term, role 1 = latest odd term, role 2 = the part's own share of the sum,
 // role 3 = its share of the other component; plane index (role * 2 + part).
 // Within a column, row i sits at (i mod 16) nq + i / 16, so a lane's 16 rows
-// are one element of 16 unit-stride wave-wide accesses (B and K are multiples
-// of 16, so a row keeps its lane slot r = i mod 16 in every block that reads
-// it). At a step start role 0 holds X~ = D_s^+ X.
+// are one element of 16 unit-stride wave-wide accesses (with R = 8 of 8 accesses
+// in two unit-stride halves; B and K are multiples of R). At a step start role 0 holds X~ = D_s^+ X.
 
 // Per-step rows of 2 Ht, the phase-weighted gauge phi w_s and w_{s+1}, in the
 // interleaved layout; rows n .. n16-1 are zero.
@@ -653,29 +655,29 @@ __global__ __launch_bounds__(256) void tridiag_stream_step_kernel(TridiagJob job
   out[5 * n16 + at] = ni;
 }
 
-template <int R, int G>
-__global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, TridiagStream st,
+template <int R>
+__global__ __launch_bounds__(256) void tridiag_stream_kernel(TridiagJob job, TridiagStream st,
                                                              const double2* __restrict__ coef,
                                                              const double* __restrict__ stc) {
-  static_assert(R == 16, "the interleaved state layout assumes 16 rows per lane");
-  static_assert(G >= 1 && G <= 4 && G <= kMaxWaves, "waves per part (512 threads at most)");
-  extern __shared__ double ysh[];  // [part][r][lane in part][2]
-  __shared__ double halo[2][2][2][kMaxWaves];
+  static_assert(R == 16 || R == 8, "the interleaved state layout");
+  extern __shared__ double ysh_all[];  // [window][part][r][lane in part][2]
 
-  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int part = wid / G, w = wid % G;
-  const int pl = w * 64 + lane;
-  const long col = blockIdx.x / st.nblk, blk = blockIdx.x % st.nblk;
+  const int win = threadIdx.x >> 7, part = (threadIdx.x >> 6) & 1, pl = threadIdx.x & 63;
+  double* ysh = ysh_all + win * (2 * R * 64 * 2);
+  const long widx = blockIdx.x * 2L + win;
+  const bool live = widx < job.ncols * st.nblk;  // (the last workgroup may have one window)
+  const long col = live ? widx / st.nblk : 0, blk = live ? widx % st.nblk : 0;
   const long n = job.n, n16 = st.n16, nq = n16 >> 4;
   const long a0 = blk * st.B;                       // first owned row
   const long own_end = (a0 + st.B < n) ? a0 + st.B : n;
-  const long q = (a0 - st.K) / 16 + pl;             // row group of this lane (may be < 0)
-  const long base = q * 16;                         // global row of this lane's first row
+  // this lane's first row (may be < 0; a window that isn't there has no rows)
+  const long base = live ? a0 - st.K + (long)pl * R : -2048;
   const double sgn = part == 0 ? 1.0 : -1.0;
   const long cn = col * n16;                        // column offset in a state plane
   auto plane_in = [&](int role, int pt) { return st.in + (role * 2 + pt) * st.plane + cn; };
   auto plane_out = [&](int role, int pt) { return st.out + (role * 2 + pt) * st.plane + cn; };
-  auto at = [&](int r) { return (long)r * nq + q; };
+  const long q = base >> 4, r0 = R == 16 ? 0 : base & 15;
+  auto at = [&](int r) { return (r0 + r) * nq + q; };
 
   double pe[R], po[R];  // latest even and odd terms
   double ys[R], yo[R];
@@ -691,7 +693,7 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
     d2[r] = in_col ? stc[at(r)] : 0.0;
     g2[r] = in_col ? stc[n16 + at(r)] : 0.0;
   }
-  if (base >= 1 && base < n) gm2 = stc[n16 + (long)(R - 1) * nq + q - 1];
+  if (base >= 1 && base < n) gm2 = stc[n16 + ((base - 1) & 15) * nq + ((base - 1) >> 4)];
 
   // load
 #pragma unroll
@@ -731,31 +733,13 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
     yo[r] = y2;
   }
 
-  // Neighbour values of the latest term: row base - 1 (up) and row base + R (dn).
-  // post() starts their exchange as soon as the term's two edge rows are final
-  // (lane shifts, and the wave ends through LDS); complete() waits for the other
-  // waves and picks up the wave ends. advance() computes the edge rows first and
-  // the interior rows between the two, so the exchange overlaps the interior.
-  int parity = 0;
+  // Neighbour values of the latest term: row base - 1 (up) and row base + R (dn),
+  // zero beyond the window. advance() computes the edge rows first and the interior
+  // rows after their shifts have been issued.
   double up = 0.0, dn = 0.0;
   auto post = [&](const double* v) {
     up = from_prev_lane(v[R - 1]);
     dn = from_next_lane(v[0]);
-    if constexpr (G > 1) {
-      if (lane == 0) halo[parity][part][0][w] = v[0];
-      if (lane == 63) halo[parity][part][1][w] = v[R - 1];
-    }
-  };
-  auto complete = [&]() {
-    if constexpr (G > 1) {
-      __syncthreads();
-      const double hu = (w > 0) ? halo[parity][part][1][w - 1] : 0.0;
-      const double hd = (w + 1 < G) ? halo[parity][part][0][w + 1] : 0.0;
-      up = (lane == 0) ? hu : up;
-      dn = (lane == 63) ? hd : dn;
-    }
-    // (one wave per part: the shifts already read zero beyond the window)
-    parity ^= 1;
   };
   auto advance = [&](const double* v, double* nw) {  // nw = 2 Ht v - nw
     {
@@ -775,7 +759,6 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
       t = fma(g2[r - 1], v[r - 1], t);
       nw[r] = fma(g2[r], v[r + 1], t);
     }
-    complete();
   };
 
   int l = st.l0;
@@ -784,7 +767,6 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
     post(pe);
   else
     post(po);
-  complete();
   if (l == 0) {  // P_0 = X~ (in pe), P_1 = G X~ (into po)
     const double c0 = coef[0].x;
 #pragma unroll
@@ -865,10 +847,9 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
       }
     }
   }
-  const int np = G * 64;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    double2* slot = reinterpret_cast<double2*>(ysh) + ((long)part * R + r) * np + pl;
+    double2* slot = reinterpret_cast<double2*>(ysh) + ((long)part * R + r) * 64 + pl;
     *slot = make_double2(ys[r], yo[r]);
   }
   __syncthreads();
@@ -876,7 +857,7 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
   for (int r = 0; r < R; ++r) {
     const long i = base + r;
     if (i < a0 || i >= own_end) continue;
-    const double2 other = reinterpret_cast<const double2*>(ysh)[((long)(1 - part) * R + r) * np + pl];
+    const double2 other = reinterpret_cast<const double2*>(ysh)[((long)(1 - part) * R + r) * 64 + pl];
     const double own = ys[r] + other.y;
     const double oth = yo[r] + other.x;
     const double yr = part == 0 ? own : oth, yi = part == 0 ? oth : own;
@@ -900,15 +881,14 @@ __global__ __launch_bounds__(512) void tridiag_stream_kernel(TridiagJob job, Tri
   }
 }
 
-template <int G>
-hipError_t launch_stream_g(const TridiagJob& job, const TridiagStream& st, hipStream_t s) {
-  constexpr int R = 16;
+template <int R>
+hipError_t launch_stream_r(const TridiagJob& job, const TridiagStream& st, hipStream_t s) {
   // only a pass that ends its step exchanges the two halves of Y through LDS
-  const size_t shmem = st.l1 > job.L ? sizeof(double) * 2 * (size_t)G * 64 * R * 2 : 0;
-  const long grid = job.ncols * st.nblk;
+  const size_t shmem = st.l1 > job.L ? sizeof(double) * 2 * 2 * 64 * R * 2 : 0;
+  const long grid = (job.ncols * st.nblk + 1) / 2;
   if (grid < 1 || grid > 0x7fffffffL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((tridiag_stream_kernel<R, G>), dim3((unsigned)grid), dim3(2 * G * 64), shmem,
-                     s, job, st, reinterpret_cast<const double2*>(job.coef), st.stepc);
+  hipLaunchKernelGGL(tridiag_stream_kernel<R>, dim3((unsigned)grid), dim3(256), shmem, s, job, st,
+                     reinterpret_cast<const double2*>(job.coef), st.stepc);
   return hipGetLastError();
 }
 
@@ -2326,17 +2306,17 @@ hipError_t launch_energy_finish(double* num, double* den, long ncols, double w, 
   return hipGetLastError();
 }
 
-long tridiag_stream_rows(int G) { return (long)G * 64 * 16; }
+long tridiag_stream_rows(int R) { return 64L * R; }
 
 hipError_t launch_tridiag_stream(const TridiagJob& job, const TridiagStream& st, hipStream_t s) {
   if (job.n < 1 || job.ncols < 1 || st.K < 2 || st.l0 < 0 || st.l1 <= st.l0 ||
       st.l1 - st.l0 > st.K || st.l1 > job.L + 1 || st.B < 1 ||
-      st.G != 1 || st.B + 2L * st.K != tridiag_stream_rows(st.G) ||
+      (st.R != 8 && st.R != 16) || st.B + 2L * st.K != tridiag_stream_rows(st.R) ||
       st.nblk != (job.n + st.B - 1) / st.B ||
-      (st.l0 == 1) || st.K % 16 || st.B % 16 || st.n16 != (job.n + 15) / 16 * 16 ||
+      (st.l0 == 1) || st.K % st.R || st.B % st.R || st.n16 != (job.n + 15) / 16 * 16 ||
       st.plane < st.n16 * job.ncols || st.stepc == nullptr)
     return hipErrorInvalidValue;
-  return launch_stream_g<1>(job, st, s);
+  return st.R == 8 ? launch_stream_r<8>(job, st, s) : launch_stream_r<16>(job, st, s);
 }
 
 hipError_t launch_tridiag_stream_step(const TridiagJob& job, const TridiagStream& st,
@@ -2404,7 +2384,7 @@ hipError_t launch_tridiag_adj_stream(const TridiagAdjStream& p, const double* ta
                                      hipStream_t s) {
   const long grid = p.ncols * p.nblk;
   if (p.n < 1 || p.ncols < 1 || p.K < 16 || p.K % 16 || p.B < 16 || p.B % 16 ||
-      p.B + 2L * p.K != tridiag_stream_rows(1) || p.nblk != (p.n + p.B - 1) / p.B ||
+      p.B + 2L * p.K != tridiag_stream_rows(16) || p.nblk != (p.n + p.B - 1) / p.B ||
       p.n16 != (p.n + 15) / 16 * 16 || p.plane < p.n16 * p.ncols || p.L < 1 || p.lo < 0 ||
       p.hi < p.lo || p.hi > p.L - 1 || p.hi - p.lo + 1 > p.K || grid > 0x7fffffffL ||
       !tab || !p.lam || !p.grad || (p.hi == p.L - 1 ? !p.seg : !p.in) ||
@@ -2438,7 +2418,7 @@ hipError_t launch_tridiag_adj_persist(const TridiagAdjStream& p, const double* t
                                       hipStream_t s) {
   const long items = p.ncols * p.nblk;
   if (p.n < 1 || p.ncols < 1 || p.K < 16 || p.K % 16 || p.B < 16 || p.B % 16 ||
-      p.B + 2L * p.K != tridiag_stream_rows(1) || p.nblk != (p.n + p.B - 1) / p.B ||
+      p.B + 2L * p.K != tridiag_stream_rows(16) || p.nblk != (p.n + p.B - 1) / p.B ||
       p.n16 != (p.n + 15) / 16 * 16 || p.plane < p.n16 * p.ncols || p.L < 1 || p.lo < 0 ||
       p.hi < p.lo || p.hi > p.L - 1 || p.hi - p.lo + 1 > p.K || items > 0x7fffffffL ||
       !tab || !p.lam || !p.grad || (p.hi == p.L - 1 ? !p.seg : !p.in) ||

@@ -130,3 +130,29 @@ def test_chain_at_every_row_count(fl, n, scheme):
     scale = max(abs(rep["e_min"]), abs(rep["e_max"]))
     print("[case] average", np.max(np.abs(got - want)) / scale, flush=True)
     assert np.max(np.abs(got - want)) < 1e-11 * scale
+
+
+# streamed columns: windows of 8 and 16 rows per lane, one to several passes a step,
+# against the same columns of a wider block (which takes other windows) and, for the
+# norm, against 1. Rounding grows with the terms: 1e-12 holds 20000 terms' worth.
+@pytest.mark.parametrize("n,M,T", [(4097, 6, 0.02), (4100, 3, 0.2), (4099, 2, 0.6), (9001, 2, 0.1)])
+def test_streamed_windows(require_gpu, n, M, T):
+    from paper_1508_07621_amd import floquet as fl
+    print("[case] streamed windows", n, M, T, flush=True)
+    i = np.arange(n, dtype=float)
+    nb = n - 1
+    d = 0.5 * 0.01 * (i * (i - 1.0) + (nb - i) * (nb - i - 1.0))
+    e = -np.sqrt((i[:-1] + 1.0) * (nb - i[:-1])).astype(complex)
+    f = 0.5 + np.cos(fl.node_times(T, M))
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=2.0 * i - nb, T=T, M=M, f_nodes=f)
+    rng = np.random.default_rng(n)
+    X0 = rng.standard_normal((n, 700)) + 1j * rng.standard_normal((n, 700))
+    X0 /= np.linalg.norm(X0, axis=0)
+    print("[case] L", ctx.report["L"], flush=True)
+    wide = ctx.propagate(X0).cpu().numpy()
+    assert np.max(np.abs(np.linalg.norm(wide, axis=0) - 1.0)) < 1e-11
+    for c in (1, 3, 40, 200):
+        X = ctx.propagate(np.ascontiguousarray(X0[:, :c])).cpu().numpy()
+        err = np.max(np.linalg.norm(X - wide[:, :c], axis=0))
+        print("[case] columns", c, "difference", err, flush=True)
+        assert err < 1e-12
