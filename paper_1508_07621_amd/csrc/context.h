@@ -116,6 +116,7 @@ struct fq_ctx {
   double* d_theta = nullptr;
   double* d_tab = nullptr;            // tridiagonal: rows of every step (resident columns)
   double* d_fgrid = nullptr;          // tridiagonal: the period average's drive samples
+  double* d_etab = nullptr;           // tridiagonal averages: operator rows in lane order
   double* d_ext = nullptr;            // tridiagonal: extreme eigenvalues of every step
   double* d_stream = nullptr;         // tridiagonal n > resident size: two 8-plane states
   double* d_adj = nullptr;            // streamed reverse sweep: 10 complex n x n vectors

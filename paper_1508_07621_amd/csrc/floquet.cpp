@@ -153,7 +153,7 @@ struct Layout {
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
          off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0,
-         off_ext = 0, off_tab = 0, off_fgrid = 0, off_store = 0, off_theta = 0, off_adj_mats = 0;
+         off_ext = 0, off_tab = 0, off_fgrid = 0, off_etab = 0, off_store = 0, off_theta = 0, off_adj_mats = 0;
   long np = 0;
   int n_tape = 0;
   TridiagAdjPlan tri_adj;
@@ -295,6 +295,8 @@ Layout plan(const fq_system* sys, const fq_params* par) {
     lay.off_gauge = take(2 * sizeof(double) * (size_t)n * (size_t)Ms);
     lay.off_ext = take(2 * sizeof(double) * (size_t)Ms);
     lay.off_fgrid = take(sizeof(double) * (size_t)Ms);
+    if (n <= fq::tridiag_resident_max_n())
+      lay.off_etab = take(3 * sizeof(double) * (size_t)pad_to(n, fq::tridiag_chain_rows(n)));
     const bool streamed_grad = streamed_adjoint(sys, par);
     const size_t n16 = (size_t)(n + 15) / 16 * 16;
     const size_t splane = sizeof(double) * n16 * (size_t)n;  // one state plane
@@ -3095,6 +3097,7 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     c->d_gauge = P(lay.off_gauge);
     c->d_ext = P(lay.off_ext);
     c->d_fgrid = P(lay.off_fgrid);
+    if (c->n <= fq::tridiag_resident_max_n()) c->d_etab = P(lay.off_etab);
     if (lay.off_tab) c->d_tab = P(lay.off_tab);
     if (lay.tri_adj.nb > 0 && !lay.off_adj) {
       c->adj_seg = lay.tri_adj.nb;
@@ -3413,6 +3416,8 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
     job.ld_x0 = ncols;
     job.avg = avg;
     job.f_grid = c->d_fgrid;
+    job.etab = c->d_etab;
+    FQ_HIP(c, fq::launch_tridiag_energy_table(job, c->d_etab, c->stream));
     job.avg_w = w;
     job.spp = spp;
     FQ_MARK(c, FQ_K_TRIDIAG);

@@ -342,12 +342,15 @@ struct TridiagJob {
   // avg: the energy averages instead of x_out: avg[col] = avg_w sum over the steps s
   // with s % spp == 0 of <x_s| H0 + f_grid[s / spp] Hmod |x_s> / <x_s|x_s>
   double* avg;
+  // (etab: launch_tridiag_energy_table's 3 nq R doubles)
   const double* f_grid;
+  const double* etab;
   double avg_w;
   int spp;
 };
 // Returns hipErrorInvalidValue when n exceeds what one workgroup can hold.
 hipError_t launch_tridiag_resident(const TridiagJob& job, int nseg, hipStream_t s);
+hipError_t launch_tridiag_energy_table(const TridiagJob& job, double* out, hipStream_t s);
 long tridiag_resident_max_n();
 int tridiag_chain_rows(long n);  // rows per lane
 // Step tables of all M steps: 4 nq tridiag_chain_rows(n) doubles each.

@@ -237,6 +237,19 @@ __global__ __launch_bounds__(256) void tridiag_table_kernel(TridiagJob job, int 
   t[3 * nr] = rot.y;
 }
 
+// The rows of H0's diagonal, of Hmod and of Hmod's differences in the lane order.
+__global__ __launch_bounds__(256) void tridiag_energy_table_kernel(TridiagJob job, int R,
+                                                                   double* __restrict__ out) {
+  const long n = job.n, nq = job.nq, nr = nq * R;
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= nr) return;
+  double* t = out + (i % R) * nq + i / R;
+  const double v = i < n ? job.v_diag[i] : 0.0;
+  t[0] = i < n ? job.h0_diag[i] : 0.0;
+  t[nr] = v;
+  t[2 * nr] = i + 1 < n ? job.v_diag[i + 1] - v : 0.0;
+}
+
 // The whole chain of one column (or one segment of it, blockIdx.y) in one
 // workgroup: G waves per part, lane pl of a part holding rows R pl .. R pl + R - 1.
 //
@@ -258,7 +271,8 @@ __global__ __launch_bounds__(256) void tridiag_table_kernel(TridiagJob job, int 
 // conj(x_i) h_i x_{i+1} = conj(x~_i) x~_{i+1} |h_i| (1 + i q) / sqrt(1 + q^2), q = b dv_i:
 // the real part of conj(x~_i) x~_{i+1} is a sum over the parts, the imaginary part
 // (q != 0) takes the other part's rows through LDS. All 1000 states of that
-// dimer: 15.9 ms, where a launch per step and two for its energies took 51 ms.
+// dimer: 14.9 ms with the operators' rows in the lane order (15.9 ms read where they
+// are, 64 lines to a load), where a launch per step and two for its energies took 51 ms.
 template <int R, bool MULTI, bool ENERGY>
 __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
     TridiagJob job, int G, const double2* __restrict__ coef, const double* __restrict__ tab,
@@ -452,20 +466,20 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
           on = xch[XB == 2 ? xp ^ 1 : 0][1 - part][0][q];
         }
         neighbours(pa, up, dn);
-        const double f = job.f_grid[s / job.spp];
-        const double2* h0o = reinterpret_cast<const double2*>(job.h0_off);
+        const double f = job.f_grid[s / job.spp], dE = 1.0 / job.inv_dE;
+        const double* et = job.etab;
+        asm volatile("" : "+s"(et));  // loads of this step: kept across steps they would spill
         double num = 0.0, den = 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const long i = base + r;
-          if (i >= n) continue;
-          const double x = pa[r], vi = job.v_diag[i];
-          num = fma((job.h0_diag[i] + f * vi) * x, x, num);
+          const double x = pa[r];
+          const double* t = et + r * nq + pl;  // h0_i, v_i, v_{i+1} - v_i; 0 from n on
+          const bool in = pl < nq;
+          num = fma((in ? fma(f, t[nr], t[0]) : 0.0) * x, x, num);
           den = fma(x, x, den);
-          if (i + 1 >= n) continue;
-          const double2 h = h0o[i];
-          const double q = b * (job.v_diag[i + 1] - vi);
-          const double c = 2.0 * sqrt((h.x * h.x + h.y * h.y) / (1.0 + q * q));
+          const double q = cross && in ? b * t[2 * nr] : 0.0;
+          // 2 |h_i| / sqrt(1 + q^2) from the step's 2 |h_i| sqrt(1 + q^2) / dE
+          const double c = cross ? g2[r] * dE / fma(q, q, 1.0) : g2[r] * dE;
           const double xn = r + 1 < R ? pa[r + 1 < R ? r + 1 : 0] : dn;
           num = fma(c * x, xn, num);
           // - q Im: part 0 adds x_i * (other part's x_{i+1}), part 1 the mirrored term
@@ -2215,10 +2229,19 @@ hipError_t launch_tridiag_table(const TridiagJob& job, int M, double* out, hipSt
   return hipGetLastError();
 }
 
+hipError_t launch_tridiag_energy_table(const TridiagJob& job, double* out, hipStream_t s) {
+  const int R = chain_rows(job.n);
+  if (job.n < 1 || job.n > tridiag_resident_max_n() || job.nq != (job.n + R - 1) / R)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(tridiag_energy_table_kernel, dim3((unsigned)((job.nq * R + 255) / 256)),
+                     dim3(256), 0, s, job, R, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_tridiag_resident(const TridiagJob& job, int nseg, hipStream_t s) {
   const int R = chain_rows(job.n);
   if (job.n < 1 || job.ncols < 1 || job.n > tridiag_resident_max_n() || nseg < 1 ||
-      nseg > 65535 || job.nq != (job.n + R - 1) / R ||
+      nseg > 65535 || job.nq != (job.n + R - 1) / R || (job.avg && !job.etab) ||
       (nseg > 1 && (!job.planes || job.x0 || job.tape || job.snap ||
                     (long)nseg * job.len0 + job.rem != (long)job.k1 - job.k0)))
     return hipErrorInvalidValue;
