@@ -1730,7 +1730,72 @@ bool small_chain_ok(const fq_ctx* c, bool record_tape) {
          !c->save_plm1;
 }
 
-fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
+// X_{k+1} to the user's snapshot buffer when one is due.
+fq_status dense_snapshot(fq_ctx* c, int k) {
+  if (!c->snap || (k + 1 - c->snap_k0) % c->snap_every != 0) return FQ_OK;
+  const long j = (k + 1 - c->snap_k0) / c->snap_every - 1;
+  char* dst = static_cast<char*>(c->snap) +
+              (size_t)j * (c->c64 ? 8 : 16) * (size_t)c->n * (size_t)c->snap_ncols;
+  FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, c->snap_ncols, dst,
+                                       c->snap_ncols, c->c64, c->stream));
+  return FQ_OK;
+}
+
+// Steps whose propagators a propagation of mrows states forms at once (0: step by
+// step). The products of a step's terms wait for each other, so that small N pays a
+// launch per term; the E_k of a batch of steps do not, and each is then applied in
+// one product. Cost of an E: its products at 70 TF/s, eight passes over the matrix and
+// its share of some nine launches; of a product on mrows rows: 5 us and 3.5 ns per
+// padded state up to 16 rows, 4 us and 11 ns per padded state and round of 16 x 16
+// blocks beyond. A step with L = 8, before and after, 200 steps: 8 states at N = 64 23 ->
+// 5.7 us, N = 256 48 -> 14 us, N = 384 52 -> 29 us; 150 states at N = 256 44 -> 15 us, N =
+// 512 125 -> 67 us; from N = 512 on 8 states stay term by term (58 us).
+int dense_batch(const fq_ctx* c, const PolyPlan& p, int steps, long mrows) {
+  if (!p.s || c->pool_mats < poly_bufs(p)) return 0;
+  const int nb = std::min(c->pool_mats / poly_bufs(p), steps);
+  const double np = (double)c->np;
+  auto product = [&](double rows) {
+    if (rows <= 16.0) return 5e-6 + 3.5e-9 * np;
+    return 4e-6 + 11e-9 * np * std::max(1.0, std::ceil(rows / 16.0 * np / 16.0 / 256.0));
+  };
+  const int prods = p.s - 1 + p.J - 1;
+  const double form = (0.6 * (p.s - 1) + p.J - 1) * 8.0 * np * np * np / 70e12 +
+                      8.0 * 16.0 * np * np / 4e12 + 45e-6 / nb;
+  // one-launch chain: about 3 us a term; else terms or one step's own polynomial
+  const double single = std::min(c->np == 64 ? 3e-6 * c->L : c->L * product((double)mrows),
+                                 prods * product(np) + product((double)mrows) + 10e-6);
+  return form + product((double)mrows) < single ? nb : 0;
+}
+
+// Called before step k with X_k in the X planes; may use the Ht and P planes.
+using StepHook = std::function<fq_status(int)>;
+
+fq_status dense_poly_batches(fq_ctx* c, const PolyPlan& p, int nb, int k0, int k1, int mrows,
+                             const StepHook& hook) {
+  const int np = (int)c->np, nbuf = poly_bufs(p);
+  const long bs = 2 * c->np * c->np;
+  std::vector<double*> b;
+  for (int r = 0; r < nbuf; ++r) b.push_back(c->pool + (size_t)r * nb * bs);
+  for (int k = k0; k < k1; k += nb) {
+    const int cnt = std::min(nb, k1 - k);
+    FQ_MARK(c, FQ_K_HEFF);
+    FQ_TRY(heff_f64(c, k, cnt, 1, 0, b[0]));  // member z: step k + z
+    FQ_TRY(poly_form_in_place(c, p, b, cnt));
+    for (int z = 0; z < cnt; ++z) {
+      if (hook) FQ_TRY(hook(k + z));
+      FQ_MARK(c, FQ_K_LAST);
+      FQ_HIP(c, fq::launch_poly_apply(c->xr, 0, b[0] + (size_t)z * bs, 0, false, c->par, 0, mrows,
+                                      np, 1, c->stream));
+      std::swap(c->xr, c->par);
+      std::swap(c->xi, c->pai);
+      FQ_TRY(dense_snapshot(c, k + z));
+    }
+  }
+  return FQ_OK;
+}
+
+fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape,
+                      const StepHook& hook = nullptr) {
   const size_t plane2 = 2 * (size_t)c->np * (size_t)c->np;
   struct Restore {
     fq_ctx* c;
@@ -1738,7 +1803,13 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
     ~Restore() { c->precision = prec; }
   } restore{c, c->precision};
   if (runs_f64(c, mrows)) c->precision = FQ_FP64;
-  if (small_chain_ok(c, record_tape)) {
+  if (c->precision == FQ_FP64 && !c->from_identity && !record_tape && !c->save_pl &&
+      !c->save_plm1 && c->pool_mats > 0 && k1 - k0 > 1) {
+    const PolyPlan p = poly_plan(c, kPoolBufs, 1.0);
+    const int nb = dense_batch(c, p, k1 - k0, mrows);
+    if (nb > 1) return dense_poly_batches(c, p, nb, k0, k1, mrows, hook);
+  }
+  if (small_chain_ok(c, record_tape) && !hook) {
     fq::SmallChain sc{};
     sc.h0r = c->h0r; sc.h0i = c->h0i;
     sc.vr = c->vr; sc.vi = c->vi;
@@ -1787,6 +1858,7 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
     FQ_HIP(c, hipMemcpyAsync(c->tape + plane2 / 2, c->xi, plane2 / 2 * sizeof(double),
                              hipMemcpyDeviceToDevice, c->stream));
   for (int k = k0; k < k1; ++k) {
+    if (hook) FQ_TRY(hook(k));
     if (poly.s) {
       FQ_TRY(dense_poly_step(c, poly, k, mrows));
     } else if (mixed_poly) {
@@ -1795,13 +1867,7 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape) {
       FQ_TRY(dense_heff(c, k));
       FQ_TRY(dense_cheb_step(c, mrows));
     }
-    if (c->snap && (k + 1 - c->snap_k0) % c->snap_every == 0) {  // X_{k+1} to the user's buffer
-      const long j = (k + 1 - c->snap_k0) / c->snap_every - 1;
-      char* dst = static_cast<char*>(c->snap) +
-                  (size_t)j * (c->c64 ? 8 : 16) * (size_t)c->n * (size_t)c->snap_ncols;
-      FQ_HIP(c, fq::launch_unpack_planar_t(c->xr, c->xi, c->np, c->n, c->snap_ncols, dst,
-                                           c->snap_ncols, c->c64, c->stream));
-    }
+    FQ_TRY(dense_snapshot(c, k));
     if (record_tape && ((k + 1) % c->ckpt == 0 || k + 1 == c->M)) {
       const int slot = (k + 1 + c->ckpt - 1) / c->ckpt;
       double* dst = c->tape + (size_t)slot * plane2;
@@ -3387,7 +3453,9 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
     const long mrows = pad_to(ncols, dense_tile(c->n)), rows = product_rows(c, ncols);
     FQ_HIP(c, fq::launch_pack_planar_t(X0, c->n, ncols, ncols, c->xr, c->xi, c->np, mrows, c->c64,
                                        c->stream));
-    for (int k = 0; k < c->M_user; ++k) {
+    const StepHook energies = [&](int sub) -> fq_status {
+      if (sub % spp) return FQ_OK;
+      const int k = sub / spp;
       // H(t_k) into the Ht planes (free between steps), H(t_k) x into the P planes
       fq::WeightedSum ws{};
       ws.re[0] = c->h0r; ws.im[0] = c->h0i; ws.w[0] = 1.0;
@@ -3403,8 +3471,9 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
                                         c->stream));
       FQ_HIP(c, fq::launch_energy_rows(c->xr, c->xi, c->par, c->pai, ncols, c->n, c->np, w, avg,
                                        c->stream));
-      FQ_TRY(dense_steps(c, k * spp, (k + 1) * spp, (int)rows, false));
-    }
+      return FQ_OK;
+    };
+    FQ_TRY(dense_steps(c, 0, c->M, (int)rows, false, energies));
   } else if (c->n <= fq::tridiag_resident_max_n()) {  // inside the chain's one launch
     FQ_HIP(c, copy_sync(c->stream, c->d_fgrid, f_grid, sizeof(double) * (size_t)c->M_user,
                         hipMemcpyHostToDevice));

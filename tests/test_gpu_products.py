@@ -236,3 +236,43 @@ def test_mixed_context_runs_in_fp64_where_faster(fl, precision, n, ncols, f64):
         assert err < 1e-6
         if precision == "bf16x3":   # not in FP64
             assert err > 1e-11
+
+
+# propagations that form the propagators of a batch of steps at once: more steps
+# than a batch holds (192 at 128 padded states, 30 at 320), remainders, one-launch
+# chain sizes, snapshots between, both schemes with one and two exponentials a step,
+# and energy averages; against U_T, against single steps (which go term by term), and
+# against their energies. All carry the same truncation; rounding is below 1e-13 a step.
+@pytest.mark.parametrize("n,ncols,M,scheme", [(30, 5, 9, "magnus4"), (64, 64, 2, "cf4"),
+                                              (100, 3, 300, "magnus4"), (100, 100, 7, "magnus6"),
+                                              (300, 9, 70, "cf4"), (300, 130, 31, "magnus4"),
+                                              (500, 200, 9, "magnus4"), (900, 100, 5, "cf4")])
+def test_batches_of_step_propagators(fl, n, ncols, M, scheme):
+    print("[case] batches", n, ncols, M, scheme, flush=True)
+    rng = np.random.default_rng(n + M)
+    H0, V = gue(n, rng), gue(n, rng)
+    T = 0.2 * M
+    f = np.cos(fl.node_times(T, M, scheme))
+    X0 = rng.standard_normal((n, ncols)) + 1j * rng.standard_normal((n, ncols))
+    X0 /= np.linalg.norm(X0, axis=0)
+    ctx = fl.FloquetContext(h0=H0, hmod=V, T=T, M=M, f_nodes=f, scheme=scheme)
+    U = ctx.build_ut().cpu().numpy()
+    every = max(1, M // 3)
+    X, snaps = ctx.propagate(X0, snap_every=every)
+    tol = M * 2e-12
+    assert orc.column_error(X.cpu().numpy(), U @ X0) < tol
+    fg = np.cos(np.arange(M) * T / M)
+    H0d, Vd = torch.from_numpy(H0).cuda(), torch.from_numpy(V).cuda()
+    Y, ref = torch.from_numpy(X0).cuda(), 0.0
+    for k in range(M):
+        H = H0d + fg[k] * Vd
+        ref = ref + torch.sum(Y.conj() * (H @ Y), dim=0).real / torch.sum(Y.abs() ** 2, dim=0)
+        Y = ctx.propagate(Y, k, k + 1)
+        if (k + 1) % every == 0:
+            err = (snaps[(k + 1) // every - 1] - Y).abs().max().item()
+            assert err < tol, (k, err)
+    assert torch.linalg.vector_norm(X - Y, dim=0).max().item() < tol
+    e = ctx.period_average(X0, fg)
+    err = float(np.max(np.abs(np.asarray(e) - (ref / M).cpu().numpy())))
+    print("[case] average", err, flush=True)
+    assert err < 1e-11
