@@ -240,8 +240,7 @@ enum {
   FQ_K_ADJ_FWD = 6,     /* gradient, streamed tridiagonal: segment recompute pass */
   FQ_K_ADJ_REV = 7,     /* gradient: reverse-sweep products (dense) or reverse passes
                            (streamed tridiagonal); after floquet_grad the dense
-                           segment recompute's products appear under FIRST / MID /
-                           LAST / HEFF */
+                           recompute's products appear under their own kinds */
   /* FQ_BF16X3 builds time their products by format instead of position: */
   FQ_K_TERM_FP64 = 8,       /* FQ_TERM_FP64 products */
   FQ_K_TERM_F64ACC = 9,     /* FQ_TERM_BF16X3_F64ACC */
@@ -252,8 +251,8 @@ enum {
   FQ_K_CHAIN = 14,          /* dense N <= 64 in FP64: every step of the range in one
                                launch (Ht, all terms and the hand-off per step; a
                                build in segments, whose products appear under LAST) */
-  FQ_K_POLY = 15,           /* FP64 dense builds: products that form a step's propagator
-                               (FQ_K_LAST then counts the products that apply it) */
+  FQ_K_POLY = 15,           /* dense: products that form a step's propagator (FQ_K_LAST,
+                               or the format of split BF16, then counts those that apply it) */
   FQ_K_SLOTS = 16
 };
 #define FQ_TERM_SLOTS 16
@@ -394,19 +393,18 @@ fq_status floquet_period_average(fq_ctx* ctx, const void* X0, int64_t ncols, con
                                  double* avg_out);
 
 /* Gradient of a real loss of U_T with respect to the 2*M drive samples (FQ_MAGNUS4), by
- * the reverse sweep through the Chebyshev recurrence of every step (beta, dE
- * and L held fixed), recomputing each segment from the tape of the last
- * floquet_build_UT. U_bar: device, n*n complex (fq_params.dtype) row-major with
+ * the reverse sweep through the Chebyshev sum of every step (beta, dE and L
+ * held fixed), after the last floquet_build_UT. U_bar: device, n*n complex (fq_params.dtype) row-major with
  * U_bar[i][j] = dLoss/dRe U[i][j] + i dLoss/dIm U[i][j]. grad_f_nodes: host,
  * 2*M float64 (2*M*S with several drive terms), same order as f_nodes (with
  * fq_params.grad_pair_sums only each step's node sum is meaningful). Needs
- * checkpoint_every > 0. Dense layouts: every step of a checkpoint segment is
- * recomputed in FP64; the reverse products run in FP64, or, for FQ_FP32
- * contexts, on FP32 matrix cores (operands rounded to FP32 as they are
- * staged, FP64 epilogues and FP64 sums of the contractions: about FP32
- * accuracy in the derivative).
- * FQ_TRIDIAG: up to n = 2048 one workgroup reverses each state column;
- * longer columns run the same recurrences in streamed passes of K terms over
+ * checkpoint_every > 0. Dense layouts: through the adjoint of every step's
+ * matrix polynomial in FP64, in segments of the chain (small N) or from the
+ * build's tape; orders that no polynomial serves go term by term from the
+ * tape, their reverse products on FP32 matrix cores in FQ_FP32 contexts
+ * (FP64 epilogues and sums: about FP32 accuracy in the derivative).
+ * FQ_TRIDIAG: up to n = 1024 one workgroup reverses each state column of each
+ * segment of the chain, up to n = 2048 each state column; longer columns run the same recurrences in streamed passes of K terms over
  * windows of rows with K ghost rows per side (K chosen per problem: at most
  * 256, at most 128 with the K contraction), one wave per real or imaginary
  * part (setting the environment variable FQ_TRIDIAG_STREAMED_ADJOINT=1 before

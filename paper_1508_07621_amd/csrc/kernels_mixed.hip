@@ -9,11 +9,11 @@
 // leading one (hh, hm, mh, hl, mm, lh) on BF16 matrix cores
 // (v_mfma_f32_32x32x16_bf16) with FP32 accumulation.
 //
-// In both, the propagated block X and the Chebyshev sum Y stay FP64: the first
-// product of a step, P_1 = Ht X, runs on FP64 matrix cores (its term carries
-// the largest weight |c_1| ~ R) and stores P_1 in the product format; the
-// kernels here form P_2 .. P_L, add each Bessel-weighted term to Y in FP64,
-// and the last one applies the step phase in FP64.
+// In both, the propagated block X and the Chebyshev sum Y stay FP64. Terms that
+// the schedule keeps in FP64 run on FP64 matrix cores; the kernels here form the
+// others, add each Bessel-weighted term to Y in FP64, and the last one applies
+// the step phase in FP64. Split-BF16 builds form each step's propagator as a
+// matrix polynomial instead where that is cheaper (the BF3_T and BF3_BLOCK kinds).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

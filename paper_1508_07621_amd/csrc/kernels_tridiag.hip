@@ -273,19 +273,36 @@ __global__ __launch_bounds__(256) void tridiag_energy_table_kernel(TridiagJob jo
 // (q != 0) takes the other part's rows through LDS. All 1000 states of that
 // dimer: 14.9 ms with the operators' rows in the lane order (15.9 ms read where they
 // are, 64 lines to a load), where a launch per step and two for its energies took 51 ms.
-template <int R, bool MULTI, bool ENERGY>
-__global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
+// Waves of a part: one, several that exchange their ends through LDS every term
+// (a barrier each), or several whose end lanes repeat the neighbour's (ghosts), which
+// exchange both latest terms of a lane every 16 terms. 16 states, ns a term: 1100 rows
+// 376 with a barrier every term, 288 with ghosts; 3000 rows 435 and 341; a 3000-row build
+// 27.0 and 21.4 ms. Four waves with ghosts hold 4000 rows, five would not leave a lane
+// 256 registers: the 96 lengths up to 4096 keep the barriers (streamed windows take
+// 2 GB of state from there on).
+constexpr int ONE_WAVE = 0, EVERY_TERM = 1, GHOST_LANES = 2;
+constexpr int kGhostStep = 62;  // lanes from one wave's first to the next one's
+
+template <int R, int WAVES, bool ENERGY>
+__global__ __launch_bounds__(WAVES != ONE_WAVE ? 512 : 128, 2) void tridiag_chain_kernel(
     TridiagJob job, int G, const double2* __restrict__ coef, const double* __restrict__ tab,
     double* __restrict__ tape, double* __restrict__ snap) {
+  constexpr bool MULTI = WAVES != ONE_WAVE, GHOST = WAVES == GHOST_LANES;
+  static_assert(!GHOST || R == 16, "16 terms between exchanges");
   constexpr int PW = MULTI ? 256 : 64;                   // lanes per part, at most
   constexpr int XB = MULTI ? 1 : 2;                      // buffers (LDS holds one of 4 waves)
   __shared__ double xch[XB][2][R][PW];                   // [buffer][part][row][lane]
   __shared__ double halo[2][2][2][MULTI ? kMaxWaves : 1];  // [parity][part][0 first row, 1 last row][wave]
   __shared__ double esum[2][2][2 * (MULTI ? kMaxWaves : 1)];  // [parity][num, den][wave]
+  // ghost lanes: [parity][part][wave][first, last owned lane][both terms]
+  __shared__ double edge[GHOST ? 2 : 1][2][GHOST ? 4 : 1][2][GHOST ? 2 * R : 1];
 
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = MULTI ? wid / G : wid, w = MULTI ? wid % G : 0;
-  const int pl = w * 64 + lane;  // lane index within its part
+  // lane index within its part; with ghost lanes the last two of a wave are the first
+  // two of the next
+  const int pl = w * (GHOST ? kGhostStep : 64) + lane;
+  const bool own = !GHOST || ((lane > 0 || w == 0) && (lane < 63 || w + 1 == G));
   const long col = blockIdx.x;
   const long n = job.n, nq = job.nq, nr = nq * R;
   const long base = (long)pl * R;
@@ -340,7 +357,7 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
       }
       const double2 g = gauge[(long)k_lo * n + i];
       v = part == 0 ? g.x * xr + g.y * xi : g.x * xi - g.y * xr;  // conj(w) x
-      if (tape && k_lo % job.ckpt == 0)  // checkpoint of X_{k_lo} (plain frame)
+      if (tape && own && k_lo % job.ckpt == 0)  // checkpoint of X_{k_lo} (plain frame)
         tape[2 * (((long)(k_lo / job.ckpt) * job.ncols + col) * n + i) + part] =
             part == 0 ? xr : xi;
     }
@@ -351,7 +368,7 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
   auto neighbours = [&](const double* v, double& up, double& dn) {
     up = from_prev_lane(v[R - 1]);
     dn = from_next_lane(v[0]);
-    if constexpr (MULTI) {  // wave ends exchange through LDS
+    if constexpr (MULTI && !GHOST) {  // wave ends exchange through LDS
       if (lane == 0) halo[parity][part][0][w] = v[0];
       if (lane == 63) halo[parity][part][1][w] = v[R - 1];
       __syncthreads();
@@ -362,11 +379,41 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
       parity ^= 1;
     }
   };
+  // GHOST: both latest terms of the ghost lanes from their owners; 16 terms later the
+  // last of their rows is stale.
+  int fresh = 0;
+  auto exchange = [&]() {
+    if constexpr (GHOST) {
+      if ((lane == 1 && w > 0) || (lane == 62 && w + 1 < G)) {
+        double* e = edge[parity][part][w][lane == 62];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          e[r] = pa[r];
+          e[R + r] = pb[r];
+        }
+      }
+      __syncthreads();
+      if (!own) {
+        const double* e = lane == 0 ? edge[parity][part][w - 1][1] : edge[parity][part][w + 1][0];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          pa[r] = e[r];
+          pb[r] = e[R + r];
+        }
+      }
+      parity ^= 1;
+      fresh = R;
+    }
+  };
   // nw = 2 G v - nw (in place over the older term). The two edge rows, which
   // take the neighbour lanes' values, go first: their inputs (the previous
   // term's edge rows) are then the oldest results in flight, and the shifted
   // values of this term's edges are ready long before the next term needs them.
   auto advance = [&](const double* v, double* nw) {
+    if constexpr (GHOST) {
+      if (fresh == 0) exchange();
+      --fresh;
+    }
     double up, dn;
     neighbours(v, up, dn);
     {
@@ -399,7 +446,8 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
   int xp = 0;
   auto trade = [&](const double* v, double* got) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) xch[xp][part][r][pl] = v[r];
+    for (int r = 0; r < R; ++r)
+      if (own) xch[xp][part][r][pl] = v[r];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < R; ++r) got[r] = xch[xp][1 - part][r][pl];
@@ -452,6 +500,11 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
       rows_of(s, d2, g2, gm2);
     }
 
+    if constexpr (GHOST) {  // X~ into the ghost lanes
+#pragma unroll
+      for (int r = 0; r < R; ++r) pb[r] = 0.0;
+      exchange();
+    }
     if constexpr (ENERGY) {
       const double b = job.ab[2 * s + 1];
       const bool at = s % job.spp == 0, cross = at && b != 0.0;
@@ -462,7 +515,7 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
         if (cross) {  // (b is the same for the whole workgroup)
           trade(pa, other);
           // the other part's row after this lane's last
-          const int q = pl + 1 < (MULTI ? G * 64 : 64) ? pl + 1 : pl;
+          const int q = pl + 1 < (GHOST ? G * kGhostStep + 2 : MULTI ? G * 64 : 64) ? pl + 1 : pl;
           on = xch[XB == 2 ? xp ^ 1 : 0][1 - part][0][q];
         }
         neighbours(pa, up, dn);
@@ -485,6 +538,7 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
           // - q Im: part 0 adds x_i * (other part's x_{i+1}), part 1 the mirrored term
           if (cross) num = fma(-q * c * sgn * x, r + 1 < R ? other[r + 1 < R ? r + 1 : 0] : on, num);
         }
+        if (!own) num = den = 0.0;
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
           num += __shfl_xor(num, o);
@@ -557,7 +611,7 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const long i = base + r;
-        if (i >= n) continue;
+        if (i >= n || !own) continue;
         if (ckpt_step)
           tape[2 * (((long)((s + 1) / job.ckpt) * job.ncols + col) * n + i) + part] = x[r];
         if (snap_step) store_part(snap, (snap_j * n + i) * job.ncols + col, part, job.c64, x[r]);
@@ -584,7 +638,7 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const long i = base + r;
-    if (i >= n) continue;
+    if (i >= n || !own) continue;
     if (job.planes)  // state-major planes of this segment
       job.planes[seg * job.bs + part * (job.bs / 2) + col * job.ld_planes + i] = pa[r];
     else
@@ -595,9 +649,9 @@ __global__ __launch_bounds__(MULTI ? 512 : 128, 2) void tridiag_chain_kernel(
 // Rows per lane for columns of n rows.
 int chain_rows(long n) { return n <= 64 ? 1 : n <= 128 ? 2 : n <= 256 ? 4 : n <= 512 ? 8 : 16; }
 
-template <int R, bool MULTI, bool ENERGY>
+template <int R, int WAVES, bool ENERGY>
 hipError_t launch_chain_r(const TridiagJob& job, int G, int nseg, hipStream_t s) {
-  hipLaunchKernelGGL((tridiag_chain_kernel<R, MULTI, ENERGY>),
+  hipLaunchKernelGGL((tridiag_chain_kernel<R, WAVES, ENERGY>),
                      dim3((unsigned)job.ncols, (unsigned)nseg), dim3(2 * G * 64), 0, s, job, G,
                      reinterpret_cast<const double2*>(job.coef), job.tab, job.tape, job.snap);
   return hipGetLastError();
@@ -606,13 +660,18 @@ hipError_t launch_chain_r(const TridiagJob& job, int G, int nseg, hipStream_t s)
 template <bool ENERGY>
 hipError_t launch_chain(const TridiagJob& job, int nseg, hipStream_t s) {
   switch (chain_rows(job.n)) {
-    case 1: return launch_chain_r<1, false, ENERGY>(job, 1, nseg, s);
-    case 2: return launch_chain_r<2, false, ENERGY>(job, 1, nseg, s);
-    case 4: return launch_chain_r<4, false, ENERGY>(job, 1, nseg, s);
-    case 8: return launch_chain_r<8, false, ENERGY>(job, 1, nseg, s);
+    case 1: return launch_chain_r<1, ONE_WAVE, ENERGY>(job, 1, nseg, s);
+    case 2: return launch_chain_r<2, ONE_WAVE, ENERGY>(job, 1, nseg, s);
+    case 4: return launch_chain_r<4, ONE_WAVE, ENERGY>(job, 1, nseg, s);
+    case 8: return launch_chain_r<8, ONE_WAVE, ENERGY>(job, 1, nseg, s);
   }
-  if (job.n <= 1024) return launch_chain_r<16, false, ENERGY>(job, 1, nseg, s);
-  return launch_chain_r<16, true, ENERGY>(job, (int)((job.n + 1023) / 1024), nseg, s);
+  if (job.n <= 1024) return launch_chain_r<16, ONE_WAVE, ENERGY>(job, 1, nseg, s);
+  // four waves with ghost lanes hold 250 groups of 16 rows
+  const long groups = (job.n + 15) / 16;
+  if (groups <= 4 * kGhostStep + 2)
+    return launch_chain_r<16, GHOST_LANES, ENERGY>(
+        job, (int)((groups - 2 + kGhostStep - 1) / kGhostStep), nseg, s);
+  return launch_chain_r<16, EVERY_TERM, ENERGY>(job, (int)((job.n + 1023) / 1024), nseg, s);
 }
 
 // ---- columns longer than one workgroup holds: k-term passes over HBM ----------------------------

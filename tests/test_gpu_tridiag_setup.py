@@ -156,3 +156,11 @@ def test_streamed_windows(require_gpu, n, M, T):
         err = np.max(np.linalg.norm(X - wide[:, :c], axis=0))
         print("[case] columns", c, "difference", err, flush=True)
         assert err < 1e-12
+
+
+# several waves per part: two with their last ghost group (2016 rows) and three (2017),
+# four with the last (4000 rows), and the form without ghost lanes beyond
+@pytest.mark.parametrize("scheme", ["magnus4", "cf4"])
+@pytest.mark.parametrize("n", [2016, 2017, 4000, 4001])
+def test_chain_of_several_waves(fl, n, scheme):
+    test_chain_at_every_row_count(fl, n, scheme)
