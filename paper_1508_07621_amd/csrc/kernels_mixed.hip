@@ -1240,7 +1240,12 @@ hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
     return dim3(KIND == BF3_T ? t * (t + 1) / 2 : grid_rows(g.tiles_m) * t);
   };
   if (KIND == BF3_T && mrows != np) return hipErrorInvalidValue;
-  if (mrows % 128 == 0 && np % 128 == 0 && (long)mrows * np >= kBigTileElems) {
+  // Hermitian products of one or two pieces: 64 x 64 tiles while the upper 128 x 128 ones
+  // make little more than one round of two workgroups per CU (N = 2048: 116 against 150
+  // us on average, N = 4096, 528 tiles for 512 places: 647 against 724 us; N = 6000 1990
+  // against 1853 us)
+  const bool small = KIND == BF3_T && NPC <= 2 && np <= 4096;
+  if (!small && mrows % 128 == 0 && np % 128 == 0 && (long)mrows * np >= kBigTileElems) {
     g.tiles_m = mrows / 128;
     g.tiles_n = np / 128;
     // one or two pieces: 64 x 64 wave tiles, four real products, two

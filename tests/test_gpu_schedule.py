@@ -163,3 +163,9 @@ def test_step_polynomials_of_matrices(fl, n, L, tol, ncols, T):
         err = orc.column_error(X[:, sub], Xref)
         _say("block e_col", err)
         assert err < 10.0 * max(rep["mixed_err_est"], 5e-7) + 1e-11
+
+
+# Hermitian products on 128 x 128 tiles (beyond 4096 padded states), one and two pieces
+@pytest.mark.parametrize("L,tol", [(4, 0.0), (4, 1e-4)])
+def test_step_polynomials_beyond_4096_states(fl, L, tol):
+    test_step_polynomials_of_matrices(fl, 4100, L, tol, 0, 0.3)
