@@ -354,10 +354,11 @@ def fd_direction(wl, kw, f, g, W, eps: float):
             "finite_difference": fd, "rel_diff": abs(ad - fd) / max(abs(fd), 1e-300)}
 
 
-ALGO_NOTE = ("algorithmic flops: 8 N^3 per complex N x N x N product (four real products); the "
-             "FP64 kernel on 128 x 128 tiles forms each complex product from Gauss's three real "
-             "products (6 N^3 MFMA flops), so its algorithmic rate can exceed the FP64 MFMA peak; "
-             "split-BF16 issues three real products per kept piece pair")
+ALGO_NOTE = ("algorithmic flops: 8 N^3 per complex N x N x N product (four real products), L "
+             "products a step; builds that form each step's propagator as a matrix polynomial run "
+             "fewer, and the FP64 kernel forms each complex product from Gauss's three real "
+             "products (6 N^3 MFMA flops), so algorithmic rates can exceed the MFMA peak; "
+             "split-BF16 issues three or four real products per kept piece pair")
 
 
 def dense_roofline(reports, n: int, precision: str, workload: str):
@@ -388,12 +389,13 @@ def dense_roofline(reports, n: int, precision: str, workload: str):
 TERM_KINDS = {8: "fp64", 9: "bf16x3_f64acc", 10: "bf16x3", 11: "bf16x2", 12: "bf16x1"}
 #: MFMA flops issued per algorithmic flop (8 N^3 per complex product) of each format:
 #: FP64 Gauss (3 of 4 real products); FP64-accumulating split-BF16: four real products
-#: x six piece pairs / 4; split-BF16 with FP32 sums: Gauss x 6, 3 or 1 piece pairs / 4
-#: (64 x 64 output tiles; on 128 x 128 tiles the one- and two-piece products run the
-#: four real products, TERM_MFMA_X4)
-TERM_MFMA = {"fp64": 0.75, "bf16x3_f64acc": 6.0, "bf16x3": 4.5, "bf16x2": 2.25, "bf16x1": 0.75}
-TERM_MFMA_X4 = {"bf16x2": 3.0, "bf16x1": 1.0}
+#: x six piece pairs / 4; split-BF16 with FP32 sums: four real products x 6, 3 or 1
+#: piece pairs / 4 (three pieces on 128 x 128 tiles: Gauss's three, TERM_MFMA_X4)
+TERM_MFMA = {"fp64": 0.75, "bf16x3_f64acc": 6.0, "bf16x3": 6.0, "bf16x2": 3.0, "bf16x1": 1.0}
+TERM_MFMA_X4 = {"bf16x3": 4.5}
 TERM_KERNEL_X4 = {
+    "bf16x3": "cheb_bf3_kernel<128,128,2,4,KIND,P,3> (BF16 MFMA 32x32x16, 3 real products x 6 "
+              "piece pairs)",
     "bf16x2": "cheb_x4_kernel<KIND,P,2> (BF16 MFMA 32x32x16 on 64 x 64 wave tiles, 4 real "
               "products x 3 piece pairs)",
     "bf16x1": "cheb_x4_kernel<KIND,P,1> (BF16 MFMA 32x32x16 on 64 x 64 wave tiles, 4 real "
@@ -419,7 +421,7 @@ def term_mfma(name: str, n: int) -> float:
 
 
 def term_kernel(name: str, n: int) -> str:
-    if name in TERM_KERNEL_X4 and x4_tiles(n):
+    if name in TERM_KERNEL_X4 and x4_tiles(n):  # 128 x 128 tiles
         return TERM_KERNEL_X4[name]
     return TERM_KERNEL[name]
 
@@ -428,10 +430,9 @@ TERM_KERNEL = {
     "fp64": "zgemm_nt_f64_kernel<64,64,8,2,4,Gauss,EpiCheb> (FP64 MFMA 16x16x4)",
     "bf16x3_f64acc": "cheb_acc_kernel<128> (BF16 MFMA 32x32x16, 4 real products x 6 piece "
                      "pairs, FP64 sums per 64-column block)",
-    "bf16x3": "cheb_bf3_kernel<128,128,2,4,KIND,P,3> (BF16 MFMA 32x32x16, 3 real products x 6 "
-              "piece pairs)",
-    "bf16x2": "cheb_bf3_kernel<128,128,2,4,KIND,P,2> (3 real products x 3 piece pairs)",
-    "bf16x1": "cheb_bf3_kernel<128,128,2,4,KIND,P,1> (3 real products x 1 piece pair)",
+    "bf16x3": "cheb_s4_kernel<KIND,P,3> (64 x 64 tiles, 4 real products x 6 piece pairs)",
+    "bf16x2": "cheb_s4_kernel<KIND,P,2> (64 x 64 tiles, 4 real products x 3 piece pairs)",
+    "bf16x1": "cheb_s4_kernel<KIND,P,1> (64 x 64 tiles, 4 real products x 1 piece pair)",
 }
 
 
@@ -624,7 +625,8 @@ def shard_share(ctx, U, wl, P: int, warmup: int, steps: int, s_full: float, prec
     t = (time.perf_counter() - t0) / steps
     kind = K_TRIDIAG
     if wl.layout == "dense":
-        kind = K_MID if any(r["n_kernel"][K_MID] for r in reps) else K_LAST
+        kind = max([K_MID, K_LAST, *TERM_KINDS],
+                   key=lambda k: sum(r["ms_kernel"][k] for r in reps))
     n_launch = sum(r["n_kernel"][kind] for r in reps)
     ms_launch = sum(r["ms_kernel"][kind] for r in reps) / max(n_launch, 1)
     res = {"P": P, "columns": cols, "s_per_share": round(t, 6),
@@ -633,7 +635,8 @@ def shard_share(ctx, U, wl, P: int, warmup: int, steps: int, s_full: float, prec
            "dominant_kernel_avg_ms": round(ms_launch, 4)}
     if wl.layout == "dense":
         flops = 8.0 * n * n * cols
-        mf = flops * mfma_flops_per_flop(precision, n, cols)
+        mf = flops * (term_mfma(TERM_KINDS[kind], n) if kind in TERM_KINDS
+                      else mfma_flops_per_flop(precision, n, cols))
         res["dominant_kernel_mfma_frac"] = round(mf / (ms_launch * 1e-3) / 1e12 / PEAKS[precision], 4)
     return res
 
@@ -784,9 +787,17 @@ def main():
         from paper_1508_07621_amd._abi import K_CHAIN
         if sum(r["n_kernel"][K_CHAIN] for r in reports):
             roof = chain_roofline(reports, n, wl.M, info["L"] * (2 if wl.scheme == "cf4" else 1))
+        elif precision != "fp64" and all(f <= 0 for f in last["term_format"]):
+            roof = dense_roofline(reports, n, "fp64", args.workload)  # the build ran in FP64
         elif precision == "bf16x3":
             rows, roof = term_schedule(reports, n, args.workload)
-            from paper_1508_07621_amd._abi import TERM_FORMAT_NAMES
+            from paper_1508_07621_amd._abi import K_POLY, TERM_FORMAT_NAMES
+            polys = sum(r["n_kernel"][K_POLY] for r in reports)
+            if polys:  # step polynomials: products of matrices, half tiles for the Hermitian ones
+                ms = sum(r["ms_kernel"][K_POLY] for r in reports)
+                extra["step_polynomials"] = {"products_per_build": polys / len(reports),
+                                             "avg_launch_ms": round(ms / polys, 4),
+                                             "ms_per_build": round(ms / len(reports), 2)}
             extra["schedule"] = {
                 "term_formats": [TERM_FORMAT_NAMES[f] for f in last["term_format"] if f >= 0],
                 "mixed_err_est": last["mixed_err_est"], "per_format": rows}
@@ -844,7 +855,7 @@ def main():
                 "traffic": tr["bytes"] if tr else None, "traffic_detail": tr,
                 "kernel": ("tridiag_chain_kernel<16> (whole chain per state column, real gauge form)"
                            if n <= TRIDIAG_RESIDENT_MAX_N else
-                           "tridiag_stream_kernel<16,1> (128-term passes; 768 owned + 2 x 128 ghost "
+                           "tridiag_stream_kernel<16> (128-term passes; 768 owned + 2 x 128 ghost "
                            "rows per workgroup, real gauge form)"),
                 "avg_launch_ms": round(ms_launch, 4), "launches_timed": n_launch,
                 "algorithmic_flops_per_launch": flops}
@@ -876,7 +887,7 @@ def main():
                         "avg_launch_ms": round(ms_rev, 4), "launches_timed": n_rev,
                         "algorithmic_flops_per_launch": flops_rev}
                 extra["gradient"]["segment_recompute_pass"] = {
-                    "kernel": "tridiag_stream_kernel<16,1> (the forward pass, saving each step's "
+                    "kernel": "tridiag_stream_kernel<16> (the forward pass, saving each step's "
                               "last two terms)", "avg_launch_ms": round(ms_fwd, 4),
                     "launches_timed": n_fwd}
 
