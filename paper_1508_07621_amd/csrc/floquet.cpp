@@ -1397,8 +1397,8 @@ void choose_schedule(fq_ctx* c) {
 // FP64 sum eight times; its polynomial with s = 4 takes the first one, half of two
 // two-piece and of a one-piece product, one one-piece product, and a pass over four
 // matrices. A step of L = 8, before and after: N = 1030 0.37 -> 0.25 ms, N = 2500 2.76
-// -> 1.75 ms; L = 7 at N = 4096 7.7 -> 5.6 ms (4.7 ms of it MFMA-bound products: the
-// one with X 2.2, four others 0.63 on average); errors as before (e_col 1.1 .. 3.6e-7).
+// -> 1.75 ms; L = 7 at N = 4096 7.7 -> 5.3 ms (4.5 ms of it MFMA-bound products: the
+// one with X 2.2, four others 0.56 on average); errors as before (e_col 1.1 .. 3.6e-7).
 
 // Units of a product: matrix instructions per tile and k-block, and its pass over
 // the operands.

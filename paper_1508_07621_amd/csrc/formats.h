@@ -45,6 +45,33 @@ __device__ __forceinline__ void tri_coords(int t, int& tm, int& tn) {
   tm = t - c * (c + 1) / 2;
 }
 
+// Tile of workgroup `bid` in the upper triangle of a tiles x tiles grid (launch
+// tri_grid(tiles) of them; false: none). The triangle is walked in blocks of 8 x 8
+// tiles, column of blocks by column of blocks, and XCD x takes the x-th eighth of that
+// walk, so that the workgroups resident on it share some 8 row and 8 column panels
+// (two-piece split-BF16 T product at N = 4096 column by column over all XCDs: 5.3 GB
+// fetched in 0.82 ms; 20 steps of that build 111.9 -> 106.6 ms with this walk).
+__host__ __device__ __forceinline__ int tri_grid(int tiles) {
+  return (tiles * (tiles + 1) / 2 + 7) / 8 * 8;
+}
+__device__ __forceinline__ bool tri_tile(int bid, int tiles, int& tm, int& tn) {
+  const int total = tiles * (tiles + 1) / 2;
+  const int t = (bid % 8) * ((total + 7) / 8) + bid / 8;
+  if (t >= total) return false;
+  tri_coords(t, tm, tn);
+  const int J = tn / 8, w = min(8, tiles - 8 * J), rem = t - 4 * J * (8 * J + 1);
+  if (rem < J * 8 * w) {
+    const int idx = rem % (8 * w);
+    tm = 8 * (rem / (8 * w)) + idx % 8;
+    tn = 8 * J + idx / 8;
+  } else {
+    tri_coords(rem - J * 8 * w, tm, tn);
+    tm += 8 * J;
+    tn += 8 * J;
+  }
+  return true;
+}
+
 // 128 x 128 output tiles only when they make at least 256 workgroups (one per
 // CU); smaller products take 64 x 64 tiles so that every CU has work.
 constexpr long kBigTileElems = 256L * 128 * 128;

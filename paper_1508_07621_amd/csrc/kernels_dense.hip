@@ -293,17 +293,21 @@ hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hip
     return hipErrorInvalidValue;
   const long a = np / 64, b = np / 32, c = np / 16;
   const long t64 = a * (a + 1) / 2, t32 = b * (b + 1) / 2, t16 = c * (c + 1) / 2;
+  Operands op = op0;
   if (t16 * batch <= 256)
     hipLaunchKernelGGL((zgemm_split_kernel<1, 8, CONJ_A, CONJ_B, false, true, Epi>),
                        dim3(t16, 1, batch), dim3(512), 0, s, op0, epi);
-  else if (take_tile64(t64 * batch, t32 * batch))
+  else if (take_tile64(t64 * batch, t32 * batch)) {
+    op.tiles_n = (int)a;
     hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, false, true, true, 4,
                                             Epi>),
-                       dim3(t64, batch), dim3(512), 0, s, op0, epi);
-  else
+                       dim3(tri_grid((int)a), batch), dim3(512), 0, s, op, epi);
+  } else {
+    op.tiles_n = (int)b;
     hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, false, true, true, 1,
                                             Epi>),
-                       dim3(t32, batch), dim3(256), 0, s, op0, epi);
+                       dim3(tri_grid((int)b), batch), dim3(256), 0, s, op, epi);
+  }
   return hipGetLastError();
 }
 

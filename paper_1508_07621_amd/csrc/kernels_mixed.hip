@@ -586,7 +586,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
 
   int tm, tn;
   if constexpr (KIND == BF3_T) {
-    tri_coords(blockIdx.x, tm, tn);
+    if (!tri_tile(blockIdx.x, g.tiles_n, tm, tn)) return;
   } else {
     tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
     if (tm >= g.tiles_m) return;  // grid padding
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
 
   int tm, tn;
   if constexpr (KIND == BF3_T) {
-    tri_coords(blockIdx.x, tm, tn);
+    if (!tri_tile(blockIdx.x, g.tiles_n, tm, tn)) return;
   } else {
     tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
     if (tm >= g.tiles_m) return;  // grid padding
@@ -954,7 +954,7 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
 
   int tm, tn;
   if constexpr (KIND == BF3_T) {
-    tri_coords(blockIdx.x, tm, tn);
+    if (!tri_tile(blockIdx.x, g.tiles_n, tm, tn)) return;
   } else {
     tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
     if (tm >= g.tiles_m) return;  // grid padding
@@ -1237,13 +1237,13 @@ hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
   const int np = g.np;
   auto grid = [&]() {
     const int t = g.tiles_n;
-    return dim3(KIND == BF3_T ? t * (t + 1) / 2 : grid_rows(g.tiles_m) * t);
+    return dim3(KIND == BF3_T ? tri_grid(t) : grid_rows(g.tiles_m) * t);
   };
   if (KIND == BF3_T && mrows != np) return hipErrorInvalidValue;
   // Hermitian products of one or two pieces: 64 x 64 tiles while the upper 128 x 128 ones
   // make little more than one round of two workgroups per CU (N = 2048: 116 against 150
   // us on average, N = 4096, 528 tiles for 512 places: 647 against 724 us; N = 6000 1990
-  // against 1853 us)
+  // against 1853 us; all before the blocked walk of tri_tile)
   const bool small = KIND == BF3_T && NPC <= 2 && np <= 4096;
   if (!small && mrows % 128 == 0 && np % 128 == 0 && (long)mrows * np >= kBigTileElems) {
     g.tiles_m = mrows / 128;

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
 
   int tm, tn;
   if constexpr (HERM) {
-    tri_coords(blockIdx.x, tm, tn);
+    if (!tri_tile(blockIdx.x, op.tiles_n, tm, tn)) return;
   } else {
     tile_coords(blockIdx.x, op.tiles_m, op.tiles_n, tm, tn);
     if (tm >= op.tiles_m) return;  // grid padding
