@@ -442,15 +442,22 @@ __global__ __launch_bounds__(WAVES != ONE_WAVE ? 512 : 128, 2) void tridiag_chai
 #pragma unroll
     for (int r = 0; r < R; ++r) yo[r] = fma(c, p[r], yo[r]);
   };
-  // this part's share v of the other part's component goes to that part
+  // this part's share v of the other part's component goes to that part; after: also
+  // the other part's row that follows this lane's last. With one buffer every read
+  // comes before the closing barrier: the next trade may follow without another one
+  // (ghost lanes wait for each other only every 16 terms).
   int xp = 0;
-  auto trade = [&](const double* v, double* got) {
+  auto trade = [&](const double* v, double* got, double* after = nullptr) {
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (own) xch[xp][part][r][pl] = v[r];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < R; ++r) got[r] = xch[xp][1 - part][r][pl];
+    if (after) {
+      const int q = pl + 1 < (GHOST ? G * kGhostStep + 2 : MULTI ? G * 64 : 64) ? pl + 1 : pl;
+      *after = xch[xp][1 - part][0][q];
+    }
     if constexpr (XB == 2)
       xp ^= 1;
     else
@@ -512,12 +519,7 @@ __global__ __launch_bounds__(WAVES != ONE_WAVE ? 512 : 128, 2) void tridiag_chai
         double other[R], up, dn, on = 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) other[r] = 0.0;
-        if (cross) {  // (b is the same for the whole workgroup)
-          trade(pa, other);
-          // the other part's row after this lane's last
-          const int q = pl + 1 < (GHOST ? G * kGhostStep + 2 : MULTI ? G * 64 : 64) ? pl + 1 : pl;
-          on = xch[XB == 2 ? xp ^ 1 : 0][1 - part][0][q];
-        }
+        if (cross) trade(pa, other, &on);  // (b is the same for the whole workgroup)
         neighbours(pa, up, dn);
         const double f = job.f_grid[s / job.spp], dE = 1.0 / job.inv_dE;
         const double* et = job.etab;
