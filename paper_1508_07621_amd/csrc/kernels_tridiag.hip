@@ -144,7 +144,8 @@ __global__ __launch_bounds__(128) void tridiag_extremes_kernel(
 // ratio of neighbours; each thread multiplies up a run of rows, the runs'
 // products are scanned, and every factor is renormalised, so a ratio is off by
 // a few roundings (a relative change of the coupling of that size), however
-// long the chain.
+// long the chain. A coupling is scaled by a power of two before it is normalised:
+// the reciprocal of a subnormal modulus would be infinite.
 __global__ __launch_bounds__(256) void tridiag_gauge_table_kernel(
     long n, const double2* __restrict__ off, const double* __restrict__ v,
     const double* __restrict__ ab, double2* __restrict__ out) {
@@ -156,8 +157,11 @@ __global__ __launch_bounds__(256) void tridiag_gauge_table_kernel(
   auto next = [&](double2 w, long i) {  // w_i -> w_{i+1}
     const double2 h = off[i];
     const double q = b * (v[i + 1] - v[i]);
-    const double er = h.x + h.y * q, ei = h.y - h.x * q;
+    double er = h.x + h.y * q, ei = h.y - h.x * q;
     if (er == 0.0 && ei == 0.0) return w;
+    const int e = -ilogb(fmax(fabs(er), fabs(ei)));
+    er = scalbn(er, e);
+    ei = scalbn(ei, e);
     const double nr = w.x * er + w.y * ei, ni = w.y * er - w.x * ei;  // w conj(e)
     const double m = 1.0 / hypot(nr, ni);
     return make_double2(nr * m, ni * m);

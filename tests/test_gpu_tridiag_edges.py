@@ -55,3 +55,27 @@ def test_period_average_of_short_steps(fl, n):
         err = np.max(np.abs(got - want)) / scale
         print("[case] L", rep["L"], "average", err, flush=True)
         assert err < 1e-12
+
+
+# couplings among and next to the subnormal numbers (2.2e-308 down to 4.9e-324): they
+# vanish in H_eff, and the gauge factors beyond them stay unit numbers
+@pytest.mark.parametrize("tiny", [5e-324, 1e-310, 5.6e-309, 3e-308])
+@pytest.mark.parametrize("n", [3, 70, 1100, 4100])
+def test_subnormal_coupling(fl, n, tiny):
+    print("[case] subnormal coupling", n, tiny, flush=True)
+    rng = np.random.default_rng(n)
+    M, T = 3, 0.3
+    d, v = rng.standard_normal(n), rng.standard_normal(n)
+    e = rng.standard_normal(n - 1) + 1j * rng.standard_normal(n - 1)
+    e[n // 2 - 1] = tiny * (1.0 if n % 2 else 1.0j)
+    f = rng.uniform(-2, 2, (M, 2))
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=f)
+    rep = ctx.report
+    cols = np.unique([0, n // 2 - 1, n // 2, n - 1])
+    X0 = np.eye(n, dtype=complex)[:, cols]
+    got = ctx.propagate(X0).cpu().numpy()
+    ref = orc.build_ut_tridiag(d, e, v, f, T, M, route="cheb", e_min=rep["e_min"],
+                               e_max=rep["e_max"], L=rep["L"], X0=X0)
+    err = orc.column_error(got, ref)
+    print("[case] e_col", err, flush=True)
+    assert err < 1e-12
