@@ -86,7 +86,13 @@ struct EpiStore {
   __device__ __forceinline__ void finish() const {}
 };
 
-// The Gram matrix is Hermitian: an element above the diagonal's tiles counts twice.
+// The larger of two values, NaN if either is one (fmax drops it).
+__device__ __forceinline__ double max_or_nan(double a, double b) {
+  return a > b || a != a ? a : b;
+}
+
+// The Gram matrix is Hermitian: an element above the diagonal's tiles counts twice. A NaN
+// is carried to the maximum: its bits compare above those of every number there.
 struct EpiUnitarity {
   int n;
   double* out;
@@ -96,14 +102,14 @@ struct EpiUnitarity {
     if (m < n && c < n) {
       const double dr = ar - (m == c ? 1.0 : 0.0);
       const double a2 = dr * dr + ai * ai;
-      mx = fmax(mx, a2);
+      mx = max_or_nan(a2, mx);
       ss += mirror ? 2.0 * a2 : a2;
     }
   }
   __device__ void finish() {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-      mx = fmax(mx, __shfl_xor(mx, o));
+      mx = max_or_nan(mx, __shfl_xor(mx, o));
       ss += __shfl_xor(ss, o);
     }
     if ((threadIdx.x & 63) == 0) {
