@@ -79,3 +79,59 @@ def test_subnormal_coupling(fl, n, tiny):
     err = orc.column_error(got, ref)
     print("[case] e_col", err, flush=True)
     assert err < 1e-12
+
+
+def _chain_80bit(d, e, v, f, T, M, e_max, L, coef):
+    """U_T of the same truncated series on [-e_max, e_max], in 80-bit arithmetic."""
+    ld = np.longdouble
+    n, h = len(d), T / M
+    a, b = orc.magnus4_weights(f, h)
+    X = np.eye(n, dtype=np.clongdouble)
+    inv = ld(1.0 / e_max)
+    dv = np.diff(v.astype(ld))
+    for k in range(M):
+        dd = ((d.astype(ld) + ld(a[k]) * v.astype(ld)) * inv)[:, None]
+        up = (e.astype(np.clongdouble) * (1 - 1j * (ld(b[k]) * dv)) * inv)[:, None]
+
+        def mv(x):
+            y = dd * x
+            y[:-1] += up * x[1:]
+            y[1:] += up.conj() * x[:-1]
+            return y
+        p0, p1 = X, mv(X)
+        Y = ld(coef[0]) * p0 + (-1j) * (ld(coef[1]) * p1)
+        for l in range(2, L + 1):
+            p0, p1 = p1, 2 * mv(p1) - p0
+            Y = Y + np.array((-1j) ** l, dtype=np.clongdouble) * (ld(coef[l]) * p1)
+        X = Y
+    return X
+
+
+# Random node differences in every step: correctly rounded gauge factors deviate from
+# unit numbers independently of each other, so the error of U_T walks at random: a step's
+# (four roundings of a rotation, about L / 2 of the sum) stays below 12 roundings of 53
+# bits, and M steps below that times sqrt(M). A deviation common to all steps would grow
+# with M. The interval is symmetric: the step phase is exactly 1.
+@pytest.mark.parametrize("n", [3, 21, 90])
+def test_gauge_factors_round_once(fl, n):
+    print("[case] long chain", n, flush=True)
+    rng = np.random.default_rng(40 + n)
+    M = 1000
+    T = 0.1 * M
+    d, v = rng.standard_normal(n), rng.standard_normal(n)
+    e = rng.standard_normal(n - 1) + 1j * rng.standard_normal(n - 1)
+    f = rng.uniform(-2, 2, (M, 2))
+    e_max = 16.0
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=f, e_min=-e_max,
+                            e_max=e_max)
+    rep = ctx.report
+    L = rep["L"]
+    assert L < 24
+    ref = _chain_80bit(d, e, v, f, T, M, e_max, L, fl.bessel_weights(T / M * e_max, L))
+    U = ctx.build_ut().cpu().numpy()
+    X = ctx.propagate(np.eye(n, dtype=complex)).cpu().numpy()
+    bound = 12 * 2.0 ** -53 * np.sqrt(M)
+    for name, A in (("build", U), ("states", X)):
+        err = float(np.max(np.sqrt(np.sum(np.abs(A.astype(np.clongdouble) - ref) ** 2, axis=0))))
+        print("[case]", name, "L", L, "e_col", err, "bound", bound, flush=True)
+        assert err < bound
