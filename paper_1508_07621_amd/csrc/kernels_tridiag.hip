@@ -97,9 +97,8 @@ __global__ __launch_bounds__(128) void tridiag_extremes_kernel(
     hi = fmax(hi, __shfl_xor(hi, o));
     emax = fmax(emax, __shfl_xor(emax, o));
   }
-  // replaces a vanishing pivot: far below any pivot that matters (those of order
-  // eps sqrt(emax)), far enough from overflow for the reciprocal below
-  const double pivmin = 1e-150 * emax;
+  // replaces a vanishing pivot, as in the host's bisection
+  const double pivmin = 2.2250738585072014e-308 * emax;
   const double pad = 1e-14 * (hi - lo) + 1e-300;
   lo -= pad;
   hi += pad;
@@ -121,10 +120,14 @@ __global__ __launch_bounds__(128) void tridiag_extremes_kernel(
       if (__all(below)) continue;  // decided for every point (of this wave)
 #pragma unroll 16
       for (int i = 0; i < m; ++i) {
-        double r = __builtin_amdgcn_rcp(q);  // 1 / q to an ulp or two: a relative
-        r = fma(fma(-q, r, 1.0), r, r);      // change of the squared coupling by eps
+        // ee / q: the reciprocal to an ulp, then the quotient's own remainder, which
+        // leaves it rounded like a division (whose scaling no pivot needs)
+        double r = __builtin_amdgcn_rcp(q);
         r = fma(fma(-q, r, 1.0), r, r);
-        q = fma(-ee[i], r, sgn * dd[i] - x);
+        r = fma(fma(-q, r, 1.0), r, r);
+        double c = ee[i] * r;
+        c = fma(fma(-q, c, ee[i]), r, c);
+        q = (sgn * dd[i] - x) - c;
         if (fabs(q) < pivmin) q = -pivmin;
         below = below || q < 0.0;
       }

@@ -135,3 +135,21 @@ def test_gauge_factors_round_once(fl, n):
         err = float(np.max(np.sqrt(np.sum(np.abs(A.astype(np.clongdouble) - ref) ** 2, axis=0))))
         print("[case]", name, "L", L, "e_col", err, "bound", bound, flush=True)
         assert err < bound
+
+
+# Real couplings and a drive constant over each step: the device and the host bisection
+# take the same pivots, operation by operation, and both end between neighbouring doubles
+@pytest.mark.parametrize("scale", [1.0, 1e-100, 1e-145, 1e100])
+@pytest.mark.parametrize("n", [2, 17, 300, 3000])
+def test_extremes_as_the_host_finds_them(fl, n, scale):
+    print("[case] extremes", n, scale, flush=True)
+    rng = np.random.default_rng(60 + n)
+    d, e = rng.standard_normal(n) * scale, rng.standard_normal(n - 1) * scale
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=np.zeros(n), T=0.01 / scale, M=1,
+                            f_nodes=np.zeros((1, 2)))
+    lo, hi = fl.tridiag_extremes(d, np.abs(e))
+    rep = ctx.report
+    print("[case]", (rep["e_min"] - lo) / np.spacing(abs(lo)),
+          (rep["e_max"] - hi) / np.spacing(abs(hi)), flush=True)
+    assert abs(rep["e_min"] - lo) <= np.spacing(abs(lo))
+    assert abs(rep["e_max"] - hi) <= np.spacing(abs(hi))
