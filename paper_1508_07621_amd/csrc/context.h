@@ -6,10 +6,13 @@
 
 // The step propagator sum_l c_l T_l(Ht) as matrix products: T_1 .. T_s, then
 // Clenshaw's recurrence in T_s over the blocks Q_0 .. Q_J-1 (g: s + 1
-// coefficients of T_0 .. T_s per block, step phase included).
+// coefficients of T_0 .. T_s per block, step phase included). FP64 plans hold the
+// propagator without its multiple c0 of the identity and the T_l as S_l = T_l - sigma_l
+// (coefficients of T_0 all zero, see poly_plan_s).
 struct PolyPlan {
   int s = 0, J = 0;
   std::vector<double> gr, gi;
+  fq::PolyScalar c0;
 };
 
 // The same in split BF16 (see choose_mixed_poly): formats of T_l (index l), of the

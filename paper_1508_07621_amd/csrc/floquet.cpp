@@ -1098,39 +1098,89 @@ fq_status dense_cheb_step(fq_ctx* c, int mrows) {
 // MFMA). Small N in segments: 100 steps at N = 64 2.36 -> 0.16 ms, a sixth-order
 // one-shot build at N = 199 18.3 -> 12.0 ms (the rest is its setup).
 
-// Blocks of length bs.
-PolyPlan poly_blocks(const fq_ctx* c, int bs) {
-  const int L = c->L;
-  PolyPlan best;
-  const int s = best.s = bs, prods = (L + s - 1) / s - 1, top = L / s;
-  const std::complex<double> ph(c->phr, c->phi);
-  std::vector<std::complex<double>> cl(L + 1);
-  for (int l = 0; l <= L; ++l)
-    cl[l] = ph * std::complex<double>(c->coef[2 * l], c->coef[2 * l + 1]);
-  best.J = prods + 1;
-  std::vector<std::complex<double>> g((size_t)(top + 1) * (s + 1), 0.0);
-  auto G = [&](int j, int l) -> std::complex<double>& { return g[(size_t)j * (s + 1) + l]; };
+using cld = std::complex<long double>;
+
+// Blocks of length s: the coefficients of T_0 .. T_s in each of the *J blocks.
+std::vector<cld> poly_coefficients(const fq_ctx* c, int s, int* J) {
+  const int L = c->L, prods = (L + s - 1) / s - 1, top = L / s;
+  const long double arg = (long double)c->beta * c->h;
+  const cld ph(std::cos(arg), -std::sin(arg));
+  std::vector<cld> cl(L + 1);
+  for (int l = 0; l <= L; ++l) cl[l] = ph * cld(c->coef[2 * l], c->coef[2 * l + 1]);
+  *J = prods + 1;
+  std::vector<cld> g((size_t)(top + 1) * (s + 1), 0.0L);
+  auto G = [&](int j, int l) -> cld& { return g[(size_t)j * (s + 1) + l]; };
   for (int j = top; j >= 1; --j) {
     G(j, 0) = cl[j * s];
     for (int i = 1; i < s && j * s + i <= L; ++i) {
-      G(j, i) = 2.0 * cl[j * s + i];
+      G(j, i) = 2.0L * cl[j * s + i];
       cl[j * s - i] -= cl[j * s + i];
     }
   }
   for (int i = 0; i < s; ++i) G(0, i) = cl[i];
   if (L % s == 0) {  // the top block is a number: no product for it
-    const std::complex<double> gt = G(top, 0);
-    G(top - 1, s) = (top - 1 >= 1 ? 2.0 : 1.0) * gt;
+    const cld gt = G(top, 0);
+    G(top - 1, s) = (top - 1 >= 1 ? 2.0L : 1.0L) * gt;
     if (top - 2 >= 0) G(top - 2, 0) -= gt;
   }
-  best.gr.resize((size_t)best.J * (s + 1));
-  best.gi.resize(best.gr.size());
-  for (int j = 0; j < best.J; ++j)
-    for (int l = 0; l <= s; ++l) {
-      best.gr[(size_t)j * (s + 1) + l] = G(j, l).real();
-      best.gi[(size_t)j * (s + 1) + l] = G(j, l).imag();
-    }
-  return best;
+  g.resize((size_t)*J * (s + 1));
+  return g;
+}
+
+PolyPlan poly_blocks(const fq_ctx* c, int s, const std::vector<cld>& g, int J) {
+  PolyPlan p;
+  p.s = s;
+  p.J = J;
+  for (const cld& v : g) {
+    p.gr.push_back((double)v.real());
+    p.gi.push_back((double)v.imag());
+  }
+  return p;
+}
+PolyPlan poly_blocks(const fq_ctx* c, int s) {
+  int J;
+  const std::vector<cld> g = poly_coefficients(c, s, &J);
+  return poly_blocks(c, s, g, J);
+}
+
+// T_l = sigma_l + S_l.
+double poly_sigma(int l) { return l % 2 ? 0.0 : l % 4 ? -1.0 : 1.0; }
+
+// S_l = 2 S_a S_b - p S_a - q S_1, a = (l + 1) / 2, b = l / 2, from T_l = 2 T_a T_b - T_{a-b}.
+struct PolyStep {
+  int a, b;
+  double p, q;
+};
+PolyStep poly_step_of(int l) {
+  const int a = (l + 1) / 2, b = l / 2;
+  // 2 (sigma_a S_b + sigma_b S_a) with S_b = S_1 for l = 3, S_b = S_a for even l
+  const double p = -2.0 * poly_sigma(b) - (l % 2 ? 0.0 : 2.0 * poly_sigma(a));
+  const double q = l % 2 ? 1.0 - 2.0 * (b == 1 ? poly_sigma(a) : 0.0) : 0.0;
+  return {a, b, p, q};
+}
+
+// The same in the S_l. A number v in block j >= 1 would pass a product as v times the
+// identity: v T_s goes to block j - 1 and -v to block j - 2 instead, so that what is
+// left is a number in block 0, c0.
+PolyPlan poly_plan_s(const fq_ctx* c, int s) {
+  int J;
+  std::vector<cld> g = poly_coefficients(c, s, &J);
+  auto G = [&](int j, int l) -> cld& { return g[(size_t)j * (s + 1) + l]; };
+  cld c0 = 0.0L;
+  for (int j = J - 1; j >= 0; --j) {
+    cld v = G(j, 0);
+    for (int l = 1; l <= s; ++l) v += (long double)poly_sigma(l) * G(j, l);
+    G(j, 0) = 0.0L;
+    if (j == 0) c0 = v;
+    if (j >= 1) G(j - 1, s) += (j > 1 ? 2.0L : 1.0L) * v;
+    if (j >= 2) G(j - 2, 0) -= v;
+  }
+  PolyPlan p = poly_blocks(c, s, g, J);
+  p.c0.r = (double)c0.real();
+  p.c0.rl = (double)(c0.real() - p.c0.r);
+  p.c0.i = (double)c0.imag();
+  p.c0.il = (double)(c0.imag() - p.c0.i);
+  return p;
 }
 
 // The cheapest block length with at most nbuf matrices beside X (T_1 .. T_s,
@@ -1150,20 +1200,22 @@ PolyPlan poly_plan(const fq_ctx* c, int nbuf, double apply) {
       bs = s;
     }
   }
-  return bs ? poly_blocks(c, bs) : PolyPlan();
+  return bs ? poly_plan_s(c, bs) : PolyPlan();
 }
 
-// E = w[0] over the Ht in t[0], for `batch` matrices with stride bs: T_2 .. T_s
-// into t[1] .. t[s - 1], the blocks into w (which may take the place of T_1 ..
-// T_s-1; with more than one block T_s stays).
+// F = w[0] over the Ht in t[0], for `batch` matrices with stride bs: S_2 .. S_s
+// into t[1] .. t[s - 1], the blocks into w (which may take the place of S_1 ..
+// S_s-1; with more than one block S_s stays).
 fq_status poly_form(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& t,
                     const std::vector<double*>& w, int batch) {
   const int np = (int)c->np, s = p.s, J = p.J;
   const long bs = 2 * c->np * c->np;
   for (int l = 2; l <= s; ++l) {
     FQ_MARK(c, FQ_K_POLY);
-    FQ_HIP(c, fq::launch_poly_t(t[l / 2 - 1], t[(l + 1) / 2 - 1], l % 2 ? t[0] : nullptr, t[l - 1],
-                                (int)c->n, np, bs, batch, c->stream));
+    const PolyStep st = poly_step_of(l);
+    FQ_HIP(c, fq::launch_poly_t(t[st.b - 1], t[st.a - 1], st.p != 0.0 ? t[st.a - 1] : nullptr,
+                                st.p, st.q != 0.0 ? t[0] : nullptr, st.q, t[l - 1], np, bs, batch,
+                                c->stream));
   }
   fq::PolyCombine q{};
   q.s = s;
@@ -1180,19 +1232,20 @@ fq_status poly_form(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& t,
   FQ_HIP(c, fq::launch_poly_combine(q, c->n, np, bs, batch, c->stream));
   for (int j = J - 2; j >= 0; --j) {  // W_{j+1} T_s = T_s W_{j+1}
     FQ_MARK(c, FQ_K_POLY);
-    FQ_HIP(c, fq::launch_poly_block(w[j + 1], bs, t[s - 1], bs, true, j >= 1 ? 2.0 : 1.0,
-                                    j + 2 < J ? w[j + 2] : nullptr, true, w[j], bs, np, batch,
+    const double f = j >= 1 ? 2.0 : 1.0;
+    FQ_HIP(c, fq::launch_poly_block(w[j + 1], bs, t[s - 1], bs, true, f, f * poly_sigma(s),
+                                    j + 2 < J ? w[j + 2] : nullptr, 1.0, true, w[j], bs, np, batch,
                                     c->stream));
   }
   return FQ_OK;
 }
 
-// The same with the blocks in the place of T's no longer needed; E over Ht.
+// The same with the blocks in the place of S's no longer needed; F over Ht.
 fq_status poly_form_in_place(fq_ctx* c, const PolyPlan& p, const std::vector<double*>& b,
                              int batch) {
   std::vector<double*> w(p.J);
   for (int j = 0, at = 0; j < p.J; ++j, ++at) {
-    if (p.J > 1 && at == p.s - 1) ++at;  // T_s stays
+    if (p.J > 1 && at == p.s - 1) ++at;  // S_s stays
     w[j] = b[at];
   }
   return poly_form(c, p, b, w, batch);
@@ -1201,7 +1254,7 @@ fq_status poly_form_in_place(fq_ctx* c, const PolyPlan& p, const std::vector<dou
 // Matrices beside Ht, Y and the two P's that an FP64 step may use.
 int extra_mats(const fq_ctx* c) { return c->n_extra + (c->htx ? 2 : 0); }
 
-// One FP64 step X <- E_k X through E_k (Ht formed here).
+// One FP64 step X <- E_k X = c0 X + F_k X (Ht formed here).
 fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
   std::vector<double*> b{c->htr, c->par, c->pbr, c->yr};
   const size_t plane2 = 2 * (size_t)c->np * (size_t)c->np;
@@ -1214,10 +1267,11 @@ fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
   FQ_TRY(poly_form_in_place(c, p, b, 1));
   FQ_MARK(c, FQ_K_LAST);
   if (c->from_identity && k == 0)  // X = 1: the state-major E is E^T
-    FQ_HIP(c, fq::launch_transpose_planar(c->htr, c->hti, c->par, c->pai, c->np, 0, 1, c->stream));
+    FQ_HIP(c, fq::launch_transpose_planar(c->htr, c->hti, c->par, c->pai, c->np, 0, 1, c->stream,
+                                          c->n, p.c0.r, p.c0.i));
   else
-    FQ_HIP(c, fq::launch_poly_apply(c->xr, 0, c->htr, 0, false, c->par, 0, mrows, (int)c->np, 1,
-                                    c->stream));
+    FQ_HIP(c, fq::launch_poly_apply(c->xr, 0, c->htr, 0, false, p.c0, c->xr, 0, c->par, 0, mrows,
+                                    (int)c->np, 1, c->stream));
   std::swap(c->xr, c->par);
   std::swap(c->xi, c->pai);
   return FQ_OK;
@@ -1234,8 +1288,8 @@ fq_status multiply_up(fq_ctx* c, double* src, double* dst, double* alt, int cnt)
     const int pairs = cnt / 2;
     double* out = cnt == 2 ? c->xr : dst;
     FQ_MARK(c, FQ_K_LAST);
-    FQ_HIP(c, fq::launch_poly_apply(src, 2 * bs, src + bs, 2 * bs, true, out, bs, np, np, pairs,
-                                    c->stream));
+    FQ_HIP(c, fq::launch_poly_apply(src, 2 * bs, src + bs, 2 * bs, true, {}, nullptr, 0, out, bs, np,
+                                    np, pairs, c->stream));
     if (cnt % 2)
       FQ_HIP(c, hipMemcpyAsync(dst + (size_t)pairs * bs, src + (size_t)(cnt - 1) * bs, bytes,
                                hipMemcpyDeviceToDevice, c->stream));
@@ -1270,10 +1324,11 @@ fq_status dense_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
     FQ_MARK(c, FQ_K_LAST);
     if (t == 0) {  // X = 1
       FQ_HIP(c, fq::launch_transpose_planar(b[0], b[0] + bs / 2, x, x + bs / 2, c->np, bs, act,
-                                            c->stream));
+                                            c->stream, c->n, p.c0.r, p.c0.i));
       continue;
     }
-    FQ_HIP(c, fq::launch_poly_apply(x, bs, b[0], bs, false, b[1], bs, np, np, act, c->stream));
+    FQ_HIP(c, fq::launch_poly_apply(x, bs, b[0], bs, false, p.c0, x, bs, b[1], bs, np, np, act,
+                                    c->stream));
     if (act == nb) {
       std::swap(x, b[1]);
     } else {  // the segments without a step t keep their X in the old place
@@ -1784,8 +1839,8 @@ fq_status dense_poly_batches(fq_ctx* c, const PolyPlan& p, int nb, int k0, int k
     for (int z = 0; z < cnt; ++z) {
       if (hook) FQ_TRY(hook(k + z));
       FQ_MARK(c, FQ_K_LAST);
-      FQ_HIP(c, fq::launch_poly_apply(c->xr, 0, b[0] + (size_t)z * bs, 0, false, c->par, 0, mrows,
-                                      np, 1, c->stream));
+      FQ_HIP(c, fq::launch_poly_apply(c->xr, 0, b[0] + (size_t)z * bs, 0, false, p.c0, c->xr, 0,
+                                      c->par, 0, mrows, np, 1, c->stream));
       std::swap(c->xr, c->par);
       std::swap(c->xi, c->pai);
       FQ_TRY(dense_snapshot(c, k + z));
@@ -2278,9 +2333,9 @@ void grad_to_nodes(const fq_ctx* c, const std::vector<double>& g, double* grad_f
 //   dW_j = dQ_j + f_j (dT_s W_{j+1} + T_s dW_{j+1}) - dW_{j+2}
 //   => Wbar_{j+1} = f_j Wbar_j T_s - Wbar_{j-1},  Tbar_s += f_j W_{j+1} Wbar_j,
 //      Tbar_l += sum_j g_jl Wbar_j;
-// and through T_l = 2 T_a T_b - T_{a-b} with the Hermitian part S_l of Tbar_l,
-// all that Hermitian differentials see: Tbar_a += 2 T_b S_l, Tbar_b += 2 T_a S_l,
-// Tbar_{a-b} -= S_l. Tbar_1 is dL/dHt; its traces with the drive block are the
+// and through S_l = 2 S_a S_b - p S_a - q S_1 with the Hermitian part H_l of Tbar_l,
+// all that Hermitian differentials see: Tbar_a += 2 S_b H_l - p H_l, Tbar_b += 2 S_a H_l,
+// Tbar_1 -= q H_l. Tbar_1 is dL/dHt; its traces with the drive block are the
 // derivatives. For L = 8 that is 12 products a step with the forming of E twice,
 // where the term-by-term sweep takes 5 L to 6 L. A drive-optimisation step
 // (build and node derivatives) at N = 256, M = 64: 38.0 -> 4.85 ms, the build in
@@ -2304,7 +2359,7 @@ PolyPlan poly_plan_adjoint(const fq_ctx* c) {
       bs = s;
     }
   }
-  return bs ? poly_blocks(c, bs) : PolyPlan();
+  return bs ? poly_plan_s(c, bs) : PolyPlan();
 }
 
 // Segments of the gradient that need no tape (all P_t of the chain at once in the
@@ -2331,16 +2386,17 @@ struct AdjBuffers {
 fq_status poly_reverse(fq_ctx* c, const PolyPlan& p, const AdjBuffers& b, int batch) {
   const int np = (int)c->np, s = p.s, J = p.J;
   const long bs = 2 * c->np * c->np;
-  auto mul = [&](const double* x, const double* y, bool herm, double f, const double* sub, bool add,
-                 double* out) -> fq_status {
+  auto mul = [&](const double* x, const double* y, bool herm, double f, double fx,
+                 const double* sub, double fs, bool add, double* out) -> fq_status {
     FQ_MARK(c, FQ_K_ADJ_REV);
-    FQ_HIP(c, fq::launch_poly_block(x, bs, y, bs, herm, f, sub, add, out, bs, np, batch,
+    FQ_HIP(c, fq::launch_poly_block(x, bs, y, bs, herm, f, fx, sub, fs, add, out, bs, np, batch,
                                     c->stream));
     return FQ_OK;
   };
   auto fac = [](int j) { return j >= 1 ? 2.0 : 1.0; };
   for (int j = 0; j + 1 < J; ++j)
-    FQ_TRY(mul(b.wb[j], b.t[s - 1], true, fac(j), j ? b.wb[j - 1] : nullptr, false, b.wb[j + 1]));
+    FQ_TRY(mul(b.wb[j], b.t[s - 1], true, fac(j), fac(j) * poly_sigma(s), j ? b.wb[j - 1] : nullptr,
+               1.0, false, b.wb[j + 1]));
   fq::PolyCombine q{};
   q.s = J;
   q.J = s;
@@ -2355,26 +2411,28 @@ fq_status poly_reverse(fq_ctx* c, const PolyPlan& p, const AdjBuffers& b, int ba
   FQ_MARK(c, FQ_K_HEFF);
   FQ_HIP(c, fq::launch_poly_combine(q, c->n, np, bs, batch, c->stream));
   for (int j = 0; j + 1 < J; ++j)
-    FQ_TRY(mul(b.w[j + 1], b.wb[j], false, fac(j), nullptr, true, b.tb[s - 1]));
+    FQ_TRY(mul(b.w[j + 1], b.wb[j], false, fac(j), 0.0, nullptr, 0.0, true, b.tb[s - 1]));
   for (int l = s; l >= 2; --l) {
     double* sl = b.tb[l - 1];
     FQ_MARK(c, FQ_K_HEFF);
     FQ_HIP(c, fq::launch_hermitian_part(sl, np, bs, batch, c->stream));
-    const int a = (l + 1) / 2, d = l / 2;
-    if (a == d) {
-      FQ_TRY(mul(b.t[a - 1], sl, true, 4.0, nullptr, true, b.tb[a - 1]));
+    const PolyStep st = poly_step_of(l);
+    double *ta = b.t[st.a - 1], *td = b.t[st.b - 1];
+    const double* sp = st.p != 0.0 ? sl : nullptr;
+    if (st.a == st.b) {
+      FQ_TRY(mul(ta, sl, true, 4.0, 0.0, sp, st.p, true, b.tb[st.a - 1]));
       continue;
     }
-    FQ_TRY(mul(b.t[d - 1], sl, true, 2.0, nullptr, true, b.tb[a - 1]));
-    FQ_TRY(mul(b.t[a - 1], sl, true, 2.0, d == 1 ? sl : nullptr, true, b.tb[d - 1]));
-    if (d != 1) {  // Tbar_1 -= S_l
+    FQ_TRY(mul(td, sl, true, 2.0, 0.0, sp, st.p, true, b.tb[st.a - 1]));
+    FQ_TRY(mul(ta, sl, true, 2.0, 0.0, st.b == 1 ? sl : nullptr, st.q, true, b.tb[st.b - 1]));
+    if (st.b != 1) {  // the share of S_1
       fq::PolyCombine x{};
       x.s = 2;
       x.J = 1;
       x.t[0] = x.q[0] = b.tb[0];
       x.t[1] = sl;
       x.gr[0][1] = 1.0;
-      x.gr[0][2] = -1.0;
+      x.gr[0][2] = -st.q;
       FQ_MARK(c, FQ_K_HEFF);
       FQ_HIP(c, fq::launch_poly_combine(x, c->n, np, bs, batch, c->stream));
     }
@@ -2394,7 +2452,8 @@ fq_status adj_poly_step(fq_ctx* c, const PolyPlan& p, AdjBuffers& b, int t, int 
   AdjBuffers r = b;
   if (pt) {
     FQ_MARK(c, FQ_K_ADJ_REV);
-    FQ_HIP(c, fq::launch_poly_apply(pt, bs, b.m[0], bs, true, b.wb[0], bs, np, np, act, c->stream));
+    FQ_HIP(c, fq::launch_poly_apply(pt, bs, b.m[0], bs, true, {}, nullptr, 0, b.wb[0], bs, np, np,
+                                    act, c->stream));
   } else {
     r.wb[0] = b.m[0];
   }
@@ -2405,7 +2464,8 @@ fq_status adj_poly_step(fq_ctx* c, const PolyPlan& p, AdjBuffers& b, int t, int 
                                  c->d_grad, c->stream));
   if (last) return FQ_OK;
   FQ_MARK(c, FQ_K_ADJ_REV);
-  FQ_HIP(c, fq::launch_poly_apply(b.m[0], bs, b.w[0], bs, true, b.m[1], bs, np, np, act, c->stream));
+  FQ_HIP(c, fq::launch_poly_apply(b.m[0], bs, b.w[0], bs, true, p.c0, b.m[0], bs, b.m[1], bs, np,
+                                  np, act, c->stream));
   if (act == nb)
     std::swap(b.m[0], b.m[1]);
   else  // the members without this step keep their M in the old place
@@ -2446,7 +2506,8 @@ fq_status segment_ends(fq_ctx* c, const std::function<double*(int)>& S, double* 
   for (int i = 1; i < nb; ++i) {
     FQ_MARK(c, FQ_K_LAST);
     FQ_HIP(c, fq::launch_poly_apply(S(i - 1), Dz(nb - i) - S(i - 1), Xz(i - 1), S(nb - i) - Xz(i - 1),
-                                    true, Xz(i), Dz(nb - 1 - i) - Xz(i), np, np, 2, c->stream));
+                                    true, {}, nullptr, 0, Xz(i), Dz(nb - 1 - i) - Xz(i), np, np, 2,
+                                    c->stream));
   }
   return FQ_OK;
 }
@@ -2468,19 +2529,30 @@ fq_status adjoint_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
     FQ_MARK(c, FQ_K_HEFF);
     FQ_TRY(heff_f64(c, t, act, len0, rem, b.t[0]));
     std::vector<double*> w = b.w;
-    if (t == 0) w[0] = P[1];  // P_1 = E_1
+    if (t == 0) w[0] = P[1];  // P_1 = E_1 = c0 + F_1
     FQ_TRY(poly_form(c, p, b.t, w, act));
-    if (t == 0) continue;
+    if (t == 0) {
+      fq::PolyCombine x{};
+      x.s = x.J = 1;
+      x.t[0] = x.q[0] = P[1];
+      x.gr[0][0] = p.c0.r;
+      x.gi[0][0] = p.c0.i;
+      x.gr[0][1] = 1.0;
+      FQ_MARK(c, FQ_K_HEFF);
+      FQ_HIP(c, fq::launch_poly_combine(x, c->n, np, bs, act, c->stream));
+      continue;
+    }
     FQ_MARK(c, FQ_K_LAST);
-    FQ_HIP(c, fq::launch_poly_apply(w[0], bs, P[t], bs, true, P[t + 1], bs, np, np, act,
-                                    c->stream));
+    FQ_HIP(c, fq::launch_poly_apply(w[0], bs, P[t], bs, true, p.c0, P[t], bs, P[t + 1], bs, np, np,
+                                    act, c->stream));
   }
   FQ_HIP(c, fq::launch_identity_rows(X, X + bs / 2, c->n, np, np, c->stream));
   FQ_HIP(c, fq::launch_conj_planar(c->lam, np, D + (size_t)(nb - 1) * bs, c->stream));
   FQ_TRY(segment_ends(c, [&](int z) { return P[z < rem ? len0 + 1 : len0] + (size_t)z * bs; }, X, D,
                       nb));
   FQ_MARK(c, FQ_K_LAST);
-  FQ_HIP(c, fq::launch_poly_apply(X, bs, D, bs, true, b.m[0], bs, np, np, nb, c->stream));
+  FQ_HIP(c, fq::launch_poly_apply(X, bs, D, bs, true, {}, nullptr, 0, b.m[0], bs, np, np, nb,
+                                  c->stream));
   for (int t = len - 1; t >= 0; --t)
     FQ_TRY(adj_poly_step(c, p, b, t, t < len0 ? nb : rem, nb, len0, rem, P[t], t == 0));
   return FQ_OK;
@@ -2505,7 +2577,8 @@ fq_status adjoint_poly_tape(fq_ctx* c, const PolyPlan& p) {
       FQ_TRY(heff_f64(c, k, 1, 0, 0, b.t[0]));
       FQ_TRY(poly_form(c, p, b.t, b.w, 1));
       FQ_MARK(c, FQ_K_LAST);
-      FQ_HIP(c, fq::launch_poly_apply(b.w[0], 0, P(k), 0, true, P(k + 1), 0, np, np, 1, c->stream));
+      FQ_HIP(c, fq::launch_poly_apply(b.w[0], 0, P(k), 0, true, p.c0, P(k), 0, P(k + 1), 0, np, np,
+                                      1, c->stream));
     }
     for (int k = k1 - 1; k >= k0; --k)
       FQ_TRY(adj_poly_step(c, p, b, k, 1, 1, 0, 0, P(k), k == 0));

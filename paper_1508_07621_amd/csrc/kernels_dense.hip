@@ -122,25 +122,28 @@ struct EpiUnitarity {
 // ---- step operators as matrix polynomials ------------------------------------------------------
 // All matrices of a batch lie at base + z * bs, re plane then im plane.
 
-// T_{a+b} = 2 T_a T_b - T_{|a-b|} (T_0 = 1 on the n x n block when sub is null);
-// Hermitian, so an element above the diagonal is also written below it.
+// O = 2 acc - f1 S1 - f2 S2 (each S optional), Hermitian: an element above the diagonal is
+// also written below it.
 struct EpiPolyT {
   double* o;
-  const double* sub;
+  const double *s1, *s2;
   long ld, plane, bs;
-  int n;
+  double f1, f2;
   __device__ __forceinline__ void batch(int z) {
     o += z * bs;
-    if (sub) sub += z * bs;
+    if (s1) s1 += z * bs;
+    if (s2) s2 += z * bs;
   }
   __device__ __forceinline__ void herm(int m, int c, double ar, double ai, bool mirror) const {
     const long idx = (long)m * ld + c;
     double r = 2.0 * ar, i = 2.0 * ai;
-    if (sub) {
-      r -= sub[idx];
-      i -= sub[plane + idx];
-    } else if (m == c && m < n) {
-      r -= 1.0;
+    if (s1) {
+      r -= f1 * s1[idx];
+      i -= f1 * s1[plane + idx];
+    }
+    if (s2) {
+      r -= f2 * s2[idx];
+      i -= f2 * s2[plane + idx];
     }
     o[idx] = r;
     o[plane + idx] = i;
@@ -153,27 +156,33 @@ struct EpiPolyT {
   __device__ __forceinline__ void finish() const {}
 };
 
-// Clenshaw block and its adjoint: O = [O +] f * acc - S (S optional).
+// Clenshaw block and its adjoint: O = [O +] f acc + fa A - fs S (S optional, A the product's
+// first operand).
 struct EpiPolyBlock {
   double* o;
-  const double* sub;
-  long ld, plane, bs;
-  double f;
+  const double *a, *sub;
+  long ld, plane, bs, a_bs;
+  double f, fa, fs;
   bool add;
   __device__ __forceinline__ void batch(int z) {
     o += z * bs;
+    a += z * a_bs;
     if (sub) sub += z * bs;
   }
   __device__ __forceinline__ void operator()(int m, int c, double ar, double ai) const {
     const long idx = (long)m * ld + c;
     double r = f * ar, i = f * ai;
+    if (fa != 0.0) {
+      r = fma(fa, a[idx], r);
+      i = fma(fa, a[plane + idx], i);
+    }
     if (add) {
       r += o[idx];
       i += o[plane + idx];
     }
     if (sub) {
-      r -= sub[idx];
-      i -= sub[plane + idx];
+      r -= fs * sub[idx];
+      i -= fs * sub[plane + idx];
     }
     o[idx] = r;
     o[plane + idx] = i;
@@ -181,13 +190,25 @@ struct EpiPolyBlock {
   __device__ __forceinline__ void finish() const {}
 };
 
-// O = acc.
-struct EpiPolyStore {
+// O = acc + c0 X (X optional; c0 in two parts, see PolyScalar).
+struct EpiPolyApply {
   double* o;
-  long ld, plane, bs;
-  __device__ __forceinline__ void batch(int z) { o += z * bs; }
-  __device__ __forceinline__ void operator()(int m, int c, double ar, double ai) const {
-    const long idx = (long)m * ld + c;
+  const double* x;
+  long ld, plane, bs, x_bs;
+  PolyScalar c;
+  __device__ __forceinline__ void batch(int z) {
+    o += z * bs;
+    if (x) x += z * x_bs;
+  }
+  __device__ __forceinline__ void operator()(int m, int n, double ar, double ai) const {
+    const long idx = (long)m * ld + n;
+    if (x) {
+      const double xr = x[idx], xi = x[plane + idx];
+      ar = fma(c.rl, xr, fma(-c.il, xi, ar));
+      ai = fma(c.rl, xi, fma(c.il, xr, ai));
+      ar = fma(c.r, xr, fma(-c.i, xi, ar));
+      ai = fma(c.r, xi, fma(c.i, xr, ai));
+    }
     o[idx] = ar;
     o[plane + idx] = ai;
   }
@@ -920,12 +941,14 @@ inline unsigned grid_for(long total, int block) {
   return (unsigned)g;
 }
 
-// dst(j, i) = src(i, j) through 32 x 32 LDS tiles (one padding column).
+// dst(j, i) = src(i, j) (+ d on the diagonal of the n x n block) through 32 x 32 LDS tiles
+// (one padding column).
 __global__ __launch_bounds__(256) void transpose_planar_kernel(const double* __restrict__ sr,
                                                                const double* __restrict__ si,
                                                                double* __restrict__ dr,
                                                                double* __restrict__ di, long np,
-                                                               long bs) {
+                                                               long bs, long n, double d_re,
+                                                               double d_im) {
   __shared__ double tr[32][33], ti[32][33];
   sr += blockIdx.z * bs;
   si += blockIdx.z * bs;
@@ -939,8 +962,9 @@ __global__ __launch_bounds__(256) void transpose_planar_kernel(const double* __r
   }
   __syncthreads();
   for (int r = ty; r < 32; r += 8) {
-    dr[(bj + r) * np + bi + tx] = tr[tx][r];
-    di[(bj + r) * np + bi + tx] = ti[tx][r];
+    const bool diag = bj + r == bi + tx && bj + r < n;
+    dr[(bj + r) * np + bi + tx] = tr[tx][r] + (diag ? d_re : 0.0);
+    di[(bj + r) * np + bi + tx] = ti[tx][r] + (diag ? d_im : 0.0);
   }
 }
 
@@ -1044,12 +1068,13 @@ hipError_t launch_heff_f64(const HeffSum& h, const double* w, int t, int batch, 
   return hipGetLastError();
 }
 
-hipError_t launch_poly_t(const double* ta, const double* tb, const double* sub, double* out, int n,
-                         int np, long bs, int batch, hipStream_t s) {
+hipError_t launch_poly_t(const double* ta, const double* tb, const double* s1, double f1,
+                         const double* s2, double f2, double* out, int np, long bs, int batch,
+                         hipStream_t s) {
   const long plane = (long)np * np;
   // T_b(k, c) = conj(T_b(c, k))
   Operands op{ta, ta + plane, tb, tb + plane, np, np, 0, 0, bs, bs};
-  return launch_gemm_herm<false, true>(op, np, batch, EpiPolyT{out, sub, np, plane, bs, n}, s);
+  return launch_gemm_herm<false, true>(op, np, batch, EpiPolyT{out, s1, s2, np, plane, bs, f1, f2}, s);
 }
 
 hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, int batch,
@@ -1062,11 +1087,11 @@ hipError_t launch_poly_combine(const PolyCombine& p, long n, long ld, long bs, i
 }
 
 hipError_t launch_poly_block(const double* a, long a_bs, const double* b, long b_bs, bool b_herm,
-                             double f, const double* sub, bool add, double* out, long o_bs, int np,
-                             int batch, hipStream_t s) {
+                             double f, double fa, const double* sub, double fs, bool add,
+                             double* out, long o_bs, int np, int batch, hipStream_t s) {
   const long plane = (long)np * np;
   Operands op{a, a + plane, b, b + plane, np, np, 0, 0, a_bs, b_bs};
-  const EpiPolyBlock e{out, sub, np, plane, o_bs, f, add};
+  const EpiPolyBlock e{out, a, sub, np, plane, o_bs, a_bs, f, fa, fs, add};
   // (A B)(m, c) = sum_k A(m, k) B(k, c), B(k, c) = conj(B(c, k)) when Hermitian
   return b_herm ? launch_gemm<false, true>(op, np, np, batch, e, s)
                 : launch_gemm<false, false, true>(op, np, np, batch, e, s);
@@ -1100,10 +1125,11 @@ hipError_t launch_conj_planar(const double* src, int np, double* dst, hipStream_
 }
 
 hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,
-                             double* out, long o_bs, int mrows, int np, int batch, hipStream_t s) {
+                             const PolyScalar& c0, const double* base, long base_bs, double* out,
+                             long o_bs, int mrows, int np, int batch, hipStream_t s) {
   const long plane = (long)np * np;
   Operands op{x, x + plane, e, e + plane, np, np, 0, 0, x_bs, e_bs, mrows <= 64 && mrows < np};
-  const EpiPolyStore epi{out, np, plane, o_bs};
+  const EpiPolyApply epi{out, base, np, plane, o_bs, base_bs, c0};
   return e_trans ? launch_gemm<false, false, true>(op, mrows, np, batch, epi, s)
                  : launch_gemm<false, false>(op, mrows, np, batch, epi, s);
 }
@@ -1191,12 +1217,13 @@ hipError_t launch_weighted_sum(const WeightedSum& ws, long total, double* outr, 
 }
 
 hipError_t launch_transpose_planar(const double* sr, const double* si, double* dr, double* di,
-                                   long np, long bs, int batch, hipStream_t s) {
+                                   long np, long bs, int batch, hipStream_t s, long n, double d_re,
+                                   double d_im) {
   if (np < 32 || np % 32 != 0 || np / 32 > 65535 || batch < 1 || batch > 65535)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(transpose_planar_kernel,
                      dim3((unsigned)(np / 32), (unsigned)(np / 32), (unsigned)batch), dim3(256), 0,
-                     s, sr, si, dr, di, np, bs);
+                     s, sr, si, dr, di, np, bs, n, d_re, d_im);
   return hipGetLastError();
 }
 
