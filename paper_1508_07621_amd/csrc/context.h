@@ -8,7 +8,7 @@
 // Clenshaw's recurrence in T_s over the blocks Q_0 .. Q_J-1 (g: s + 1
 // coefficients of T_0 .. T_s per block, step phase included). FP64 plans hold the
 // propagator without its multiple c0 of the identity and the T_l as S_l = T_l - sigma_l
-// (coefficients of T_0 all zero, see poly_plan_s).
+// (see poly_plan_s).
 struct PolyPlan {
   int s = 0, J = 0;
   std::vector<double> gr, gi;

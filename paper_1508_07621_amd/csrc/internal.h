@@ -83,7 +83,7 @@ struct SmallChain {
   double* xi;
   long ld;                                     // np (must be 64)
   int n, L, k0, k1;
-  double beta, inv_dE, phr, phi;
+  double beta, inv_dE, phr, phi, phr_lo, phi_lo;
   // nseg > 1: the steps k0+1 .. k1 in nseg segments (the first rem of len0 + 1
   // steps, the others of len0), each propagating the identity into planes at
   // xr + z * bs, xi + z * bs
@@ -219,10 +219,8 @@ constexpr int kPolyMaxS = 6, kPolyMaxBlocks = 6;
 hipError_t launch_poly_t(const double* ta, const double* tb, const double* s1, double f1,
                          const double* s2, double f2, double* out, int np, long bs, int batch,
                          hipStream_t s);
-// The multiple c0 of the identity beside F, its parts as high + low doubles: rounded to one
-// it would be off by the same amount in every step.
 struct PolyScalar {
-  double r = 0.0, rl = 0.0, i = 0.0, il = 0.0;
+  double r = 0.0, i = 0.0;
 };
 // Q_q = sum_{l <= s} g_ql T_l, q < J (a Q may overwrite a T).
 struct PolyCombine {
@@ -259,9 +257,11 @@ hipError_t launch_trace_dot(const double* a, int np, long bs, int batch, const d
 // dst = conj(src), planar.
 hipError_t launch_conj_planar(const double* src, int np, double* dst, hipStream_t s);
 // State-major blocks times operators: out(j, i) = c0 base(j, i) + sum_k x(j, k) E(i, k) over
-// rows [0, mrows) (base null: no such term); e_trans: E is stored state-major, E(i, k) at
-// row k, column i.
-hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,
+// rows [0, mrows) (base null: no such term). POLY_STATES: E is stored state-major, E(i, k)
+// at row k, column i. POLY_STATES_SHIFTED: the same as c0 x + x (E - c0) with base = x, for an
+// E near c0 that is given as it is.
+enum PolyLayout { POLY_OPERATOR = 0, POLY_STATES = 1, POLY_STATES_SHIFTED = 2 };
+hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, int e_layout,
                              const PolyScalar& c0, const double* base, long base_bs, double* out,
                              long o_bs, int mrows, int np, int batch, hipStream_t s);
 // dst = src^T + d (on the diagonal of the n x n block) for np x np planar pairs (dst must not

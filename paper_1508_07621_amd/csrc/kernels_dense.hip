@@ -190,7 +190,7 @@ struct EpiPolyBlock {
   __device__ __forceinline__ void finish() const {}
 };
 
-// O = acc + c0 X (X optional; c0 in two parts, see PolyScalar).
+// O = acc + c0 X (X optional).
 struct EpiPolyApply {
   double* o;
   const double* x;
@@ -204,8 +204,6 @@ struct EpiPolyApply {
     const long idx = (long)m * ld + n;
     if (x) {
       const double xr = x[idx], xi = x[plane + idx];
-      ar = fma(c.rl, xr, fma(-c.il, xi, ar));
-      ai = fma(c.rl, xi, fma(c.il, xr, ai));
       ar = fma(c.r, xr, fma(-c.i, xi, ar));
       ai = fma(c.r, xi, fma(c.i, xr, ai));
     }
@@ -247,10 +245,10 @@ inline int split_rows(long m16, long n16, long batch) {
   return (m16 + 1) / 2 * n16 * batch <= 256 ? 32 : 0;
 }
 
-template <int FM, bool CONJ_A, bool CONJ_B, bool TRANS_B, class Epi>
+template <int FM, bool CONJ_A, bool CONJ_B, int LB, class Epi>
 hipError_t launch_split(const Operands& op, int mrows, int ncols, int batch, Epi epi,
                         hipStream_t s) {
-  hipLaunchKernelGGL((zgemm_split_kernel<FM, 8, CONJ_A, CONJ_B, TRANS_B, false, Epi>),
+  hipLaunchKernelGGL((zgemm_split_kernel<FM, 8, CONJ_A, CONJ_B, LB, false, Epi>),
                      dim3(ncols / 16, (mrows + 16 * FM - 1) / (16 * FM), batch), dim3(512), 0, s,
                      op, epi);
   return hipGetLastError();
@@ -274,38 +272,38 @@ hipError_t launch_few(const Operands& op, int mrows, int ncols, Epi epi, hipStre
     case 48:
     case 64:  // (48 rows: the second block's upper half is scratch rows below 64)
       return split_rows(mrows / 16, ncols / 16, 1) == 16
-                 ? launch_split<1, false, false, false>(op, mrows, ncols, 1, epi, s)
-                 : launch_split<2, false, false, false>(op, mrows, ncols, 1, epi, s);
+                 ? launch_split<1, false, false, B_ROWS>(op, mrows, ncols, 1, epi, s)
+                 : launch_split<2, false, false, B_ROWS>(op, mrows, ncols, 1, epi, s);
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 // C_z(m, n) over mrows x ncols (multiples of 64) for `batch` operand pairs.
-template <bool CONJ_A, bool CONJ_B, bool TRANS_B = false, class Epi>
+template <bool CONJ_A, bool CONJ_B, int LB = B_ROWS, class Epi>
 hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi epi,
                        hipStream_t s) {
   if (ncols % 64 != 0 || op0.kdim % 64 != 0 || batch < 1 || batch > 65535)
     return hipErrorInvalidValue;
-  if constexpr (!CONJ_A && !CONJ_B && !TRANS_B)
+  if constexpr (!CONJ_A && !CONJ_B && LB == B_ROWS)
     if (op0.few) return batch == 1 ? launch_few(op0, mrows, ncols, epi, s) : hipErrorInvalidValue;
   if (mrows % 64 != 0) return hipErrorInvalidValue;
   switch (op0.tiles ? 0 : split_rows(mrows / 16, ncols / 16, batch)) {
-    case 16: return launch_split<1, CONJ_A, CONJ_B, TRANS_B>(op0, mrows, ncols, batch, epi, s);
-    case 32: return launch_split<2, CONJ_A, CONJ_B, TRANS_B>(op0, mrows, ncols, batch, epi, s);
+    case 16: return launch_split<1, CONJ_A, CONJ_B, LB>(op0, mrows, ncols, batch, epi, s);
+    case 32: return launch_split<2, CONJ_A, CONJ_B, LB>(op0, mrows, ncols, batch, epi, s);
   }
   Operands op = op0;
   const long t64 = (long)(mrows / 64) * (ncols / 64) * batch;
   if (take_tile64(t64, 4 * t64)) {
     op.tiles_m = mrows / 64;
     op.tiles_n = ncols / 64;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, TRANS_B, true, false,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, LB, true, false,
                                             4, Epi>),
                        dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(512), 0, s, op, epi);
   } else {
     op.tiles_m = mrows / 32;
     op.tiles_n = ncols / 32;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, TRANS_B, true, false,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, LB, true, false,
                                             1, Epi>),
                        dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(256), 0, s, op, epi);
   }
@@ -322,16 +320,16 @@ hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hip
   const long t64 = a * (a + 1) / 2, t32 = b * (b + 1) / 2, t16 = c * (c + 1) / 2;
   Operands op = op0;
   if (t16 * batch <= 256)
-    hipLaunchKernelGGL((zgemm_split_kernel<1, 8, CONJ_A, CONJ_B, false, true, Epi>),
+    hipLaunchKernelGGL((zgemm_split_kernel<1, 8, CONJ_A, CONJ_B, B_ROWS, true, Epi>),
                        dim3(t16, 1, batch), dim3(512), 0, s, op0, epi);
   else if (take_tile64(t64 * batch, t32 * batch)) {
     op.tiles_n = (int)a;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, false, true, true, 4,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, B_ROWS, true, true, 4,
                                             Epi>),
                        dim3(tri_grid((int)a), batch), dim3(512), 0, s, op, epi);
   } else {
     op.tiles_n = (int)b;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, false, true, true, 1,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, B_ROWS, true, true, 1,
                                             Epi>),
                        dim3(tri_grid((int)b), batch), dim3(256), 0, s, op, epi);
   }
@@ -812,8 +810,9 @@ __global__ void fill_zero_kernel(double* __restrict__ p, long count) {
 // 2274 us per 100-step build in one segment); the segments' operators are multiplied up
 // afterwards. Per step a workgroup forms Ht_k = (H0 + a_k V + b_k K - beta) / dE in
 // LDS, runs the L Chebyshev terms with its 16 x 64 block of P_{l-1}, P_l in
-// LDS, keeps its share of the sum Y in registers, and ends the step with
-// X_k = exp(-i beta h) Y in LDS. One barrier per term, none between
+// LDS, keeps its share of the sum Y of the terms from P_1 on in registers (the large one,
+// c_0 X, is added once, last), and ends the step with X_k = exp(-i beta h) (c_0 X + Y) in LDS
+// (the phase in two parts: one part would be off alike in every step). One barrier per term, none between
 // workgroups; the only HBM traffic is the operators (L2-resident, 192 KB) and
 // the block of X read once and written once.
 // Wave j computes output columns i = 16 j .. 16 j + 15 of each product
@@ -867,7 +866,7 @@ __global__ __launch_bounds__(256) void small_chain_kernel(SmallChain c) {
       hs[1][i * kSmallLd + kk] = im;
     }
     __syncthreads();
-    double yr[4], yi[4];
+    double yr[4], yi[4], x0r[4], x0i[4];
     const int prv = cur ^ 1;  // P_{l-1} buffer (P_0 = X stays in `cur` for the first term)
     for (int l = 0; l < L; ++l) {
       // acc = Ht P_l for this lane's four (state, column) pairs; P_l in buffer `src`
@@ -898,8 +897,9 @@ __global__ __launch_bounds__(256) void small_chain_kernel(SmallChain c) {
           vr = accR[r];
           vi = accI[r];
           const double xr = ps[cur][0][idx], xi = ps[cur][1][idx];
-          yr[r] = c.coef[0] * xr - c.coef[1] * xi;
-          yi[r] = c.coef[0] * xi + c.coef[1] * xr;
+          x0r[r] = xr;
+          x0i[r] = xi;
+          yr[r] = yi[r] = 0.0;
         } else {
           vr = 2.0 * accR[r] - ps[dst][0][idx];
           vi = 2.0 * accI[r] - ps[dst][1][idx];
@@ -921,8 +921,10 @@ __global__ __launch_bounds__(256) void small_chain_kernel(SmallChain c) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int idx = (4 * r + kq) * kSmallLd + ci;
-      ps[xb][0][idx] = c.phr * yr[r] - c.phi * yi[r];
-      ps[xb][1][idx] = c.phr * yi[r] + c.phi * yr[r];
+      const double sr = c.coef[0] * x0r[r] - c.coef[1] * x0i[r] + yr[r];
+      const double si = c.coef[0] * x0i[r] + c.coef[1] * x0r[r] + yi[r];
+      ps[xb][0][idx] = fma(c.phr, sr, fma(-c.phi, si, c.phr_lo * sr - c.phi_lo * si));
+      ps[xb][1][idx] = fma(c.phr, si, fma(c.phi, sr, c.phr_lo * si + c.phi_lo * sr));
     }
     cur = xb;
   }
@@ -1094,7 +1096,7 @@ hipError_t launch_poly_block(const double* a, long a_bs, const double* b, long b
   const EpiPolyBlock e{out, a, sub, np, plane, o_bs, a_bs, f, fa, fs, add};
   // (A B)(m, c) = sum_k A(m, k) B(k, c), B(k, c) = conj(B(c, k)) when Hermitian
   return b_herm ? launch_gemm<false, true>(op, np, np, batch, e, s)
-                : launch_gemm<false, false, true>(op, np, np, batch, e, s);
+                : launch_gemm<false, false, B_TRANS>(op, np, np, batch, e, s);
 }
 
 hipError_t launch_hermitian_part(double* a, int np, long bs, int batch, hipStream_t s) {
@@ -1124,14 +1126,22 @@ hipError_t launch_conj_planar(const double* src, int np, double* dst, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, bool e_trans,
+hipError_t launch_poly_apply(const double* x, long x_bs, const double* e, long e_bs, int e_layout,
                              const PolyScalar& c0, const double* base, long base_bs, double* out,
                              long o_bs, int mrows, int np, int batch, hipStream_t s) {
   const long plane = (long)np * np;
   Operands op{x, x + plane, e, e + plane, np, np, 0, 0, x_bs, e_bs, mrows <= 64 && mrows < np};
   const EpiPolyApply epi{out, base, np, plane, o_bs, base_bs, c0};
-  return e_trans ? launch_gemm<false, false, true>(op, mrows, np, batch, epi, s)
-                 : launch_gemm<false, false>(op, mrows, np, batch, epi, s);
+  switch (e_layout) {
+    case POLY_OPERATOR: return launch_gemm<false, false>(op, mrows, np, batch, epi, s);
+    case POLY_STATES: return launch_gemm<false, false, B_TRANS>(op, mrows, np, batch, epi, s);
+    case POLY_STATES_SHIFTED:
+      if (base != x || base_bs != x_bs) return hipErrorInvalidValue;
+      op.sr = c0.r;
+      op.si = c0.i;
+      return launch_gemm<false, false, B_SHIFTED>(op, mrows, np, batch, epi, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_scale_planar(const double* sr, const double* si, double dr, double di,

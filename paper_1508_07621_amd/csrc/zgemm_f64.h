@@ -21,6 +21,11 @@ __device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// How B is stored: B_z(n, k) at row n, column k, or (B_TRANS) at row k, column n, so that
+// C = A B^T reads a state-major block as the operator it stands for. B_SHIFTED: B_TRANS
+// with a number subtracted from the diagonal.
+enum BLayout { B_ROWS = 0, B_TRANS = 1, B_SHIFTED = 2 };
+
 struct Operands {
   const double* ar;
   const double* ai;
@@ -34,6 +39,7 @@ struct Operands {
   long b_bs;
   bool few = false;  // few rows of A: take the kernels below rather than tiles
   bool tiles = false;  // tiles for more rows: sums over k in the same order in any block
+  double sr = 0.0, si = 0.0;  // B_SHIFTED: subtracted from B's diagonal
 };
 
 // One workgroup computes a BM x BN complex tile with WGM x WGN waves. K is
@@ -53,12 +59,14 @@ struct Operands {
 // HERM: C is known to be Hermitian: the grid holds the tiles on and above the
 // diagonal and the epilogue writes each element above it twice.
 //
-// TRANS_B: B is stored transposed, B_z(n, k) at row k, column n (so that
-// C = A B^T reads a state-major block as the operator it stands for); the
-// staging transposes it on the way into LDS.
-template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, bool TRANS_B,
-          bool GAUSS, bool HERM, int MINW, class Epi>
+// LB: with B_TRANS and B_SHIFTED the staging transposes B on the way into LDS. These
+// products multiply dense operators, where the rounding of the running sums is the whole
+// error: every 16 k the sums are added to totals and start again from zero (N = 256: 2.5
+// to 3 times less error, as do the eight partial sums of zgemm_split_kernel).
+template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, int LB, bool GAUSS,
+          bool HERM, int MINW, class Epi>
 __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Operands op, Epi epi) {
+  constexpr bool TRANS_B = LB != B_ROWS, FOLD = TRANS_B;
   constexpr int NT = WGM * WGN * 64;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int FM = WTM / 16, FN = WTN / 16;
@@ -69,6 +77,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   static_assert(BM * CPR % 64 == 0, "a wave's chunks belong to one operand");
   static_assert(BK % 8 == 0, "BK");
   static_assert(!HERM || BM == BN, "Hermitian products take square tiles");
+  static_assert(!FOLD || (GAUSS && (BK == 8 || BK == 16)), "sums of 16 k");
 
   __shared__ __attribute__((aligned(16))) double sh[2][2][(BM + BN) * S];  // [stage][re, im]
 
@@ -98,12 +107,19 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   for (int i = 0; i < SM; ++i)
 #pragma unroll
     for (int j = 0; j < SN; ++j) accS[i][j] = d4{0, 0, 0, 0};
+  constexpr int TM = FOLD ? FM : 1, TN = FOLD ? FN : 1;
+  d4 totR[TM][TN], totI[TM][TN];  // FOLD: Re, Im
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) totR[i][j] = totI[i][j] = d4{0, 0, 0, 0};
 
   // this thread's chunks: global addresses (at k = 0) and LDS offsets
   const double* gr[RC];
   const double* gi[RC];
   int lo[RC];
   bool of_a[RC];
+  int diag[RC];  // B_SHIFTED: column minus row of a chunk's first element at k = 0
 #pragma unroll
   for (int r = 0; r < RC; ++r) {
     const int c = tid + r * NT, row = c / CPR, col = 2 * (c % CPR);
@@ -115,6 +131,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
       const int cb = c - BM * CPR, kr = cb / (BN / 2), nc = 2 * (cb % (BN / 2));
       off = (long)kr * ld + n0 + nc + blockIdx.y * op.b_bs;
       lo[r] = (BM + nc) * S + kr;
+      diag[r] = n0 + nc - kr;
     }
     gr[r] = (is_a ? op.ar : op.br) + off;
     gi[r] = (is_a ? op.ai : op.bi) + off;
@@ -129,9 +146,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
       vi[r] = *reinterpret_cast<const d2*>(gi[r] + step);
     }
   };
-  auto lstore = [&](int st) {
+  auto lstore = [&](int st, int k0) {
 #pragma unroll
     for (int r = 0; r < RC; ++r) {
+      if constexpr (LB == B_SHIFTED) {
+        if (!of_a[r] && (diag[r] == k0 || diag[r] + 1 == k0)) {
+          const int e = diag[r] == k0 ? 0 : 1;
+          vr[r][e] -= op.sr;
+          vi[r][e] -= op.si;
+        }
+      }
       const bool neg = of_a[r] ? CONJ_A : CONJ_B;
       const d2 im = neg ? -vi[r] : vi[r];
       if (TRANS_B && !of_a[r]) {
@@ -148,12 +172,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
 
   const int nk = op.kdim / BK;
   gload(0);
-  lstore(0);
+  lstore(0, 0);
   if (nk > 1) gload(BK);
   __syncthreads();
   for (int kb = 0; kb < nk; ++kb) {
     const int cur = kb & 1;
-    if (kb + 1 < nk) lstore(cur ^ 1);  // that stage was last read before the previous barrier
+    if (kb + 1 < nk) lstore(cur ^ 1, (kb + 1) * BK);  // that stage was last read before the previous barrier
     if (kb + 2 < nk) gload((kb + 2) * BK);
     const int rr = lane & 15;
 #pragma unroll
@@ -212,6 +236,19 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
         }
       }
     }
+    if constexpr (FOLD) {
+      if (BK == 16 || (kb & 1)) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            d4& t3 = accS[i % SM][j % SN];
+            totR[i % TM][j % TN] += accR[i][j] - accI[i][j];
+            totI[i % TM][j % TN] += t3 - accR[i][j] - accI[i][j];
+            accR[i][j] = accI[i][j] = t3 = d4{0, 0, 0, 0};
+          }
+      }
+    }
     __syncthreads();
   }
 
@@ -226,7 +263,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
         const int m = m0 + wm * WTM + i * 16 + 4 * r + (lane >> 4);
         const int n = n0 + wn * WTN + j * 16 + (lane & 15);
         double re = accR[i][j][r], im = accI[i][j][r];
-        if constexpr (GAUSS) {
+        if constexpr (FOLD) {
+          re = totR[i % TM][j % TN][r];
+          im = totI[i % TM][j % TN][r];
+        } else if constexpr (GAUSS) {
           const double t1 = re, t2 = im;
           re = t1 - t2;
           im = accS[i % SM][j % SN][r] - t1 - t2;
@@ -248,10 +288,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
 // -> 3.9 us. What bounds it is the vector memory path: a fragment load touches 16
 // rows of 64 bytes (N = 2048, 16 rows: 31.8 us, the same without the MFMAs, 18 us
 // without the loads of A). Splitting the reduction over workgroups as well loses
-// to the device-scope fences that takes (124 us). HERM and TRANS_B as above.
-template <int FM, int W, bool CONJ_A, bool CONJ_B, bool TRANS_B, bool HERM, class Epi>
+// to the device-scope fences that takes (124 us). HERM and LB as above.
+template <int FM, int W, bool CONJ_A, bool CONJ_B, int LB, bool HERM, class Epi>
 __global__ __launch_bounds__(W * 64) void zgemm_split_kernel(Operands op, Epi epi) {
   static_assert(!HERM || FM == 1, "Hermitian products take square tiles");
+  constexpr bool TRANS_B = LB != B_ROWS;
   __shared__ double red[W][FM * 8][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int tm = blockIdx.y, tn = blockIdx.x;
@@ -276,6 +317,13 @@ __global__ __launch_bounds__(W * 64) void zgemm_split_kernel(Operands op, Epi ep
     if constexpr (TRANS_B) {
       fbr = d2{br[k * ld], br[(k + 1) * ld]};
       fbi = d2{bi[k * ld], bi[(k + 1) * ld]};
+      if constexpr (LB == B_SHIFTED) {
+        const int e = n0 + rr - kp - (int)k;  // the diagonal element of this pair, if 0 or 1
+        if (e == 0 || e == 1) {
+          fbr[e] -= op.sr;
+          fbi[e] -= op.si;
+        }
+      }
     } else {
       fbr = *reinterpret_cast<const d2*>(br + k);
       fbi = *reinterpret_cast<const d2*>(bi + k);

@@ -198,3 +198,26 @@ def test_batches_of_steps(fl, n, M, scheme):
         err, bound = _worst_column(X, part), _bound(ctx, n, M, scheme)
         print("[case] states", cols, "e_col", err, "bound", bound, flush=True)
         assert err < bound
+
+
+# Builds cut into segments whose operators are multiplied up. A product A B of the operators
+# of len steps each rounds three times elementwise, and sums the change of B, min(1, R len),
+# with eight or N / 16 partial sums: sqrt(12 + N / 10) u for a whole column (u^2 (4 / 3)
+# (8.5 + N / 32) in blocks of 16, u^2 N / 12 + 6 in eight parts)
+@pytest.mark.parametrize("n,M,T,segments", [(40, 60, 1.2, 30), (64, 100, 2.0, 50), (100, 100, 2.0, 100),
+                                            (199, 50, 1.0, 32), (256, 64, 1.28, 32), (500, 40, 0.8, 8)])
+def test_segments_multiplied_up(fl, n, M, T, segments):
+    print("[case] rounding, segments", n, M, T, flush=True)
+    kw = _problem(n, M, T, "magnus4")
+    ctx = fl.FloquetContext(**kw)
+    ref = _reference(fl, kw, ctx.report["L"], np.eye(n, dtype=complex))
+    R, u = ctx.report["R"], 2.0 ** -53
+    products, cnt, length = 0.0, segments, M / segments
+    while cnt > 1:
+        products += cnt // 2 * (9.0 + (12.0 + n / 10) * min(1.0, R * length) ** 2)
+        cnt, length = (cnt + 1) // 2, 2 * length
+    steps = M * (3.0 + 0.5 * R * math.sqrt(n)) ** 2
+    bound = u * math.sqrt(steps + products) + 0.5 * u * R * M
+    err = _worst_column(ctx.build_ut(), ref)
+    print("[case] L", ctx.report["L"], "e_col", err, "bound", bound, flush=True)
+    assert err < bound
