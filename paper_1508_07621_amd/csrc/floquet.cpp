@@ -1477,10 +1477,9 @@ double product_units(int tf) {
   return (tf == fq::TF_ACC ? 24 : tf == fq::TF_X3 ? 18 : tf == fq::TF_X2 ? 12 : 4) + 5.0;
 }
 
-// Formats and cost of the polynomial with blocks of length s: each product takes the
-// cheapest format whose own contribution to the error of the build is within an
-// allowance that shrinks until the root sum of squares meets the target, as for the
-// terms. false if a T needs more than three pieces or a block more than two.
+// Formats and cost of the polynomial with blocks of length s: the cheapest choice whose
+// contributions, root sum of squares over the products as over the terms, stay within
+// `tol`. false if that needs more than three pieces for a T or two for a block.
 bool mixed_poly_formats(const fq_ctx* c, int s, double tol, MixedPoly* out) {
   MixedPoly m;
   m.plan = poly_blocks(c, s);
@@ -1527,46 +1526,56 @@ bool mixed_poly_formats(const fq_ctx* c, int s, double tol, MixedPoly* out) {
   const long nk = c->np / 16;
   m.t_fmt.assign(s + 1, fq::TF_X3);
   m.b_fmt.assign(J, fq::TF_X3);
-  double allowance = tol;
-  for (int pass = 0; pass < 64; ++pass, allowance *= 0.7) {
-    double e2 = 0.0;
-    bool ok = true;
-    auto pick = [&](double weight, std::initializer_list<int> formats) {
-      for (int f : formats) {
-        const double e = weight * sm * term_error(f, nk);
-        if (e > allowance) continue;
-        e2 += e * e;
-        return f;
-      }
-      ok = false;
-      return (int)fq::TF_X1;
-    };
-    for (int l = 2; l <= s; ++l) m.t_fmt[l] = pick(d[l], {fq::TF_X1, fq::TF_X2, fq::TF_X3});
-    for (int j = 0; j + 1 < J; ++j)
-      m.b_fmt[j] = pick((j ? 2.0 : 1.0) * w[j + 1], {fq::TF_X1, fq::TF_X2});
-    m.x_fmt = pick(w[0], {fq::TF_X1, fq::TF_X2, fq::TF_X3, fq::TF_ACC});
-    if (!ok) return false;
-    m.err = std::sqrt(e2);
-    if (m.err <= tol) break;
-  }
-  if (m.err > tol) return false;
-  m.form = 2.0;  // the combination
+  // every choice of formats: T_2 .. T_s in up to three pieces, the products that complete
+  // blocks J - 2 .. 0 in up to two, the one with X in all
+  struct Product {
+    int* fmt;
+    double weight, share;
+    std::vector<int> formats;
+  };
+  std::vector<Product> prods;
   for (int l = 2; l <= s; ++l)
-    m.form += 0.65 * product_units(m.t_fmt[l]);
-  for (int j = 0; j + 1 < J; ++j) m.form += product_units(m.b_fmt[j]);
+    prods.push_back({&m.t_fmt[l], d[l], 0.65, {fq::TF_X1, fq::TF_X2, fq::TF_X3}});
+  for (int j = 0; j + 1 < J; ++j)
+    prods.push_back({&m.b_fmt[j], (j ? 2.0 : 1.0) * w[j + 1], 1.0, {fq::TF_X1, fq::TF_X2}});
+  prods.push_back({&m.x_fmt, w[0], 1.0, {fq::TF_X1, fq::TF_X2, fq::TF_X3, fq::TF_ACC}});
+  std::vector<int> best(prods.size()), cur(prods.size());
+  double best_cost = 0.0, best_e2 = 0.0;
+  std::function<void(size_t, double, double)> search = [&](size_t i, double cost, double e2) {
+    if (e2 > tol * tol || (best_cost > 0.0 && cost >= best_cost)) return;
+    if (i == prods.size()) {
+      best = cur;
+      best_cost = cost;
+      best_e2 = e2;
+      return;
+    }
+    for (int f : prods[i].formats) {
+      const double e = prods[i].weight * sm * term_error(f, nk);
+      cur[i] = f;
+      search(i + 1, cost + prods[i].share * product_units(f), e2 + e * e);
+    }
+  };
+  search(0, 2.0, 0.0);  // (2: the combination)
+  if (best_cost == 0.0) return false;
+  for (size_t i = 0; i < prods.size(); ++i) *prods[i].fmt = best[i];
+  m.err = std::sqrt(best_e2);
+  m.form = best_cost - product_units(m.x_fmt);
   *out = m;
   return true;
 }
 
 // The cheapest polynomial for the present drive (empty when none meets the target
-// or the caller fixed the formats).
+// or the caller fixed the formats), with an estimated error no larger than the
+// target and than that of the terms' own schedule: steps of small R meet the target with
+// formats well below it, and a polynomial at the target would be up to three times
+// further off (520 states, 200 steps: e_col 4.1e-7, terms 1.4e-7; with this bound 1.3e-7).
 void choose_mixed_poly(fq_ctx* c, double tol) {
   c->mpoly = MixedPoly();
   for (int s = 2; s <= std::min(4, c->L); ++s) {
     const int J = (c->L + s - 1) / s;
     if (J > 4 || (s == 2 && J > 1)) continue;  // (a block needs T_s itself)
     MixedPoly m;
-    if (!mixed_poly_formats(c, s, tol, &m)) continue;
+    if (!mixed_poly_formats(c, s, std::min(tol, c->mixed_err_est), &m)) continue;
     if (c->mpoly.plan.s == 0 || m.form + product_units(m.x_fmt) <
                                     c->mpoly.form + product_units(c->mpoly.x_fmt))
       c->mpoly = m;

@@ -1,0 +1,45 @@
+"""Split-BF16 builds by step polynomials: how far they are from the FP64 build, against the
+estimate that their formats were chosen for."""
+import math
+
+import numpy as np
+import pytest
+
+from workloads import gue
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fl(require_gpu):
+    from paper_1508_07621_amd import floquet
+    floquet.node_times(1.0, 1)          # loads the library or raises
+    return floquet
+
+
+def _build(fl, n, M, omega, tol):
+    import torch
+    rng = np.random.default_rng(n + M)
+    T = 2.0 * math.pi / omega
+    kw = dict(h0=gue(n, rng), hmod=gue(n, rng), T=T, M=M,
+              f_nodes=np.cos(omega * fl.node_times(T, M)))
+    exact = fl.FloquetContext(precision="fp64", **kw).build_ut()
+    ctx = fl.FloquetContext(precision="bf16x3", mixed_tol=tol, **kw)
+    terms = ctx.report["mixed_err_est"]  # of the schedule of terms, before a build
+    U = ctx.build_ut()
+    rep = ctx.last_report
+    err = torch.linalg.vector_norm(U - exact, dim=0).max().item()
+    print("[case] L", rep["L"], "e_col", err, "estimates", terms, rep["mixed_err_est"],
+          "formats", rep["term_format"][:8], flush=True)
+    return err, terms, rep["mixed_err_est"]
+
+
+# steps of small R, whose terms stay well below the target: a polynomial is taken only at
+# an estimate no larger than theirs, and stays below that estimate
+@pytest.mark.parametrize("tol", [0.0, 1e-6])
+@pytest.mark.parametrize("n,M,omega", [(520, 200, 1.0), (1030, 200, 1.0), (1500, 100, 1.0)])
+def test_polynomial_no_further_off_than_the_terms(fl, n, M, omega, tol):
+    print("[case] split-BF16 estimate", n, M, omega, tol, flush=True)
+    err, terms, est = _build(fl, n, M, omega, tol)
+    assert est <= terms * (1 + 1e-12)
+    assert err < terms
