@@ -987,9 +987,14 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
   const int aoff = arow * 32 + 16 * ((lane >> 5) ^ ((arow >> 3) & 1));
   const int boff = NL * SA + brow * 32 + 16 * ((lane >> 5) ^ ((brow >> 3) & 1));
 
-  f16v cre, cim;
+  // the sums of Ar B and of Ai B; three pieces keep them apart (one running sum of both
+  // rounds twice as often on sums of the same size)
+  constexpr int NS = NPC == 3 ? 2 : 1;
+  f16v cre[NS], cim[NS];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) cre[r] = cim[r] = 0.f;
+  for (int i = 0; i < NS; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) cre[i][r] = cim[i][r] = 0.f;
 
   gload(0, st[0]);
 #pragma unroll
@@ -1020,10 +1025,10 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
 #pragma unroll
         for (int i = w; i >= 0; --i) {
           const int j = w - i;
-          cre = mfma32_bf16(fa[i], fb[j], cre);
-          cim = mfma32_bf16(POLY ? ma[i] : fa[i], fb[NPC + j], cim);
-          cre = mfma32_bf16(POLY ? fa[NPC + i] : ma[i], fb[NPC + j], cre);
-          cim = mfma32_bf16(fa[NPC + i], fb[j], cim);
+          cre[0] = mfma32_bf16(fa[i], fb[j], cre[0]);
+          cim[0] = mfma32_bf16(POLY ? ma[i] : fa[i], fb[NPC + j], cim[0]);
+          cre[NS - 1] = mfma32_bf16(POLY ? fa[NPC + i] : ma[i], fb[NPC + j], cre[NS - 1]);
+          cim[NS - 1] = mfma32_bf16(fa[NPC + i], fb[j], cim[NS - 1]);
         }
       // the next k-block into the other buffer (last read before the previous
       // barrier), the one D further into its registers
@@ -1041,8 +1046,8 @@ __global__ __launch_bounds__(256, 2) void cheb_s4_kernel(Bf3Args g) {
     const int col = wn * 32 + (lane & 31);
     const int slot = ((col >> 3) & 1) ^ ((row >> 3) & 1);
     const int f = ((col >> 4) * BM + row) * 16 + 8 * slot + (col & 7);
-    ere[f] = cre[r];
-    eim[f] = cim[r];
+    ere[f] = NS == 2 ? cre[0][r] + cre[NS - 1][r] : cre[0][r];
+    eim[f] = NS == 2 ? cim[0][r] + cim[NS - 1][r] : cim[0][r];
   }
   __syncthreads();
   if constexpr (POLY) {
