@@ -102,7 +102,8 @@ struct fq_ctx {
   // of a build run as one batch; extra: further matrices of a single step.
   std::vector<std::pair<const double*, const double*>> heff_ops;
   std::vector<int> heff_slot;
-  double* d_w = nullptr;
+  double* d_w = nullptr;  // null: the weights go with the launches (PLAN_LEAN)
+  int w_stride = 0;
   double* pool = nullptr;
   int pool_mats = 0;
   double* extra = nullptr;
@@ -120,7 +121,6 @@ struct fq_ctx {
   double* d_tab = nullptr;            // tridiagonal: rows of every step (resident columns)
   double* d_fgrid = nullptr;          // tridiagonal: the period average's drive samples
   double* d_etab = nullptr;           // tridiagonal averages: operator rows in lane order
-  double* d_ext = nullptr;            // tridiagonal: extreme eigenvalues of every step
   double* d_stream = nullptr;         // tridiagonal n > resident size: two 8-plane states
   double* d_adj = nullptr;            // streamed reverse sweep: 10 complex n x n vectors
   double* d_vec = nullptr;            // 3 n doubles: period-average accumulators

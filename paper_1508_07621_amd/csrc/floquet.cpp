@@ -153,7 +153,7 @@ struct Layout {
          off_seg = 0, off_stack = 0, off_lam = 0, off_grad = 0, off_gauge = 0, off_stream = 0,
          off_adj = 0,
          off_comm6 = 0, off_vec = 0, off_drive32 = 0, off_w = 0, off_pool = 0, off_extra = 0,
-         off_ext = 0, off_tab = 0, off_fgrid = 0, off_etab = 0, off_store = 0, off_theta = 0, off_adj_mats = 0;
+         off_tab = 0, off_fgrid = 0, off_etab = 0, off_store = 0, off_theta = 0, off_adj_mats = 0;
   long np = 0;
   int n_tape = 0;
   TridiagAdjPlan tri_adj;
@@ -170,7 +170,8 @@ constexpr long kBf16F64Np = 512;
 // workgroups per CU (N = 256: 32 segments), kPoolBufs matrices each, within
 // kPoolBytes. Above, a single step fills the chip and two matrices beyond the
 // propagation's own planes extend the polynomials it can take. Both keep inside
-// the static scratch of the one-shot build wherever the rest does.
+// the static scratch of the one-shot build wherever the rest does, and a problem that
+// fits there only without any such scratch is planned without (PLAN_LEAN).
 constexpr int kPoolBufs = 6, kExtraBufs = 2, kPoolSegments = 128;
 constexpr size_t kPoolBudget = size_t(250) << 20, kPoolBytes = size_t(144) << 20;
 constexpr size_t kStaticBytes = size_t(256) << 20;  // the one-shot build's static scratch
@@ -230,8 +231,20 @@ TridiagAdjPlan tridiag_adj_plan(long n, long M, long ckpt) {
   return p;
 }
 
-Layout plan(const fq_system* sys, const fq_params* par) {
+// Operators in H_eff: H0, then Hmod and K (the nine commutators), or the drive block.
+int heff_terms(const fq_system* sys, const fq_params* par) {
+  const int S = drive_terms(sys);
+  if (S > 1) return 1 + drive_block(S, par->scheme);
+  return par->scheme == FQ_MAGNUS6 ? 2 + kComm6 : 3;
+}
+
+// PLAN_LEAN: nothing beyond the planes and tables that a build cannot do without; steps
+// then run one by one, from weights passed with each launch.
+enum PlanTier { PLAN_FULL, PLAN_LEAN };
+
+Layout plan(const fq_system* sys, const fq_params* par, PlanTier tier) {
   Layout lay;
+  const bool lean = tier == PLAN_LEAN;
   size_t cur = 0;
   auto take = [&](size_t bytes) {
     size_t o = cur;
@@ -293,10 +306,10 @@ Layout plan(const fq_system* sys, const fq_params* par) {
       lay.off_y = take(plane2);
     }
     lay.off_gauge = take(2 * sizeof(double) * (size_t)n * (size_t)Ms);
-    lay.off_ext = take(2 * sizeof(double) * (size_t)Ms);
-    lay.off_fgrid = take(sizeof(double) * (size_t)Ms);
-    if (n <= fq::tridiag_resident_max_n())
+    if (!lean && n <= fq::tridiag_resident_max_n()) {
+      lay.off_fgrid = take(sizeof(double) * (size_t)Ms);
       lay.off_etab = take(3 * sizeof(double) * (size_t)pad_to(n, fq::tridiag_chain_rows(n)));
+    }
     const bool streamed_grad = streamed_adjoint(sys, par);
     const size_t n16 = (size_t)(n + 15) / 16 * 16;
     const size_t splane = sizeof(double) * n16 * (size_t)n;  // one state plane
@@ -328,13 +341,13 @@ Layout plan(const fq_system* sys, const fq_params* par) {
       }
     }
   }
-  if (dense_like(sys->layout))  // (whole blocks of 64 steps)
-    lay.off_w = take(fq::kHeffTerms * sizeof(double) * (size_t)pad_to(Ms, 64));
+  if (dense_like(sys->layout) && !lean)  // (in whole 8 KiB)
+    lay.off_w = take((size_t)pad_to((long)sizeof(double) * heff_terms(sys, par) * Ms, 8192));
   lay.off_small = take(64 * sizeof(double));
   lay.off_vec = take(3 * sizeof(double) * (size_t)n);
   lay.off_ab = take(2 * sizeof(double) * (size_t)Ms);
   lay.off_coef = take(2 * sizeof(double) * (size_t)(kMaxOrder + 1));
-  if (!dense_like(sys->layout) && n <= fq::tridiag_resident_max_n()) {
+  if (!dense_like(sys->layout) && n <= fq::tridiag_resident_max_n() && !lean) {
     // segments of a build and their products; then the rows of every step, while
     // both keep inside the static scratch (or the rest does not anyway)
     const size_t plane2 = 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np;
@@ -360,19 +373,18 @@ Layout plan(const fq_system* sys, const fq_params* par) {
   }
   if (lay.adj_mats > 0)
     lay.off_seg = take(lay.adj_mats * 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np);
-  if (dense_like(sys->layout) && par->n_term_formats == 0 &&
+  if (dense_like(sys->layout) && !lean && par->n_term_formats == 0 &&
       (par->precision != FQ_BF16X3 || lay.np <= kBf16F64Np)) {
     const size_t plane2 = 2 * sizeof(double) * (size_t)lay.np * (size_t)lay.np;
     // (a gradient tape is never in the static scratch)
-    const size_t left = par->checkpoint_every > 0 ? kPoolBudget
-                        : kPoolBudget > cur       ? kPoolBudget - cur
-                                                  : 0;
+    const bool held = par->checkpoint_every > 0;
+    const size_t left = held ? kPoolBudget : kPoolBudget > cur ? kPoolBudget - cur : 0;
     if (lay.np < 1024) {
       lay.pool_mats = (int)std::min<size_t>(kPoolBufs * (size_t)pool_segments(lay.np),
                                             std::min(left, kPoolBytes) / plane2);
       if (lay.pool_mats > 0) lay.off_pool = take(plane2 * (size_t)lay.pool_mats);
     } else if (par->precision == FQ_FP64) {  // (others have two matrices more already)
-      lay.n_extra = left == 0 || par->checkpoint_every > 0
+      lay.n_extra = held || cur > kStaticBytes
                         ? kExtraBufs
                         : (int)std::min<size_t>(kExtraBufs, left / plane2);
       if (lay.n_extra > 0) lay.off_extra = take(plane2 * (size_t)lay.n_extra);
@@ -380,6 +392,15 @@ Layout plan(const fq_system* sys, const fq_params* par) {
   }
   lay.total = cur;
   return lay;
+}
+
+// The plan that fq_workspace_bytes reports: all the scratch, but none where that alone
+// would put a one-shot build beyond its static array.
+Layout plan(const fq_system* sys, const fq_params* par) {
+  const Layout full = plan(sys, par, PLAN_FULL);
+  if (par->checkpoint_every > 0 || full.total <= kStaticBytes) return full;
+  const Layout lean = plan(sys, par, PLAN_LEAN);
+  return lean.total <= kStaticBytes ? lean : full;
 }
 
 fq_status validate(const fq_system* sys, const fq_params* par) {
@@ -876,12 +897,15 @@ fq_status dense_inner_bounds(fq_ctx* ctx, double* lo_out, double* hi_out) {
 // Exact extremes over all steps, and the gauge factors of every step for the
 // kernels' real-symmetric form of Ht_s (reads the step scalars in d_ab).
 fq_status tridiag_cover(fq_ctx* ctx, double* lo_out, double* hi_out) {
-  FQ_HIP(ctx, fq::launch_tridiag_setup(ctx->n, ctx->M, ctx->sys.h0_diag, ctx->sys.h0_off,
-                                       ctx->sys.hmod_diag, ctx->d_ab, ctx->d_ext, ctx->d_gauge,
-                                       ctx->stream));
+  // (2 M extremes in the place of the 2 n M factors, formed after they are read)
+  FQ_HIP(ctx, fq::launch_tridiag_extremes(ctx->n, ctx->M, ctx->sys.h0_diag, ctx->sys.h0_off,
+                                          ctx->sys.hmod_diag, ctx->d_ab, ctx->d_gauge,
+                                          ctx->stream));
   std::vector<double> ext(2 * (size_t)ctx->M);
-  FQ_HIP(ctx, copy_sync(ctx->stream, ext.data(), ctx->d_ext, ext.size() * sizeof(double),
+  FQ_HIP(ctx, copy_sync(ctx->stream, ext.data(), ctx->d_gauge, ext.size() * sizeof(double),
                         hipMemcpyDeviceToHost));
+  FQ_HIP(ctx, fq::launch_tridiag_gauge(ctx->n, ctx->M, ctx->sys.h0_off, ctx->sys.hmod_diag,
+                                       ctx->d_ab, ctx->d_gauge, ctx->stream));
   double lo = std::numeric_limits<double>::infinity(), hi = -lo;
   for (int k = 0; k < ctx->M; ++k) {
     lo = std::min(lo, ext[2 * k]);
@@ -936,9 +960,30 @@ fq_status collect_profile(fq_ctx* c) {
 
 // ---- dense step loop ----------------------------------------------------------------------------
 
-// FP64 Ht of step t of `batch` segments (see launch_heff_f64) at out + z bs.
+// Weights of the operators of H_eff in (sub)step k (see upload_heff_weights).
+void heff_weights(const fq_ctx* c, int k, double* w) {
+  w[0] = 1.0;
+  if (c->S > 1) {
+    std::copy_n(&c->wS[(size_t)c->J * k], c->J, w + 1);
+    return;
+  }
+  w[1] = c->a[k];
+  if (c->scheme == FQ_MAGNUS6)
+    std::copy_n(&c->w6[(size_t)kComm6 * k], kComm6, w + 2);
+  else
+    w[2] = c->b[k];
+}
+
+// FP64 Ht of step t of `batch` segments (see launch_heff_f64) at out + z bs; without a
+// table of weights on the device one step at a time.
 fq_status heff_f64(fq_ctx* c, int t, int batch, int len0, int rem, double* out) {
   fq::HeffSum h{};
+  if (!c->d_w) {
+    double w[fq::kHeffTerms];
+    heff_weights(c, t, w);
+    for (size_t j = 0; j < c->heff_ops.size(); ++j) h.w[j] = w[c->heff_slot[j]];
+  }
+  h.stride = c->w_stride;
   for (size_t j = 0; j < c->heff_ops.size(); ++j) {
     h.re[j] = c->heff_ops[j].first;
     h.im[j] = c->heff_ops[j].second;
@@ -2395,7 +2440,7 @@ PolyPlan poly_plan_adjoint(const fq_ctx* c) {
 // Segments of the gradient that need no tape (all P_t of the chain at once in the
 // gradient's scratch); 0 where they do not fit or one product fills the chip.
 int adj_segments(const fq_ctx* c, const PolyPlan& p) {
-  if (!p.s || c->np >= 1024 || !c->adj_mats) return 0;
+  if (!p.s || c->np >= 1024 || !c->adj_mats || !c->d_w) return 0;
   // one launch of the two chains over the segments costs as much as a step's
   // batch, so no more segments than steps in each
   int nb = (int)std::min<long>(pool_segments(c->np), c->M);
@@ -3036,7 +3081,6 @@ fq_status fq_workspace_bytes(const fq_system* sys, const fq_params* par, size_t*
 // whose weight vanishes in every step is left out of the sum.
 static fq_status upload_heff_weights(fq_ctx* c) {
   const size_t plane = (size_t)c->np * (size_t)c->np;
-  std::vector<double> w((size_t)fq::kHeffTerms * c->M, 0.0);
   std::vector<std::pair<const double*, const double*>> ops{{c->h0r, c->h0i}};
   if (c->S > 1) {
     for (int j = 0; j < c->J; ++j) ops.push_back({c->vr + j * plane, c->vi + j * plane});
@@ -3048,30 +3092,22 @@ static fq_status upload_heff_weights(fq_ctx* c) {
     else
       ops.push_back({c->kr, c->ki});
   }
-  for (int k = 0; k < c->M; ++k) {
-    double* wk = &w[(size_t)fq::kHeffTerms * k];
-    wk[0] = 1.0;
-    if (c->S > 1) {
-      std::copy_n(&c->wS[(size_t)c->J * k], c->J, wk + 1);
-    } else {
-      wk[1] = c->a[k];
-      if (c->scheme == FQ_MAGNUS6)
-        std::copy_n(&c->w6[(size_t)kComm6 * k], kComm6, wk + 2);
-      else
-        wk[2] = c->b[k];
-    }
-  }
+  const size_t stride = ops.size();
+  c->w_stride = (int)stride;
+  std::vector<double> w(stride * c->M);
+  for (int k = 0; k < c->M; ++k) heff_weights(c, k, &w[stride * k]);
   c->heff_ops.clear();
   c->heff_slot.clear();
-  for (int j = 0; j < (int)ops.size(); ++j) {
+  for (size_t j = 0; j < stride; ++j) {
     bool used = false;
-    for (int k = 0; k < c->M && !used; ++k) used = w[(size_t)fq::kHeffTerms * k + j] != 0.0;
+    for (int k = 0; k < c->M && !used; ++k) used = w[stride * k + j] != 0.0;
     if (!used) continue;
     c->heff_ops.push_back(ops[j]);
-    c->heff_slot.push_back(j);
+    c->heff_slot.push_back((int)j);
   }
-  FQ_HIP(c, copy_sync(c->stream, c->d_w, w.data(), w.size() * sizeof(double),
-                      hipMemcpyHostToDevice));
+  if (c->d_w)
+    FQ_HIP(c, copy_sync(c->stream, c->d_w, w.data(), w.size() * sizeof(double),
+                        hipMemcpyHostToDevice));
   return FQ_OK;
 }
 
@@ -3207,7 +3243,8 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
   *out = nullptr;
   fq_status st = validate(sys, par);
   if (st != FQ_OK) return st;
-  const Layout lay = plan(sys, par);
+  Layout lay = plan(sys, par);
+  if (ws_bytes < lay.total) lay = plan(sys, par, PLAN_LEAN);
   if (!workspace) return fail(FQ_ERR_ARG, "workspace is null");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0)
     return fail(FQ_ERR_ARG, "workspace must be %zu-byte aligned", kAlign);
@@ -3264,9 +3301,10 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
       c->yr = P(lay.off_y);   c->yi = c->yr + plane;
     }
     c->d_gauge = P(lay.off_gauge);
-    c->d_ext = P(lay.off_ext);
-    c->d_fgrid = P(lay.off_fgrid);
-    if (c->n <= fq::tridiag_resident_max_n()) c->d_etab = P(lay.off_etab);
+    if (lay.off_fgrid) {
+      c->d_fgrid = P(lay.off_fgrid);
+      c->d_etab = P(lay.off_etab);
+    }
     if (lay.off_tab) c->d_tab = P(lay.off_tab);
     if (lay.tri_adj.nb > 0 && !lay.off_adj) {
       c->adj_seg = lay.tri_adj.nb;
@@ -3303,7 +3341,7 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
     if (par->precision != FQ_FP64) c->htx = P(lay.off_htx);
     if (par->precision != FQ_FP64) c->pcr = P(lay.off_pc);
     if (par->scheme == FQ_MAGNUS6) c->comm6 = P(lay.off_comm6);
-    c->d_w = P(lay.off_w);
+    if (lay.off_w) c->d_w = P(lay.off_w);
     if (lay.pool_mats > 0) {
       c->pool = P(lay.off_pool);
       c->pool_mats = lay.pool_mats;
@@ -3577,7 +3615,7 @@ fq_status floquet_period_average(fq_ctx* c, const void* X0, int64_t ncols, const
       return FQ_OK;
     };
     FQ_TRY(dense_steps(c, 0, c->M, (int)rows, false, energies));
-  } else if (c->n <= fq::tridiag_resident_max_n()) {  // inside the chain's one launch
+  } else if (c->d_fgrid) {  // resident columns: inside the chain's one launch
     FQ_HIP(c, copy_sync(c->stream, c->d_fgrid, f_grid, sizeof(double) * (size_t)c->M_user,
                         hipMemcpyHostToDevice));
     fq::TridiagJob job = tridiag_job(c);

@@ -192,12 +192,15 @@ hipError_t launch_identity_rows(double* re, double* im, long n, long m, long ld,
 // Rescaled Hamiltonians Ht_z = (sum_j w[k_z][slot_j] M_j - beta 1) / dE on the
 // n x n block, z < batch, written to out + z * bs (re plane, then im plane).
 // k_z = z len0 + min(z, rem) + t: step t of segment z when the chain is cut into
-// segments (a single one: len0 = rem = 0). w: device, kHeffTerms weights per step.
+// segments (a single one: len0 = rem = 0). w: device, h.stride weights per step; null: h.w
+// serves every member.
 constexpr int kHeffTerms = 16;
 struct HeffSum {
   const double* re[kHeffTerms];
   const double* im[kHeffTerms];
   int slot[kHeffTerms];  // weight of M_j
+  double w[kHeffTerms];  // the weights themselves, without a table
+  int stride;            // weights per step in the table
   int count;
   int len0, rem;
 };
@@ -485,11 +488,13 @@ hipError_t launch_tridiag_adj_persist(const TridiagAdjStream& p, const double* t
 hipError_t launch_tridiag_stream(const TridiagJob& job, const TridiagStream& st, hipStream_t s);
 
 // Per (sub)step k: extremes[2k], [2k + 1] = the smallest and the largest
-// eigenvalue of H_eff,k, and the unit gauge factors gauge[k][i] (complex): w_0 =
+// eigenvalue of H_eff,k; the unit gauge factors gauge[k][i] (complex): w_0 =
 // 1, w_{i+1} = w_i conj(u_i) with u_i = e_i / |e_i| the phase of Ht[i][i+1] (u_i = 1
 // where e_i = 0). All pointers device memory.
-hipError_t launch_tridiag_setup(long n, int M, const double* h0_diag, const void* h0_off,
-                                const double* v_diag, const double* ab, double* extremes,
-                                double* gauge, hipStream_t s);
+hipError_t launch_tridiag_extremes(long n, int M, const double* h0_diag, const void* h0_off,
+                                   const double* v_diag, const double* ab, double* extremes,
+                                   hipStream_t s);
+hipError_t launch_tridiag_gauge(long n, int M, const void* h0_off, const double* v_diag,
+                                const double* ab, double* gauge, hipStream_t s);
 
 }  // namespace fq

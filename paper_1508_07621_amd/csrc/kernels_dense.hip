@@ -348,7 +348,7 @@ __global__ __launch_bounds__(256) void heff_kernel(HeffSum h, const double* __re
                                                    double* __restrict__ out, long bs) {
   const int z = blockIdx.y;
   const long k = (long)z * h.len0 + (z < h.rem ? z : h.rem) + t;
-  const double* wk = w + k * kHeffTerms;
+  const double* wk = w ? w + k * h.stride : nullptr;
   const long plane = ld * ld;
   double* o = out + z * bs;
   const long half = ld / 2, total = ld * half;  // padding included: zero in the operators
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void heff_kernel(HeffSum h, const double* __re
     const long i = e / half, c = 2 * (e - i * half), idx = i * ld + c;
     double r0 = 0.0, r1 = 0.0, i0 = 0.0, i1 = 0.0;
     for (int j = 0; j < h.count; ++j) {
-      const double wj = wk[h.slot[j]];
+      const double wj = wk ? wk[h.slot[j]] : h.w[j];
       const d2 a = *reinterpret_cast<const d2*>(h.re[j] + idx);
       const d2 b = *reinterpret_cast<const d2*>(h.im[j] + idx);
       r0 = fma(wj, a[0], r0);
@@ -1063,7 +1063,8 @@ hipError_t launch_identity_rows(double* re, double* im, long n, long m, long ld,
 
 hipError_t launch_heff_f64(const HeffSum& h, const double* w, int t, int batch, double beta,
                            double dE, long n, long ld, double* out, long bs, hipStream_t s) {
-  if (h.count < 1 || h.count > kHeffTerms || batch < 1 || batch > 65535 || ld % 2 != 0)
+  if (h.count < 1 || h.count > kHeffTerms || batch < 1 || batch > 65535 || ld % 2 != 0 ||
+      (!w && batch != 1))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(heff_kernel, dim3(grid_for(ld * (ld / 2), 256), batch), dim3(256), 0, s, h, w,
                      t, beta, 1.0 / dE, n, ld, out, bs);

@@ -2301,15 +2301,21 @@ __global__ __launch_bounds__(128) void tridiag_adj_persist_kernel(TridiagAdjStre
 
 }  // namespace
 
-hipError_t launch_tridiag_setup(long n, int M, const double* h0_diag, const void* h0_off,
-                                const double* v_diag, const double* ab, double* extremes,
-                                double* gauge, hipStream_t s) {
+hipError_t launch_tridiag_extremes(long n, int M, const double* h0_diag, const void* h0_off,
+                                   const double* v_diag, const double* ab, double* extremes,
+                                   hipStream_t s) {
   if (n < 1 || M < 1 || (n > 1 && !h0_off)) return hipErrorInvalidValue;
-  const double2* off = reinterpret_cast<const double2*>(h0_off);
-  hipLaunchKernelGGL(tridiag_extremes_kernel, dim3((unsigned)M), dim3(128), 0, s, n, h0_diag, off,
-                     v_diag, ab, extremes);
-  hipLaunchKernelGGL(tridiag_gauge_table_kernel, dim3((unsigned)M), dim3(256), 0, s, n, off, v_diag,
-                     ab, reinterpret_cast<double2*>(gauge));
+  hipLaunchKernelGGL(tridiag_extremes_kernel, dim3((unsigned)M), dim3(128), 0, s, n, h0_diag,
+                     reinterpret_cast<const double2*>(h0_off), v_diag, ab, extremes);
+  return hipGetLastError();
+}
+
+hipError_t launch_tridiag_gauge(long n, int M, const void* h0_off, const double* v_diag,
+                                const double* ab, double* gauge, hipStream_t s) {
+  if (n < 1 || M < 1 || (n > 1 && !h0_off)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(tridiag_gauge_table_kernel, dim3((unsigned)M), dim3(256), 0, s, n,
+                     reinterpret_cast<const double2*>(h0_off), v_diag, ab,
+                     reinterpret_cast<double2*>(gauge));
   return hipGetLastError();
 }
 
