@@ -188,8 +188,9 @@ typedef struct fq_params {
   double tol;                /* truncation tolerance used when L == 0 (> 0) */
   int32_t precision;         /* fq_precision (FQ_TRIDIAG supports FQ_FP64 only) */
   int32_t checkpoint_every;  /* > 0: floquet_build_UT keeps X_0, X_s, X_2s, ...
-                                (s = checkpoint_every) for floquet_grad;
-                                0 = no tape. FQ_MAGNUS4 only. */
+                                (s = checkpoint_every) for floquet_grad, or what
+                                else that needs (see fq_workspace_bytes);
+                                0 = no gradient. FQ_MAGNUS4 and FQ_CF4. */
   int32_t profile;           /* 1: time every kernel launch of a build with HIP
                                 events on the library's stream and report the
                                 per-kind sums in fq_report; 0: off */
@@ -327,15 +328,26 @@ fq_status fq_tridiag_extremes(int64_t n, const double* d, const double* e_abs,
  * lo, hi: host. Runs on the host. */
 fq_status fq_hermitian_cover(int64_t n, const void* a, double* lo, double* hi);
 
-/* Bytes of device workspace a context for (sys, par) needs (256-byte aligned
- * pointer expected). Checks the arguments like fq_create. */
+/* Bytes of device workspace with which a context for (sys, par) runs fastest
+ * (256-byte aligned pointer expected). Beyond the minimum below they hold scratch: up to
+ * 144 MiB for batches of steps, step rows of tridiagonal chains (up to 2 GiB), and for
+ * gradients up to 4 GiB for segments of the chain (dense below 1024 states, tridiagonal up
+ * to 1024; these use no tape, whatever checkpoint_every) or, for larger dense problems, 26
+ * matrices of n x n. Checks the arguments like fq_create. */
 fq_status fq_workspace_bytes(const fq_system* sys, const fq_params* par, size_t* bytes);
+
+/* The least workspace that fq_create takes: operators, propagation planes, step tables, and
+ * with checkpoint_every = s the tape (X_0, X_s, ..) and three matrices per step of one of
+ * its segments. Calls then run step by step; a workspace between the two sizes is used as
+ * far as it goes. */
+fq_status fq_workspace_min_bytes(const fq_system* sys, const fq_params* par, size_t* bytes);
 
 /* Create a context: validates, computes K (FQ_MAGNUS6: the nine nested
  * commutators), the spectral interval, R, L, the Bessel weights and the node
  * scalars (host FP64 except the commutators, which are formed on the device
  * with FP64 matrix products). The operator arrays of sys must stay valid and unchanged for
- * the life of the context. workspace: device, ws_bytes >= fq_workspace_bytes.
+ * the life of the context. workspace: device, ws_bytes >=
+ * fq_workspace_min_bytes (fq_workspace_bytes for the fastest forms).
  * stream: a hipStream_t (NULL = default stream). */
 fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par,
                     void* workspace, size_t ws_bytes, void* stream);

@@ -88,7 +88,8 @@ struct fq_ctx {
   int n_tape = 0;
   // gradient: per segment step X_{k-1}, P_{L-1}, P_L; two stacks; Lambda; d/da, d/db per step
   double* seg = nullptr;
-  double* adj_pool = nullptr;         // the same memory as adj_mats matrices (step polynomials)
+  long seg_mats = 0;                  // ... of this many matrices (also for step polynomials)
+  double* adj_pool = nullptr;         // tape and seg as adj_mats matrices (the sweep in segments)
   long adj_mats = 0;
   double* stack[2] = {nullptr, nullptr};
   double* lam = nullptr;

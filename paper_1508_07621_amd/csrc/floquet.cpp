@@ -158,7 +158,7 @@ struct Layout {
   int n_tape = 0;
   TridiagAdjPlan tri_adj;
   int pool_mats = 0, n_extra = 0;
-  size_t adj_mats = 0;
+  size_t adj_mats = 0, seg_mats = 0;
 };
 
 // Split-BF16 contexts up to this padded size run in FP64 (see runs_f64).
@@ -222,7 +222,9 @@ TridiagAdjPlan tridiag_adj_plan(long n, long M, long ckpt) {
     }
     p.g = p.nb;
   } else {
-    const long len = std::max(ckpt, std::min(16L, M));
+    // a segment's four matrices are what a tape holds for as many checkpoints: four
+    // times their spacing, while the store of that many steps fits
+    const long len = std::min(M, std::max({ckpt, 16L, std::min(4 * ckpt, (long)(kTridiagStore / step))}));
     p.nb = (int)((M + len - 1) / len);
     const long fit = (long)(kTridiagStore / (step * (size_t)len));
     p.g = (int)std::max(1L, std::min<long>({p.nb, fit, (long)std::ceil(slots / n)}));
@@ -238,9 +240,11 @@ int heff_terms(const fq_system* sys, const fq_params* par) {
   return par->scheme == FQ_MAGNUS6 ? 2 + kComm6 : 3;
 }
 
-// PLAN_LEAN: nothing beyond the planes and tables that a build cannot do without; steps
-// then run one by one, from weights passed with each launch.
-enum PlanTier { PLAN_FULL, PLAN_LEAN };
+// PLAN_TAPE: gradients from the tape only (no segments of the chain). PLAN_LEAN: nothing
+// beyond the planes and tables that a build cannot do without (a gradient: the tape and
+// three matrices per step of a checkpoint segment); steps then run one by one, from weights
+// passed with each launch.
+enum PlanTier { PLAN_FULL, PLAN_TAPE, PLAN_LEAN };
 
 Layout plan(const fq_system* sys, const fq_params* par, PlanTier tier) {
   Layout lay;
@@ -280,16 +284,16 @@ Layout plan(const fq_system* sys, const fq_params* par, PlanTier tier) {
     if (par->scheme == FQ_MAGNUS6) lay.off_comm6 = take(kComm6 * plane2);
     if (par->checkpoint_every > 0) {
       lay.n_tape = (Ms + cks - 1) / cks + 1;
-      lay.off_tape = take(plane2 * (size_t)lay.n_tape);
-      // the segment store of the term-by-term sweep, or the scratch of the step
-      // polynomials (and, with every P_t of the chain, of the sweep in segments)
-      size_t mats = 3 * (size_t)cks;
-      if (kAdjBufs * plane2 <= kAdjBudget) {
-        mats = std::max(mats, kAdjBufs + (size_t)cks);
-        const size_t all = (size_t)std::min(pool_segments(lay.np), Ms) * (kAdjBufs + 3) + Ms;
-        if (lay.np < 1024 && all * plane2 <= kAdjSegBudget) mats = std::max(mats, all);
-      }
-      lay.adj_mats = mats;
+      // the tape, and the segment store of the term-by-term sweep or the scratch of the
+      // step polynomials; in their place, with every P_t of the chain, the sweep in
+      // segments, which needs no tape
+      lay.seg_mats = 3 * (size_t)cks;
+      if (!lean && kAdjBufs * plane2 <= kAdjBudget)
+        lay.seg_mats = std::max(lay.seg_mats, kAdjBufs + (size_t)cks);
+      lay.adj_mats = (size_t)lay.n_tape + lay.seg_mats;
+      const size_t all = (size_t)std::min(pool_segments(lay.np), Ms) * (kAdjBufs + 3) + Ms;
+      if (tier == PLAN_FULL && lay.np < 1024 && all * plane2 <= kAdjSegBudget)
+        lay.adj_mats = std::max(lay.adj_mats, all);
       lay.off_stack = take(4 * plane2);
       lay.off_lam = take(plane2);
       lay.off_grad = take((size_t)J * sizeof(double) * (size_t)Ms);
@@ -316,7 +320,7 @@ Layout plan(const fq_system* sys, const fq_params* par, PlanTier tier) {
     if (n > fq::tridiag_resident_max_n() || streamed_grad)  // two 8-plane states, per-step rows
       lay.off_stream = take(2 * 8 * splane + sizeof(double) * 6 * n16);
     // (the environment's switch adds the streamed sweep's buffers to these)
-    if (par->checkpoint_every > 0) lay.tri_adj = tridiag_adj_plan(n, Ms, cks);
+    if (par->checkpoint_every > 0 && tier == PLAN_FULL) lay.tri_adj = tridiag_adj_plan(n, Ms, cks);
     if (lay.tri_adj.nb > 0) {
       // the segments' operators; these operator-major and X state-major, X, Lambda^+
       // (a build multiplies the operators up there)
@@ -392,6 +396,18 @@ Layout plan(const fq_system* sys, const fq_params* par, PlanTier tier) {
   }
   lay.total = cur;
   return lay;
+}
+
+// The first plan that fits `bytes`, or the smallest of all (usually the leanest; segments of a
+// tridiagonal gradient can take less than a tape with few checkpoints).
+Layout plan_within(const fq_system* sys, const fq_params* par, size_t bytes) {
+  Layout least = plan(sys, par, PLAN_LEAN);
+  for (PlanTier tier : {PLAN_FULL, PLAN_TAPE}) {
+    const Layout lay = plan(sys, par, tier);
+    if (lay.total <= bytes) return lay;
+    if (lay.total < least.total) least = lay;
+  }
+  return least;
 }
 
 // The plan that fq_workspace_bytes reports: all the scratch, but none where that alone
@@ -2549,10 +2565,9 @@ fq_status adj_poly_step(fq_ctx* c, const PolyPlan& p, AdjBuffers& b, int t, int 
   return FQ_OK;
 }
 
-// Buffers of nb members from the gradient's scratch; *next: what follows them.
-AdjBuffers adj_carve(fq_ctx* c, const PolyPlan& p, int nb, double** next) {
+// Buffers of nb members from `at` on; *next: what follows them.
+AdjBuffers adj_carve(fq_ctx* c, const PolyPlan& p, int nb, double* at, double** next) {
   const size_t step = (size_t)nb * 2 * (size_t)c->np * (size_t)c->np;
-  double* at = c->adj_pool;
   auto take = [&]() {
     double* r = at;
     at += step;
@@ -2594,7 +2609,7 @@ fq_status adjoint_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
   const int np = (int)c->np, len0 = c->M / nb, rem = c->M % nb, len = len0 + (rem ? 1 : 0);
   const long bs = 2 * c->np * c->np;
   double* at;
-  AdjBuffers b = adj_carve(c, p, nb, &at);
+  AdjBuffers b = adj_carve(c, p, nb, c->adj_pool, &at);
   std::vector<double*> P(len + 1, nullptr);  // P[t]: the nb matrices P_t, t >= 1
   for (int t = 1; t <= len; ++t, at += (size_t)nb * bs) P[t] = at;
   double* X = at;
@@ -2639,7 +2654,7 @@ fq_status adjoint_poly_tape(fq_ctx* c, const PolyPlan& p) {
   const int np = (int)c->np, s = c->ckpt;
   const long bs = 2 * c->np * c->np;
   double* at;
-  AdjBuffers b = adj_carve(c, p, 1, &at);
+  AdjBuffers b = adj_carve(c, p, 1, c->seg, &at);
   FQ_HIP(c, fq::launch_conj_planar(c->lam, np, b.m[0], c->stream));
   for (int sg = (c->M + s - 1) / s - 1; sg >= 0; --sg) {
     const int k0 = sg * s, k1 = std::min(c->M, k0 + s);
@@ -2667,7 +2682,7 @@ int adj_mode(const fq_ctx* c, PolyPlan* p, int* nb) {
   *p = poly_plan_adjoint(c);
   *nb = adj_segments(c, *p);
   if (*nb > 0) return 1;
-  return p->s && adj_bufs(*p) + c->ckpt <= c->adj_mats ? 2 : 0;
+  return p->s && adj_bufs(*p) + c->ckpt <= c->seg_mats ? 2 : 0;
 }
 
 fq_status adjoint(fq_ctx* c, const void* U_bar, double* grad_f_nodes) {
@@ -3076,6 +3091,14 @@ fq_status fq_workspace_bytes(const fq_system* sys, const fq_params* par, size_t*
   return FQ_OK;
 }
 
+fq_status fq_workspace_min_bytes(const fq_system* sys, const fq_params* par, size_t* bytes) {
+  fq_status st = validate(sys, par);
+  if (st != FQ_OK) return st;
+  if (!bytes) return fail(FQ_ERR_ARG, "bytes is null");
+  *bytes = plan_within(sys, par, 0).total;
+  return FQ_OK;
+}
+
 // The matrices of H_eff and their weights per (sub)step: slot 0 H0, then Hmod
 // and K, the drive block, or Hmod and the nine nested commutators. A matrix
 // whose weight vanishes in every step is left out of the sum.
@@ -3243,8 +3266,7 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
   *out = nullptr;
   fq_status st = validate(sys, par);
   if (st != FQ_OK) return st;
-  Layout lay = plan(sys, par);
-  if (ws_bytes < lay.total) lay = plan(sys, par, PLAN_LEAN);
+  const Layout lay = plan_within(sys, par, ws_bytes);
   if (!workspace) return fail(FQ_ERR_ARG, "workspace is null");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0)
     return fail(FQ_ERR_ARG, "workspace must be %zu-byte aligned", kAlign);
@@ -3351,10 +3373,11 @@ fq_status fq_create(fq_ctx** out, const fq_system* sys, const fq_params* par, vo
       c->n_extra = lay.n_extra;
     }
     if (lay.n_tape > 0) {
-      c->tape = P(lay.off_tape);
+      c->tape = c->adj_pool = P(lay.off_seg);
       c->n_tape = lay.n_tape;
-      c->seg = c->adj_pool = P(lay.off_seg);
       c->adj_mats = (long)lay.adj_mats;
+      c->seg = c->tape + 2 * plane * (size_t)lay.n_tape;
+      c->seg_mats = (long)lay.seg_mats;
       c->stack[0] = P(lay.off_stack);
       c->stack[1] = c->stack[0] + 4 * plane;
       c->lam = P(lay.off_lam);

@@ -173,6 +173,13 @@ def _marshal(self, *, T: float, M: int, f_nodes, h0=None, hmod=None, h0_eigenval
     self._sys, self._par = sysd, par
 
 
+def _free_bytes(device) -> int:
+    """Device memory that a torch allocation can still get."""
+    torch = _torch()
+    free, _ = torch.cuda.mem_get_info(device)
+    return free + torch.cuda.memory_reserved(device) - torch.cuda.memory_allocated(device)
+
+
 class FloquetContext:
     """One problem H(t) = H0 + f(t) Hmod on one GPU, set up once, built many times.
 
@@ -204,8 +211,12 @@ class FloquetContext:
         L_ = lib()
         sysd, par = self._sys, self._par
         import ctypes
-        nbytes = ctypes.c_size_t(0)
+        nbytes, least = ctypes.c_size_t(0), ctypes.c_size_t(0)
         check(L_.fq_workspace_bytes(ctypes.byref(sysd), ctypes.byref(par), ctypes.byref(nbytes)))
+        check(L_.fq_workspace_min_bytes(ctypes.byref(sysd), ctypes.byref(par), ctypes.byref(least)))
+        # the scratch beyond the minimum: while it takes no more than half of what that leaves
+        if nbytes.value - least.value > (_free_bytes(self.device) - least.value) // 2:
+            nbytes = least
         self.workspace = torch.empty(int(nbytes.value), dtype=torch.uint8, device=self.device)
         self._stream = torch.cuda.current_stream(self.device)
         handle = ctypes.c_void_p()

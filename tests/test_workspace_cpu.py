@@ -105,3 +105,42 @@ def test_tridiagonal_problems_that_fit_the_static_array(scheme, reortho):
             needs = _tridiag_needs(n, M, scheme, reortho)
             _check(_system(n, _abi.FQ_TRIDIAG), _params(M, scheme, reortho=reortho), needs,
                    (n, M, scheme, reortho))
+
+
+# ---- gradients -----------------------------------------------------------------------------------
+
+def _least(s, p):
+    n = ctypes.c_size_t(0)
+    assert _abi.lib().fq_workspace_min_bytes(ctypes.byref(s), ctypes.byref(p), ctypes.byref(n)) == 0
+    return n.value
+
+
+def _grad_needs(n, M, scheme, every, tridiag):
+    """The tape and three matrices per step of a checkpoint segment; dense also the two
+    stacks of the term-by-term sweep, Lambda and the accumulators."""
+    sub = 2 if scheme == _abi.FQ_CF4 else 1
+    steps, seg = M * sub, every * sub
+    tape = -(-steps // seg) + 1
+    np_ = _pad(n, 128 if n > 1984 else 64)
+    if tridiag:
+        return _tridiag_needs(n, M, scheme, 0) + 16 * n * n * (tape + 3 * seg) + 16 * steps
+    return _dense_needs(n, M, scheme, 1, 0) + 16 * np_ * np_ * (tape + 3 * seg + 5) + 16 * steps
+
+
+# the least workspace follows the caller's checkpoint spacing; the recommended one adds at
+# most the scratch that the header names
+@pytest.mark.parametrize("scheme", [_abi.FQ_MAGNUS4, _abi.FQ_CF4])
+@pytest.mark.parametrize("tridiag", [False, True])
+def test_gradient_workspace_follows_the_checkpoints(scheme, tridiag):
+    layout = _abi.FQ_TRIDIAG if tridiag else _abi.FQ_DENSE
+    for n in (16, 256, 400, 960, 1000, 1500, 2048) + (() if tridiag else (10000,)):
+        for M, every in ((64, 1), (64, 8), (128, 16), (100, 100), (5000, 16), (5000, 100)):
+            s, p = _system(n, layout), _params(M, scheme, checkpoint_every=every)
+            label = (n, M, every, scheme, tridiag)
+            needs, least, full = _grad_needs(n, M, scheme, every, tridiag), _least(s, p), _bytes(s, p)
+            assert least <= min(needs + 4096, full), label
+            np_ = _pad(n, 128 if n > 1984 else 64)
+            scratch = (144 << 20) + (2 << 30) + (5 << 30) + 26 * 16 * np_ * np_
+            if tridiag:  # four matrices per segment in the place of the tape
+                scratch += max(0, needs - 3 * 16 * n * n * every)
+            assert full <= needs + scratch, (label, needs, full)
