@@ -297,14 +297,14 @@ hipError_t launch_gemm(const Operands& op0, int mrows, int ncols, int batch, Epi
   if (take_tile64(t64, 4 * t64)) {
     op.tiles_m = mrows / 64;
     op.tiles_n = ncols / 64;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, LB, true, false,
-                                            4, Epi>),
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, LB, false, 4,
+                                            Epi>),
                        dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(512), 0, s, op, epi);
   } else {
     op.tiles_m = mrows / 32;
     op.tiles_n = ncols / 32;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, LB, true, false,
-                                            1, Epi>),
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, LB, false, 1,
+                                            Epi>),
                        dim3(grid_rows(op.tiles_m) * op.tiles_n, batch), dim3(256), 0, s, op, epi);
   }
   return hipGetLastError();
@@ -324,12 +324,12 @@ hipError_t launch_gemm_herm(const Operands& op0, int np, int batch, Epi epi, hip
                        dim3(t16, 1, batch), dim3(512), 0, s, op0, epi);
   else if (take_tile64(t64 * batch, t32 * batch)) {
     op.tiles_n = (int)a;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, B_ROWS, true, true, 4,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<64, 64, 8, 2, 4, CONJ_A, CONJ_B, B_ROWS, true, 4,
                                             Epi>),
                        dim3(tri_grid((int)a), batch), dim3(512), 0, s, op, epi);
   } else {
     op.tiles_n = (int)b;
-    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, B_ROWS, true, true, 1,
+    hipLaunchKernelGGL((zgemm_nt_f64_kernel<32, 32, 16, 2, 2, CONJ_A, CONJ_B, B_ROWS, true, 1,
                                             Epi>),
                        dim3(tri_grid((int)b), batch), dim3(256), 0, s, op, epi);
   }
@@ -806,7 +806,7 @@ __global__ void fill_zero_kernel(double* __restrict__ p, long count) {
 // propagations (Sec. 5: the identity is split into blocks of columns), so each
 // workgroup takes 16 states (rows of the state-major block) through its steps
 // on its own. A build splits the chain into gridDim.y segments of consecutive
-// steps, each propagating the identity (16 N CUs alone would work otherwise:
+// steps, each propagating the identity (N / 16 CUs alone would work otherwise:
 // 2274 us per 100-step build in one segment); the segments' operators are multiplied up
 // afterwards. Per step a workgroup forms Ht_k = (H0 + a_k V + b_k K - beta) / dE in
 // LDS, runs the L Chebyshev terms with its 16 x 64 block of P_{l-1}, P_l in

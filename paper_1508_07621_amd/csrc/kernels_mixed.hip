@@ -297,18 +297,6 @@ struct Bf3Args {
 // tiles on and above the diagonal.
 constexpr int BF3_T = 4, BF3_BLOCK = 5;
 
-// The leading `npc` pieces of x (fp32): hi, or hi and mid, or all three.
-template <int NPC>
-__device__ __forceinline__ void split_n(float x, u16* out) {
-  if constexpr (NPC == 3) {
-    split3(x, out[0], out[1], out[2]);
-  } else {
-    const __bf16 bh = (__bf16)x;
-    out[0] = bf16_bits(bh);
-    if constexpr (NPC == 2) out[1] = bf16_bits((__bf16)(x - (float)bh));
-  }
-}
-
 // Epilogue of a split-BF16 product tile from its Re and Im in LDS (FP32,
 // k-blocked order, see the writers): each thread takes 8 consecutive columns
 // of one row at a time (one 16-byte chunk of every BF16 plane), reads P_{l-1}
@@ -556,20 +544,23 @@ __device__ __forceinline__ void bf3_poly_epilogue(const Bf3Args& g, const float*
   }
 }
 
-// Split-BF16 product on 32x32x16 matrix cores with NPC = 1, 2 or 3 pieces per
+// Split-BF16 products on 32x32x16 matrix cores take NPC = 1, 2 or 3 pieces per
 // operand: the piece pairs of weight at least 2^-8 (NPC - 1) of the leading one
-// ((hh); (hh, hm, mh); (hh, hm, mh, hl, mm, lh)), so the product carries about
+// ((hh); (hh, hm, mh); (hh, hm, mh, hl, mm, lh)), so a product carries about
 // 8, 16 or 24 significant bits. The stored matrices always hold three pieces;
 // fewer pieces read fewer planes. KIND CHEB_FIRST / CHEB_FIRST_LAST take
 // A = X (a BF16X3 copy) and p = X in FP64 for the c_0 X of the sum.
-template <int BM, int BN, int WGM, int WGN, int KIND, bool P_F64, int NPC>
-__global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
+//
+// This kernel: three pieces on 128 x 128 tiles, Gauss's three real products (the
+// four-product form of the kernels below would need 96 KiB of LDS).
+template <int KIND, bool P_F64>
+__global__ __launch_bounds__(512) void cheb_bf3_kernel(Bf3Args g) {
+  constexpr int BM = 128, BN = 128, WGM = 2, WGN = 4, NPC = 3;
   constexpr int NT = WGM * WGN * 64;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int FM = WTM / 32, FN = WTN / 32;
   constexpr int NL = 2 * NPC;                // stored planes read per operand (re, im pieces)
   constexpr int NP = 3 * NPC;                // planes in LDS (re, im, re + im pieces)
-  constexpr int NS = BF3_PLANES;             // stored planes written by the epilogue
   constexpr int SA = BM * 32, SB = BN * 32;  // bytes per plane and k-block
   constexpr int STAGE = NP * (SA + SB);
   constexpr int NCA = 2 * BM;                // 16-byte chunks of A per plane and k-block
@@ -578,8 +569,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
   constexpr bool FIRST = KIND == CHEB_FIRST || KIND == CHEB_FIRST_LAST;
   constexpr bool POLY = KIND >= BF3_T;
   static_assert(2 * (BM + BN) == NT, "one 16-byte chunk column of A or B per thread");
-  static_assert(FM >= 1 && FN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
-  static_assert(NPC >= 1 && NPC <= 3, "pieces");
   static_assert(!FIRST || P_F64, "the first product reads X in FP64");
 
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
@@ -633,7 +622,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
           im += piece(NPC + p);
         }
         u16 hs[NPC];
-        split_n<NPC>(POLY && !is_a ? re - im : re + im, hs);
+        split3(POLY && !is_a ? re - im : re + im, hs[0], hs[1], hs[2]);
 #pragma unroll
         for (int q = 0; q < NPC; ++q) o[q] |= (uint32_t)hs[q] << sh;
       }
@@ -693,15 +682,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void cheb_bf3_kernel(Bf3Args g) {
     t3[i][j] = mfma32_bf16(fa[2 * NPC + pa], fb[2 * NPC + pb][j], t3[i][j]);    \
   }
       FQ_PAIR(0, 0)
-      if constexpr (NPC >= 2) {
-        FQ_PAIR(0, 1)
-        FQ_PAIR(1, 0)
-      }
-      if constexpr (NPC >= 3) {
-        FQ_PAIR(0, 2)
-        FQ_PAIR(1, 1)
-        FQ_PAIR(2, 0)
-      }
+      FQ_PAIR(0, 1)
+      FQ_PAIR(1, 0)
+      FQ_PAIR(0, 2)
+      FQ_PAIR(1, 1)
+      FQ_PAIR(2, 0)
 #undef FQ_PAIR
     }
     // After this k-block's products: the next k-block (in registers since the
@@ -1259,8 +1244,7 @@ hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
     if constexpr (NPC <= 2)
       hipLaunchKernelGGL((cheb_x4_kernel<KIND, P_F64, NPC>), grid(), dim3(256), 0, s, g);
     else
-      hipLaunchKernelGGL((cheb_bf3_kernel<128, 128, 2, 4, KIND, P_F64, NPC>), grid(), dim3(512), 0,
-                         s, g);
+      hipLaunchKernelGGL((cheb_bf3_kernel<KIND, P_F64>), grid(), dim3(512), 0, s, g);
   } else if (mrows % 64 == 0 && np % 64 == 0) {
     g.tiles_m = mrows / 64;
     g.tiles_n = np / 64;

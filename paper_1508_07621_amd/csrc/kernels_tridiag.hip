@@ -1014,7 +1014,7 @@ hipError_t launch_stream_r(const TridiagJob& job, const TridiagStream& st, hipSt
 
 // ---- reverse sweep (gradient) ----------------------------------------------------------------
 //
-// One workgroup per state column, W waves, R consecutive rows per lane, complex
+// One workgroup per state column, 8 waves, 4 consecutive rows per lane, complex
 // values (real and imaginary parts side by side; no gauge: the operator is
 // applied in its complex tridiagonal form). For every checkpoint segment, last
 // first: the segment is recomputed forward from its tape entry, storing each
@@ -1033,8 +1033,8 @@ struct Cx {  // complex scalar helpers on (re, im) pairs
   }
 };
 
-template <int R, int W>
-__global__ __launch_bounds__(W * 64) void tridiag_adjoint_kernel(TridiagAdjJob job) {
+__global__ __launch_bounds__(512) void tridiag_adjoint_kernel(TridiagAdjJob job) {
+  constexpr int R = 4, W = 8;
   __shared__ double halo[2][4][2][W];  // [parity][value][first row / last row][wave]
 
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(W * 64) void tridiag_adjoint_kernel(TridiagAdjJob j
     nb[5] = from_next_lane(xi[0]);
     nb[6] = from_next_lane(yr[0]);
     nb[7] = from_next_lane(yi[0]);
-    if constexpr (W > 1) {
+    {
       if (lane == 0) {
         halo[parity][0][0][wid] = xr[0];
         halo[parity][1][0][wid] = xi[0];
@@ -1316,13 +1316,6 @@ __global__ __launch_bounds__(W * 64) void tridiag_adjoint_kernel(TridiagAdjJob j
       }
     }
   }
-}
-
-template <int R, int W>
-hipError_t launch_adj_r(const TridiagAdjJob& job, hipStream_t s) {
-  hipLaunchKernelGGL((tridiag_adjoint_kernel<R, W>), dim3((unsigned)job.ncols), dim3(W * 64), 0, s,
-                     job);
-  return hipGetLastError();
 }
 
 // ---- reverse sweep of resident columns in the gauge frame ------------------------------------
@@ -2467,10 +2460,10 @@ long tridiag_adjoint_max_n() { return 8L * 64 * 4; }
 
 hipError_t launch_tridiag_adjoint(const TridiagAdjJob& job, hipStream_t s) {
   if (job.n < 1 || job.ncols < 1 || job.L < 1 || job.M < 1 || job.ckpt < 1 ||
-      job.ncols > 0x7fffffffL)
+      job.ncols > 0x7fffffffL || job.n > tridiag_adjoint_max_n())
     return hipErrorInvalidValue;
-  if (job.n <= tridiag_adjoint_max_n()) return launch_adj_r<4, 8>(job, s);
-  return hipErrorInvalidValue;
+  hipLaunchKernelGGL(tridiag_adjoint_kernel, dim3((unsigned)job.ncols), dim3(512), 0, s, job);
+  return hipGetLastError();
 }
 
 long tridiag_adj_chain_max_n() { return 1024; }

@@ -51,7 +51,7 @@ struct Operands {
 // The staged 16-byte chunks of A and B are dealt to the threads as one list, so
 // a tile may have fewer A chunks than threads.
 //
-// GAUSS: three real products per k-step instead of four, T1 = Ar Br, T2 = Ai Bi,
+// Three real products per k-step instead of four, T1 = Ar Br, T2 = Ai Bi,
 // T3 = (Ar + Ai)(Br + Bi), Re = T1 - T2, Im = T3 - T1 - T2 (Gauss's complex
 // multiplication). The sums Ar + Ai and Br + Bi are formed in registers from
 // the fragments just read, so LDS keeps two planes per operand.
@@ -63,8 +63,8 @@ struct Operands {
 // products multiply dense operators, where the rounding of the running sums is the whole
 // error: every 16 k the sums are added to totals and start again from zero (N = 256: 2.5
 // to 3 times less error, as do the eight partial sums of zgemm_split_kernel).
-template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, int LB, bool GAUSS,
-          bool HERM, int MINW, class Epi>
+template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, int LB, bool HERM,
+          int MINW, class Epi>
 __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Operands op, Epi epi) {
   constexpr bool TRANS_B = LB != B_ROWS, FOLD = TRANS_B;
   constexpr int NT = WGM * WGN * 64;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   static_assert(BM * CPR % 64 == 0, "a wave's chunks belong to one operand");
   static_assert(BK % 8 == 0, "BK");
   static_assert(!HERM || BM == BN, "Hermitian products take square tiles");
-  static_assert(!FOLD || (GAUSS && (BK == 8 || BK == 16)), "sums of 16 k");
+  static_assert(!FOLD || BK == 8 || BK == 16, "sums of 16 k");
 
   __shared__ __attribute__((aligned(16))) double sh[2][2][(BM + BN) * S];  // [stage][re, im]
 
@@ -93,20 +93,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   const int wm = wid / WGN, wn = wid % WGN;
   const long ld = op.ld;
 
-  // 4M: accR = Re, accI = Im; GAUSS: accR = T1, accI = T2, accS = T3
-  constexpr int SM = GAUSS ? FM : 1, SN = GAUSS ? FN : 1;
-  d4 accR[FM][FN], accI[FM][FN], accS[SM][SN];
+  d4 acc1[FM][FN], acc2[FM][FN], acc3[FM][FN];  // T1, T2, T3
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      accR[i][j] = d4{0, 0, 0, 0};
-      accI[i][j] = d4{0, 0, 0, 0};
-    }
-#pragma unroll
-  for (int i = 0; i < SM; ++i)
-#pragma unroll
-    for (int j = 0; j < SN; ++j) accS[i][j] = d4{0, 0, 0, 0};
+    for (int j = 0; j < FN; ++j) acc1[i][j] = acc2[i][j] = acc3[i][j] = d4{0, 0, 0, 0};
   constexpr int TM = FOLD ? FM : 1, TN = FOLD ? FN : 1;
   d4 totR[TM][TN], totI[TM][TN];  // FOLD: Re, Im
 #pragma unroll
@@ -196,43 +187,20 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
         fbr[j] = *reinterpret_cast<const d2*>(&sh[cur][0][row * S + kk]);
         fbi[j] = *reinterpret_cast<const d2*>(&sh[cur][1][row * S + kk]);
       }
-      if constexpr (GAUSS) {
-        d2 fbs[FN];
+      d2 fbs[FN];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) fbs[j] = fbr[j] + fbi[j];
+      for (int j = 0; j < FN; ++j) fbs[j] = fbr[j] + fbi[j];
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-          const d2 fas = far_[i] + fai[i];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accR[i][j] = mfma_f64(far_[i][t], fbr[j][t], accR[i][j]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accI[i][j] = mfma_f64(fai[i][t], fbi[j][t], accI[i][j]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-              accS[i % SM][j % SN] = mfma_f64(fas[t], fbs[j][t], accS[i % SM][j % SN]);
-          }
-        }
-      } else {
+      for (int i = 0; i < FM; ++i) {
+        const d2 fas = far_[i] + fai[i];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
 #pragma unroll
-          for (int i = 0; i < FM; ++i)
+          for (int j = 0; j < FN; ++j) acc1[i][j] = mfma_f64(far_[i][t], fbr[j][t], acc1[i][j]);
 #pragma unroll
-            for (int j = 0; j < FN; ++j) accR[i][j] = mfma_f64(far_[i][t], fbr[j][t], accR[i][j]);
+          for (int j = 0; j < FN; ++j) acc2[i][j] = mfma_f64(fai[i][t], fbi[j][t], acc2[i][j]);
 #pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accI[i][j] = mfma_f64(far_[i][t], fbi[j][t], accI[i][j]);
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accR[i][j] = mfma_f64(-fai[i][t], fbi[j][t], accR[i][j]);
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) accI[i][j] = mfma_f64(fai[i][t], fbr[j][t], accI[i][j]);
+          for (int j = 0; j < FN; ++j) acc3[i][j] = mfma_f64(fas[t], fbs[j][t], acc3[i][j]);
         }
       }
     }
@@ -242,10 +210,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
-            d4& t3 = accS[i % SM][j % SN];
-            totR[i % TM][j % TN] += accR[i][j] - accI[i][j];
-            totI[i % TM][j % TN] += t3 - accR[i][j] - accI[i][j];
-            accR[i][j] = accI[i][j] = t3 = d4{0, 0, 0, 0};
+            totR[i % TM][j % TN] += acc1[i][j] - acc2[i][j];
+            totI[i % TM][j % TN] += acc3[i][j] - acc1[i][j] - acc2[i][j];
+            acc1[i][j] = acc2[i][j] = acc3[i][j] = d4{0, 0, 0, 0};
           }
       }
     }
@@ -262,14 +229,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + wm * WTM + i * 16 + 4 * r + (lane >> 4);
         const int n = n0 + wn * WTN + j * 16 + (lane & 15);
-        double re = accR[i][j][r], im = accI[i][j][r];
+        double re, im;
         if constexpr (FOLD) {
           re = totR[i % TM][j % TN][r];
           im = totI[i % TM][j % TN][r];
-        } else if constexpr (GAUSS) {
-          const double t1 = re, t2 = im;
+        } else {
+          const double t1 = acc1[i][j][r], t2 = acc2[i][j][r];
           re = t1 - t2;
-          im = accS[i % SM][j % SN][r] - t1 - t2;
+          im = acc3[i][j][r] - t1 - t2;
         }
         if constexpr (HERM)
           epi.herm(m, n, re, im, mirror);
