@@ -77,7 +77,7 @@ def parse():
                     help="arithmetic of the dense Chebyshev products (default: bf16x3, fp64 for "
                          "gue64; the tridiagonal path is FP64)")
     ap.add_argument("--no-small-chain", action="store_true",
-                    help="N <= 64: time the launch-per-product form instead of the one-launch chain")
+                    help="N <= 64: time batched step polynomials instead of the one-launch chain")
     ap.add_argument("--no-fp64-ref", action="store_true",
                     help="skip the FP64 reference build of a mixed-precision run")
     ap.add_argument("--no-eig", action="store_true", help="skip the host eigenphase comparison")
@@ -205,34 +205,23 @@ def _blas_threads() -> int:
 
 #: MFMA operations issued per algorithmic real flop of a complex product
 #: (algorithmic: four real products, 8 N^3 flop): FP32 runs the four real
-#: products once; FP64 runs three (Gauss), 3 / 4; BF16x3 runs three real products (Gauss) for each of six piece
-#: pairs, 18 / 4 = 4.5.
-MFMA_FLOPS_PER_FLOP = {"fp64": 0.75, "fp32": 1.0, "bf16x3": 4.5}
+#: products once; FP64 runs three (Gauss), 3 / 4; split BF16 in three pieces: TERM_MFMA.
+MFMA_FLOPS_PER_FLOP = {"fp64": 0.75, "fp32": 1.0}
 
 #: products of at least this many output elements use 128 x 128 tiles
 BIG_TILE_ELEMS = 256 * 128 * 128
 
-
-def mfma_flops_per_flop(precision: str, n: int, rows: int = 0) -> float:
-    """MFMA flops per algorithmic flop of a product with (rows or n) x n outputs."""
-    return MFMA_FLOPS_PER_FLOP[precision]
 PEAKS = {"fp64": PEAK_FP64_MFMA_TFLOPS, "fp32": PEAK_FP32_MFMA_TFLOPS,
          "bf16x3": PEAK_BF16_MFMA_TFLOPS}
-KERNEL_NAMES = {"fp64": "zgemm_nt_f64_kernel<64,64,8,2,4,Gauss> (FP64 MFMA 16x16x4, 3 real "
-                        "products; the product that applies a step's propagator)",
-                "fp32": "cheb_f32_kernel<128,128,32,2,4,EpiMix<MID>> (FP32 MFMA 16x16x4)",
-                "bf16x3": "cheb_bf3_kernel<128,128,2,4,MID> (BF16 MFMA 32x32x16, 3 real products "
-                          "x 6 piece pairs)"}
-
 def kernel_name(precision: str, n: int) -> str:
-    """The middle product's kernel: 128 x 128 tiles, or 64 x 64 below BIG_TILE_ELEMS outputs."""
-    if n * n >= BIG_TILE_ELEMS:
-        return KERNEL_NAMES[precision]
-    return {"fp64": "zgemm_nt_f64_kernel<64,64,8,2,4> or <32,32,16,2,2> (FP64 MFMA 16x16x4, 3 real "
-                    "products; the product that applies a step's propagator)",
-            "fp32": "cheb_f32_kernel<64,64,32,2,2,EpiMix<MID>> (FP32 MFMA 16x16x4)",
-            "bf16x3": "cheb_bf3_kernel<64,64,2,2,MID> (BF16 MFMA 32x32x16, 3 real products "
-                      "x 6 piece pairs)"}[precision]
+    """The kernel of FP64 builds' applying product or of FP32 builds' middle product."""
+    big = n * n >= BIG_TILE_ELEMS
+    if precision == "fp64":
+        return ("zgemm_nt_f64_kernel<64,64,8,2,4>" + ("" if big else " or <32,32,16,2,2>") +
+                " (FP64 MFMA 16x16x4, 3 real products; the product that applies a step's "
+                "propagator)")
+    return ("cheb_f32_kernel<128,128,32,2,4,EpiMix<MID>>" if big else
+            "cheb_f32_kernel<64,64,32,2,2,EpiMix<MID>>") + " (FP32 MFMA 16x16x4)"
 
 
 #: Kernel sources behind each roofline entry; HBM traffic recorded under
@@ -365,13 +354,17 @@ def dense_roofline(reports, n: int, precision: str, workload: str):
     """The middle Chebyshev product (FP64 builds: the product that applies a
     step's propagator): achieved = algorithmic flops (8 N^3) per launch over the
     launch time, against the MFMA peak of the precision the product runs in; the
-    MFMA flops actually issued are reported beside it."""
+    MFMA flops actually issued are reported beside it. None for FP64 builds in segments
+    (below 1024 states), whose launches hold step t of several segments or pairs of operators."""
     from paper_1508_07621_amd._abi import K_LAST, K_MID
     kind = K_MID if any(r["n_kernel"][K_MID] for r in reports) else K_LAST
     n_launch = sum(r["n_kernel"][kind] for r in reports)
-    ms_launch = sum(r["ms_kernel"][kind] for r in reports) / max(n_launch, 1)
+    # (a build step by step applies every step's propagator but the first to a block)
+    if not n_launch or (kind == K_LAST and n_launch < sum(r["M"] - 1 for r in reports)):
+        return None
+    ms_launch = sum(r["ms_kernel"][kind] for r in reports) / n_launch
     flops = 8.0 * n ** 3                                   # one complex N x N x N product
-    mfma_flops = flops * mfma_flops_per_flop(precision, n)
+    mfma_flops = flops * MFMA_FLOPS_PER_FLOP[precision]
     achieved = flops / (ms_launch * 1e-3) / 1e12
     issued = mfma_flops / (ms_launch * 1e-3) / 1e12
     peak = PEAKS[precision]
@@ -414,7 +407,7 @@ def x4_tiles(n: int) -> bool:
 
 def term_mfma(name: str, n: int) -> float:
     if name == "fp64":
-        return mfma_flops_per_flop("fp64", n)
+        return MFMA_FLOPS_PER_FLOP["fp64"]
     if name in TERM_MFMA_X4 and x4_tiles(n):
         return TERM_MFMA_X4[name]
     return TERM_MFMA[name]
@@ -476,22 +469,22 @@ def term_schedule(reports, n: int, workload: str):
 
 
 def chain_roofline(reports, n: int, M: int, terms_per_step: int):
-    """The one-launch chain of N <= 64 FP64 builds: every step's products in
-    one kernel on N/16 workgroups (one per 16 states), so the launch's
-    algorithmic work is M x (terms per step) x 8 N^3 over the chain's time; it
-    uses N/16 of the 256 compute units, so its fraction of the FP64 peak is
-    bounded by (N/16)/256 by construction."""
+    """The one-launch chain of N <= 64 FP64 builds: up to 64 segments of the chain
+    side by side, each on N/16 workgroups (one per 16 states). The launch's algorithmic
+    work is M x (terms per step) x 8 N^3 over the chain's time; the products that
+    multiply the segments up are launches of their own."""
     from paper_1508_07621_amd._abi import K_CHAIN
     cnt = sum(r["n_kernel"][K_CHAIN] for r in reports)
     ms = sum(r["ms_kernel"][K_CHAIN] for r in reports) / cnt
     flops = float(M) * terms_per_step * 8.0 * n ** 3
     ach = flops / (ms * 1e-3) / 1e12
-    cus = max(n // 16, 1)
+    length = -(-M // 64)                                   # steps per segment
+    cus = min(256, max(n // 16, 1) * -(-M // length))
     return {"bound": "mfma", "achieved": round(ach, 4), "peak": PEAK_FP64_MFMA_TFLOPS,
             "unit": "TFLOP/s", "frac": round(ach / PEAK_FP64_MFMA_TFLOPS, 5), "traffic": None,
             "traffic_detail": None,
-            "kernel": "small_chain_kernel (whole build in one launch, 16 states per workgroup, "
-                      "FP64 MFMA 16x16x4)",
+            "kernel": "small_chain_kernel (all steps in one launch, 16 states of a segment per "
+                      "workgroup, FP64 MFMA 16x16x4)",
             "avg_launch_ms": round(ms, 4), "launches_timed": cnt,
             "algorithmic_flops_per_launch": flops,
             "compute_units_used": cus,
@@ -636,7 +629,7 @@ def shard_share(ctx, U, wl, P: int, warmup: int, steps: int, s_full: float, prec
     if wl.layout == "dense":
         flops = 8.0 * n * n * cols
         mf = flops * (term_mfma(TERM_KINDS[kind], n) if kind in TERM_KINDS
-                      else mfma_flops_per_flop(precision, n, cols))
+                      else MFMA_FLOPS_PER_FLOP[precision])
         res["dominant_kernel_mfma_frac"] = round(mf / (ms_launch * 1e-3) / 1e12 / PEAKS[precision], 4)
     return res
 

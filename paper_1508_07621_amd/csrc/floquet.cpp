@@ -1327,8 +1327,9 @@ fq_status dense_poly_step(fq_ctx* c, const PolyPlan& p, int k, int mrows) {
   }
   FQ_TRY(dense_heff(c, k));
   FQ_TRY(poly_form_in_place(c, p, b, 1));
-  FQ_MARK(c, FQ_K_LAST);
-  if (c->from_identity && k == 0)  // X = 1: the state-major E is E^T
+  const bool first = c->from_identity && k == 0;
+  FQ_MARK(c, first ? FQ_K_CONVERT : FQ_K_LAST);
+  if (first)  // X = 1: the state-major E is E^T
     FQ_HIP(c, fq::launch_transpose_planar(c->htr, c->hti, c->par, c->pai, c->np, 0, 1, c->stream,
                                           c->n, p.c0.r, p.c0.i));
   else
@@ -1398,7 +1399,7 @@ fq_status dense_poly_segments(fq_ctx* c, const PolyPlan& p, int nb) {
     FQ_MARK(c, FQ_K_HEFF);
     FQ_TRY(heff_f64(c, t, act, len0, rem, b[0]));
     FQ_TRY(poly_form_in_place(c, p, b, act));
-    FQ_MARK(c, FQ_K_LAST);
+    FQ_MARK(c, t == 0 ? FQ_K_CONVERT : FQ_K_LAST);
     if (t == 0) {  // X = 1
       FQ_HIP(c, fq::launch_transpose_planar(b[0], b[0] + bs / 2, x, x + bs / 2, c->np, bs, act,
                                             c->stream, c->n, p.c0.r, p.c0.i));
