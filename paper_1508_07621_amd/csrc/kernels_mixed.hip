@@ -913,7 +913,8 @@ __global__ __launch_bounds__(256, 2) void cheb_x4_kernel(Bf3Args g) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// One- to three-piece products on 64 x 64 tiles (N < 2048), four waves of 32 x 32 and
+// One- to three-piece products on 64 x 64 tiles (N < 2048; Hermitian ones of one or two
+// pieces up to N = 4480, see launch_bf3), four waves of 32 x 32 and
 // the four real products. With about one workgroup per CU the time of a k-block is
 // the latency of its loads unless they are issued far ahead, so every thread
 // keeps its chunks of the next D = 4 k-blocks in registers (each iteration
@@ -1231,10 +1232,12 @@ hipError_t launch_bf3(const Bf3Args& g0, int mrows, hipStream_t s) {
   };
   if (KIND == BF3_T && mrows != np) return hipErrorInvalidValue;
   // Hermitian products of one or two pieces: 64 x 64 tiles while the upper 128 x 128 ones
-  // make little more than one round of two workgroups per CU (N = 2048: 116 against 150
-  // us on average, N = 4096, 528 tiles for 512 places: 647 against 724 us; N = 6000 1990
-  // against 1853 us; all before the blocked walk of tri_tile)
-  const bool small = KIND == BF3_T && NPC <= 2 && np <= 4096;
+  // make at most a quarter more than one round of two workgroups per CU (512 places). ms a
+  // step in three such products and one full one, 64 against 128 tiles: N = 2048 (136 upper
+  // tiles) 0.44, 0.60; 3072 (300) 1.12, 1.25; 4096 (528) 2.40, 2.86; 4224 (561) 2.67, 3.01;
+  // 5120 (820) 4.65, 4.39; 6016 (1128) 7.45, 7.08.
+  const int big = np / 128;
+  const bool small = KIND == BF3_T && NPC <= 2 && big * (big + 1) / 2 <= 640;
   if (!small && mrows % 128 == 0 && np % 128 == 0 && (long)mrows * np >= kBigTileElems) {
     g.tiles_m = mrows / 128;
     g.tiles_n = np / 128;

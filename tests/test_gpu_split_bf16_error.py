@@ -53,3 +53,12 @@ def test_three_piece_products_sum_parts_apart(fl, n):
     print("[case] split-BF16 three pieces", n, flush=True)
     err, terms, est = _build(fl, n, 20, 10.0, 0.0)
     assert err < 0.85 * est
+
+
+# Hermitian products on both sides of their tile choice: the largest states on 64 x 64 tiles
+# (padded to 4480) and the first on 128 x 128 (4608), below the estimate
+@pytest.mark.parametrize("n", [4225, 4480, 4481])
+def test_hermitian_products_on_either_tile(fl, n):
+    print("[case] split-BF16 tiles", n, flush=True)
+    err, terms, est = _build(fl, n, 3, 20.0, 0.0)
+    assert err < est <= terms * (1 + 1e-12)
