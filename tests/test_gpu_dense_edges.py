@@ -50,6 +50,7 @@ def test_fp32_gradient_term_by_term(fl, monkeypatch, n, M, L, T, lean):
     g0 = exact.grad(W)
     if lean:
         monkeypatch.setattr(fl, "_free_bytes", lambda device: 0)
+        monkeypatch.setattr(fl, "_UNASKED_SCRATCH", 0)
     ctx = fl.FloquetContext(precision="fp32", profile=True, **kw)
     ctx.build_ut()
     g = ctx.grad(W)

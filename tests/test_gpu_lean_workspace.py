@@ -36,6 +36,7 @@ def _lean(fl, monkeypatch, kw):
     """A context where almost nothing is free beyond the least workspace."""
     with monkeypatch.context() as m:
         m.setattr(fl, "_free_bytes", lambda device: 0)
+        m.setattr(fl, "_UNASKED_SCRATCH", 0)
         ctx = fl.FloquetContext(**kw)
     return ctx
 
@@ -120,3 +121,24 @@ def test_workspaces_in_between(fl):
         print("[case] workspace", size, (U - U0).abs().max().item(), np.max(np.abs(g - g0)), flush=True)
         assert (U - U0).abs().max().item() < 1e-12
         assert np.max(np.abs(g - g0)) < 1e-10 * np.max(np.abs(g0))
+
+
+# an allocation that fails for the scratch falls back to the least, one that fails for that raises
+def test_out_of_memory_falls_back(fl, monkeypatch):
+    import torch
+    kw = _dense(100, 8, checkpoint_every=4)
+    full = fl.FloquetContext(**kw)
+    limit = [full.workspace.numel() - 1]
+    empty = torch.empty
+
+    def short(*size, **k):
+        if k.get("dtype") == torch.uint8 and size[0] > limit[0]:
+            raise torch.cuda.OutOfMemoryError("no room")
+        return empty(*size, **k)
+    monkeypatch.setattr(torch, "empty", short)
+    lean = fl.FloquetContext(**kw)
+    assert lean.workspace.numel() < full.workspace.numel()
+    assert (lean.build_ut() - full.build_ut()).abs().max().item() < 1e-13
+    limit[0] = lean.workspace.numel() - 1
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        fl.FloquetContext(**kw)
