@@ -1354,7 +1354,7 @@ fq::PolyScalar step_phase(const fq_ctx* c, long k) {
 // planes. A pair A, B is multiplied as p A + A (B - p) with B's common phase p: the operators of
 // short segments are near a multiple of the identity, which would round the diagonal as often
 // as the sum has terms. Errors of whole builds against the same series in 106 bits, without
-// and with this and the sums of 16 k: 100 states in 99 products 8.9e-15 -> 1.1e-15, 256 states
+// and with this and the sums of 32 k: 100 states in 99 products 8.9e-15 -> 1.1e-15, 256 states
 // in 31 products 4.5e-15 -> 1.2e-15 (term by term in one chain: 2.1e-15, 1.9e-15).
 fq_status multiply_up(fq_ctx* c, double* src, double* dst, double* alt, int cnt, double len) {
   const int np = (int)c->np;
@@ -1865,7 +1865,8 @@ fq_status dense_cheb_step_mixed(fq_ctx* c, int mrows) {
 // The one-launch chain of small_chain_kernel serves FP64 steps of one drive
 // term whose Ht is H0 + a_k V + b_k K (Magnus-4, commutator-free) at np = 64,
 // without tape, snapshots or saved terms. FQ_SMALL_CHAIN=0 in the environment
-// (read at fq_create) keeps the launch-per-product form instead.
+// (read at fq_create) takes the forms of larger N instead (step polynomials in
+// segments and batches).
 bool small_chain_ok(const fq_ctx* c, bool record_tape) {
   return c->small_chain && c->precision == FQ_FP64 && c->np == fq::small_chain_max_n() &&
          c->scheme != FQ_MAGNUS6 && c->S == 1 && !record_tape && !c->snap && !c->save_pl &&

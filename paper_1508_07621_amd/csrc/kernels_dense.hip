@@ -196,14 +196,23 @@ struct EpiPolyApply {
   const double* x;
   long ld, plane, bs, x_bs;
   PolyScalar c;
+  double px = 0.0, pxi = 0.0;  // prefetched elements of X
+  bool ahead = false;
   __device__ __forceinline__ void batch(int z) {
     o += z * bs;
     if (x) x += z * x_bs;
   }
+  __device__ __forceinline__ void prefetch(int m, int n) {
+    if (!x) return;
+    const long idx = (long)m * ld + n;
+    px = x[idx];
+    pxi = x[plane + idx];
+    ahead = true;
+  }
   __device__ __forceinline__ void operator()(int m, int n, double ar, double ai) const {
     const long idx = (long)m * ld + n;
     if (x) {
-      const double xr = x[idx], xi = x[plane + idx];
+      const double xr = ahead ? px : x[idx], xi = ahead ? pxi : x[plane + idx];
       ar = fma(c.r, xr, fma(-c.i, xi, ar));
       ai = fma(c.r, xi, fma(c.i, xr, ai));
     }

@@ -7,6 +7,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "formats.h"
 
 namespace fq {
@@ -61,8 +63,9 @@ struct Operands {
 //
 // LB: with B_TRANS and B_SHIFTED the staging transposes B on the way into LDS. These
 // products multiply dense operators, where the rounding of the running sums is the whole
-// error: every 16 k the sums are added to totals and start again from zero (N = 256: 2.5
-// to 3 times less error, as do the eight partial sums of zgemm_split_kernel).
+// error: every 32 k the sums are added to totals and start again from zero (N = 256: 2.5
+// times less error, as with the eight partial sums of zgemm_split_kernel; every 16 k gains
+// no more and takes 46.9 us where this takes 44.2 and none 40.0: 32 products of 256 states).
 template <int BM, int BN, int BK, int WGM, int WGN, bool CONJ_A, bool CONJ_B, int LB, bool HERM,
           int MINW, class Epi>
 __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Operands op, Epi epi) {
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   static_assert(BM * CPR % 64 == 0, "a wave's chunks belong to one operand");
   static_assert(BK % 8 == 0, "BK");
   static_assert(!HERM || BM == BN, "Hermitian products take square tiles");
-  static_assert(!FOLD || BK == 8 || BK == 16, "sums of 16 k");
+  static_assert(!FOLD || BK == 8 || BK == 16, "sums of 32 k");
 
   __shared__ __attribute__((aligned(16))) double sh[2][2][(BM + BN) * S];  // [stage][re, im]
 
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
       }
     }
     if constexpr (FOLD) {
-      if (BK == 16 || (kb & 1)) {
+      if ((kb + 1) % (32 / BK) == 0) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -246,6 +249,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
   epi.finish();
 }
 
+// Epilogues that read another operand may load it ahead of the sum: prefetch(m, n).
+template <class Epi, class = void>
+struct HasPrefetch : std::false_type {};
+template <class Epi>
+struct HasPrefetch<Epi, std::void_t<decltype(&Epi::prefetch)>> : std::true_type {};
+
 // The same product where tiles would leave most of the chip idle (few rows m
 // against a large operator, small N): a workgroup takes 16 FM rows of A and 16
 // rows of B, its W waves share the reduction in steps of 8 k and meet in LDS, and
@@ -259,12 +268,19 @@ __global__ __launch_bounds__(WGM* WGN * 64, MINW) void zgemm_nt_f64_kernel(Opera
 template <int FM, int W, bool CONJ_A, bool CONJ_B, int LB, bool HERM, class Epi>
 __global__ __launch_bounds__(W * 64) void zgemm_split_kernel(Operands op, Epi epi) {
   static_assert(!HERM || FM == 1, "Hermitian products take square tiles");
+  static_assert(W * 64 >= FM * 256, "at most one element per thread");
   constexpr bool TRANS_B = LB != B_ROWS;
   __shared__ double red[W][FM * 8][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int tm = blockIdx.y, tn = blockIdx.x;
   if constexpr (HERM) tri_coords(blockIdx.x, tm, tn);
   const int m0 = tm * 16 * FM, n0 = tn * 16;
+  // this thread's element of the result
+  const int q = threadIdx.x, l = q & 63, qi = q >> 8, qr = (q >> 6) & 3;
+  const int qm = m0 + 16 * qi + 4 * qr + (l >> 4), qn = n0 + (l & 15);
+  epi.batch(blockIdx.z);
+  if constexpr (HasPrefetch<Epi>::value)
+    if (q < FM * 256) epi.prefetch(qm, qn);
   const int rr = lane & 15, kp = 2 * (lane >> 4);
   const long ld = op.ld;
   const int units = op.kdim / 8;
@@ -319,20 +335,18 @@ __global__ __launch_bounds__(W * 64) void zgemm_split_kernel(Operands op, Epi ep
       red[wave][8 * i + 4 + r][lane] = a3[i][r] - a1[i][r] - a2[i][r];
     }
   __syncthreads();
-  epi.batch(blockIdx.z);
-  for (int q = threadIdx.x; q < FM * 256; q += W * 64) {
-    const int l = q & 63, i = q >> 8, r = (q >> 6) & 3, v = 8 * i + r;
+  if (q < FM * 256) {
+    const int v = 8 * qi + qr;
     double re = 0.0, im = 0.0;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
       re += red[w][v][l];
       im += red[w][v + 4][l];
     }
-    const int m = m0 + 16 * i + 4 * r + (l >> 4), n = n0 + (l & 15);
     if constexpr (HERM)
-      epi.herm(m, n, re, im, tm != tn);
+      epi.herm(qm, qn, re, im, tm != tn);
     else
-      epi(m, n, re, im);
+      epi(qm, qn, re, im);
   }
   epi.finish();
 }
