@@ -68,7 +68,8 @@ struct fq_ctx {
   double e_min = 0, e_max = 0, beta = 0, dE = 0, R = 0;
   std::vector<double> weights;        // a_l = (2 - delta_l0) J_l(R), l = 0..L
   std::vector<double> coef;           // c_l = (2 - delta_l0) (-i)^l J_l(R), interleaved
-  double phr = 1, phi = 0;            // exp(-i beta h)
+  double phr = 1, phi = 0;            // exp(-i beta h), and what the doubles leave of it
+  double phr_lo = 0, phi_lo = 0;
   // device
   hipStream_t stream = nullptr;
   char* ws = nullptr;

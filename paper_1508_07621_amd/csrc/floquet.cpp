@@ -1164,8 +1164,7 @@ using cld = std::complex<long double>;
 // Blocks of length s: the coefficients of T_0 .. T_s in each of the *J blocks.
 std::vector<cld> poly_coefficients(const fq_ctx* c, int s, int* J) {
   const int L = c->L, prods = (L + s - 1) / s - 1, top = L / s;
-  const long double arg = (long double)c->beta * c->h;
-  const cld ph(std::cos(arg), -std::sin(arg));
+  const cld ph((long double)c->phr + c->phr_lo, (long double)c->phi + c->phi_lo);
   std::vector<cld> cl(L + 1);
   for (int l = 0; l <= L; ++l) cl[l] = ph * cld(c->coef[2 * l], c->coef[2 * l + 1]);
   *J = prods + 1;
@@ -1969,9 +1968,8 @@ fq_status dense_steps(fq_ctx* c, int k0, int k1, int mrows, bool record_tape,
     sc.inv_dE = 1.0 / c->dE;
     sc.phr = c->phr;
     sc.phi = c->phi;
-    const long double arg = (long double)c->beta * c->h;
-    sc.phr_lo = (double)(std::cos(arg) - (long double)c->phr);
-    sc.phi_lo = (double)(-std::sin(arg) - (long double)c->phi);
+    sc.phr_lo = c->phr_lo;
+    sc.phi_lo = c->phi_lo;
     FQ_MARK(c, FQ_K_CHAIN);
     // a build: segments for the other CUs (4 workgroups each), multiplied up
     const int most = c->from_identity ? std::min({c->pool_mats / 2, 64, k1 - k0}) : 1;
@@ -2102,6 +2100,8 @@ fq::TridiagJob tridiag_job(const fq_ctx* c) {
   job.inv_dE = 1.0 / c->dE;
   job.phr = c->phr;
   job.phi = c->phi;
+  job.phr_lo = c->phr_lo;
+  job.phi_lo = c->phi_lo;
   job.c64 = c->c64 ? 1 : 0;
   const long R = fq::tridiag_chain_rows(c->n);
   job.nq = (c->n + R - 1) / R;
@@ -3249,8 +3249,11 @@ fq_status apply_drive(fq_ctx* c, const double* f_nodes) {
     c->coef[2 * l] = (q == 0) ? w : (q == 2 ? -w : 0.0);
     c->coef[2 * l + 1] = (q == 1) ? -w : (q == 3 ? w : 0.0);
   }
-  c->phr = std::cos(c->beta * c->h);
-  c->phi = -std::sin(c->beta * c->h);
+  const long double arg = (long double)c->beta * c->h;
+  c->phr = (double)std::cos(arg);
+  c->phi = (double)-std::sin(arg);
+  c->phr_lo = (double)(std::cos(arg) - (long double)c->phr);
+  c->phi_lo = (double)(-std::sin(arg) - (long double)c->phi);
   if (c->precision != FQ_FP64 && c->layout == FQ_DENSE) choose_schedule(c);
   if (c->layout == FQ_DENSE) FQ_TRY(upload_heff_weights(c));
   if (c->d_tab) FQ_HIP(c, fq::launch_tridiag_table(tridiag_job(c), c->M, c->d_tab, c->stream));

@@ -333,7 +333,7 @@ struct TridiagJob {
   const double* gauge;   // device, M x n complex: w[s][i], D_s = diag(w[s]) makes D_s^+ Ht_s D_s real
   int L;
   int k0, k1;            // steps k0+1 .. k1
-  double beta, inv_dE, phr, phi;
+  double beta, inv_dE, phr, phi, phr_lo, phi_lo;  // the phase's parts, and what they leave
   const void* x0;        // device complex128 n x ncols row-major, or nullptr = identity
   long ld_x0;
   int x0_colmajor;       // streamed passes: x0 is complex128 column-major (col at col * n)

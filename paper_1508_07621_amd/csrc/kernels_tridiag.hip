@@ -174,6 +174,15 @@ __device__ __forceinline__ DDComplex dd_cmul(DDComplex a, DDComplex b) {
           dd_add(dd_mul(a.x, b.y), dd_mul(a.y, b.x))};
 }
 
+// z / |z| for |z| near 1 (0.5 to 4, say): one Newton step from the rounded reciprocal root.
+__device__ __forceinline__ DDComplex dd_unit(DDComplex z) {
+  const DD s = dd_add(dd_mul(z.x, z.x), dd_mul(z.y, z.y));
+  const double y = 1.0 / sqrt(s.h);
+  const DD r = dd_add({1.0, 0.0}, dd_neg(dd_mul(s, dd_mul({y, 0.0}, {y, 0.0}))));
+  const DD m = dd_norm(y, 0.5 * y * (r.h + r.l));
+  return {dd_mul(z.x, m), dd_mul(z.y, m)};
+}
+
 // Unit gauge factors of every step, one workgroup per step: w_0 = 1, w_{i+1} =
 // w_i conj(u_i) with u_i the phase of Ht[i][i+1] = h_i (1 - i b dv_i) (1 where that
 // vanishes), which makes D^+ Ht D real for D = diag(w). Each thread multiplies up a
@@ -204,12 +213,8 @@ __global__ __launch_bounds__(256) void tridiag_gauge_table_kernel(
     const int ee = -ilogb(fmax(fabs(er.h), fabs(ei.h)));
     er = {scalbn(er.h, ee), scalbn(er.l, ee)};
     ei = {scalbn(ei.h, ee), scalbn(ei.l, ee)};
-    // 1 / |e|: one Newton step from the rounded reciprocal square root
-    const DD s = dd_add(dd_mul(er, er), dd_mul(ei, ei));
-    const double y = 1.0 / sqrt(s.h);
-    const DD r = dd_add({1.0, 0.0}, dd_neg(dd_mul(s, dd_mul({y, 0.0}, {y, 0.0}))));
-    const DD m = dd_norm(y, 0.5 * y * (r.h + r.l));
-    return dd_cmul(w, {dd_mul(er, m), dd_neg(dd_mul(ei, m))});
+    const DDComplex u = dd_unit({er, ei});
+    return dd_cmul(w, {u.x, dd_neg(u.y)});
   };
   const DDComplex one{{1.0, 0.0}, {0.0, 0.0}};
   DDComplex p = one;
@@ -262,10 +267,21 @@ __device__ __forceinline__ double2 tridiag_rotation(const TridiagJob& job, int s
   return make_double2(rr, ri);
 }
 
+// x rounded for its turn s: x.h, or a neighbour as often as x.l asks for.
+__device__ __forceinline__ double round_by_turns(DD x, int s) {
+  if (x.h == 0.0) return x.h;
+  const double ulp = scalbn(1.0, ilogb(x.h) - 52), share = x.l / ulp;
+  return x.h + ulp * (rint((s + 1.0) * share) - rint(s * share));
+}
+
 // Rows of every step in the lane order of the chain kernel: 2 d_i, 2 g_i, and the
 // rotation phase w_s conj(w_{s+1}) that ends step s (phase w_s after the last
 // one); row i at (i mod R) nq + i / R, so that the R rows a lane owns are
-// unit-stride loads across the wave. Rows from n on are zero.
+// unit-stride loads across the wave. Rows from n on are zero. The factors of two steps
+// are divided by their moduli, which are 1 to a rounding only: with a gauge that stays
+// (b_k = 0) their square would come in with every step. So would the rounding of the step
+// phase, all that is left then: it is rounded up or down by turns, so that any run of steps
+// is off by a rounding (4 states, 200 steps of two exponentials: error of U_T 2.7e-14 -> 5.1e-15).
 __global__ __launch_bounds__(256) void tridiag_table_kernel(TridiagJob job, int R, int M,
                                                             double* __restrict__ out) {
   const long n = job.n, nq = job.nq, nr = nq * R;
@@ -274,7 +290,19 @@ __global__ __launch_bounds__(256) void tridiag_table_kernel(TridiagJob job, int 
   if (i >= nr) return;
   const TridiagRow row = tridiag_row(job, s, i);
   double2 rot = make_double2(0.0, 0.0);
-  if (i < n) rot = tridiag_rotation(job, s, i, s + 1 < M);
+  if (i < n && s + 1 < M) {
+    const double2* gauge = reinterpret_cast<const double2*>(job.gauge);
+    const double2 w = gauge[(long)s * n + i], wn = gauge[(long)(s + 1) * n + i];
+    const DDComplex u = dd_unit(dd_cmul({{w.x, 0.0}, {w.y, 0.0}}, {{wn.x, 0.0}, {-wn.y, 0.0}}));
+    const DDComplex r = dd_cmul(u, {{job.phr, job.phr_lo}, {job.phi, job.phi_lo}});
+    rot = make_double2(r.x.h, r.y.h);
+    if (w.x == wn.x && w.y == wn.y) {
+      rot.x = round_by_turns(r.x, s);
+      rot.y = round_by_turns(r.y, s);
+    }
+  } else if (i < n) {
+    rot = tridiag_rotation(job, s, i, false);
+  }
   double* t = out + (long)s * 4 * nr + (i % R) * nq + i / R;
   t[0] = row.d2;
   t[nr] = row.g2;

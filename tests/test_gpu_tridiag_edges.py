@@ -153,3 +153,50 @@ def test_extremes_as_the_host_finds_them(fl, n, scale):
           (rep["e_max"] - hi) / np.spacing(abs(hi)), flush=True)
     assert abs(rep["e_min"] - lo) <= np.spacing(abs(lo))
     assert abs(rep["e_max"] - hi) <= np.spacing(abs(hi))
+
+
+# Commutator-free steps: the gauge stays, so that a step ends with the bare phase in every
+# row and step. Rounded alike each time, that alone would put U_T off by up to one rounding per
+# exponential, 1000 of them here; by turns it stays within one, and the rest walks as above
+@pytest.mark.parametrize("n", [2, 4, 33])
+def test_step_phase_rounds_by_turns(fl, n):
+    print("[case] phase by turns", n, flush=True)
+    rng = np.random.default_rng(70 + n)
+    ld, M = np.longdouble, 500
+    T = 0.2 * M
+    d, v = rng.standard_normal(n), rng.standard_normal(n)
+    e = rng.standard_normal(n - 1) + 1j * rng.standard_normal(n - 1)
+    f = rng.uniform(-2, 2, (M, 2))
+    lo, hi = -15.0, 16.4
+    ctx = fl.FloquetContext(h0_diag=d, h0_off=e, hmod_diag=v, T=T, M=M, f_nodes=f, scheme="cf4",
+                            e_min=lo, e_max=hi)
+    L, beta, dE, h = ctx.report["L"], 0.5 * (hi + lo), 0.5 * (hi - lo), T / (2 * M)
+    assert L < 24
+    coef = fl.bessel_weights(h * dE, L)
+    arg = ld(beta) * ld(h)
+    phase = np.cos(arg) - 1j * np.sin(arg)
+    p, q = 0.5 + 0.57735026918962576451, 0.5 - 0.57735026918962576451
+    X = np.eye(n, dtype=np.clongdouble)
+    inv = ld(1.0 / dE)
+    up = (e.astype(np.clongdouble) * inv)[:, None]
+    for f1, f2 in f:
+        for a in (p * f1 + q * f2, q * f1 + p * f2):
+            dd = ((d.astype(ld) + ld(a) * v.astype(ld) - ld(beta)) * inv)[:, None]
+
+            def mv(x):
+                y = dd * x
+                y[:-1] += up * x[1:]
+                y[1:] += up.conj() * x[:-1]
+                return y
+            p0, p1 = X, mv(X)
+            Y = ld(coef[0]) * p0 + (-1j) * (ld(coef[1]) * p1)
+            for l in range(2, L + 1):
+                p0, p1 = p1, 2 * mv(p1) - p0
+                Y = Y + np.array((-1j) ** l, dtype=np.clongdouble) * (ld(coef[l]) * p1)
+            X = phase * Y
+    bound = 12 * 2.0 ** -53 * np.sqrt(2 * M)
+    for name, A in (("build", ctx.build_ut()), ("states", ctx.propagate(np.eye(n, dtype=complex)))):
+        A = A.cpu().numpy().astype(np.clongdouble)
+        err = float(np.max(np.sqrt(np.sum(np.abs(A - X) ** 2, axis=0))))
+        print("[case]", name, "L", L, "e_col", err, "bound", bound, flush=True)
+        assert err < bound
