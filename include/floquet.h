@@ -86,9 +86,12 @@ typedef enum { FQ_DENSE = 0, FQ_TRIDIAG = 1, FQ_DENSE_EIGEN = 2 } fq_layout;
  * FQ_BF16X3: products on BF16 matrix cores with operands split into BF16
  * pieces, each term in its own fq_term_format chosen from its Bessel weight;
  * P_l stored as three BF16 pieces (about 24 bits); X and the Chebyshev sum
- * float64. Setup, coefficients and checks are always float64. FQ_FP32 and
- * FQ_BF16X3 allow these products; calls that run faster in FP64 (small N, few
- * states, most FQ_FP32 builds) run there, unless fq_params.term_formats is set. */
+ * float64. Where a step's sum is formed as a matrix first, c_0 + F applied to
+ * all columns in one product, F (of norm about R) is kept in three BF16 pieces
+ * and c_0 X + F X is summed in float64. Setup, coefficients and checks are
+ * always float64. FQ_FP32 and FQ_BF16X3 allow these products; calls that run
+ * faster in FP64 (small N, few states, most FQ_FP32 builds) run there, unless
+ * fq_params.term_formats is set. */
 typedef enum { FQ_FP64 = 0, FQ_FP32 = 1, FQ_BF16X3 = 2 } fq_precision;
 
 /* Format of one Chebyshev product P_l = 2 Ht P_{l-1} - P_{l-2} (P_1 = Ht X) of

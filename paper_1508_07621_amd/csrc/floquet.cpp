@@ -1156,8 +1156,8 @@ fq_status dense_cheb_step(fq_ctx* c, int mrows) {
 // With a Hermitian product at 0.6 of a full one (measured at N = 1536 and
 // 4096), L = 7 takes 3.8 instead of 7 products, L = 12 takes 4.8 instead of 12.
 // 50 steps of L = 10 at N = 1500: 195 -> 91 ms (1.83 ms a step, 57 TF/s of issued
-// MFMA). Small N in segments: 100 steps at N = 64 2.36 -> 0.16 ms, a sixth-order
-// one-shot build at N = 199 18.3 -> 12.0 ms (the rest is its setup).
+// MFMA). Small N in segments: 100 steps at N = 64 2.36 -> 0.15 ms, a sixth-order
+// one-shot build at N = 199 18.3 -> 12.0 ms (2.3 ms with its covers on the device).
 
 using cld = std::complex<long double>;
 
@@ -1530,7 +1530,8 @@ void choose_schedule(fq_ctx* c) {
 // two-piece and of a one-piece product, one one-piece product, and a pass over four
 // matrices. A step of L = 8, before and after: N = 1030 0.37 -> 0.25 ms, N = 2500 2.76
 // -> 1.75 ms; L = 7 at N = 4096 7.7 -> 5.3 ms (4.5 ms of it MFMA-bound products: the
-// one with X 2.2, four others 0.56 on average); errors as before (e_col 1.1 .. 3.6e-7).
+// one with X 2.2, four others 0.56 on average). e_col against the terms' own: 0.70 to 1.02
+// times up to 1984 states, 0.99 to 1.12 times beyond.
 
 // Units of a product: matrix instructions per tile and k-block, and its pass over
 // the operands.

@@ -13,7 +13,8 @@
 // the schedule keeps in FP64 run on FP64 matrix cores; the kernels here form the
 // others, add each Bessel-weighted term to Y in FP64, and the last one applies
 // the step phase in FP64. Split-BF16 builds form each step's propagator as a
-// matrix polynomial instead where that is cheaper (the BF3_T and BF3_BLOCK kinds).
+// matrix polynomial instead where that is cheaper (the BF3_T and BF3_BLOCK kinds):
+// its sum of terms F = E - c_0 is held in three pieces, c_0 X + F X is summed in FP64.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

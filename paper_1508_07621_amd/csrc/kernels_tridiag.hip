@@ -328,13 +328,13 @@ __global__ __launch_bounds__(256) void tridiag_energy_table_kernel(TridiagJob jo
 //
 // Bound by FP64 vector issue for many columns: per row and term three FMAs for
 // the stencil and one for the sum. 1000-state dimer, 500 steps of 68 terms, 2 waves
-// per SIMD: 11.5 ms, 76 TF/s at 26 flop per element and term and 60 % of the FMA issue at 2.4
+// per SIMD: 11.8 ms, 75 TF/s at 26 flop per element and term and 59 % of the FMA issue at 2.4
 // GHz (17.0 ms when every column formed its rows, square roots included, from
 // strided operator loads in every step, and both halves of the sum went through
 // LDS). For few or short columns bound by the latency of one term after the other, which is why a
 // build with fewer columns than the chip has room for runs its segments side by
 // side, and why short columns take fewer rows per lane (R = 1 up to 64 rows): a
-// 21-state, 200-step build 653 -> 100 us. Per step a
+// 21-state, 200-step build 653 -> 92 us. Per step a
 // lane reads its rows from the step table (R <= 8: loaded during the step
 // before; R = 16 has no registers to spare) and sends its half of the other
 // part's sum through LDS, one value per row and one barrier.
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void tridiag_energy_table_kernel(TridiagJob jo
 // conj(x_i) h_i x_{i+1} = conj(x~_i) x~_{i+1} |h_i| (1 + i q) / sqrt(1 + q^2), q = b dv_i:
 // the real part of conj(x~_i) x~_{i+1} is a sum over the parts, the imaginary part
 // (q != 0) takes the other part's rows through LDS. All 1000 states of that
-// dimer: 14.9 ms with the operators' rows in the lane order (15.9 ms read where they
+// dimer: 14.8 ms with the operators' rows in the lane order (15.9 ms read where they
 // are, 64 lines to a load), where a launch per step and two for its energies took 51 ms.
 // Waves of a part: one, several that exchange their ends through LDS every term
 // (a barrier each), or several whose end lanes repeat the neighbour's (ghosts), which
@@ -1371,7 +1371,7 @@ __global__ __launch_bounds__(512) void tridiag_adjoint_kernel(TridiagAdjJob job)
 // No term mixes the parts, so there is no exchange between the waves within a step.
 //
 // Bound by FP64 vector issue: 8 instructions per row, part and term backwards and
-// 4 forwards. 400-state dimer, 128 steps: 2.45 ms, where the sweep in complex values
+// 4 forwards. 400-state dimer, 128 steps: 2.41 ms, where the sweep in complex values
 // with a barrier per term and all segments one after the other took 19.0 ms.
 template <int R, bool KC>
 __global__ __launch_bounds__(128, R > 8 ? 1 : 2) void tridiag_adj_chain_kernel(
