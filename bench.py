@@ -387,7 +387,7 @@ TERM_KINDS = {8: "fp64", 9: "bf16x3_f64acc", 10: "bf16x3", 11: "bf16x2", 12: "bf
 TERM_MFMA = {"fp64": 0.75, "bf16x3_f64acc": 6.0, "bf16x3": 6.0, "bf16x2": 3.0, "bf16x1": 1.0}
 TERM_MFMA_X4 = {"bf16x3": 4.5}
 TERM_KERNEL_X4 = {
-    "bf16x3": "cheb_bf3_kernel<128,128,2,4,KIND,P,3> (BF16 MFMA 32x32x16, 3 real products x 6 "
+    "bf16x3": "cheb_bf3_kernel<KIND,P> (BF16 MFMA 32x32x16, 3 real products x 6 "
               "piece pairs)",
     "bf16x2": "cheb_x4_kernel<KIND,P,2> (BF16 MFMA 32x32x16 on 64 x 64 wave tiles, 4 real "
               "products x 3 piece pairs)",
@@ -420,7 +420,7 @@ def term_kernel(name: str, n: int) -> str:
 
 
 TERM_KERNEL = {
-    "fp64": "zgemm_nt_f64_kernel<64,64,8,2,4,Gauss,EpiCheb> (FP64 MFMA 16x16x4)",
+    "fp64": "zgemm_nt_f64_kernel<64,64,8,2,4,...,EpiCheb> (FP64 MFMA 16x16x4)",
     "bf16x3_f64acc": "cheb_acc_kernel<128> (BF16 MFMA 32x32x16, 4 real products x 6 piece "
                      "pairs, FP64 sums per 64-column block)",
     "bf16x3": "cheb_s4_kernel<KIND,P,3> (64 x 64 tiles, 4 real products x 6 piece pairs)",
